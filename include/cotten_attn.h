@@ -225,7 +225,7 @@ size_t cotten_attn_workspace_bytes(int B, int H, int N, int d_h, int dtype, int 
 
 /* The same for a call with these params (dtype, causal and feature_map are looked at): what
  * params->workspace must hold.  Differs from the function above for the causal variant, whose
- * sequences of more than 208 rows pass one d x d state per 208-row chunk and slice through the
+ * sequences of more than 208 rows pass up to one d x d state per 208 rows and slice through the
  * workspace (two in the backward call).  0 for invalid arguments or params == NULL.  Host
  * only, no device work. */
 size_t cotten_attn_workspace_bytes_ex(int B, int H, int N, int d_h, int is_bwd,

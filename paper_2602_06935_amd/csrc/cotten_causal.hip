@@ -3,328 +3,545 @@
 //
 //     S_i = sum_{j <= i} m_j khat_j^T v_j          O_i = scale * qhat_i S_i
 //
-// computed as a scan over chunks of 16 rows with the d x d prefix state carried in LDS:
+// as a walk over chunks of 16 * WAVES rows by one workgroup, one 16-row tile per wave, with the
+// d x d state of everything before the chunk carried along:
 //
 //     O_c = scale * ( Qhat_c S_before  +  tril(Qhat_c Khat_c^T) V_c ),     S_before += Khat_c^T V_c
 //
-// and, for the backward, one sweep forwards (dQ needs the prefix state) and one sweep backwards
-// (dK, dV need the suffix state T = scale * sum_{i later} qhat_i^T dO_i), as two independent
-// halves of one launch:
+// and, for the backward, one walk forwards (dQ needs the prefix state) and one walk backwards
+// (dK, dV need the suffix state T = sum_{i later} qhat_i^T dO_i), as two roles of one launch:
 //
-//     G = dO_c V_c^T, P = Qhat_c Khat_c^T          (16 x 16, lower triangle, valid keys)
-//     g_c  = scale * (dO_c S_before^T + G Khat_c)              -> dQ
-//     dV_c = Khat_c T_after + scale * P^T dO_c
-//     h_c  = V_c T_after^T  + scale * G^T Qhat_c               -> dK
+//     G = dO_c V_c^T, P = Qhat_c Khat_c^T          (lower triangle, valid keys)
+//     g_c  = scale * (dO_c S_before^T + G Khat_c)           -> dQ
+//     dV_c = scale * (Khat_c T_after + P^T dO_c)
+//     h_c  = scale * (V_c T_after^T  + G^T Qhat_c)          -> dK
 //
-// Vector-ALU kernels, one workgroup of 256 threads per slice, any supported element type,
-// d_h in {16, 32, 64}.  Not tuned: the bidirectional kernels are the benchmarked path.  They
-// serve the shapes the matrix-core kernels do not take (fp32 d_h = 64); every other call is
-// routed to those by launch_causal() below, which for sequences of more than one chunk also
-// launches the scan over the chunk states defined at the end of this file.
-#include "cotten_device.h"
+// Everything is a matrix-core product: the triangle tile pair by tile pair (`dots`,
+// `add_transposed_product` of the element format), the carried state as operand images in LDS
+// (`apply`), its update one 32 x 32 block per wave.  What a wave needs of its own rows it loads
+// straight in the layout of the products; only the rows that other waves read go through LDS.
+//
+// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 16 / 30, where a scan on the vector
+// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 32 / 77, where 208-row
+// chunks joined by states in memory took 60 / 105 (three launches, 13 * 14 / 2 tile pairs per chunk
+// instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - memory, at about 3.7 TB/s (the two roles of
+// the backward each read all they need) with one chunk of loads in flight per wave; fp32 - the
+// matrix rate (64 flop per cycle and SIMD) of the tile pairs.
 #include "cotten_launch.h"
+#include "cotten_mfma_core.h"
 
 namespace cotten {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kChunk = 16;  // rows per step of the scan
+using namespace mfma;
 
-struct ElemStrides {
-  long long batch, head, row;
-  __device__ __forceinline__ size_t slice_base(int bh, int H) const {
-    return static_cast<size_t>(bh / H) * batch + static_cast<size_t>(bh % H) * head;
-  }
-};
-
-// Sum over the 16 consecutive lanes that share a row.
-__device__ __forceinline__ float sum16(float x) {
-  x += __shfl_xor(x, 1);
-  x += __shfl_xor(x, 2);
-  x += __shfl_xor(x, 4);
-  x += __shfl_xor(x, 8);
-  return x;
-}
-
-// LDS of one workgroup: the carried d x d state and the rows of the current chunk.
-template <int D>
-struct Lds {
-  float state[D][D + 1];
-  float q[kChunk][D + 1];     // qhat rows
-  float k[kChunk][D + 1];     // khat rows (zero for masked or absent keys)
-  float v[kChunk][D + 1];     // v rows    (zero for masked or absent keys)
-  float g[kChunk][D + 1];     // dO rows   (backward)
-  float P[kChunk][kChunk + 1];
-  float G[kChunk][kChunk + 1];
-};
-
-// Thread (r, c) of the workgroup: row r of the chunk, columns c, c + 16, c + 32, ...
-struct Who {
-  int r, c;
-  __device__ __forceinline__ Who() : r(threadIdx.x >> 4), c(threadIdx.x & 15) {}
-};
-
-// Loads row (row0 + r) of X into x[] (zeros if the row does not take part).
-template <typename T, int D>
-__device__ __forceinline__ void load_row(const T* __restrict__ X, size_t base, long long row_stride,
-                                         int row, bool live, const Who& w, float (&x)[D / 16]) {
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i)
-    x[i] = live ? to_float(X[base + static_cast<size_t>(row) * row_stride + w.c + 16 * i]) : 0.0f;
-}
-
-// x <- x / sqrt(|row|^2 + eps); returns 1/r (0 if the row does not take part).
-template <int D>
-__device__ __forceinline__ float normalise(float (&x)[D / 16], float eps, bool live) {
-  float ss = 0.0f;
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i) ss += x[i] * x[i];
-  const float inv = live ? 1.0f / sqrtf(sum16(ss) + eps) : 0.0f;
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i) x[i] *= inv;
-  return inv;
-}
-
-template <int D>
-__device__ __forceinline__ void put_row(float (*dst)[D + 1], const Who& w, const float (&x)[D / 16]) {
-#pragma unroll
-  for (int i = 0; i < D / 16; ++i) dst[w.r][w.c + 16 * i] = x[i];
-}
-
-// state[a][c] += factor * sum_j X[j][a] * Y[j][c] over the chunk
-template <int D>
-__device__ __forceinline__ void add_outer(float (*state)[D + 1], const float (*X)[D + 1],
-                                          const float (*Y)[D + 1], float factor) {
-  for (int e = threadIdx.x; e < D * D; e += kThreads) {
-    const int a = e / D, c = e % D;
-    float acc = 0.0f;
-#pragma unroll
-    for (int j = 0; j < kChunk; ++j) acc += X[j][a] * Y[j][c];
-    state[a][c] += factor * acc;
-  }
-}
+extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
 struct Args {
-  const void* Q;
-  const void* K;
-  const void* V;
-  const void* dO;
+  const unsigned char* Q;
+  const unsigned char* K;
+  const unsigned char* V;
+  const unsigned char* dO;
   const uint8_t* mask;
-  void* O;
-  void* dQ;
-  void* dK;
-  void* dV;
+  unsigned char* O;
+  unsigned char* dQ;
+  unsigned char* dK;
+  unsigned char* dV;
   int H, N;
+  int segments, segment_chunks;  // a slice is cut into segments of so many chunks, a workgroup each
+  Strides st;
   float scale, eps;
   const float* scales;
-  ElemStrides lay;
+  // sums of the states before / after every segment, [slice][segment][D*D] floats row-major, or
+  // nullptr: the workgroup walks the chunks before (after) its segment for their states alone
+  const float* before;
+  const float* after;
 };
 
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void causal_fwd_kernel(const Args a) {
-  __shared__ Lds<D> s;
-  const Who w;
-  const int bh = blockIdx.x, N = a.N;
-  const size_t base = a.lay.slice_base(bh, a.H);
-  const T* Q = static_cast<const T*>(a.Q);
-  const T* K = static_cast<const T*>(a.K);
-  const T* V = static_cast<const T*>(a.V);
-  T* O = static_cast<T*>(a.O);
-  const uint8_t* mask = a.mask != nullptr ? a.mask + static_cast<size_t>(bh / a.H) * N : nullptr;
-  const float scale = a.scales != nullptr ? a.scales[bh] : a.scale;
-  for (int e = threadIdx.x; e < D * (D + 1); e += kThreads) (&s.state[0][0])[e] = 0.0f;
+enum Role { kO = 0, kDq = 1, kDkDv = 2 };
 
-  for (int row0 = 0; row0 < N; row0 += kChunk) {
-    const int row = row0 + w.r;
-    const bool there = row < N;
-    const bool key = there && (mask == nullptr || mask[row] != 0);
-    float q[D / 16], k[D / 16], v[D / 16];
-    load_row<T, D>(Q, base, a.lay.row, row, there, w, q);
-    load_row<T, D>(K, base, a.lay.row, row, key, w, k);
-    load_row<T, D>(V, base, a.lay.row, row, key, w, v);
-    normalise<D>(q, a.eps, there);
-    normalise<D>(k, a.eps, key);
-    __syncthreads();  // the previous chunk is done with the row buffers and the state update
-    put_row<D>(s.q, w, q);
-    put_row<D>(s.k, w, k);
-    put_row<D>(s.v, w, v);
-    __syncthreads();
-    {  // P[r][c] = qhat_r . khat_c for keys of the chunk not later than the row
-      float p = 0.0f;
-      if (w.c <= w.r) {
-#pragma unroll 8
-        for (int x = 0; x < D; ++x) p += s.q[w.r][x] * s.k[w.c][x];
-      }
-      s.P[w.r][w.c] = p;
-    }
-    __syncthreads();
-    float o[D / 16];
-#pragma unroll
-    for (int i = 0; i < D / 16; ++i) o[i] = 0.0f;
-#pragma unroll 4
-    for (int x = 0; x < D; ++x) {
-      const float qx = s.q[w.r][x];
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i) o[i] += qx * s.state[x][w.c + 16 * i];
-    }
-#pragma unroll
-    for (int j = 0; j < kChunk; ++j) {
-      const float p = s.P[w.r][j];
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i) o[i] += p * s.v[j][w.c + 16 * i];
-    }
-    if (there) {
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i)
-        O[base + static_cast<size_t>(row) * a.lay.row + w.c + 16 * i] = from_float<T>(scale * o[i]);
-    }
-    __syncthreads();  // everyone has read the state
-    add_outer<D>(s.state, s.k, s.v, 1.0f);
+// LDS: [per wave: x tile, y tile, P pieces each][two sets of P x P operand images][one flag per wave]
+template <class F, int P, int WAVES>
+struct ScanLds {
+  static constexpr int kWaveBytes = 2 * P * kTileBytes;
+  static constexpr int kImages = WAVES * kWaveBytes;
+  static constexpr int kSet = P * P * F::kImageBytes;
+  static constexpr int kLive = kImages + 2 * kSet;
+  static constexpr int kBytes = kLive + 16 * 4;
+};
+
+// A 16-row tile of a tensor pair on its way to LDS (load layout): piece [h][c] is bytes 128 c + 16 ch
+// .. + 15 of row r8 + 8 h; `live` bit h: the row takes part.
+template <int P>
+struct SharedRaw {
+  u32x4_t x[2][P], y[2][P];
+  int live;
+};
+
+// The wave's own 16 rows of one tensor, loaded from global memory in the layout of the products
+// (lane (i16, g16): bytes 128 c + 64 j + 16 g16 .. + 15 of row i16), so that they need no LDS at all.
+template <int P>
+struct OwnRaw {
+  u32x4_t r[P][2];
+};
+
+struct Buffers {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Buffers(const unsigned char* base, int N, RowAddr row) {
+    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0,
+                                          (N - 1) * row.stride + row.bytes, 0x00020000);
   }
+};
+
+// Bit h: row row0 + r8 + 8 h exists and, if a mask is given, is a valid key.
+__device__ __forceinline__ int row_bits(const uint8_t* __restrict__ mask, int row0, int N, const Lane& L) {
+  int bits = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = row0 + L.r8 + 8 * h;
+    if (row < N) bits |= static_cast<int>(mask == nullptr || mask[row] != 0) << h;
+  }
+  return bits;
 }
 
-// blockIdx.y == 0: forward sweep, dQ.   blockIdx.y == 1: backward sweep, dK and dV.
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
-  __shared__ Lds<D> s;
-  const Who w;
-  const int bh = blockIdx.x, N = a.N;
-  const bool backwards = blockIdx.y == 1;
-  const size_t base = a.lay.slice_base(bh, a.H);
-  const T* Q = static_cast<const T*>(a.Q);
-  const T* K = static_cast<const T*>(a.K);
-  const T* V = static_cast<const T*>(a.V);
-  const T* dO = static_cast<const T*>(a.dO);
-  const uint8_t* mask = a.mask != nullptr ? a.mask + static_cast<size_t>(bh / a.H) * N : nullptr;
-  const float scale = a.scales != nullptr ? a.scales[bh] : a.scale;
-  for (int e = threadIdx.x; e < D * (D + 1); e += kThreads) (&s.state[0][0])[e] = 0.0f;
-
-  const int n_chunks = (N + kChunk - 1) / kChunk;
-  for (int step = 0; step < n_chunks; ++step) {
-    const int row0 = (backwards ? n_chunks - 1 - step : step) * kChunk;
-    const int row = row0 + w.r;
-    const bool there = row < N;
-    const bool key = there && (mask == nullptr || mask[row] != 0);
-    float q[D / 16], k[D / 16], v[D / 16], g[D / 16];
-    load_row<T, D>(Q, base, a.lay.row, row, there, w, q);
-    load_row<T, D>(K, base, a.lay.row, row, key, w, k);
-    load_row<T, D>(V, base, a.lay.row, row, key, w, v);
-    load_row<T, D>(dO, base, a.lay.row, row, there, w, g);
-    const float inv_q = normalise<D>(q, a.eps, there);
-    const float inv_k = normalise<D>(k, a.eps, key);
-    __syncthreads();
-    put_row<D>(s.q, w, q);
-    put_row<D>(s.k, w, k);
-    put_row<D>(s.v, w, v);
-    put_row<D>(s.g, w, g);
-    __syncthreads();
-    {  // lower triangle of the chunk: P = qhat . khat,  G = dO . v
-      float p = 0.0f, gg = 0.0f;
-      if (w.c <= w.r) {
-#pragma unroll 8
-        for (int x = 0; x < D; ++x) {
-          p += s.q[w.r][x] * s.k[w.c][x];
-          gg += s.g[w.r][x] * s.v[w.c][x];
-        }
-      }
-      s.P[w.r][w.c] = p;
-      s.G[w.r][w.c] = gg;
+template <int P>
+__device__ __forceinline__ void load_shared(SharedRaw<P>& t, const Lane& L, const Buffers& X, const Buffers& Y,
+                                            RowAddr addr, int row0, int bits) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const bool live = ((bits >> h) & 1) != 0;
+    // rows narrower than 128 bytes (one piece only): the lanes beyond them load zeros
+    const uint32_t off = (live && L.ch * 16 < addr.bytes)
+                             ? static_cast<uint32_t>(row0 + L.r8 + 8 * h) * addr.stride + L.ch * 16
+                             : kOutOfBuffer;
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+      t.x[h][c] = __builtin_amdgcn_raw_buffer_load_b128(X.r, off + c * kRowBytes, 0, 0);
+      t.y[h][c] = __builtin_amdgcn_raw_buffer_load_b128(Y.r, off + c * kRowBytes, 0, 0);
     }
-    __syncthreads();
-    if (!backwards) {
-      // state = S before the chunk:  g_r = scale * (dO_r S^T + sum_j G[r][j] khat_j)
-      float t[D / 16];
+  }
+  t.live = bits;
+}
+
+template <int P>
+__device__ __forceinline__ void load_own(OwnRaw<P>& t, const Lane& L, const Buffers& X, RowAddr addr,
+                                         int row0, bool live) {
+  const uint32_t at = static_cast<uint32_t>(row0 + L.i16) * addr.stride + L.g16 * 16;
 #pragma unroll
-      for (int i = 0; i < D / 16; ++i) t[i] = 0.0f;
-#pragma unroll 4
-      for (int x = 0; x < D; ++x) {
-        const float gx = s.g[w.r][x];
+  for (int c = 0; c < P; ++c)
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) t[i] += gx * s.state[w.c + 16 * i][x];
-      }
+    for (int j = 0; j < 2; ++j) {
+      const int col = c * kRowBytes + 64 * j;
+      t.r[c][j] = __builtin_amdgcn_raw_buffer_load_b128(
+          X.r, live && col + L.g16 * 16 < addr.bytes ? at + col : kOutOfBuffer, 0, 0);
+    }
+}
+
+// The shared tile into LDS: xhat pieces, then y pieces.
+template <class F, int P>
+__device__ __forceinline__ void stage_shared(const SharedRaw<P>& t, const Lane& L, float eps,
+                                             unsigned char* tiles) {
 #pragma unroll
-      for (int j = 0; j < kChunk; ++j) {
-        const float gj = s.G[w.r][j];
+  for (int h = 0; h < 2; ++h) {
+    float f[P][F::EPL];
+    float ss = 0.0f;
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i) t[i] += gj * s.k[j][w.c + 16 * i];
-      }
-      float proj = 0.0f;
+    for (int c = 0; c < P; ++c) {
+      F::unpack(t.x[h][c], f[c]);
 #pragma unroll
-      for (int i = 0; i < D / 16; ++i) {
-        t[i] *= scale;
-        proj += q[i] * t[i];
-      }
-      proj = sum16(proj);
-      if (there) {
-        T* out = static_cast<T*>(a.dQ);
+      for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
+    }
+    const float inv = inv_norm_or_zero(row_sum8(ss), eps, ((t.live >> h) & 1) != 0);
+    const int off = (L.r8 + 8 * h) * kTileStride + L.ch * 16;
 #pragma unroll
-        for (int i = 0; i < D / 16; ++i)
-          out[base + static_cast<size_t>(row) * a.lay.row + w.c + 16 * i] =
-              from_float<T>((t[i] - q[i] * proj) * inv_q);
-      }
-      __syncthreads();
-      add_outer<D>(s.state, s.k, s.v, 1.0f);
-    } else {
-      // state = T after the chunk (scale included):
-      //   dV_r = khat_r T + scale * sum_{i >= r} P[i][r] dO_i
-      //   h_r  = v_r T^T  + scale * sum_{i >= r} G[i][r] qhat_i
-      float dv[D / 16], h[D / 16];
+    for (int c = 0; c < P; ++c) {
 #pragma unroll
-      for (int i = 0; i < D / 16; ++i) dv[i] = h[i] = 0.0f;
-#pragma unroll 4
-      for (int x = 0; x < D; ++x) {
-        const float kx = s.k[w.r][x], vx = s.v[w.r][x];
-#pragma unroll
-        for (int i = 0; i < D / 16; ++i) {
-          dv[i] += kx * s.state[x][w.c + 16 * i];
-          h[i] += vx * s.state[w.c + 16 * i][x];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < kChunk; ++j) {
-        const float p = scale * s.P[j][w.r], gg = scale * s.G[j][w.r];  // zero for j < r
-#pragma unroll
-        for (int i = 0; i < D / 16; ++i) {
-          dv[i] += p * s.g[j][w.c + 16 * i];
-          h[i] += gg * s.q[j][w.c + 16 * i];
-        }
-      }
-      float proj = 0.0f;
-#pragma unroll
-      for (int i = 0; i < D / 16; ++i) proj += k[i] * h[i];
-      proj = sum16(proj);
-      if (there) {
-        T* out_k = static_cast<T*>(a.dK);
-        T* out_v = static_cast<T*>(a.dV);
-#pragma unroll
-        for (int i = 0; i < D / 16; ++i) {
-          const size_t at = base + static_cast<size_t>(row) * a.lay.row + w.c + 16 * i;
-          // masked keys: khat, v and 1/r are zero, so both come out as exact zeros
-          out_k[at] = from_float<T>(key ? (h[i] - k[i] * proj) * inv_k : 0.0f);
-          out_v[at] = from_float<T>(key ? dv[i] : 0.0f);
-        }
-      }
-      __syncthreads();
-      add_outer<D>(s.state, s.q, s.g, scale);
+      for (int i = 0; i < F::EPL; ++i) f[c][i] *= inv;
+      *reinterpret_cast<u32x4_t*>(tiles + c * kTileBytes + off) = F::pack(f[c]);
+      *reinterpret_cast<u32x4_t*>(tiles + (P + c) * kTileBytes + off) = t.y[h][c];
     }
   }
 }
 
-template <typename T, int D>
-hipError_t run(const Problem& p, bool bwd) {
-  Args a{};
-  a.Q = p.Q; a.K = p.K; a.V = p.V; a.dO = p.dO; a.mask = p.mask;
-  a.O = p.O; a.dQ = p.dQ; a.dK = p.dK; a.dV = p.dV;
-  a.H = p.H; a.N = p.N;
-  a.scale = p.scale; a.eps = p.eps; a.scales = p.slice_scale;
-  a.lay = ElemStrides{p.stride_batch, p.stride_head, p.stride_row};
-  const unsigned BH = static_cast<unsigned>(p.B) * p.H;
-  if (bwd)
-    hipLaunchKernelGGL((causal_bwd_kernel<T, D>), dim3(BH, 2), dim3(kThreads), 0, p.stream, a);
-  else
-    hipLaunchKernelGGL((causal_fwd_kernel<T, D>), dim3(BH), dim3(kThreads), 0, p.stream, a);
-  return hipGetLastError();
+// What a wave carries of the state: one 32 x 32 block.  NATURAL / TRANSPOSED: which operand images
+// it keeps up to date.  The transposed one is written four values at a time from an accumulator that
+// holds the block as it is, the natural one likewise from one that holds it transposed (operands
+// swapped).  Where both are kept, or in fp32, there is one accumulator (registers; matrix-core time)
+// and the natural image is written value by value (32 lanes write a run of one row).
+template <class F, int P, bool NATURAL, bool TRANSPOSED>
+struct Carried {
+  typedef typename F::BlockAcc Acc;
+  static constexpr int kPerPair = Acc::kBlocks, kBlocks = P * P * kPerPair;
+  static constexpr bool kScatter = NATURAL && (TRANSPOSED || F::kElemBytes == 4);
+  static constexpr bool kPlain = TRANSPOSED || kScatter, kSwapped = NATURAL && !kScatter;
+  Acc plain, swapped;
+  int p, q, block;  // block `block` of piece p of x against piece q of y
+  __device__ __forceinline__ explicit Carried(int index)
+      : p(index / kPerPair / P), q(index / kPerPair % P), block(index % kPerPair) {
+    if (kPlain) plain.zero();
+    if (kSwapped) swapped.zero();
+  }
+  // M: a row-major state of side D
+  __device__ __forceinline__ void read(const float* __restrict__ M, int D, const Lane& L) {
+    const int r0 = p * F::D + Acc::block_row0(block), c0 = q * F::D + Acc::block_col0(block);
+    const int run = 4 * (L.lane >> 5), col = L.lane & 31;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (kPlain) plain.v[4 * j + i] = M[(r0 + 8 * j + run + i) * D + c0 + col];
+        if (kSwapped) swapped.v[4 * j + i] = M[(r0 + col) * D + c0 + 8 * j + run + i];
+      }
+  }
+  __device__ __forceinline__ void add(const unsigned char* tiles, const Lane& L) {
+    const typename Acc::Frag f =
+        Acc::fetch(tiles + p * kTileBytes, tiles + (P + q) * kTileBytes, L, block);
+    if (kPlain) plain.mma(f);
+    if (kSwapped) swapped.mma_swapped(f);
+  }
+  __device__ __forceinline__ void write(unsigned char* natural, unsigned char* transposed, const Lane& L) const {
+    const int r0 = Acc::block_row0(block), c0 = Acc::block_col0(block), at = (p * P + q) * F::kImageBytes;
+    if (TRANSPOSED) plain.write_image(L, r0, c0, 1.0f, transposed + at);
+    if (kSwapped) swapped.write_image(L, c0, r0, 1.0f, natural + at);
+    if (kScatter) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          F::write_one_at(natural + at + F::image_offset(r0 + 8 * j + 4 * (L.lane >> 5) + i, c0 + (L.lane & 31)),
+                          plain.v[4 * j + i]);
+    }
+  }
+};
+
+// out[piece] = sum_c X[piece c] W(first + c * step) over the images of a set
+template <class F, int P>
+__device__ __forceinline__ void apply_set(const typename F::TileRows (&X)[P], const unsigned char* images,
+                                          int first, int step, const Lane& L, f32x4_t (&out)[F::NT]) {
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    typename F::Operand W;
+    W.load(images + (first + c * step) * F::kImageBytes, L);
+    if (c == 0) F::apply(X[c], W, out);
+    else F::apply_onto(X[c], W, out);
+  }
 }
+
+template <class F, int P>
+__device__ __forceinline__ void own_rows(const OwnRaw<P>& t, typename F::TileRows (&x)[P]) {
+#pragma unroll
+  for (int c = 0; c < P; ++c)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) x[c].put(j, t.r[c][j]);
+}
+
+// 1/r of the lane's own row (0 if the row does not take part)
+template <class F, int P>
+__device__ __forceinline__ float own_inv(const typename F::TileRows (&x)[P], float eps, bool live, const Lane& L) {
+  float ss = 0.0f;
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    float f[2 * F::EPL];
+    x[c].unpack(f);
+#pragma unroll
+    for (int i = 0; i < 2 * F::EPL; ++i) ss += f[i] * f[i];
+  }
+  return inv_norm_or_zero(row_sum_groups(ss, L), eps, live);
+}
+
+// g <- (g - u (u.g)) / r over all pieces, from the raw rows x = r u:  g/r - x (x.g) / r^3
+template <class F, int P>
+__device__ __forceinline__ void project_own(float (&g)[P][2 * F::EPL], const typename F::TileRows (&x)[P],
+                                            float inv_r, const Lane& L) {
+  float proj = 0.0f;
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    float f[2 * F::EPL];
+    x[c].unpack(f);
+#pragma unroll
+    for (int i = 0; i < 2 * F::EPL; ++i) proj += f[i] * g[c][i];
+  }
+  // one factor at a time: 1/r^3 alone leaves the fp32 range for rows next to zero
+  proj = row_sum_groups(proj, L) * inv_r * inv_r * inv_r;
+#pragma unroll
+  for (int c = 0; c < P; ++c) {
+    float f[2 * F::EPL];
+    x[c].unpack(f);
+#pragma unroll
+    for (int i = 0; i < 2 * F::EPL; ++i) g[c][i] = g[c][i] * inv_r - f[i] * proj;
+  }
+}
+
+template <class F, int P>
+__device__ __forceinline__ void store_own(unsigned char* dst, int row, int N, RowAddr addr, const Lane& L,
+                                          const float (&o)[P][2 * F::EPL]) {
+  if (row >= N) return;
+#pragma unroll
+  for (int c = 0; c < P; ++c)
+    store_product_row<F, kStoreStreamed>(dst + c * kRowBytes, row,
+                                         RowAddr{addr.stride, addr.bytes - c * kRowBytes}, L, o[c]);
+}
+
+// Per chunk (B = workgroup barrier):
+//   stage the wave's shared tile (roles O, dQ: khat, v; role dK, dV: qhat, dO), write the state
+//   carried so far into the operand images, request everything of the next chunk         B
+//   own rows: carried state, then the tile pairs; epilogue, stores.  Then the waves with the
+//   fewest pairs add the chunk to the carried state, one 32 x 32 block each              B
+template <class F, int P, int WAVES, int ROLE>
+__device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment) {
+  typedef ScanLds<F, P, WAVES> Lds;
+  typedef typename F::TileRows TileRows;
+  constexpr bool kUp = ROLE != kDkDv;  // ascending chunks
+  constexpr int kState = F::D * P;
+  const Lane L;
+  const int N = a.N, wave = L.wave;
+  const int n_tiles = (N + TR - 1) / TR, chunks = (n_tiles + WAVES - 1) / WAVES;
+  const size_t base = a.st.slice_base(bh, a.H);
+  const RowAddr addr = a.st.row;
+  const uint8_t* keys = a.mask == nullptr ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * N;
+  const uint8_t* shared_mask = kUp ? keys : nullptr;
+  const float scale = a.scales != nullptr ? a.scales[bh] : a.scale;
+  const Buffers sx((kUp ? a.K : a.Q) + base, N, addr), sy((kUp ? a.V : a.dO) + base, N, addr);
+  const Buffers ox((kUp ? a.Q : a.K) + base, N, addr), oy((ROLE == kDq ? a.dO : a.V) + base, N, addr);
+
+  const int first = segment * a.segment_chunks;
+  const int last = first + a.segment_chunks < chunks ? first + a.segment_chunks : chunks;
+  const float* given = kUp ? a.before : a.after;
+  // the walk starts at the segment when the states around it are given, at the sequence's end otherwise
+  const int begin = kUp ? (given != nullptr ? first : 0) : (given != nullptr ? last - 1 : chunks - 1);
+  int steps = kUp ? last - begin : begin - first + 1;
+
+  unsigned char* mine = smem + wave * Lds::kWaveBytes;
+  unsigned char* natural = smem + Lds::kImages;
+  unsigned char* transposed = smem + Lds::kImages + (ROLE == kO ? 0 : Lds::kSet);
+  int* live = reinterpret_cast<int*>(smem + Lds::kLive);
+
+  // the state blocks go to the waves with the fewest tile pairs
+  typedef Carried<F, P, ROLE != kO, ROLE != kDq> State;
+  const int duty = kUp ? wave : WAVES - 1 - wave;
+  const bool on_duty = duty < State::kBlocks;
+  State state(on_duty ? duty : 0);
+  bool have = false;  // the images stand for something (uniform)
+  if (given != nullptr && (kUp ? segment > 0 : segment < a.segments - 1)) {
+    have = true;
+    if (on_duty)
+      state.read(given + (static_cast<size_t>(bh) * a.segments + segment) * kState * kState, kState, L);
+  }
+
+  const auto tile_of = [&](int step) { return (kUp ? begin + step : begin - step) * WAVES + wave; };
+  const auto applies = [&](int step) { return kUp ? begin + step >= first : begin - step < last; };
+  const auto own_live = [&](int tile) {
+    const int row = tile * TR + L.i16;
+    return row < N && (kUp || keys == nullptr || keys[row] != 0);
+  };
+
+  SharedRaw<P> shared;
+  OwnRaw<P> nx, ny;
+  bool next_live = false;
+  {
+    const int row0 = tile_of(0) * TR;
+    load_shared<P>(shared, L, sx, sy, addr, row0, row_bits(shared_mask, row0, N, L));
+    if (applies(0)) {
+      next_live = own_live(tile_of(0));
+      load_own<P>(nx, L, ox, addr, row0, next_live);
+      if (ROLE != kO) load_own<P>(ny, L, oy, addr, row0, next_live);
+    }
+  }
+  if (!kUp && keys != nullptr && steps > 4) {
+    // Chunks below the first valid key of the segment get zeros and are not walked.  (Looking for it
+    // costs a trip to memory before the walk: 16-bit, 256 x 1001 rows, left-padded, 93 -> 77 us;
+    // with four chunks or fewer it is not worth it.)
+    int lo = N;
+#pragma unroll 4
+    for (int row = first * WAVES * TR + static_cast<int>(threadIdx.x); row < last * WAVES * TR; row += 64 * WAVES)
+      if (row < N && keys[row] != 0 && row < lo) lo = row;
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1) {
+      const int other = __shfl_xor(lo, w);
+      lo = other < lo ? other : lo;
+    }
+    if (L.lane == 0) live[wave] = lo;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) lo = live[w] < lo ? live[w] : lo;
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    __syncthreads();
+    steps = lo < N ? begin - lo / (WAVES * TR) + 1 : 0;
+    const int below = lo < N ? lo / (WAVES * TR) : last;  // chunks first .. below-1
+    float zeros[P][2 * F::EPL];
+#pragma unroll
+    for (int c = 0; c < P; ++c)
+#pragma unroll
+      for (int i = 0; i < 2 * F::EPL; ++i) zeros[c][i] = 0.0f;
+#pragma unroll 1
+    for (int t = first * WAVES + wave; t < below * WAVES; t += WAVES) {
+      store_own<F, P>(a.dV + base, t * TR + L.i16, N, addr, L, zeros);
+      store_own<F, P>(a.dK + base, t * TR + L.i16, N, addr, L, zeros);
+    }
+  }
+#pragma unroll 1
+  for (int step = 0; step < steps; ++step) {
+    const bool tile_live = __builtin_amdgcn_ballot_w64(shared.live != 0) != 0;
+    if (tile_live) stage_shared<F, P>(shared, L, a.eps, mine);
+    if (L.lane == 0) live[wave] = tile_live;
+    if (have && on_duty && applies(step)) state.write(natural, transposed, L);
+    TileRows x[P], y[P];
+    own_rows<F, P>(nx, x);
+    if (ROLE != kO) own_rows<F, P>(ny, y);
+    const bool row_live = next_live;
+    const int tile = tile_of(step);
+    if (step + 1 < steps) {
+      const int row0 = tile_of(step + 1) * TR;
+      load_shared<P>(shared, L, sx, sy, addr, row0, row_bits(shared_mask, row0, N, L));
+      if (applies(step + 1)) {
+        next_live = own_live(tile_of(step + 1));
+        load_own<P>(nx, L, ox, addr, row0, next_live);
+        if (ROLE != kO) load_own<P>(ny, L, oy, addr, row0, next_live);
+      }
+    }
+    __syncthreads();
+    int flags = 0;  // bit u: tile u of the chunk has rows that take part
+#pragma unroll
+    for (int u = 0; u < WAVES; ++u) flags |= (live[u] != 0) << u;
+    flags = __builtin_amdgcn_readfirstlane(flags);
+
+    if (applies(step) && tile < n_tiles) {
+      const int row = tile * TR + L.i16;
+      if (kUp) {
+        const TileRows(&own)[P] = ROLE == kO ? x : y;
+        f32x4_t out[P][F::NT];
+#pragma unroll
+        for (int c = 0; c < P; ++c) {
+          if (have) {
+            if (ROLE == kO) apply_set<F, P>(own, transposed, c, P, L, out[c]);
+            else apply_set<F, P>(own, natural, P * c, 1, L, out[c]);
+          } else {
+#pragma unroll
+            for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+          }
+        }
+#pragma unroll 1
+        for (int u = 0; u <= wave; ++u) {
+          if (((flags >> u) & 1) == 0) continue;  // no valid key in the tile
+          const unsigned char* tu = smem + u * Lds::kWaveBytes;
+          // [key 4g+v][query i16]: khat . q (role O), v . dO (role dQ)
+          f32x4_t pt = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int c = 0; c < P; ++c) {
+            TileRows key;
+            key.load(tu + ((ROLE == kO ? 0 : P) + c) * kTileBytes, L);
+            pt = F::dots(key, own[c], pt);
+          }
+          if (u == wave) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (4 * L.g16 + v > L.i16) pt[v] = 0.0f;
+          }
+#pragma unroll
+          for (int c = 0; c < P; ++c)
+            F::add_transposed_product(tu + ((ROLE == kO ? P : 0) + c) * kTileBytes, L, pt, out[c]);
+        }
+        const float inv_r = own_inv<F, P>(x, a.eps, row_live, L);
+        const float factor = ROLE == kO ? inv_r * scale : scale;
+        float o[P][2 * F::EPL];
+#pragma unroll
+        for (int c = 0; c < P; ++c) {
+          product_rows<F>(out[c], o[c]);
+#pragma unroll
+          for (int i = 0; i < 2 * F::EPL; ++i) o[c][i] *= factor;
+        }
+        if (ROLE == kDq) project_own<F, P>(o, x, inv_r, L);
+        store_own<F, P>((ROLE == kO ? a.O : a.dQ) + base, row, N, addr, L, o);
+      } else {
+        // dV, then dK: each product pair reads what the other does not, so doing them one after the
+        // other costs no LDS reads and halves the accumulators in flight
+        const bool any_key = __builtin_amdgcn_ballot_w64(row_live) != 0;
+        const float inv_r = any_key ? own_inv<F, P>(x, a.eps, row_live, L) : 0.0f;
+#pragma unroll
+        for (int kind = 0; kind < 2; ++kind) {
+          float o[P][2 * F::EPL];
+#pragma unroll
+          for (int c = 0; c < P; ++c)
+#pragma unroll
+            for (int i = 0; i < 2 * F::EPL; ++i) o[c][i] = 0.0f;
+          if (any_key) {
+            const TileRows(&own)[P] = kind == 0 ? x : y;
+            // tiles whose rows meet the own ones in dots(), and those the result is made of
+            const int left = (kind == 0 ? 0 : P) * kTileBytes, right = (kind == 0 ? P : 0) * kTileBytes;
+            f32x4_t out[P][F::NT];
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+              if (have) {
+                if (kind == 0) apply_set<F, P>(own, transposed, c, P, L, out[c]);
+                else apply_set<F, P>(own, natural, P * c, 1, L, out[c]);
+              } else {
+#pragma unroll
+                for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+              }
+            }
+#pragma unroll 1
+            for (int t = wave; t < WAVES; ++t) {
+              if (((flags >> t) & 1) == 0) continue;  // beyond the sequence
+              const unsigned char* tt = smem + t * Lds::kWaveBytes;
+              // [query 4g+v][key i16]: qhat . k (dV), dO . v (dK)
+              f32x4_t p = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int c = 0; c < P; ++c) {
+                TileRows query;
+                query.load(tt + left + c * kTileBytes, L);
+                p = F::dots(query, own[c], p);
+              }
+              if (t == wave) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                  if (L.i16 > 4 * L.g16 + v) p[v] = 0.0f;
+              }
+#pragma unroll
+              for (int c = 0; c < P; ++c)
+                F::add_transposed_product(tt + right + c * kTileBytes, L, p, out[c]);
+            }
+            const float factor = kind == 0 ? inv_r * scale : scale;
+#pragma unroll
+            for (int c = 0; c < P; ++c) {
+              product_rows<F>(out[c], o[c]);
+#pragma unroll
+              for (int i = 0; i < 2 * F::EPL; ++i) o[c][i] *= factor;
+            }
+            if (kind == 1) project_own<F, P>(o, x, inv_r, L);
+#pragma unroll
+            for (int c = 0; c < P; ++c)
+#pragma unroll
+              for (int i = 0; i < 2 * F::EPL; ++i) o[c][i] = row_live ? o[c][i] : 0.0f;  // masked: exact zeros
+          }
+          store_own<F, P>((kind == 0 ? a.dV : a.dK) + base, row, N, addr, L, o);
+        }
+      }
+    }
+    if (step + 1 < steps && flags != 0) {
+      have = true;
+      if (on_duty) {
+#pragma unroll 2
+        for (int u = 0; u < WAVES; ++u)
+          if ((flags >> u) & 1) state.add(smem + u * Lds::kWaveBytes, L);
+      }
+    }
+    __syncthreads();  // the tiles and images are written again next
+  }
+}
+
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, P == 1 ? 4 : 2) void causal_scan_fwd_kernel(const Args a) {
+  scan_segment<F, P, WAVES, kO>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+}
+
+// blockIdx.y == 0: dQ.   blockIdx.y == 1: dK and dV.
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, P == 1 ? 4 : 2) void causal_scan_bwd_kernel(const Args a) {
+  if (blockIdx.y == 0) scan_segment<F, P, WAVES, kDq>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+  else scan_segment<F, P, WAVES, kDkDv>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+}
+
+constexpr int kThreads = 256;
 
 // Chunked matrix-core path: the states of the chunks, [slice][chunk][dd] floats, become in
 // place the sums a chunk needs.  Block row 0: every S_c is replaced by the sum of the S before
@@ -332,8 +549,6 @@ hipError_t run(const Problem& p, bool bwd) {
 // by the sum of the T after chunk c, added from the last chunk down.  One thread per four
 // consecutive floats of a state; the values of up to kAhead chunks are requested together.
 // The last S and the first T were never written and are not read.
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-
 __global__ __launch_bounds__(kThreads) void chunk_scan_kernel(float* states, int slices, int chunks,
                                                               int quads) {
   constexpr int kAhead = 8;
@@ -363,6 +578,79 @@ __global__ __launch_bounds__(kThreads) void chunk_scan_kernel(float* states, int
   }
 }
 
+
+template <class F, int P, int WAVES>
+hipError_t run_scan(const Problem& p, bool bwd) {
+  Args a{};
+  a.Q = static_cast<const unsigned char*>(p.Q);
+  a.K = static_cast<const unsigned char*>(p.K);
+  a.V = static_cast<const unsigned char*>(p.V);
+  a.dO = static_cast<const unsigned char*>(p.dO);
+  a.mask = p.mask;
+  a.O = static_cast<unsigned char*>(p.O);
+  a.dQ = static_cast<unsigned char*>(p.dQ);
+  a.dK = static_cast<unsigned char*>(p.dK);
+  a.dV = static_cast<unsigned char*>(p.dV);
+  a.H = p.H;
+  a.N = p.N;
+  a.st = Strides{p.stride_batch * p.elem_bytes(), p.stride_head * p.elem_bytes(),
+                 RowAddr{static_cast<int>(p.stride_row * p.elem_bytes()),
+                         static_cast<int>(p.D * p.elem_bytes())}};
+  a.scale = p.scale;
+  a.eps = p.eps;
+  a.scales = p.slice_scale;
+  const int slices = p.B * p.H, chunk_rows = 16 * WAVES, chunks = (p.N + chunk_rows - 1) / chunk_rows;
+  a.segments = 1;
+  a.segment_chunks = chunks;
+  // Segments: about one workgroup per compute unit and role (16-bit rows, fp32 rows of 256 bytes), two
+  // where the tiles are small and the matrix cores slow (fp32 rows of 128 bytes).  Measured with 1,
+  // 2, 4, 8 segments (fwd / bwd, us):  bf16 d = 64, 256 slices x 1001 rows 32 / 77, 35 / 77, 45 / 91,
+  // 68 / 120; 64 x 1001 29 / 53, 22 / 34, 19 / 29, 20 / 34;  fp32 d = 64, 128 x 200 22 / 35,
+  // 16 / 30, 16 / 32; 32 x 2048 184 / 324, 128 / 192, 99 / 125, 83 / 107;  fp32 d = 32,
+  // 128 x 1000 47 / 77, 41 / 63, 46 / 58.
+  const int target = (P == 1 && F::kElemBytes == 4) ? 512 : 256;
+  const int most = P == 1 && causal_chunks(p.N) > 1 ? causal_chunks(p.N) : 16;
+  int n = (target + slices - 1) / slices;
+  if (n > chunks) n = chunks;
+  if (n > most) n = most;
+  // The states around the segments: every workgroup walks the chunks before (after) its segment
+  // itself, for their states alone, while that is little; from more than four segments on, and in a
+  // forward with long segments or slow matrix cores, two launches ahead sum them up in the
+  // workspace (where there is one: it holds causal_chunks(N) states per slice, none for one chunk).
+  // 64 x 4096 bf16, 4 segments: 67 / 100 us walked, 52 / 106 us given; 8 segments: 69 / 127, 50 / 111.
+  bool states_given = P == 1 && n > 1 && causal_chunks(p.N) > 1 &&
+                      (n > 4 || (!bwd && (F::kElemBytes == 4 || p.N > 2048)));
+  if (states_given) {
+    constexpr int kMostRows = 16384;  // the key flags of a segment must fit LDS
+    const int at_least = (p.N + kMostRows - 1) / kMostRows;
+    if (n < at_least) n = at_least;
+  }
+  a.segment_chunks = (chunks + n - 1) / n;
+  a.segments = (chunks + a.segment_chunks - 1) / a.segment_chunks;
+  if (states_given) {
+    if (p.workspace == nullptr || a.segments > causal_chunks(p.N)) return hipErrorInvalidValue;
+    const int side = mfma_state_dim(p.dtype);
+    hipError_t err = launch_chunk_states(p, a.segment_chunks * WAVES, a.segments, bwd);
+    if (err != hipSuccess) return err;
+    err = launch_chunk_scan(p.workspace, slices, a.segments, side * side, bwd, p.stream);
+    if (err != hipSuccess) return err;
+    a.before = p.workspace;
+    a.after = p.workspace + static_cast<size_t>(slices) * a.segments * side * side;
+  }
+  constexpr int lds = ScanLds<F, P, WAVES>::kBytes;
+  static_assert(lds <= 80 * 1024, "two workgroups per compute unit");
+  const void* kern = bwd ? reinterpret_cast<const void*>(causal_scan_bwd_kernel<F, P, WAVES>)
+                         : reinterpret_cast<const void*>(causal_scan_fwd_kernel<F, P, WAVES>);
+  const hipError_t err = grant_dynamic_lds(kern, lds);
+  if (err != hipSuccess) return err;
+  const unsigned grid = static_cast<unsigned>(slices) * a.segments;
+  if (bwd)
+    hipLaunchKernelGGL((causal_scan_bwd_kernel<F, P, WAVES>), dim3(grid, 2), dim3(64 * WAVES), lds, p.stream, a);
+  else
+    hipLaunchKernelGGL((causal_scan_fwd_kernel<F, P, WAVES>), dim3(grid), dim3(64 * WAVES), lds, p.stream, a);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_chunk_scan(float* states, int slices, int chunks, int dd, bool with_queries,
@@ -385,21 +673,25 @@ size_t causal_workspace_floats(int B, int H, int N, int D, int dtype, bool is_bw
 
 hipError_t launch_causal(const Problem& p, bool bwd) {
   if (!causal_resident_supports(p.dtype, p.D)) {
-    // the one shape left to the scan; its other instances would be reached by no call
     if (p.dtype != 0 || p.D != 64) return hipErrorInvalidValue;
-    return run<float, 64>(p, bwd);
+    return run_scan<F32x32, 2, 4>(p, bwd);
   }
-  // tile pairs on the matrix cores, up to 208 rows resident in LDS per workgroup
-  const int chunks = causal_chunks(p.N);
-  if (chunks > 1) {
-    if (p.workspace == nullptr) return hipErrorInvalidValue;
-    const int side = mfma_state_dim(p.dtype);
-    hipError_t err = launch_chunk_states(p, kCausalChunkRows / 16, chunks, bwd);
-    if (err != hipSuccess) return err;
-    err = launch_chunk_scan(p.workspace, p.B * p.H, chunks, side * side, bwd, p.stream);
-    if (err != hipSuccess) return err;
-  }
-  return launch_resident_causal(p, bwd, chunks);
+  if (p.dtype == 0) return run_scan<F32x32, 1, 4>(p, bwd);
+  // 16-bit rows.  The walk reads what its two backward roles share twice; a slice of at most 208
+  // rows held in LDS is read once and wins as long as its workgroups (one per compute unit) do
+  // not queue up, or are well filled when they do.  us, resident against the walk with 8 (4)
+  // waves, bf16 d = 64, forward / backward:
+  //   N = 200: 256 slices 8.2 / 13.7, 9.5 / 18.2;  512: 13.9 / 26.9, 11.6 / 29.1;  4096: 100 / 161, 71 / 203
+  //   N = 100: 512 slices 9.7 / 15.7, 7.4 / 17.2 (8.9 / 16.3);  4096: 62 / 103, 38 / 114 (35 / 96)
+  //   N = 50:  256 slices 4.8 / 6.2, (4.5 / 8.0);  512: 7.8 / 10.6, (5.2 / 9.4);  4096: 48 / 76, (18 / 48)
+  const long slices = static_cast<long>(p.B) * p.H;
+  const bool resident = causal_chunks(p.N) == 1 &&
+                        (bwd ? slices <= 256 || p.N > 128 || (p.N > 64 && slices < 1024)
+                             : slices <= 256 && p.N > 128);
+  if (resident) return launch_resident_causal(p, bwd);
+  if (p.N <= 64 || (p.N <= 128 && slices >= 1024))
+    return p.dtype == 1 ? run_scan<Bf16x64, 1, 4>(p, bwd) : run_scan<F16x64, 1, 4>(p, bwd);
+  return p.dtype == 1 ? run_scan<Bf16x64, 1, 8>(p, bwd) : run_scan<F16x64, 1, 8>(p, bwd);
 }
 
 }  // namespace cotten

@@ -2,7 +2,6 @@
 // three-launch structure of the kernels for wide rows (partial states -> fixed-order reduction ->
 // apply), the reduction kernel itself, <S, dS> for d loss / d log(scale), and the kernels of
 // the learnable normaliser.
-#include "cotten_device.h"
 #include "cotten_launch.h"
 
 namespace cotten {

@@ -2,7 +2,8 @@
 // lane geometry, the two element formats with their MFMA products, tile loads through
 // buffer resources, staging into LDS tiles, and the epilogue helpers.
 #pragma once
-#include "cotten_device.h"
+#include <hip/hip_runtime.h>
+#include <stdint.h>
 
 namespace cotten {
 namespace mfma {
@@ -165,7 +166,7 @@ struct Half64 {
   static constexpr int kMap = 0;  // what is done to the rows of Q and K: see FeatureMap
   typedef typename E::v8 v8_t;
   typedef typename E::v4 v4_t;
-  static constexpr int D = 64, EPL = 8, NT = 4;
+  static constexpr int D = 64, EPL = 8, NT = 4, kElemBytes = 2;
   // tiles in flight ahead of the one being processed, per pass (register budget permitting)
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 2, kDepthKV = 2, kDepthQAccum = 1;
   // keep-all-tiles-in-registers variants of the fused kernels: forward only (the backward
@@ -269,6 +270,8 @@ struct Half64 {
       for (int ks = 0; ks < 2; ++ks)
         a[ks] = *reinterpret_cast<const v8_t*>(T + L.i16 * kTileStride + (8 * L.g16 + 32 * ks) * 2);
     }
+    // 16-byte piece j of the lane's row, as a 128-bit load of global memory brings it
+    __device__ __forceinline__ void put(int j, u32x4_t r) { a[j] = __builtin_bit_cast(v8_t, r); }
     __device__ __forceinline__ void unpack(float (&f)[16]) const {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -318,8 +321,8 @@ struct Half64 {
 
   // Products of two 16-row tiles, for the kernels that work tile pair by tile pair:
   // dots(a, b) = X_a X_b^T: lane (j, g) gets rows 4g .. 4g+3 (rows of a) of column j (row of b).
-  static __device__ __forceinline__ f32x4_t dots(const TileRows& a, const TileRows& b) {
-    f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+  static __device__ __forceinline__ f32x4_t dots(const TileRows& a, const TileRows& b,
+                                                 f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f}) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) d = E::mfma16(a.a[ks], b.a[ks], d);
     return d;
@@ -415,6 +418,9 @@ struct Half64 {
   static __device__ __forceinline__ void write_pair_at(unsigned char* at, float v0, float v1) {
     *reinterpret_cast<uint32_t*>(at) = E::pack2(v0, v1);
   }
+  static __device__ __forceinline__ void write_one_at(unsigned char* at, float v) {
+    *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(E::pack2(v, 0.0f));
+  }
   // element k of image row n
   static __device__ __forceinline__ float image_at(const unsigned char* image, int n, int k) {
     const uint32_t h =
@@ -429,7 +435,7 @@ typedef Half64<F16Elem> F16x64;
 struct F32x32 {
   typedef float io_t;
   static constexpr int kMap = 0;
-  static constexpr int D = 32, EPL = 4, NT = 2;
+  static constexpr int D = 32, EPL = 4, NT = 2, kElemBytes = 4;
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 3, kDepthKV = 2, kDepthQAccum = 2;
   static constexpr bool kShortFwd = true, kShortBwd = true;
   static constexpr int kImageStride = 36;
@@ -509,6 +515,10 @@ struct F32x32 {
         a[4 + i] = hi[i];
       }
     }
+    __device__ __forceinline__ void put(int j, u32x4_t r) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[4 * j + i] = __uint_as_float(r[i]);
+    }
     __device__ __forceinline__ void unpack(float (&f)[8]) const {
 #pragma unroll
       for (int i = 0; i < 8; ++i) f[i] = a[i];
@@ -543,8 +553,8 @@ struct F32x32 {
 
   // Products of two 16-row tiles (see Half64): dots(a, b) = X_a X_b^T, lane (j, g) gets rows
   // 4g .. 4g+3 of column j; eight 16x16x4 steps, each lane feeding the column it holds.
-  static __device__ __forceinline__ f32x4_t dots(const TileRows& a, const TileRows& b) {
-    f32x4_t d = {0.f, 0.f, 0.f, 0.f};
+  static __device__ __forceinline__ f32x4_t dots(const TileRows& a, const TileRows& b,
+                                                 f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f}) {
 #pragma unroll
     for (int s = 0; s < 8; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.a[s], b.a[s], d, 0, 0, 0);
     return d;
@@ -564,6 +574,48 @@ struct F32x32 {
       }
   }
 
+  // The state as the one 32 x 32 block it is (see Half64::BlockAcc).
+  struct BlockAcc {
+    static constexpr int kBlocks = 1;
+    f32x16_t v;
+    __device__ __forceinline__ void zero() {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] = 0.0f;
+    }
+    struct Frag {
+      float a[8], b[8];
+    };
+    static __device__ __forceinline__ Frag fetch(const unsigned char* Xt, const unsigned char* Yt,
+                                                 const Lane& L, int) {
+      const int off = (L.lane >> 5) * kTileStride + (L.lane & 31) * 4;
+      Frag f;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) {
+        f.a[s] = *reinterpret_cast<const float*>(Xt + off + 2 * s * kTileStride);
+        f.b[s] = *reinterpret_cast<const float*>(Yt + off + 2 * s * kTileStride);
+      }
+      return f;
+    }
+    __device__ __forceinline__ void mma(const Frag& f) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[s], f.b[s], v, 0, 0, 0);
+    }
+    __device__ __forceinline__ void mma_swapped(const Frag& f) {
+#pragma unroll
+      for (int s = 0; s < 8; ++s) v = __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[s], f.a[s], v, 0, 0, 0);
+    }
+    __device__ __forceinline__ void write_image(const Lane& L, int r0, int c0, float scale,
+                                                unsigned char* image) const {
+      const int c = c0 + (L.lane & 31);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<f32x4_t*>(image + (c * kImageStride + r0 + 8 * j + 4 * (L.lane >> 5)) * 4) =
+            quad(v, j) * scale;
+    }
+    static __device__ __forceinline__ int block_row0(int) { return 0; }
+    static __device__ __forceinline__ int block_col0(int) { return 0; }
+  };
+
   static __device__ __forceinline__ void write_image_pair(unsigned char* image, int n, int k,
                                                           float v0, float v1) {
     float* p = reinterpret_cast<float*>(image + (n * kImageStride + k) * 4);
@@ -575,6 +627,9 @@ struct F32x32 {
     float* p = reinterpret_cast<float*>(at);
     p[0] = v0;
     p[1] = v1;
+  }
+  static __device__ __forceinline__ void write_one_at(unsigned char* at, float v) {
+    *reinterpret_cast<float*>(at) = v;
   }
   static __device__ __forceinline__ float image_at(const unsigned char* image, int n, int k) {
     return *reinterpret_cast<const float*>(image + (n * kImageStride + k) * 4);

@@ -130,6 +130,49 @@ def test_causal_over_several_chunks(oracle, dtype, B, H, N, d):
     assert rel_l2(to_f64(O)[:, :, -1], to_f64(full)[:, :, -1]) <= 2 * bar
 
 
+@pytest.mark.parametrize("dtype,B,H,N,d", [
+    ("f32", 3, 2, 64, 64),       # one chunk of four tiles exactly
+    ("f32", 3, 2, 65, 64),       # two segments, the second of one row
+    ("f32", 1, 1, 1100, 64),     # as many segments as there may be, walked without given states
+    ("f32", 150, 2, 100, 64),    # one segment, two chunks
+    ("f32", 2, 2, 2100, 32),     # many segments, states given
+    ("f32", 8, 2, 260, 32),
+    ("f32", 128, 4, 321, 32),    # one segment of six chunks: padded chunks of the key role skipped
+    ("bf16", 1, 2, 1300, 64),    # states given
+    ("bf16", 70, 1, 520, 64),    # four segments, walked
+    ("f16", 260, 1, 209, 64),    # one segment, the second chunk short
+    ("bf16", 64, 4, 700, 16),    # one segment of six chunks, narrow rows
+    ("bf16", 300, 1, 60, 64),    # four-wave workgroups, one chunk
+    ("f16", 1030, 1, 100, 32),   # the same, two chunks
+    ("bf16", 300, 1, 150, 64),   # forward walked, backward resident
+])
+def test_causal_walk(oracle, dtype, B, H, N, d):
+    """The chunk walk of cotten_causal.hip on every workgroup shape and both ways of reaching a
+    segment, against the N x N oracle."""
+    print(f"[causal] walk {dtype} B={B} H={H} N={N} d={d}", flush=True)
+    Q, K, V, dO, mask = _inputs(4900 + N + d, dtype, B, H, N, d)
+    mask[B // 2:] = 0                    # left-padded histories of every length
+    for b in range(B // 2, B):
+        mask[b, N - 1 - (37 * b) % N:] = 1
+    tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
+    tm = torch.from_numpy(mask).cuda()
+    O = binding.cotten_attn_fwd(tq, tk, tv, tm, scale=0.2, causal=True)
+    grads = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, scale=0.2, causal=True)
+    O2 = binding.cotten_attn_fwd(tq, tk, tv, tm, scale=0.2, causal=True)
+    grads2 = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, scale=0.2, causal=True)
+    torch.cuda.synchronize()
+    ref = (oracle.causal_fwd(Q, K, V, mask, scale=0.2), *oracle.causal_bwd(Q, K, V, dO, mask, scale=0.2))
+    # Rows that attend one key are a single cosine times a row: the error of a 16-bit cosine (two
+    # roundings of 2^-9 per factor) is absolute, so the whole tensor is held to the bar.
+    for n, g, r in zip(("O", "dQ", "dK", "dV"), (O, *grads), ref):
+        e = rel_l2(to_f64(g), r)
+        print(f"[causal]   {n}: {e:.2e}", flush=True)
+        assert e <= bar_for(dtype), (n, e)
+    dead = np.broadcast_to((mask == 0)[:, None, :, None], ref[0].shape)
+    assert np.all(to_f64(grads[1])[dead] == 0.0) and np.all(to_f64(grads[2])[dead] == 0.0)
+    assert torch.equal(O, O2) and all(torch.equal(a, c) for a, c in zip(grads, grads2))
+
+
 def test_causal_chunks_layout_scales_workspace(oracle):
     """[B,N,H,d] layout and per-slice scales over several chunks; the caller's own workspace;
     a workspace that is too small is refused."""
