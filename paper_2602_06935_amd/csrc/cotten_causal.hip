@@ -25,8 +25,8 @@
 // units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 32 / 77, where 208-row
 // chunks joined by states in memory took 60 / 105 (three launches, 13 * 14 / 2 tile pairs per chunk
 // instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - memory, at about 3.7 TB/s (the two roles of
-// the backward each read all they need) with one chunk of loads in flight per wave; fp32 - the
-// matrix rate (64 flop per cycle and SIMD) of the tile pairs.
+// the backward each read all they need) with one chunk of loads in flight per wave; fp32 - latency:
+// with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is.
 #include "cotten_launch.h"
 #include "cotten_mfma_core.h"
 
@@ -58,16 +58,22 @@ struct Args {
   const float* after;
 };
 
-enum Role { kO = 0, kDq = 1, kDkDv = 2 };
+enum Role { kO = 0, kDq = 1, kDkDv = 2, kDv = 3, kDk = 4 };
+constexpr bool role_up(int role) { return role == kO || role == kDq; }  // ascending chunks
+// Rows of two pieces: one image set per workgroup is what lets two of them share a compute unit, so
+// dV and dK, which need different sets, are roles of their own there.
+template <int P>
+constexpr bool separate_dv_dk() { return P == 2; }
 
-// LDS: [per wave: x tile, y tile, P pieces each][two sets of P x P operand images][one flag per wave]
+// LDS: [per wave: x tile, y tile, P pieces each][one flag per wave][one (forward) or two sets of
+// P x P operand images]
 template <class F, int P, int WAVES>
 struct ScanLds {
-  static constexpr int kWaveBytes = 2 * P * kTileBytes;
-  static constexpr int kImages = WAVES * kWaveBytes;
+  static constexpr int kWaveBytes = 2 * P * F::kTileBytes;
+  static constexpr int kLive = WAVES * kWaveBytes;
+  static constexpr int kImages = kLive + 16 * 4;
   static constexpr int kSet = P * P * F::kImageBytes;
-  static constexpr int kLive = kImages + 2 * kSet;
-  static constexpr int kBytes = kLive + 16 * 4;
+  static constexpr int bytes(bool bwd) { return kImages + (bwd && !separate_dv_dk<P>() ? 2 : 1) * kSet; }
 };
 
 // A 16-row tile of a tensor pair on its way to LDS (load layout): piece [h][c] is bytes 128 c + 16 ch
@@ -76,21 +82,6 @@ template <int P>
 struct SharedRaw {
   u32x4_t x[2][P], y[2][P];
   int live;
-};
-
-// The wave's own 16 rows of one tensor, loaded from global memory in the layout of the products
-// (lane (i16, g16): bytes 128 c + 64 j + 16 g16 .. + 15 of row i16), so that they need no LDS at all.
-template <int P>
-struct OwnRaw {
-  u32x4_t r[P][2];
-};
-
-struct Buffers {
-  __amdgpu_buffer_rsrc_t r;
-  __device__ __forceinline__ Buffers(const unsigned char* base, int N, RowAddr row) {
-    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0,
-                                          (N - 1) * row.stride + row.bytes, 0x00020000);
-  }
 };
 
 // Bit h: row row0 + r8 + 8 h exists and, if a mask is given, is a valid key.
@@ -123,20 +114,6 @@ __device__ __forceinline__ void load_shared(SharedRaw<P>& t, const Lane& L, cons
   t.live = bits;
 }
 
-template <int P>
-__device__ __forceinline__ void load_own(OwnRaw<P>& t, const Lane& L, const Buffers& X, RowAddr addr,
-                                         int row0, bool live) {
-  const uint32_t at = static_cast<uint32_t>(row0 + L.i16) * addr.stride + L.g16 * 16;
-#pragma unroll
-  for (int c = 0; c < P; ++c)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int col = c * kRowBytes + 64 * j;
-      t.r[c][j] = __builtin_amdgcn_raw_buffer_load_b128(
-          X.r, live && col + L.g16 * 16 < addr.bytes ? at + col : kOutOfBuffer, 0, 0);
-    }
-}
-
 // The shared tile into LDS: xhat pieces, then y pieces.
 template <class F, int P>
 __device__ __forceinline__ void stage_shared(const SharedRaw<P>& t, const Lane& L, float eps,
@@ -152,13 +129,12 @@ __device__ __forceinline__ void stage_shared(const SharedRaw<P>& t, const Lane& 
       for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
     }
     const float inv = inv_norm_or_zero(row_sum8(ss), eps, ((t.live >> h) & 1) != 0);
-    const int off = (L.r8 + 8 * h) * kTileStride + L.ch * 16;
 #pragma unroll
     for (int c = 0; c < P; ++c) {
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[c][i] *= inv;
-      *reinterpret_cast<u32x4_t*>(tiles + c * kTileBytes + off) = F::pack(f[c]);
-      *reinterpret_cast<u32x4_t*>(tiles + (P + c) * kTileBytes + off) = t.y[h][c];
+      F::put(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[c]);
+      F::put_raw(tiles + (P + c) * F::kTileBytes, L.r8 + 8 * h, L.ch, t.y[h][c]);
     }
   }
 }
@@ -172,7 +148,7 @@ template <class F, int P, bool NATURAL, bool TRANSPOSED>
 struct Carried {
   typedef typename F::BlockAcc Acc;
   static constexpr int kPerPair = Acc::kBlocks, kBlocks = P * P * kPerPair;
-  static constexpr bool kScatter = NATURAL && (TRANSPOSED || F::kElemBytes == 4);
+  static constexpr bool kScatter = NATURAL && TRANSPOSED;
   static constexpr bool kPlain = TRANSPOSED || kScatter, kSwapped = NATURAL && !kScatter;
   Acc plain, swapped;
   int p, q, block;  // block `block` of piece p of x against piece q of y
@@ -184,18 +160,20 @@ struct Carried {
   // M: a row-major state of side D
   __device__ __forceinline__ void read(const float* __restrict__ M, int D, const Lane& L) {
     const int r0 = p * F::D + Acc::block_row0(block), c0 = q * F::D + Acc::block_col0(block);
-    const int run = 4 * (L.lane >> 5), col = L.lane & 31;
+    const int col = Acc::run_col(L);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) {
+      const int run = Acc::run_row(j, L);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        if (kPlain) plain.v[4 * j + i] = M[(r0 + 8 * j + run + i) * D + c0 + col];
-        if (kSwapped) swapped.v[4 * j + i] = M[(r0 + col) * D + c0 + 8 * j + run + i];
+        if (kPlain) plain.v[4 * j + i] = M[(r0 + run + i) * D + c0 + col];
+        if (kSwapped) swapped.v[4 * j + i] = M[(r0 + col) * D + c0 + run + i];
       }
+    }
   }
   __device__ __forceinline__ void add(const unsigned char* tiles, const Lane& L) {
     const typename Acc::Frag f =
-        Acc::fetch(tiles + p * kTileBytes, tiles + (P + q) * kTileBytes, L, block);
+        Acc::fetch(tiles + p * F::kTileBytes, tiles + (P + q) * F::kTileBytes, L, block);
     if (kPlain) plain.mma(f);
     if (kSwapped) swapped.mma_swapped(f);
   }
@@ -208,7 +186,7 @@ struct Carried {
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          F::write_one_at(natural + at + F::image_offset(r0 + 8 * j + 4 * (L.lane >> 5) + i, c0 + (L.lane & 31)),
+          F::write_one_at(natural + at + F::image_offset(r0 + Acc::run_row(j, L) + i, c0 + Acc::run_col(L)),
                           plain.v[4 * j + i]);
     }
   }
@@ -225,14 +203,6 @@ __device__ __forceinline__ void apply_set(const typename F::TileRows (&X)[P], co
     if (c == 0) F::apply(X[c], W, out);
     else F::apply_onto(X[c], W, out);
   }
-}
-
-template <class F, int P>
-__device__ __forceinline__ void own_rows(const OwnRaw<P>& t, typename F::TileRows (&x)[P]) {
-#pragma unroll
-  for (int c = 0; c < P; ++c)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) x[c].put(j, t.r[c][j]);
 }
 
 // 1/r of the lane's own row (0 if the row does not take part)
@@ -291,7 +261,7 @@ template <class F, int P, int WAVES, int ROLE>
 __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment) {
   typedef ScanLds<F, P, WAVES> Lds;
   typedef typename F::TileRows TileRows;
-  constexpr bool kUp = ROLE != kDkDv;  // ascending chunks
+  constexpr bool kUp = role_up(ROLE), kTwoOwn = ROLE != kO && ROLE != kDv;
   constexpr int kState = F::D * P;
   const Lane L;
   const int N = a.N, wave = L.wave;
@@ -313,11 +283,11 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 
   unsigned char* mine = smem + wave * Lds::kWaveBytes;
   unsigned char* natural = smem + Lds::kImages;
-  unsigned char* transposed = smem + Lds::kImages + (ROLE == kO ? 0 : Lds::kSet);
+  unsigned char* transposed = smem + Lds::kImages + (ROLE == kDkDv ? Lds::kSet : 0);
   int* live = reinterpret_cast<int*>(smem + Lds::kLive);
 
   // the state blocks go to the waves with the fewest tile pairs
-  typedef Carried<F, P, ROLE != kO, ROLE != kDq> State;
+  typedef Carried<F, P, ROLE != kO && ROLE != kDv, ROLE != kDq && ROLE != kDk> State;
   const int duty = kUp ? wave : WAVES - 1 - wave;
   const bool on_duty = duty < State::kBlocks;
   State state(on_duty ? duty : 0);
@@ -344,7 +314,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
     if (applies(0)) {
       next_live = own_live(tile_of(0));
       load_own<P>(nx, L, ox, addr, row0, next_live);
-      if (ROLE != kO) load_own<P>(ny, L, oy, addr, row0, next_live);
+      if (kTwoOwn) load_own<P>(ny, L, oy, addr, row0, next_live);
     }
   }
   if (!kUp && keys != nullptr && steps > 4) {
@@ -375,8 +345,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
       for (int i = 0; i < 2 * F::EPL; ++i) zeros[c][i] = 0.0f;
 #pragma unroll 1
     for (int t = first * WAVES + wave; t < below * WAVES; t += WAVES) {
-      store_own<F, P>(a.dV + base, t * TR + L.i16, N, addr, L, zeros);
-      store_own<F, P>(a.dK + base, t * TR + L.i16, N, addr, L, zeros);
+      if (ROLE != kDk) store_own<F, P>(a.dV + base, t * TR + L.i16, N, addr, L, zeros);
+      if (ROLE != kDv) store_own<F, P>(a.dK + base, t * TR + L.i16, N, addr, L, zeros);
     }
   }
 #pragma unroll 1
@@ -387,7 +357,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
     if (have && on_duty && applies(step)) state.write(natural, transposed, L);
     TileRows x[P], y[P];
     own_rows<F, P>(nx, x);
-    if (ROLE != kO) own_rows<F, P>(ny, y);
+    if (kTwoOwn) own_rows<F, P>(ny, y);
     const bool row_live = next_live;
     const int tile = tile_of(step);
     if (step + 1 < steps) {
@@ -396,7 +366,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
       if (applies(step + 1)) {
         next_live = own_live(tile_of(step + 1));
         load_own<P>(nx, L, ox, addr, row0, next_live);
-        if (ROLE != kO) load_own<P>(ny, L, oy, addr, row0, next_live);
+        if (kTwoOwn) load_own<P>(ny, L, oy, addr, row0, next_live);
       }
     }
     __syncthreads();
@@ -429,7 +399,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll
           for (int c = 0; c < P; ++c) {
             TileRows key;
-            key.load(tu + ((ROLE == kO ? 0 : P) + c) * kTileBytes, L);
+            key.load(tu + ((ROLE == kO ? 0 : P) + c) * F::kTileBytes, L);
             pt = F::dots(key, own[c], pt);
           }
           if (u == wave) {
@@ -439,7 +409,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
           }
 #pragma unroll
           for (int c = 0; c < P; ++c)
-            F::add_transposed_product(tu + ((ROLE == kO ? P : 0) + c) * kTileBytes, L, pt, out[c]);
+            F::add_transposed_product(tu + ((ROLE == kO ? P : 0) + c) * F::kTileBytes, L, pt, out[c]);
         }
         const float inv_r = own_inv<F, P>(x, a.eps, row_live, L);
         const float factor = ROLE == kO ? inv_r * scale : scale;
@@ -459,6 +429,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
         const float inv_r = any_key ? own_inv<F, P>(x, a.eps, row_live, L) : 0.0f;
 #pragma unroll
         for (int kind = 0; kind < 2; ++kind) {
+          if (ROLE == (kind == 0 ? kDk : kDv)) continue;
           float o[P][2 * F::EPL];
 #pragma unroll
           for (int c = 0; c < P; ++c)
@@ -467,7 +438,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
           if (any_key) {
             const TileRows(&own)[P] = kind == 0 ? x : y;
             // tiles whose rows meet the own ones in dots(), and those the result is made of
-            const int left = (kind == 0 ? 0 : P) * kTileBytes, right = (kind == 0 ? P : 0) * kTileBytes;
+            const int left = (kind == 0 ? 0 : P) * F::kTileBytes, right = (kind == 0 ? P : 0) * F::kTileBytes;
             f32x4_t out[P][F::NT];
 #pragma unroll
             for (int c = 0; c < P; ++c) {
@@ -488,7 +459,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll
               for (int c = 0; c < P; ++c) {
                 TileRows query;
-                query.load(tt + left + c * kTileBytes, L);
+                query.load(tt + left + c * F::kTileBytes, L);
                 p = F::dots(query, own[c], p);
               }
               if (t == wave) {
@@ -498,7 +469,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
               }
 #pragma unroll
               for (int c = 0; c < P; ++c)
-                F::add_transposed_product(tt + right + c * kTileBytes, L, p, out[c]);
+                F::add_transposed_product(tt + right + c * F::kTileBytes, L, p, out[c]);
             }
             const float factor = kind == 0 ? inv_r * scale : scale;
 #pragma unroll
@@ -534,11 +505,13 @@ __global__ __launch_bounds__(64 * WAVES, P == 1 ? 4 : 2) void causal_scan_fwd_ke
   scan_segment<F, P, WAVES, kO>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
 }
 
-// blockIdx.y == 0: dQ.   blockIdx.y == 1: dK and dV.
+// blockIdx.y == 0: dQ.   blockIdx.y == 1: dK and dV, or (1, 2) dV, dK.
 template <class F, int P, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, P == 1 ? 4 : 2) void causal_scan_bwd_kernel(const Args a) {
   if (blockIdx.y == 0) scan_segment<F, P, WAVES, kDq>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
-  else scan_segment<F, P, WAVES, kDkDv>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+  else if constexpr (!separate_dv_dk<P>()) scan_segment<F, P, WAVES, kDkDv>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+  else if (blockIdx.y == 1) scan_segment<F, P, WAVES, kDv>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+  else scan_segment<F, P, WAVES, kDk>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
 }
 
 constexpr int kThreads = 256;
@@ -637,15 +610,14 @@ hipError_t run_scan(const Problem& p, bool bwd) {
     a.before = p.workspace;
     a.after = p.workspace + static_cast<size_t>(slices) * a.segments * side * side;
   }
-  constexpr int lds = ScanLds<F, P, WAVES>::kBytes;
-  static_assert(lds <= 80 * 1024, "two workgroups per compute unit");
+  const int lds = ScanLds<F, P, WAVES>::bytes(bwd);
   const void* kern = bwd ? reinterpret_cast<const void*>(causal_scan_bwd_kernel<F, P, WAVES>)
                          : reinterpret_cast<const void*>(causal_scan_fwd_kernel<F, P, WAVES>);
   const hipError_t err = grant_dynamic_lds(kern, lds);
   if (err != hipSuccess) return err;
   const unsigned grid = static_cast<unsigned>(slices) * a.segments;
   if (bwd)
-    hipLaunchKernelGGL((causal_scan_bwd_kernel<F, P, WAVES>), dim3(grid, 2), dim3(64 * WAVES), lds, p.stream, a);
+    hipLaunchKernelGGL((causal_scan_bwd_kernel<F, P, WAVES>), dim3(grid, separate_dv_dk<P>() ? 3 : 2), dim3(64 * WAVES), lds, p.stream, a);
   else
     hipLaunchKernelGGL((causal_scan_fwd_kernel<F, P, WAVES>), dim3(grid), dim3(64 * WAVES), lds, p.stream, a);
   return hipGetLastError();

@@ -88,7 +88,7 @@ const float* reduce_generic(const Problem& p, const Plan& plan, int nstates) {
 // states, their reduction, the kept state, the apply kernels, <S, dS>; one launch per direction
 // where the sequence is not cut.
 hipError_t run_wide(const Problem& p, const Plan& plan, bool bwd) {
-  if (wide_fused_applies(p.dtype, p.D, p.B, p.H, plan.splits, bwd)) return launch_wide_fused(p, plan, bwd);
+  if (wide_fused_applies(p.dtype, p.B, p.H, plan.splits, bwd)) return launch_wide_fused(p, plan, bwd);
   const int BH = p.B * p.H;
   const int dd = p.D * p.D;
   if (hipError_t err = launch_wide_states(p, plan, bwd)) return err;
@@ -184,7 +184,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, bool allow_re
     // partial states, plus the reduced states when there is more than one partial
     // (one launch per direction: the state never leaves the compute unit)
     plan.workspace_floats =
-        wide_fused_applies(dtype, D, B, H, static_cast<int>(splits), is_bwd)
+        wide_fused_applies(dtype, B, H, static_cast<int>(splits), is_bwd)
             ? 0
             : static_cast<size_t>(BH) * D * D * nstates * (splits + (splits > 1 ? 1 : 0));
   }

@@ -81,8 +81,13 @@ hipError_t launch_wide_apply(const Problem& p, const Plan& plan, const float* st
                              const float* dstates, bool bwd);
 // Sequences that are not cut (wide_fused_applies): one launch per direction, the state stays in
 // LDS, no workspace; the forward writes p.saved_state, the backward p.dlog_scale, when given.
-bool wide_fused_applies(int dtype, int D, int B, int H, int splits, bool bwd);
+bool wide_fused_applies(int dtype, int B, int H, int splits, bool bwd);
 hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd);
+// The same three for fp32 rows (cotten_wide32.hip); the functions above hand over to them.
+hipError_t launch_wide32_states(const Problem& p, const Plan& plan, bool bwd);
+hipError_t launch_wide32_fused(const Problem& p, const Plan& plan, bool bwd);
+hipError_t launch_wide32_apply(const Problem& p, const Plan& plan, const float* states,
+                               const float* dstates, bool bwd);
 
 // MFMA path: bf16 or fp16 I/O with d_h = 64 and fp32 I/O with d_h = 32 (128-byte rows), and
 // the half-width shapes (16-bit d_h = 32, fp32 d_h = 16) zero-padded onto the same kernels.
@@ -91,9 +96,8 @@ int mfma_state_dim(int dtype);  // side of the (possibly zero-padded) state the 
 hipError_t launch_mfma_fwd(const Problem& p, const Plan& plan);
 hipError_t launch_mfma_bwd(const Problem& p, const Plan& plan);
 
-// Resident kernels: short bf16 / fp16 sequences (a slice fits the LDS of one compute unit).  With
-// fp32 rows the matrix cores, 16 times slower there, bound each of their phases and the
-// tile-streaming kernels are faster, so those keep all fp32 shapes.
+// Resident kernels: short bf16 / fp16 sequences (a slice fits the LDS of one compute unit; fp32 rows
+// take three times the room there and stay on the tile-streaming kernels).
 bool resident_supports(int dtype, int D, int N);
 hipError_t launch_resident_fwd(const Problem& p);
 hipError_t launch_resident_bwd(const Problem& p);

@@ -1,4 +1,4 @@
-// Device code shared by the MFMA kernels for 128-byte rows (bf16 d_h = 64, fp32 d_h = 32):
+// Device code shared by the MFMA kernels: rows in pieces of 128 bytes (16-bit d_h = 64, fp32 d_h = 32):
 // lane geometry, the two element formats with their MFMA products, tile loads through
 // buffer resources, staging into LDS tiles, and the epilogue helpers.
 #pragma once
@@ -172,6 +172,7 @@ struct Half64 {
   // keep-all-tiles-in-registers variants of the fused kernels: forward only (the backward
   // does not have the registers)
   static constexpr bool kShortFwd = true, kShortBwd = false;
+  static constexpr int kTileStride = mfma::kTileStride, kTileBytes = mfma::kTileBytes;
   static constexpr int kImageStride = 72;                 // elements per image row
   static constexpr int kImageBytes = D * kImageStride * 2;
   // Apply products leave lane (i16, g16) with the columns 32j + 8*g16 .. +7 (j = 0, 1) of tile
@@ -197,6 +198,14 @@ struct Half64 {
 #pragma unroll
     for (int i = 0; i < 4; ++i) r[i] = E::pack2(f[2 * i], f[2 * i + 1]);
     return r;
+  }
+
+  // the lane's EPL values (load layout: columns 8*ch ..) of tile row `row`
+  static __device__ __forceinline__ void put(unsigned char* T, int row, int ch, const float (&f)[8]) {
+    put_raw(T, row, ch, pack(f));
+  }
+  static __device__ __forceinline__ void put_raw(unsigned char* T, int row, int ch, u32x4_t r) {
+    *reinterpret_cast<u32x4_t*>(T + row * kTileStride + ch * 16) = r;
   }
 
   // Operand of the 32x32x16 MFMA for a contraction over the 16 tile rows: lane gets, for
@@ -270,8 +279,21 @@ struct Half64 {
       for (int ks = 0; ks < 2; ++ks)
         a[ks] = *reinterpret_cast<const v8_t*>(T + L.i16 * kTileStride + (8 * L.g16 + 32 * ks) * 2);
     }
-    // 16-byte piece j of the lane's row, as a 128-bit load of global memory brings it
-    __device__ __forceinline__ void put(int j, u32x4_t r) { a[j] = __builtin_bit_cast(v8_t, r); }
+    // the two 16-byte pieces of the lane's row as 128-bit loads of global memory bring them
+    __device__ __forceinline__ void set(u32x4_t r0, u32x4_t r1) {
+      a[0] = __builtin_bit_cast(v8_t, r0);
+      a[1] = __builtin_bit_cast(v8_t, r1);
+    }
+    // from the row's values: f[8j + i] is column 32j + 8*g16 + i
+    __device__ __forceinline__ void set(const float (&f)[16]) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        float h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h[i] = f[8 * ks + i];
+        a[ks] = __builtin_bit_cast(v8_t, Half64::pack(h));
+      }
+    }
     __device__ __forceinline__ void unpack(float (&f)[16]) const {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -369,6 +391,8 @@ struct Half64 {
     __device__ __forceinline__ void mma_swapped(const Frag& f) {
       v = E::mfma32(f.b, f.a, v);
     }
+    static __device__ __forceinline__ int run_row(int j, const Lane& L) { return 8 * j + 4 * (L.lane >> 5); }
+    static __device__ __forceinline__ int run_col(const Lane& L) { return L.lane & 31; }
     // The lane holds, of the accumulated block, column lane%32 and rows 8j + 4*(lane/32) .. +3:
     // four neighbours of image row (c0 + column), which go out as one 64-bit write.
     //   after mma():          r0 = 32*(block/2), c0 = 32*(block%2)  ->  image[n][m] (transposed)
@@ -415,6 +439,9 @@ struct Half64 {
   static __device__ __forceinline__ int image_offset(int n, int k) {
     return (image_row(n) * kImageStride + k) * 2;
   }
+  static __device__ __forceinline__ void write_four_at(unsigned char* at, f32x4_t v) {
+    *reinterpret_cast<u32x2_t*>(at) = u32x2_t{E::pack2(v[0], v[1]), E::pack2(v[2], v[3])};
+  }
   static __device__ __forceinline__ void write_pair_at(unsigned char* at, float v0, float v1) {
     *reinterpret_cast<uint32_t*>(at) = E::pack2(v0, v1);
   }
@@ -432,18 +459,58 @@ struct Half64 {
 typedef Half64<Bf16Elem> Bf16x64;
 typedef Half64<F16Elem> F16x64;
 
+// fp32 rows on the bf16 matrix cores (1/16 of whose rate the fp32 products run at): a value is cut
+// into three bf16 pieces, x = h + m + l exactly (8 + 8 + 8 of its 24 significant bits: h the
+// upper half of the word, m the remainder rounded to bf16, l what is left, which fits), and a
+// product of two values is the sum of the six products of pieces that reach its 24 bits,
+//     h h' + (h m' + m h') + (h l' + l h' + m m'),
+// each exact, accumulated in fp32.  What is left out (m l', l m', l l') is below 2^-24 of the product
+// and of either sign.  Six products at 16 times the rate: 2.7 times the fp32 matrix rate, for 11
+// vector operations per pair of values cut.  Measured (a training step, us, fp32 products before and
+// this): 512 slices x 200 rows, d_h = 128 333 and 202 (with the kernels of cotten_wide32.hip), d_h = 32
+// 31.3 and 30.1; distance from a 64-bit evaluation 1.5e-7 ... 2.5e-7 and 1.1e-7 ... 1.5e-7.
+// An infinity has no such pieces: it comes out as NaN in every element it reaches.
+struct Pieces {
+  bf16x8_t h, m, l;  // of eight values
+};
+__device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+  h = __builtin_amdgcn_perm(ub, ua, 0x07060302);  // the upper halves
+  const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
+  m = pack_bf16(ra, rb);
+  const float sa = ra - Bf16Elem::lo(m), sb = rb - Bf16Elem::hi(m);
+  l = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302);
+}
+// the two values back, exactly
+__device__ __forceinline__ float whole_lo(uint32_t h, uint32_t m, uint32_t l) {
+  return Bf16Elem::lo(h) + (Bf16Elem::lo(m) + Bf16Elem::lo(l));
+}
+__device__ __forceinline__ float whole_hi(uint32_t h, uint32_t m, uint32_t l) {
+  return Bf16Elem::hi(h) + (Bf16Elem::hi(m) + Bf16Elem::hi(l));
+}
+
 struct F32x32 {
   typedef float io_t;
   static constexpr int kMap = 0;
   static constexpr int D = 32, EPL = 4, NT = 2, kElemBytes = 4;
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 3, kDepthKV = 2, kDepthQAccum = 2;
   static constexpr bool kShortFwd = true, kShortBwd = true;
-  static constexpr int kImageStride = 36;
-  static constexpr int kImageBytes = D * kImageStride * 4;
+  // A row of an LDS tile, or of an operand image: its 32 h pieces, its 32 m pieces, its 32 l pieces
+  // (16 bytes of padding make the stride an odd number of 16-byte units).  Within a plane column
+  // 16j + 4g + i sits at place 8g + 4j + i: the eight columns that a lane of group g holds in the
+  // product layout next to each other.
+  static constexpr int kPlane = 64, kTileStride = 3 * kPlane + 16, kTileBytes = TR * kTileStride;
+  static constexpr int kImageStride = kTileStride;
+  static constexpr int kImageBytes = D * kImageStride;
+  static __device__ __forceinline__ int place(int column) {
+    return 8 * ((column >> 2) & 3) + 4 * (column >> 4) + (column & 3);
+  }
+  static __device__ __forceinline__ int column(int place) {
+    return 16 * ((place >> 2) & 1) + 4 * (place >> 3) + (place & 3);
+  }
   // Apply products leave lane (i16, g16) with the columns 16j + 4*g16 .. +3 (j = 0, 1) of tile
   // row i16 (value 4*nt + v is column out_col(nt, g16) + v); image rows stay in place.
   static __device__ __forceinline__ int out_col(int nt, int g16) { return 16 * nt + 4 * g16; }
-  static __device__ __forceinline__ int image_row(int n) { return n; }
 
   static __device__ __forceinline__ void unpack(const u32x4_t r, float (&f)[4]) {
 #pragma unroll
@@ -456,48 +523,87 @@ struct F32x32 {
     return r;
   }
 
+  // four neighbouring places (multiples of four) of a plane row
+  static __device__ __forceinline__ void write_four(unsigned char* at, float a, float b, float c, float d) {
+    u32x2_t h, m, l;
+    uint32_t ph, pm, pl;
+    split_pair(a, b, ph, pm, pl);
+    h[0] = ph, m[0] = pm, l[0] = pl;
+    split_pair(c, d, ph, pm, pl);
+    h[1] = ph, m[1] = pm, l[1] = pl;
+    *reinterpret_cast<u32x2_t*>(at) = h;
+    *reinterpret_cast<u32x2_t*>(at + kPlane) = m;
+    *reinterpret_cast<u32x2_t*>(at + 2 * kPlane) = l;
+  }
+  // the lane's EPL values (load layout: columns 4*ch ..) of tile row `row`
+  static __device__ __forceinline__ void put(unsigned char* T, int row, int ch, const float (&f)[4]) {
+    write_four(T + row * kTileStride + 16 * (ch & 3) + 8 * (ch >> 2), f[0], f[1], f[2], f[3]);
+  }
+  static __device__ __forceinline__ void put_raw(unsigned char* T, int row, int ch, u32x4_t r) {
+    float f[4];
+    unpack(r, f);
+    put(T, row, ch, f);
+  }
+
+  static __device__ __forceinline__ f32x16_t mfma32(const Pieces& a, const Pieces& b, f32x16_t v) {
+    v = Bf16Elem::mfma32(a.l, b.h, v);
+    v = Bf16Elem::mfma32(a.h, b.l, v);
+    v = Bf16Elem::mfma32(a.m, b.m, v);
+    v = Bf16Elem::mfma32(a.m, b.h, v);
+    v = Bf16Elem::mfma32(a.h, b.m, v);
+    return Bf16Elem::mfma32(a.h, b.h, v);
+  }
+  static __device__ __forceinline__ f32x4_t mfma16(const Pieces& a, const Pieces& b, f32x4_t v) {
+    v = Bf16Elem::mfma16(a.l, b.h, v);
+    v = Bf16Elem::mfma16(a.h, b.l, v);
+    v = Bf16Elem::mfma16(a.m, b.m, v);
+    v = Bf16Elem::mfma16(a.m, b.h, v);
+    v = Bf16Elem::mfma16(a.h, b.m, v);
+    return Bf16Elem::mfma16(a.h, b.h, v);
+  }
+  // Operand of the 32x32x16 MFMA for a contraction over the 16 tile rows (see Half64): lane gets,
+  // for place lane%32, the 8 rows 8*(lane/32) .. +7.
+  static __device__ __forceinline__ bf16x8_t plane_operand(const unsigned char* p) {
+    const bf16x4_t lo = Bf16Elem::read_tr(p);
+    const bf16x4_t hi = Bf16Elem::read_tr(p + 4 * kTileStride);
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
+  static __device__ __forceinline__ Pieces rows_operand(const unsigned char* T, const Lane& L) {
+    const int row = 8 * (L.g16 >> 1) + (L.i16 >> 2), at = 16 * (L.g16 & 1) + 4 * (L.i16 & 3);
+    const unsigned char* p = T + row * kTileStride + at * 2;
+    return Pieces{plane_operand(p), plane_operand(p + kPlane), plane_operand(p + 2 * kPlane)};
+  }
+  // what a lane holds of a 32 x 32 result: column column(lane%32), and rows 16*(lane/32) + 4g .. +3
+  static __device__ __forceinline__ int run_row(int g, const Lane& L) { return 4 * g + 16 * (L.lane >> 5); }
+  static __device__ __forceinline__ int run_col(const Lane& L) { return column(L.lane & 31); }
+
   struct Acc {
     f32x16_t v;
     __device__ __forceinline__ void zero() {
 #pragma unroll
       for (int i = 0; i < 16; ++i) v[i] = 0.0f;
     }
-    // += (X tile)^T (Y tile): 32x32x2 steps, lane = column, half-wave = row of the pair
+    // += (X tile)^T (Y tile)
     __device__ __forceinline__ void mfma(const unsigned char* Xt, const unsigned char* Yt,
                                          const Lane& L) {
-      const int off = (L.lane >> 5) * kTileStride + (L.lane & 31) * 4;
-      float a[8], b[8];
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        a[s] = *reinterpret_cast<const float*>(Xt + off + 2 * s * kTileStride);
-        b[s] = *reinterpret_cast<const float*>(Yt + off + 2 * s * kTileStride);
-      }
-#pragma unroll
-      for (int s = 0; s < 8; ++s) v = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], v, 0, 0, 0);
+      v = mfma32(rows_operand(Xt, L), rows_operand(Yt, L), v);
     }
     __device__ __forceinline__ f32x4_t group(int g) const { return quad(v, g); }
-    static __device__ __forceinline__ int group_row(int g, const Lane& L) {
-      return 8 * g + 4 * (L.lane >> 5);
-    }
-    static __device__ __forceinline__ int group_col(int, const Lane& L) { return L.lane & 31; }
+    static __device__ __forceinline__ int group_row(int g, const Lane& L) { return run_row(g, L); }
+    static __device__ __forceinline__ int group_col(int, const Lane& L) { return run_col(L); }
     static constexpr int kGroups = 4;
   };
 
-  // frag[nt][s] = W[k(s)][16*nt + i16], contraction step s taking column
-  // k(s) = 16*(s/4) + 4*g16 + s%4: the columns a TileRows lane holds.
+  // frag[nt] = W[k][16*nt + i16] for the eight columns k that a TileRows lane holds.
   struct Operand {
-    float frag[2][8];
+    Pieces frag[2];
     __device__ __forceinline__ void load(const unsigned char* image, const Lane& L) {
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) {
-        const f32x4_t* p = reinterpret_cast<const f32x4_t*>(
-            image + ((16 * nt + L.i16) * kImageStride + 4 * L.g16) * 4);
-        const f32x4_t lo = p[0], hi = p[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          frag[nt][i] = lo[i];
-          frag[nt][4 + i] = hi[i];
-        }
+        const unsigned char* p = image + (16 * nt + L.i16) * kImageStride + 16 * L.g16;
+        frag[nt].h = *reinterpret_cast<const bf16x8_t*>(p);
+        frag[nt].m = *reinterpret_cast<const bf16x8_t*>(p + kPlane);
+        frag[nt].l = *reinterpret_cast<const bf16x8_t*>(p + 2 * kPlane);
       }
     }
   };
@@ -505,35 +611,49 @@ struct F32x32 {
   // Lane (i16, g16) holds bytes 64j + 16*g16 .. +15 (j = 0, 1) of tile row i16: the columns
   // an apply product leaves it with.
   struct TileRows {
-    float a[8];
+    Pieces a;
     __device__ __forceinline__ void load(const unsigned char* T, const Lane& L) {
-      const f32x4_t* p = reinterpret_cast<const f32x4_t*>(T + L.i16 * kTileStride + 16 * L.g16);
-      const f32x4_t lo = p[0], hi = p[4];
+      const unsigned char* p = T + L.i16 * kTileStride + 16 * L.g16;
+      a.h = *reinterpret_cast<const bf16x8_t*>(p);
+      a.m = *reinterpret_cast<const bf16x8_t*>(p + kPlane);
+      a.l = *reinterpret_cast<const bf16x8_t*>(p + 2 * kPlane);
+    }
+    // from the row's values: f[4j + i] is column 16j + 4*g16 + i
+    __device__ __forceinline__ void set(const float (&f)[8]) {
+      u32x4_t h, m, l;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        a[i] = lo[i];
-        a[4 + i] = hi[i];
+        uint32_t ph, pm, pl;
+        split_pair(f[2 * i], f[2 * i + 1], ph, pm, pl);
+        h[i] = ph, m[i] = pm, l[i] = pl;
       }
+      a = Pieces{__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, m),
+                 __builtin_bit_cast(bf16x8_t, l)};
     }
-    __device__ __forceinline__ void put(int j, u32x4_t r) {
+    __device__ __forceinline__ void set(u32x4_t r0, u32x4_t r1) {
+      float f[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[4 * j + i] = __uint_as_float(r[i]);
+      for (int i = 0; i < 4; ++i) {
+        f[i] = __uint_as_float(r0[i]);
+        f[4 + i] = __uint_as_float(r1[i]);
+      }
+      set(f);
     }
     __device__ __forceinline__ void unpack(float (&f)[8]) const {
+      const u32x4_t h = __builtin_bit_cast(u32x4_t, a.h), m = __builtin_bit_cast(u32x4_t, a.m),
+                    l = __builtin_bit_cast(u32x4_t, a.l);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) f[i] = a[i];
+      for (int i = 0; i < 4; ++i) {
+        f[2 * i] = whole_lo(h[i], m[i], l[i]);
+        f[2 * i + 1] = whole_hi(h[i], m[i], l[i]);
+      }
     }
     __device__ __forceinline__ void forget_unpacked() {}
   };
   static __device__ __forceinline__ void apply(const TileRows& X, const Operand& W,
                                                f32x4_t (&out)[2]) {
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      out[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-        out[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W.frag[nt][s], X.a[s], out[nt], 0, 0, 0);
-    }
+    out[0] = out[1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    apply_onto(X, W, out);
   }
   static __device__ __forceinline__ void apply(const unsigned char* T, const Operand& W,
                                                const Lane& L, f32x4_t (&out)[2]) {
@@ -545,33 +665,44 @@ struct F32x32 {
   static __device__ __forceinline__ void apply_onto(const TileRows& X, const Operand& W,
                                                     f32x4_t (&out)[2]) {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int s = 0; s < 8; ++s)
-        out[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(W.frag[nt][s], X.a[s], out[nt], 0, 0, 0);
+    for (int nt = 0; nt < 2; ++nt) out[nt] = mfma16(W.frag[nt], X.a, out[nt]);
   }
 
   // Products of two 16-row tiles (see Half64): dots(a, b) = X_a X_b^T, lane (j, g) gets rows
-  // 4g .. 4g+3 of column j; eight 16x16x4 steps, each lane feeding the column it holds.
+  // 4g .. 4g+3 of column j.
   static __device__ __forceinline__ f32x4_t dots(const TileRows& a, const TileRows& b,
                                                  f32x4_t d = f32x4_t{0.f, 0.f, 0.f, 0.f}) {
-#pragma unroll
-    for (int s = 0; s < 8; ++s) d = __builtin_amdgcn_mfma_f32_16x16x4f32(a.a[s], b.a[s], d, 0, 0, 0);
-    return d;
+    return mfma16(a.a, b.a, d);
   }
-  // out += X^T P: step v contracts over the rows 4g + v (g = 0..3), which is the row of P a lane
-  // of group g holds in p[v]; the matching element of X is read from the LDS tile directly.
+  // out += X^T P (see Half64).  The contraction runs over 16 rows where a 16x16x32 product takes 32:
+  // the two halves of its depth carry two products of pieces at a time, three instead of six.
   static __device__ __forceinline__ void add_transposed_product(const unsigned char* T,
                                                                 const Lane& L, f32x4_t p,
                                                                 f32x4_t (&out)[2]) {
+    u32x2_t h, m, l;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int i = 0; i < 2; ++i) {
+      uint32_t ph, pm, pl;
+      split_pair(p[2 * i], p[2 * i + 1], ph, pm, pl);
+      h[i] = ph, m[i] = pm, l[i] = pl;
+    }
+    const bf16x4_t bh = __builtin_bit_cast(bf16x4_t, h), bm = __builtin_bit_cast(bf16x4_t, m),
+                   bl = __builtin_bit_cast(bf16x4_t, l);
+    const bf16x8_t hh = both(bh, bh), mm = both(bm, bm), hl = both(bh, bl);
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const float x = *reinterpret_cast<const float*>(T + (4 * L.g16 + v) * kTileStride +
-                                                        (16 * nt + L.i16) * 4);
-        out[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, p[v], out[nt], 0, 0, 0);
-      }
+    for (int nt = 0; nt < 2; ++nt) {
+      const unsigned char* at =
+          T + (4 * L.g16 + (L.i16 >> 2)) * kTileStride + (8 * (L.i16 & 3) + 4 * nt) * 2;
+      const bf16x4_t xh = Bf16Elem::read_tr(at), xm = Bf16Elem::read_tr(at + kPlane),
+                     xl = Bf16Elem::read_tr(at + 2 * kPlane);
+      const bf16x8_t xhm = both(xh, xm);
+      out[nt] = Bf16Elem::mfma16(both(xl, xh), hl, out[nt]);  // l h' + h l'
+      out[nt] = Bf16Elem::mfma16(xhm, mm, out[nt]);           // h m' + m m'
+      out[nt] = Bf16Elem::mfma16(xhm, hh, out[nt]);           // h h' + m h'
+    }
+  }
+  static __device__ __forceinline__ bf16x8_t both(bf16x4_t a, bf16x4_t b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
   }
 
   // The state as the one 32 x 32 block it is (see Half64::BlockAcc).
@@ -583,34 +714,21 @@ struct F32x32 {
       for (int i = 0; i < 16; ++i) v[i] = 0.0f;
     }
     struct Frag {
-      float a[8], b[8];
+      Pieces a, b;
     };
     static __device__ __forceinline__ Frag fetch(const unsigned char* Xt, const unsigned char* Yt,
                                                  const Lane& L, int) {
-      const int off = (L.lane >> 5) * kTileStride + (L.lane & 31) * 4;
-      Frag f;
-#pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        f.a[s] = *reinterpret_cast<const float*>(Xt + off + 2 * s * kTileStride);
-        f.b[s] = *reinterpret_cast<const float*>(Yt + off + 2 * s * kTileStride);
-      }
-      return f;
+      return Frag{rows_operand(Xt, L), rows_operand(Yt, L)};
     }
-    __device__ __forceinline__ void mma(const Frag& f) {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) v = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[s], f.b[s], v, 0, 0, 0);
-    }
-    __device__ __forceinline__ void mma_swapped(const Frag& f) {
-#pragma unroll
-      for (int s = 0; s < 8; ++s) v = __builtin_amdgcn_mfma_f32_32x32x2f32(f.b[s], f.a[s], v, 0, 0, 0);
-    }
+    __device__ __forceinline__ void mma(const Frag& f) { v = mfma32(f.a, f.b, v); }
+    __device__ __forceinline__ void mma_swapped(const Frag& f) { v = mfma32(f.b, f.a, v); }
+    static __device__ __forceinline__ int run_row(int j, const Lane& L) { return F32x32::run_row(j, L); }
+    static __device__ __forceinline__ int run_col(const Lane& L) { return F32x32::run_col(L); }
     __device__ __forceinline__ void write_image(const Lane& L, int r0, int c0, float scale,
                                                 unsigned char* image) const {
-      const int c = c0 + (L.lane & 31);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<f32x4_t*>(image + (c * kImageStride + r0 + 8 * j + 4 * (L.lane >> 5)) * 4) =
-            quad(v, j) * scale;
+        write_four_at(image + image_offset(c0 + run_col(L), r0 + run_row(j, L)), quad(v, j) * scale);
     }
     static __device__ __forceinline__ int block_row0(int) { return 0; }
     static __device__ __forceinline__ int block_col0(int) { return 0; }
@@ -618,21 +736,31 @@ struct F32x32 {
 
   static __device__ __forceinline__ void write_image_pair(unsigned char* image, int n, int k,
                                                           float v0, float v1) {
-    float* p = reinterpret_cast<float*>(image + (n * kImageStride + k) * 4);
-    p[0] = v0;
-    p[1] = v1;
+    write_pair_at(image + image_offset(n, k), v0, v1);
   }
-  static __device__ __forceinline__ int image_offset(int n, int k) { return (n * kImageStride + k) * 4; }
+  static __device__ __forceinline__ int image_offset(int n, int k) {
+    return n * kImageStride + place(k) * 2;
+  }
+  static __device__ __forceinline__ void write_four_at(unsigned char* at, f32x4_t v) {
+    write_four(at, v[0], v[1], v[2], v[3]);
+  }
   static __device__ __forceinline__ void write_pair_at(unsigned char* at, float v0, float v1) {
-    float* p = reinterpret_cast<float*>(at);
-    p[0] = v0;
-    p[1] = v1;
+    uint32_t h, m, l;
+    split_pair(v0, v1, h, m, l);
+    *reinterpret_cast<uint32_t*>(at) = h;
+    *reinterpret_cast<uint32_t*>(at + kPlane) = m;
+    *reinterpret_cast<uint32_t*>(at + 2 * kPlane) = l;
   }
   static __device__ __forceinline__ void write_one_at(unsigned char* at, float v) {
-    *reinterpret_cast<float*>(at) = v;
+    uint32_t h, m, l;
+    split_pair(v, 0.0f, h, m, l);
+    *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(h);
+    *reinterpret_cast<uint16_t*>(at + kPlane) = static_cast<uint16_t>(m);
+    *reinterpret_cast<uint16_t*>(at + 2 * kPlane) = static_cast<uint16_t>(l);
   }
   static __device__ __forceinline__ float image_at(const unsigned char* image, int n, int k) {
-    return *reinterpret_cast<const float*>(image + (n * kImageStride + k) * 4);
+    const uint16_t* p = reinterpret_cast<const uint16_t*>(image + image_offset(n, k));
+    return whole_lo(p[0], p[kPlane / 2], p[kPlane]);
   }
 };
 
@@ -764,24 +892,22 @@ __device__ __forceinline__ void stage(const Raw& r, const Lane& L, float eps, un
       inv[h] = live ? 1.0f : 0.0f;
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[i] = (live && cols) ? elu1(f[i]) : 0.0f;
-      const int off = (L.r8 + 8 * h) * kTileStride + L.ch * 16;
-      *reinterpret_cast<u32x4_t*>(Xt + off) = F::pack(f);
-      if (USE_Y) *reinterpret_cast<u32x4_t*>(Yt + off) = r.y[h];
+      F::put(Xt, L.r8 + 8 * h, L.ch, f);
+      if (USE_Y) F::put_raw(Yt, L.r8 + 8 * h, L.ch, r.y[h]);
       continue;
     }
     float ss = 0.0f;
 #pragma unroll
     for (int i = 0; i < F::EPL; ++i) ss += f[i] * f[i];
     inv[h] = inv_norm_or_zero(row_sum8(ss), eps, (r.live >> h) & 1);
-    const int off = (L.r8 + 8 * h) * kTileStride + L.ch * 16;
     if (XMODE == kXNormalized) {
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[i] *= inv[h];
-      *reinterpret_cast<u32x4_t*>(Xt + off) = F::pack(f);
+      F::put(Xt, L.r8 + 8 * h, L.ch, f);
     } else if (XMODE == kXRaw) {
-      *reinterpret_cast<u32x4_t*>(Xt + off) = r.x[h];
+      F::put_raw(Xt, L.r8 + 8 * h, L.ch, r.x[h]);
     }
-    if (USE_Y) *reinterpret_cast<u32x4_t*>(Yt + off) = r.y[h];
+    if (USE_Y) F::put_raw(Yt, L.r8 + 8 * h, L.ch, r.y[h]);
   }
 }
 
@@ -844,19 +970,25 @@ __device__ __forceinline__ void feature_grad_rows(float (&p)[2 * F::EPL],
   for (int c = 0; c < 2 * F::EPL; ++c) p[c] *= fminf(u[c], 1.0f);
 }
 
-// The same with the raw row x = r * u in `e`:  (p - u (u.p)) / r = p/r - x (x.p) / r^3.
+// The same with the raw row x = r * u:  (p - u (u.p)) / r = p/r - x (x.p) / r^3.
+template <class F>
+__device__ __forceinline__ void project_values(float (&p)[2 * F::EPL], const float (&x)[2 * F::EPL],
+                                               float inv_r, const Lane& L) {
+  float proj = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 2 * F::EPL; ++c) proj += x[c] * p[c];
+  // one factor at a time: 1/r^3 alone leaves the fp32 range for rows next to zero
+  proj = row_sum_groups(proj, L) * inv_r * inv_r * inv_r;
+#pragma unroll
+  for (int c = 0; c < 2 * F::EPL; ++c) p[c] = p[c] * inv_r - x[c] * proj;
+}
 template <class F>
 __device__ __forceinline__ void project_rows_raw(float (&p)[2 * F::EPL],
                                                  const typename F::TileRows& e, float inv_r,
                                                  const Lane& L) {
   float x[2 * F::EPL];
   e.unpack(x);
-  float proj = 0.0f;
-#pragma unroll
-  for (int c = 0; c < 2 * F::EPL; ++c) proj += x[c] * p[c];
-  proj = row_sum_groups(proj, L) * (inv_r * inv_r * inv_r);
-#pragma unroll
-  for (int c = 0; c < 2 * F::EPL; ++c) p[c] = p[c] * inv_r - x[c] * proj;
+  project_values<F>(p, x, inv_r, L);
 }
 
 // Cache policy of the result stores.  Results are not read again by these kernels, and with
@@ -885,6 +1017,100 @@ __device__ __forceinline__ void store_product_row(unsigned char* __restrict__ ds
     const uint32_t off = static_cast<uint32_t>(row) * addr.stride + 64 * j + 16 * L.g16;
     if (POLICY != kStoreDefault) __builtin_amdgcn_raw_buffer_store_b128(F::pack(c), out, off, 0, POLICY);
     else *reinterpret_cast<u32x4_t*>(dst + off) = F::pack(c);
+  }
+}
+
+// ---- rows that only their own wave reads ---------------------------------------------------
+
+// The wave's own 16 rows of one tensor, loaded from global memory in the layout of the products
+// (lane (i16, g16): bytes 128 c + 64 j + 16 g16 .. + 15 of row i16), so that they need no LDS at all.
+template <int P>
+struct OwnRaw {
+  u32x4_t r[P][2];
+};
+
+struct Buffers {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ Buffers(const unsigned char* base, int N, RowAddr row) {
+    r = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(base), 0,
+                                          (N - 1) * row.stride + row.bytes, 0x00020000);
+  }
+};
+
+template <int P>
+__device__ __forceinline__ void load_own(OwnRaw<P>& t, const Lane& L, __amdgpu_buffer_rsrc_t X, RowAddr addr,
+                                         int row0, bool live) {
+  const uint32_t at = static_cast<uint32_t>(row0 + L.i16) * addr.stride + L.g16 * 16;
+#pragma unroll
+  for (int c = 0; c < P; ++c)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int col = c * kRowBytes + 64 * j;
+      t.r[c][j] = __builtin_amdgcn_raw_buffer_load_b128(
+          X, live && col + L.g16 * 16 < addr.bytes ? at + col : kOutOfBuffer, 0, 0);
+    }
+}
+template <int P>
+__device__ __forceinline__ void load_own(OwnRaw<P>& t, const Lane& L, const Buffers& X, RowAddr addr,
+                                         int row0, bool live) {
+  load_own<P>(t, L, X.r, addr, row0, live);
+}
+
+// The lane's values of piece c.
+template <class F, int P>
+__device__ __forceinline__ void own_values(const OwnRaw<P>& t, int c, float (&f)[2 * F::EPL]) {
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    float h[F::EPL];
+    F::unpack(t.r[c][j], h);
+#pragma unroll
+    for (int i = 0; i < F::EPL; ++i) f[F::EPL * j + i] = h[i];
+  }
+}
+
+template <class F, int P>
+__device__ __forceinline__ void own_rows(const OwnRaw<P>& t, typename F::TileRows (&x)[P]) {
+#pragma unroll
+  for (int c = 0; c < P; ++c) x[c].set(t.r[c][0], t.r[c][1]);
+}
+
+// ---- states into operand images --------------------------------------------------------------
+
+// A quadrant of scale * M from the accumulator layout (`get(g)`: group g, four consecutive rows of
+// one column) into its operand image: transposed straight from the lane (two row pairs of its
+// column), natural with the neighbouring lane's column (even lanes write the first two rows of a
+// group, odd lanes the last two; each gets the other column of its rows from its neighbour).
+template <class F, bool NATURAL, class Get>
+__device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned char* image, const Lane& L) {
+  // (row, column) of the first value of a group = a part that depends on the lane only plus a
+  // part that depends on the group only; the image offsets of the two add up, so the second
+  // becomes the immediate offset of the write
+  const int lane_row = F::Acc::group_row(0, L), lane_col = F::Acc::group_col(0, L);
+  const bool odd = (lane_col & 1) != 0;
+  Lane zero = L;
+  zero.set(0);
+  unsigned char* at = image + (NATURAL ? F::image_offset(lane_row + (odd ? 2 : 0), lane_col & ~1)
+                                       : F::image_offset(lane_col, lane_row));
+#pragma unroll
+  for (int g = 0; g < F::Acc::kGroups; ++g) {
+    const f32x4_t v = get(g) * scale;
+    const int row = F::Acc::group_row(g, zero), col = F::Acc::group_col(g, zero);  // the group's part
+    if (!NATURAL) {
+      F::write_four_at(at + F::image_offset(col, row), v);
+    } else {
+      // The lane sends what its neighbour wants (the choice is made on the sending side: a
+      // choice between two values received from the neighbour would be evaluated over there).
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float mine = odd ? v[2 + i] : v[i];
+        int sent = __builtin_bit_cast(int, odd ? v[i] : v[2 + i]);
+        asm volatile("" : "+v"(sent));
+        int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+        asm volatile("" : "+v"(got));
+        const float other = __builtin_bit_cast(float, got);
+        F::write_pair_at(at + F::image_offset(row + i, col), odd ? other : mine, odd ? mine : other);
+      }
+    }
   }
 }
 

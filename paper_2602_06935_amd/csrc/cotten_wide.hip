@@ -1,6 +1,6 @@
-// Matrix-core kernels for 256-byte rows: fp32 I/O with d_h = 64, bf16 / fp16 I/O with d_h = 128
-// (d_model = 128 or 256 with two heads, "Sequence Length and Embedding Size") - and, in their
-// three-launch form, for the 512-byte rows of fp32 I/O with d_h = 128.
+// Matrix-core kernels for 256-byte rows of 16-bit elements: bf16 / fp16 I/O with d_h = 128 (d_model = 256
+// with two heads, "Sequence Length and Embedding Size").  (fp32 rows of 256 and 512 bytes:
+// cotten_wide32.hip; the entry points at the end of this file hand over to it.)
 //
 // A 256-byte row is handled as two 128-byte halves, a d_h x d_h state as four quadrants of
 // the size the 128-byte-row formats work on (cotten_mfma_core.h), so that their tile layout,
@@ -35,10 +35,7 @@ using namespace mfma;
 // Every kernel exists for workgroups of 4 and of 8 waves (template parameter WAVES): 4 when there
 // are workgroups enough to put two on every compute unit, 8 when there are not.
 //
-// Template parameter P: the 128-byte pieces of a row.  2 for the 256-byte rows above; the kernels
-// of the three-launch structure also exist for P = 4, fp32 rows of 512 bytes (d_h = 128): the
-// state in 4 x 4 blocks of 32 x 32, four of them per wave of the state kernel, one set of sixteen
-// operand images in the LDS of an apply workgroup of four waves.
+// Template parameter P: the 128-byte pieces of a row (2).
 constexpr int kHalfBytes = kRowBytes;    // one piece of a row
 
 // A 16-row tile of a tensor pair in the load layout: piece [h][c] is bytes 128 c + 16 ch .. + 15 of
@@ -557,7 +554,7 @@ __global__ __launch_bounds__(64 * WAVES) void wide_fwd_kernel(const LaunchArgs a
   r.mask = nullptr;  // queries are not masked
   r.state = a.states + static_cast<size_t>(bh) * D * D;
   r.out = a.O + base;
-  plain_role<F, WAVES, P == 2, P>(r);  // operands held in registers where they fit
+  plain_role<F, WAVES, true, P>(r);  // operands held in registers
 }
 
 // blockIdx.y: 0 dQ, 1 dV, 2 dK
@@ -645,45 +642,6 @@ __device__ __forceinline__ void fused_state_pass(typename F::Acc& acc, const Wid
       acc.mfma(tile + left, tile + right, L);
     }
     __syncthreads();  // the tile sets are overwritten next
-  }
-}
-
-// A quadrant of scale * M from the accumulator layout (`get(g)`: group g, four consecutive rows of
-// one column) into its operand image: transposed straight from the lane (two row pairs of its
-// column), natural with the neighbouring lane's column (even lanes write the first two rows of a
-// group, odd lanes the last two; each gets the other column of its rows from its neighbour).
-template <class F, bool NATURAL, class Get>
-__device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned char* image, const Lane& L) {
-  // (row, column) of the first value of a group = a part that depends on the lane only plus a
-  // part that depends on the group only; the image offsets of the two add up, so the second
-  // becomes the immediate offset of the write
-  const int lane_row = F::Acc::group_row(0, L), lane_col = F::Acc::group_col(0, L);
-  const bool odd = (lane_col & 1) != 0;
-  Lane zero = L;
-  zero.set(0);
-  unsigned char* at = image + (NATURAL ? F::image_offset(lane_row + (odd ? 2 : 0), lane_col & ~1)
-                                       : F::image_offset(lane_col, lane_row));
-#pragma unroll
-  for (int g = 0; g < F::Acc::kGroups; ++g) {
-    const f32x4_t v = get(g) * scale;
-    const int row = F::Acc::group_row(g, zero), col = F::Acc::group_col(g, zero);  // the group's part
-    if (!NATURAL) {
-      F::write_pair_at(at + F::image_offset(col, row), v[0], v[1]);
-      F::write_pair_at(at + F::image_offset(col, row + 2), v[2], v[3]);
-    } else {
-      // The lane sends what its neighbour wants (the choice is made on the sending side: a
-      // choice between two values received from the neighbour would be evaluated over there).
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const float mine = odd ? v[2 + i] : v[i];
-        int sent = __builtin_bit_cast(int, odd ? v[i] : v[2 + i]);
-        asm volatile("" : "+v"(sent));
-        int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
-        asm volatile("" : "+v"(got));
-        const float other = __builtin_bit_cast(float, got);
-        F::write_pair_at(at + F::image_offset(row + i, col), odd ? other : mine, odd ? mine : other);
-      }
-    }
   }
 }
 
@@ -1101,12 +1059,10 @@ LaunchArgs launch_args(const Problem& p, const Plan& plan, const float* states, 
 
 // Workgroups of 8 waves (the whole LDS of a compute unit at their disposal) when the launch has
 // no more workgroups than there are compute units, of 4 waves (two per compute unit) otherwise.
-// With rows of four pieces one set of images and four tile sets fill the LDS of a compute unit:
-// the apply workgroups have 4 waves and a compute unit to themselves.
 constexpr int kUnits = 256;
 template <int WAVES, int P = 2>
 constexpr int max_lds_bytes() {
-  return (WAVES == 8 || P == 4) ? 160 * 1024 : 80 * 1024;
+  return WAVES == 8 ? 160 * 1024 : 80 * 1024;
 }
 
 template <class F, int WAVES, int P>
@@ -1157,7 +1113,6 @@ hipError_t states(const Problem& p, const Plan& plan, bool bwd) {
 
 template <class F, int P>
 hipError_t apply(const Problem& p, const Plan& plan, const float* st, const float* dst, bool bwd) {
-  if (P == 4) return apply_w<F, 4, P>(p, plan, st, dst, bwd);
   return few_workgroups(p, plan, bwd ? 3 : 1) ? apply_w<F, 8, 2>(p, plan, st, dst, bwd)
                                               : apply_w<F, 4, 2>(p, plan, st, dst, bwd);
 }
@@ -1205,48 +1160,37 @@ hipError_t fused(const Problem& p, const Plan& plan, bool bwd) {
 bool wide_supports(int dtype, int D) { return dtype == 0 ? (D == 64 || D == 128) : D == 128; }
 
 namespace {
-// rows of four 128-byte pieces: fp32 d_h = 128 (three-launch structure only)
-inline bool four_pieces(int dtype, int D) { return dtype == 0 && D == 128; }
-
-// fn(F{}) for the element format of the problem, with the feature map of its params
+// fn(F{}) for the element format of the problem (16-bit), with the feature map of its params
 template <class Fn>
 hipError_t for_format(const Problem& p, Fn fn) {
   using namespace mfma;
-  if (p.feature_map == kMapElu1)
-    return p.dtype == 0   ? fn(WithElu1<F32x32>{})
-           : p.dtype == 1 ? fn(WithElu1<Bf16x64>{})
-                          : fn(WithElu1<F16x64>{});
-  return p.dtype == 0 ? fn(F32x32{}) : p.dtype == 1 ? fn(Bf16x64{}) : fn(F16x64{});
+  if (p.feature_map == kMapElu1) return p.dtype == 1 ? fn(WithElu1<Bf16x64>{}) : fn(WithElu1<F16x64>{});
+  return p.dtype == 1 ? fn(Bf16x64{}) : fn(F16x64{});
 }
 }  // namespace
 
 hipError_t launch_wide_states(const Problem& p, const Plan& plan, bool bwd) {
-  using namespace mfma;
-  if (four_pieces(p.dtype, p.D))
-    return p.feature_map == kMapElu1 ? wide::states<WithElu1<F32x32>, 4>(p, plan, bwd)
-                                     : wide::states<F32x32, 4>(p, plan, bwd);
+  if (p.dtype == 0) return launch_wide32_states(p, plan, bwd);
   return for_format(p, [&](auto f) { return wide::states<decltype(f), 2>(p, plan, bwd); });
 }
 
-// One launch per direction whenever the sequence is not cut - except a backward over so few
-// slices that its three roles as workgroups of their own are what fills the chip (64 slices of
-// 200 rows, bf16 d_h = 128: 17.5 us against 19.4 us in one launch; the forward: 13.8 against 10.0),
-// and except rows of four pieces, for which only the three-launch kernels exist.
-bool wide_fused_applies(int dtype, int D, int B, int H, int splits, bool bwd) {
-  return !four_pieces(dtype, D) && splits == 1 && !(bwd && static_cast<long>(B) * H * 3 <= wide::kUnits);
+// One launch per direction whenever the sequence is not cut - except, with 16-bit rows, a backward
+// over so few slices that its three roles as workgroups of their own are what fills the chip (64
+// slices of 200 rows, bf16 d_h = 128: 17.5 us against 19.4 us in one launch; the forward: 13.8
+// against 10.0).
+bool wide_fused_applies(int dtype, int B, int H, int splits, bool bwd) {
+  return splits == 1 && !(dtype != 0 && bwd && static_cast<long>(B) * H * 3 <= wide::kUnits);
 }
 
 hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd) {
-  if (!wide_fused_applies(p.dtype, p.D, p.B, p.H, plan.splits, bwd)) return hipErrorInvalidValue;
+  if (!wide_fused_applies(p.dtype, p.B, p.H, plan.splits, bwd)) return hipErrorInvalidValue;
+  if (p.dtype == 0) return launch_wide32_fused(p, plan, bwd);
   return for_format(p, [&](auto f) { return wide::fused<decltype(f)>(p, plan, bwd); });
 }
 
 hipError_t launch_wide_apply(const Problem& p, const Plan& plan, const float* states,
                              const float* dstates, bool bwd) {
-  using namespace mfma;
-  if (four_pieces(p.dtype, p.D))
-    return p.feature_map == kMapElu1 ? wide::apply<WithElu1<F32x32>, 4>(p, plan, states, dstates, bwd)
-                                     : wide::apply<F32x32, 4>(p, plan, states, dstates, bwd);
+  if (p.dtype == 0) return launch_wide32_apply(p, plan, states, dstates, bwd);
   return for_format(p, [&](auto f) { return wide::apply<decltype(f), 2>(p, plan, states, dstates, bwd); });
 }
 
