@@ -573,6 +573,9 @@ struct F32x32 {
     const unsigned char* p = T + row * kTileStride + at * 2;
     return Pieces{plane_operand(p), plane_operand(p + kPlane), plane_operand(p + 2 * kPlane)};
   }
+  static __device__ __forceinline__ bf16x8_t both(bf16x4_t a, bf16x4_t b) {
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  }
   // what a lane holds of a 32 x 32 result: column column(lane%32), and rows 16*(lane/32) + 4g .. +3
   static __device__ __forceinline__ int run_row(int g, const Lane& L) { return 4 * g + 16 * (L.lane >> 5); }
   static __device__ __forceinline__ int run_col(const Lane& L) { return column(L.lane & 31); }
@@ -589,6 +592,10 @@ struct F32x32 {
       v = mfma32(rows_operand(Xt, L), rows_operand(Yt, L), v);
     }
     __device__ __forceinline__ f32x4_t group(int g) const { return quad(v, g); }
+    __device__ __forceinline__ void add_group(int g, f32x4_t x) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[4 * g + i] += x[i];
+    }
     static __device__ __forceinline__ int group_row(int g, const Lane& L) { return run_row(g, L); }
     static __device__ __forceinline__ int group_col(int, const Lane& L) { return run_col(L); }
     static constexpr int kGroups = 4;
@@ -701,10 +708,6 @@ struct F32x32 {
       out[nt] = Bf16Elem::mfma16(xhm, hh, out[nt]);           // h h' + m h'
     }
   }
-  static __device__ __forceinline__ bf16x8_t both(bf16x4_t a, bf16x4_t b) {
-    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
-  }
-
   // The state as the one 32 x 32 block it is (see Half64::BlockAcc).
   struct BlockAcc {
     static constexpr int kBlocks = 1;

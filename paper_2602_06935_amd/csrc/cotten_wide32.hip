@@ -7,18 +7,20 @@
 //
 // State walk: the rows go through LDS, where the matrix cores read them transposed, cut into
 // pieces once on the way.
-//   P = 2  a workgroup of four waves; a wave adds its own tiles to a state of its own (no barriers),
-//          the four sums meet at the end
-//   P = 4  eight waves, rounds of 64 rows staged by all of them; a wave adds two of the four tiles of
-//          a round to a quadrant of 2 x 2 blocks, the two sums of a quadrant meet at the end
+//   P = 2, four waves   a wave adds its own tiles to a state of its own (no barriers), the four sums
+//                       meet at the end
+//   P = 2, eight waves  (few workgroups) rounds of 128 rows, a wave adds the tiles of its half of the
+//                       workgroup to one block, the two sums of a block meet at the end
+//   P = 4, eight waves  rounds of 64 rows, a wave adds two of the four tiles of a round to a quadrant
+//                       of 2 x 2 blocks, the two sums of a quadrant meet at the end
 // Apply: a wave loads its own rows straight in the layout of the products (no LDS), the state is
-// read from the operand images.
+// read from operand images that lie over the tiles of the walk.
 //
 // A sequence that is not cut takes one launch per direction and the state never leaves the compute
 // unit; the backward has two roles, side by side on one XCD, each of which reads all four tensors:
 //   S from (K, V), then dQ;      dS from (Q, dO), then dV and dK
 // A cut one takes three launches: partial states into the caller's workspace, their sum in split
-// order (reduce_states_kernel), apply (backward: dQ, dV, dK as three roles).
+// order (reduce_states_kernel), apply (backward: three roles).
 #include "cotten_launch.h"
 #include "cotten_mfma_core.h"
 
@@ -30,21 +32,18 @@ using namespace mfma;
 
 extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
-template <int P>
-constexpr int waves() { return P == 2 ? 4 : 8; }
-
 // LDS: the tiles of the state walk; over them, once the state is complete, the sums that meet and
-// then the operand images (P = 2: two sets, P = 4: one); behind them a few words.
-template <class F, int P>
+// then the operand images; behind them a few words.
+template <class F, int P, int WAVES>
 struct Lds {
   static constexpr int kPair = 2 * P * F::kTileBytes;   // [x pieces | y pieces] of 16 rows
-  static constexpr int kTiles = 4 * kPair;              // P = 2: one pair per wave; P = 4: a round of 64 rows
+  static constexpr int kPairs = P == 2 ? WAVES : 4;     // one per wave; P = 4: a round of 64 rows
+  static constexpr int kTiles = kPairs * kPair;
   static constexpr int kSet = P * P * F::kImageBytes;
-  static constexpr int kSets = P == 2 ? 2 : 1;
-  static constexpr int kMeet = P == 2 ? 12 * 4096 : 16 * 4096;
+  static constexpr int kSets = P == 2 ? 2 : 1;          // image sets there is room for
   static constexpr int kWords = kTiles;
+  static_assert(kSets * kSet <= kTiles, "the images lie over the tiles");
   static constexpr int kBytes = kWords + 64;
-  static_assert(kSets * kSet <= kTiles && kMeet <= kTiles, "images and sums lie over the tiles");
 };
 
 struct Args {
@@ -139,37 +138,121 @@ __device__ __forceinline__ void stage_plain(const Half16<P>& t, const Lane& L, u
     for (int c = 0; c < P; ++c) F::put_raw(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, t.r[h][c]);
 }
 
-// The blocks of the complete state that a wave ends up with: block j is piece p of x against piece
-// q0 + j of y (of the transposed state when the walk was `swapped`, see below).
-template <int P>
+// The blocks of the complete state that a wave ends up with: block j is piece p of the left rows
+// against piece q0 + j of the right ones.  With two groups of four waves the second has none.
+template <class F, int P>
 struct State {
-  static constexpr int kBlocks = P * P / waves<P>();  // 1 or 2
-  f32x16_t v[kBlocks];
+  static constexpr int kBlocks = P == 2 ? 1 : 2;
+  typename F::Acc v[kBlocks];
   int p, q0;
+  bool here;
 };
 
-// v += (x tile piece)^T (y tile piece), or with the operands exchanged, i.e. the transposed block (whose
-// natural image is the one that can be written straight from the lane).
-template <class F, bool SWAPPED>
-__device__ __forceinline__ void add_block(f32x16_t& v, const Pieces& x, const Pieces& y) {
-  v = SWAPPED ? F::mfma32(y, x, v) : F::mfma32(x, y, v);
+// The first row at which a key is valid, down to a multiple of 16 (N if there is none; 0 without looking
+// for long sequences): a left-padded history of at most 512 rows is walked from there (rows of two
+// pieces: the live tiles are dealt evenly to the waves; 512 slices x 200 rows, forward 25.5 -> 24.7 us).
+__device__ __forceinline__ int first_live_tile(const uint8_t* __restrict__ m, int N, const Lane& L) {
+  constexpr int kMost = 512;
+  if (m == nullptr || N > kMost) return 0;
+  int lo = N;
+#pragma unroll
+  for (int i = kMost / 64 - 1; i >= 0; --i) {
+    const int row = 64 * i + L.lane;
+    const uint64_t set = __builtin_amdgcn_ballot_w64(row < N && m[row < N ? row : 0] != 0);
+    if (set != 0) lo = 64 * i + __builtin_ctzll(set);
+  }
+  return lo == N ? N : lo & ~(TR - 1);
 }
 
-// sum over the rows begin .. end-1 (those with a valid key, if `m` is given) of xhat^T y.
-// The LDS area of the tiles is free afterwards (ends with a barrier).
-template <class F, bool SWAPPED>
-__device__ __forceinline__ void state_walk(State<2>& out, const Buffers& X, const Buffers& Y, int stride,
-                                           const uint8_t* __restrict__ m, int begin, int end, float eps,
-                                           const Lane& L) {
+template <int P>
+__device__ __forceinline__ int walk_begin(const uint8_t* __restrict__ m, int N, const Lane& L) {
+  return P == 4 ? 0 : first_live_tile(m, N, L);
+}
+
+// The walks: sum over the rows begin .. end-1 (those with a valid key, if `m` is given) of xhat^T y - or,
+// SWAPPED, y^T xhat, the transposed state, whose natural images are the ones that can be written
+// straight from the lanes.  The LDS area of the tiles is free afterwards (they end with a barrier).
+// `request` asks for what comes next, once the rows have arrived and only the sums are left to meet.
+
+// P = 2, eight waves: one block per wave (wave & 3) and group of four waves; every wave stages one tile
+// pair per round, a group adds its own four.
+template <class F, bool SWAPPED, class Request>
+__device__ __forceinline__ void walk_shared(State<F, 2>& out, const Buffers& X, const Buffers& Y, int stride,
+                                            const uint8_t* __restrict__ m, int begin, int end, float eps,
+                                            const Lane& L, Request&& request) {
+  constexpr int P = 2, WAVES = 8, kRound = WAVES * TR;
+  typedef Lds<F, P, WAVES> Map;
+  const int group = L.wave >> 2, p = (L.wave >> 1) & 1, q = L.wave & 1;
+  unsigned char* mine = smem + L.wave * Map::kPair;
+  int* live_tiles = reinterpret_cast<int*>(smem + Map::kWords);
+  const int left = (SWAPPED ? P + p : p) * F::kTileBytes, right = (SWAPPED ? q : P + q) * F::kTileBytes;
+  typename F::Acc& acc = out.v[0];
+  acc.zero();
+  out.p = p;
+  out.q0 = q;
+  out.here = group == 0;
+  Half16<P> x, y;
+  int row0 = begin + L.wave * TR;
+  int bits = row_bits(m, row0, end, L), next_bits = row_bits(m, row0 + kRound, end, L);
+  load_half(x, L, X, stride, row0, bits);
+  load_half(y, L, Y, stride, row0, bits);
+#pragma unroll 1
+  for (int r0 = begin; r0 < end; r0 += kRound, row0 += kRound) {
+    const bool live = __builtin_amdgcn_ballot_w64(bits != 0) != 0;
+    if (live) {
+      stage_mapped<F, P>(x, bits, L, eps, mine);
+      stage_plain<F, P>(y, L, mine + P * F::kTileBytes);
+    }
+    if (L.lane == 0) live_tiles[L.wave] = live;
+    bits = next_bits;
+    load_half(x, L, X, stride, row0 + kRound, bits);
+    load_half(y, L, Y, stride, row0 + kRound, bits);
+    next_bits = row_bits(m, row0 + 2 * kRound, end, L);
+    __syncthreads();
+    int flags = 0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) flags |= (live_tiles[4 * group + t] != 0) << t;
+    flags = __builtin_amdgcn_readfirstlane(flags);
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if ((flags >> t) & 1) {
+        const unsigned char* pair = smem + (4 * group + t) * Map::kPair;
+        acc.mfma(pair + left, pair + right, L);
+      }
+    __syncthreads();  // the tiles are overwritten next
+  }
+  request();
+  {  // first group's sum + second group's sum
+    static_assert(4 * F::Acc::kGroups * 64 * 16 <= Map::kTiles, "the sums meet in the tiles");
+    f32x4_t* meet = reinterpret_cast<f32x4_t*>(smem) + (L.wave & 3) * F::Acc::kGroups * 64 + L.lane;
+    if (group == 1) {
+#pragma unroll
+      for (int g = 0; g < F::Acc::kGroups; ++g) meet[g * 64] = acc.group(g);
+    }
+    __syncthreads();
+    if (group == 0) {
+#pragma unroll
+      for (int g = 0; g < F::Acc::kGroups; ++g) acc.add_group(g, meet[g * 64]);
+    }
+    __syncthreads();
+  }
+}
+
+// P = 2, four waves: a wave adds its own tiles (every fourth) to a state of its own.
+template <class F, bool SWAPPED, class Request>
+__device__ __forceinline__ void walk_private(State<F, 2>& out, const Buffers& X, const Buffers& Y, int stride,
+                                             const uint8_t* __restrict__ m, int begin, int end, float eps,
+                                             const Lane& L, Request&& request) {
   constexpr int P = 2, kStep = 4 * TR;
-  unsigned char* mine = smem + L.wave * Lds<F, P>::kPair;
-  f32x16_t acc[P][P];
+  typedef Lds<F, P, 4> Map;
+  unsigned char* mine = smem + L.wave * Map::kPair;
+  const unsigned char* left = mine + (SWAPPED ? P : 0) * F::kTileBytes;
+  const unsigned char* right = mine + (SWAPPED ? 0 : P) * F::kTileBytes;
+  typename F::Acc acc[P][P];
 #pragma unroll
   for (int p = 0; p < P; ++p)
 #pragma unroll
-    for (int q = 0; q < P; ++q)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) acc[p][q][i] = 0.0f;
+    for (int q = 0; q < P; ++q) acc[p][q].zero();
   Half16<P> x, y;
   int row0 = begin + L.wave * TR;
   int bits = row_bits(m, row0, end, L), next_bits = row_bits(m, row0 + kStep, end, L);
@@ -188,30 +271,33 @@ __device__ __forceinline__ void state_walk(State<2>& out, const Buffers& X, cons
     next_bits = row_bits(m, row0 + 2 * kStep, end, L);
     if (live) {
       wave_lds_fence();
-      const Pieces x0 = F::rows_operand(mine, L), x1 = F::rows_operand(mine + F::kTileBytes, L);
+      const Pieces l0 = F::rows_operand(left, L), l1 = F::rows_operand(left + F::kTileBytes, L);
 #pragma unroll
       for (int q = 0; q < P; ++q) {
-        const Pieces b = F::rows_operand(mine + (P + q) * F::kTileBytes, L);
-        add_block<F, SWAPPED>(acc[0][q], x0, b);
-        add_block<F, SWAPPED>(acc[1][q], x1, b);
+        const Pieces r = F::rows_operand(right + q * F::kTileBytes, L);
+        acc[0][q].v = F::mfma32(l0, r, acc[0][q].v);
+        acc[1][q].v = F::mfma32(l1, r, acc[1][q].v);
       }
       wave_lds_fence();
     }
   }
+  request();
   // wave w completes block w; the sums of the four waves are added in wave order
   out.p = L.wave >> 1;
   out.q0 = L.wave & 1;
+  out.here = true;
   f32x4_t* meet = reinterpret_cast<f32x4_t*>(smem) + L.lane;  // [block][three other waves][quad][lane]
+  static_assert(12 * 4 * 64 * 16 <= Map::kTiles, "the sums meet in the tiles");
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < 4; ++w)
     if (w != L.wave) {
       const int slot = 3 * w + (L.wave < w ? L.wave : L.wave - 1);
 #pragma unroll
-      for (int g = 0; g < 4; ++g) meet[(slot * 4 + g) * 64] = quad(acc[w >> 1][w & 1], g);
+      for (int g = 0; g < 4; ++g) meet[(slot * 4 + g) * 64] = acc[w >> 1][w & 1].group(g);
     }
   __syncthreads();
-  f32x16_t own = acc[0][0];
+  typename F::Acc own = acc[0][0];
 #pragma unroll
   for (int w = 1; w < 4; ++w)
     if (w == L.wave) own = acc[w >> 1][w & 1];
@@ -221,120 +307,176 @@ __device__ __forceinline__ void state_walk(State<2>& out, const Buffers& X, cons
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const f32x4_t part =
-          w == L.wave ? quad(own, g) : meet[((3 * L.wave + (w < L.wave ? w : w - 1)) * 4 + g) * 64];
+          w == L.wave ? own.group(g) : meet[((3 * L.wave + (w < L.wave ? w : w - 1)) * 4 + g) * 64];
       sum[g] = w == 0 ? part : sum[g] + part;
     }
+  out.v[0].zero();
 #pragma unroll
-  for (int g = 0; g < 4; ++g)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) out.v[0][4 * g + i] = sum[g][i];
+  for (int g = 0; g < 4; ++g) out.v[0].add_group(g, sum[g]);
   __syncthreads();
 }
 
-template <class F, bool SWAPPED>
-__device__ __forceinline__ void state_walk(State<4>& out, const Buffers& X, const Buffers& Y, int stride,
-                                           const uint8_t* __restrict__ m, int begin, int end, float eps,
-                                           const Lane& L) {
-  constexpr int P = 4, kRound = 4 * TR;
-  typedef Lds<F, P> Map;
-  const int tile = L.wave & 3, part = L.wave >> 2;  // waves 0-3 stage x tiles, waves 4-7 y tiles
-  unsigned char* mine = smem + tile * Map::kPair + part * P * F::kTileBytes;
-  int* live_tiles = reinterpret_cast<int*>(smem + Map::kWords);
+// P = 4: rounds of 32 rows in two LDS buffers.  Waves 0-3 stage 8 rows of x each, waves 4-7 8 rows of y;
+// a wave adds one of the two tiles of a round to its quadrant of 2 x 2 blocks.  One barrier per round; of
+// the two waves of a SIMD one stages the next round (vector units) before, the other after its products
+// (matrix cores), so that both are busy.  (All waves staging, then all multiplying: 28 k of the 56 k cycles of
+// a slice of 200 rows; forward of 256 slices x 1000 rows 124 -> 117 us, of 16 slices x 200 24.4 -> 22.5.)
+template <class F, bool SWAPPED, class Request>
+__device__ __forceinline__ void walk_quadrants(State<F, 4>& out, const Buffers& X, const Buffers& Y, int stride,
+                                               const uint8_t* __restrict__ m, int begin, int end, float eps,
+                                               const Lane& L, Request&& request) {
+  constexpr int P = 4, kRound = 2 * TR;
+  typedef Lds<F, P, 8> Map;
+  constexpr int kBuffer = 2 * Map::kPair;
+  const int part = L.wave >> 2;  // what the wave stages (x or y), and the tile of a round that it adds
+  const int row = 16 * ((L.wave >> 1) & 1) + 8 * (L.wave & 1) + L.r8;  // of a round, that it stages
+  unsigned char* mine = smem + (row >> 4) * Map::kPair + part * P * F::kTileBytes;
+  int* live_halves = reinterpret_cast<int*>(smem + Map::kWords);  // [buffer][wave 0-3]
   const int p0 = L.wave & 2, q0 = 2 * (L.wave & 1);
-  f32x16_t acc[2][2];
+  const int left = part * Map::kPair + ((SWAPPED ? P : 0) + p0) * F::kTileBytes;
+  const int right = part * Map::kPair + ((SWAPPED ? 0 : P) + q0) * F::kTileBytes;
+  typename F::Acc acc[2][2];
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b) acc[a][b].zero();
+  const Buffers& source = part == 0 ? X : Y;
+  u32x4_t raw[2][P];  // rounds on their way (two ahead of the one being staged)
+  bool live[2];
+  const auto row_at = [&](int r0) { return r0 + row < end && (m == nullptr || m[r0 + row] != 0); };
+  const auto load = [&](u32x4_t (&t)[P], int r0, bool on) {
+    const uint32_t off = on ? static_cast<uint32_t>(r0 + row) * stride + L.ch * 16 : kOutOfBuffer;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
-  const Buffers& mine_src = part == 0 ? X : Y;
-  Half16<P> t;
-  int row0 = begin + tile * TR;
-  int bits = row_bits(m, row0, end, L), next_bits = row_bits(m, row0 + kRound, end, L);
-  load_half(t, L, mine_src, stride, row0, bits);
-#pragma unroll 1
-  for (int r0 = begin; r0 < end; r0 += kRound, row0 += kRound) {
-    const bool live = __builtin_amdgcn_ballot_w64(bits != 0) != 0;
-    if (live) {
-      if (part == 0) stage_mapped<F, P>(t, bits, L, eps, mine);
-      else stage_plain<F, P>(t, L, mine);
+    for (int c = 0; c < P; ++c) t[c] = __builtin_amdgcn_raw_buffer_load_b128(source.r, off + c * kRowBytes, 0, 0);
+  };
+  const auto stage = [&](const u32x4_t (&t)[P], bool on, int buffer) {
+    float f[P][F::EPL];
+    float ss = 0.0f;
+#pragma unroll
+    for (int c = 0; c < P; ++c) F::unpack(t[c], f[c]);
+    if (part == 0) {
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+#pragma unroll
+        for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
+      const float inv = F::kMap == kMapElu1 ? 1.0f : inv_norm_or_zero(row_sum8(ss), eps, on);
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+#pragma unroll
+        for (int i = 0; i < F::EPL; ++i)
+          f[c][i] = F::kMap == kMapElu1 ? (on ? elu1(f[c][i]) : 0.0f) : f[c][i] * inv;
+      const bool any = __builtin_amdgcn_ballot_w64(on) != 0;
+      if (L.lane == 0) live_halves[4 * buffer + L.wave] = any;
     }
-    if (part == 0 && L.lane == 0) live_tiles[tile] = live;
-    bits = next_bits;
-    load_half(t, L, mine_src, stride, row0 + kRound, bits);
-    next_bits = row_bits(m, row0 + 2 * kRound, end, L);
-    __syncthreads();
-#pragma unroll 1
-    for (int u = 2 * part; u < 2 * part + 2; ++u) {
-      if (__builtin_amdgcn_readfirstlane(live_tiles[u]) == 0) continue;
-      const unsigned char* pair = smem + u * Map::kPair;
-      const Pieces x0 = F::rows_operand(pair + p0 * F::kTileBytes, L);
-      const Pieces x1 = F::rows_operand(pair + (p0 + 1) * F::kTileBytes, L);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        const Pieces y = F::rows_operand(pair + (P + q0 + b) * F::kTileBytes, L);
-        add_block<F, SWAPPED>(acc[0][b], x0, y);
-        add_block<F, SWAPPED>(acc[1][b], x1, y);
+    for (int c = 0; c < P; ++c) F::put(mine + buffer * kBuffer + c * F::kTileBytes, row & 15, L.ch, f[c]);
+  };
+  bool next_live = row_at(begin + 2 * kRound);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) live[i] = row_at(begin + i * kRound);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) load(raw[i], begin + i * kRound, live[i]);
+  stage(raw[0], live[0], 0);
+  live[0] = next_live;
+  load(raw[0], begin + 2 * kRound, live[0]);
+  next_live = row_at(begin + 3 * kRound);
+#pragma unroll 1
+  for (int r0 = begin; r0 < end; r0 += 2 * kRound) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int r = r0 + j * kRound;  // the round that is added, from buffer j; the next one goes to 1 - j
+      if (r < end) {
+        __syncthreads();  // round r is staged; nobody reads the other buffer any more
+        const auto advance = [&] {
+          stage(raw[1 - j], live[1 - j], 1 - j);
+          live[1 - j] = next_live;
+          load(raw[1 - j], r + 3 * kRound, live[1 - j]);
+          next_live = row_at(r + 4 * kRound);
+        };
+        const int* flags = live_halves + 4 * j + 2 * part;
+        const bool any = __builtin_amdgcn_readfirstlane(flags[0] | flags[1]) != 0;
+        if (part == 0) advance();
+        if (any) {
+          const unsigned char* at = smem + j * kBuffer;
+          const Pieces l0 = F::rows_operand(at + left, L);
+          const Pieces l1 = F::rows_operand(at + left + F::kTileBytes, L);
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const Pieces y = F::rows_operand(at + right + b * F::kTileBytes, L);
+            acc[0][b].v = F::mfma32(l0, y, acc[0][b].v);
+            acc[1][b].v = F::mfma32(l1, y, acc[1][b].v);
+          }
+        }
+        if (part == 1) advance();
       }
     }
-    __syncthreads();  // the tiles are overwritten next
   }
+  request();
+  __syncthreads();  // the tiles are overwritten next
   // of the 2 x 2 blocks of a quadrant the first half of the workgroup completes the first row, the
   // second half the second; first half's sum + second half's sum
   out.p = p0 + part;
   out.q0 = q0;
+  out.here = true;
   f32x4_t* meet = reinterpret_cast<f32x4_t*>(smem) + L.lane;  // [wave that reads][block][quad][lane]
+  static_assert(16 * 4 * 64 * 16 <= Map::kTiles, "the sums meet in the tiles");
 #pragma unroll
   for (int b = 0; b < 2; ++b)
 #pragma unroll
     for (int g = 0; g < 4; ++g)
-      meet[(((L.wave ^ 4) * 2 + b) * 4 + g) * 64] = part == 0 ? quad(acc[1][b], g) : quad(acc[0][b], g);
+      meet[(((L.wave ^ 4) * 2 + b) * 4 + g) * 64] = part == 0 ? acc[1][b].group(g) : acc[0][b].group(g);
   __syncthreads();
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < 2; ++b) {
+    out.v[b].zero();
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const f32x4_t own = part == 0 ? quad(acc[0][b], g) : quad(acc[1][b], g);
-      const f32x4_t sum = own + meet[((L.wave * 2 + b) * 4 + g) * 64];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out.v[b][4 * g + i] = sum[i];
+      const f32x4_t own = part == 0 ? acc[0][b].group(g) : acc[1][b].group(g);
+      out.v[b].add_group(g, own + meet[((L.wave * 2 + b) * 4 + g) * 64]);
     }
+  }
   __syncthreads();
 }
 
-// The wave's blocks of scale * state into a set of images.  DIRECT: as the accumulators hold them
-// (transposed images; natural ones after a swapped walk), otherwise the natural ones after a plain walk.
+template <class F, int P, int WAVES, bool SWAPPED, class Request>
+__device__ __forceinline__ void state_walk(State<F, P>& out, const Buffers& X, const Buffers& Y, int stride,
+                                           const uint8_t* __restrict__ m, int begin, int end, float eps,
+                                           const Lane& L, Request&& request) {
+  if constexpr (P == 4) walk_quadrants<F, SWAPPED>(out, X, Y, stride, m, begin, end, eps, L, request);
+  else if constexpr (WAVES == 4) walk_private<F, SWAPPED>(out, X, Y, stride, m, begin, end, eps, L, request);
+  else walk_shared<F, SWAPPED>(out, X, Y, stride, m, begin, end, eps, L, request);
+}
+
+// The wave's blocks of scale * state into a set of images, image (p, q) that of piece p of x against piece q
+// of y: DIRECT, straight from the lanes (transposed images after a plain walk, natural ones after a swapped
+// one), or the other ones, by way of the neighbouring lanes.
 template <class F, int P, bool SWAPPED, bool DIRECT>
-__device__ __forceinline__ void state_images(const State<P>& s, float scale, unsigned char* images, const Lane& L) {
+__device__ __forceinline__ void state_images(const State<F, P>& s, float scale, unsigned char* images, const Lane& L) {
+  if (!s.here) return;
 #pragma unroll
-  for (int j = 0; j < State<P>::kBlocks; ++j)
-    quadrant_image<F, !DIRECT>([&](int g) { return quad(s.v[j], g); }, scale,
-                               images + (P * s.p + s.q0 + j) * F::kImageBytes, L);
+  for (int j = 0; j < State<F, P>::kBlocks; ++j) {
+    const int index = SWAPPED ? P * (s.q0 + j) + s.p : P * s.p + s.q0 + j;
+    quadrant_image<F, !DIRECT>([&](int g) { return s.v[j].group(g); }, scale, images + index * F::kImageBytes, L);
+  }
 }
 
 // The wave's blocks (of a plain walk) into a row-major D x D array.
 template <class F, int P>
-__device__ __forceinline__ void state_rows(const State<P>& s, float* __restrict__ out, const Lane& L) {
+__device__ __forceinline__ void state_rows(const State<F, P>& s, float* __restrict__ out, const Lane& L) {
   constexpr int D = P * F::D;
+  if (!s.here) return;
 #pragma unroll
-  for (int j = 0; j < State<P>::kBlocks; ++j)
+  for (int j = 0; j < State<F, P>::kBlocks; ++j)
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
+    for (int g = 0; g < F::Acc::kGroups; ++g) {
+      const f32x4_t v = s.v[j].group(g);
+      float* at = out + (s.p * F::D + F::Acc::group_row(g, L)) * D + (s.q0 + j) * F::D + F::Acc::group_col(g, L);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        out[(s.p * F::D + F::run_row(g, L) + i) * D + (s.q0 + j) * F::D + F::run_col(L)] = s.v[j][4 * g + i];
+      for (int i = 0; i < 4; ++i) at[i * D] = v[i];
+    }
 }
 
 // ---- apply ----------------------------------------------------------------------------------------------
-
-template <int P>
-__device__ __forceinline__ void floats_of(const OwnRaw<P>& t, int c, float (&f)[8]) {
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f[4 * j + i] = __uint_as_float(t.r[c][j][i]);
-}
 
 // 1/r of the lane's row under the cosine map (0 for a row that does not take part), 1 under ELU + 1.
 template <class F, int P>
@@ -343,10 +485,10 @@ __device__ __forceinline__ float own_factor(const OwnRaw<P>& t, float eps, bool 
   float ss = 0.0f;
 #pragma unroll
   for (int c = 0; c < P; ++c) {
-    float f[8];
-    floats_of(t, c, f);
+    float f[2 * F::EPL];
+    own_values<F, P>(t, c, f);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ss += f[i] * f[i];
+    for (int i = 0; i < 2 * F::EPL; ++i) ss += f[i] * f[i];
   }
   return inv_norm_or_zero(row_sum_groups(ss, L), eps, live);
 }
@@ -354,14 +496,16 @@ __device__ __forceinline__ float own_factor(const OwnRaw<P>& t, float eps, bool 
 // The rows as they enter a product whose result is multiplied by own_factor(): raw, or phi(x).
 template <class F, int P>
 __device__ __forceinline__ void own_mapped(const OwnRaw<P>& t, bool live, typename F::TileRows (&x)[P]) {
+  if (F::kMap != kMapElu1) {
+    own_rows<F, P>(t, x);
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < P; ++c) {
-    float f[8];
-    floats_of(t, c, f);
-    if (F::kMap == kMapElu1) {
+    float f[2 * F::EPL];
+    own_values<F, P>(t, c, f);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) f[i] = live ? elu1(f[i]) : 0.0f;
-    }
+    for (int i = 0; i < 2 * F::EPL; ++i) f[i] = live ? elu1(f[i]) : 0.0f;
     x[c].set(f);
   }
 }
@@ -369,7 +513,7 @@ __device__ __forceinline__ void own_mapped(const OwnRaw<P>& t, bool live, typena
 // out = sum_c X[c] W(first + c * step)
 template <class F, int P>
 __device__ __forceinline__ void product(const typename F::TileRows (&X)[P], const unsigned char* images, int first,
-                                        int step, const Lane& L, float (&out)[8]) {
+                                        int step, const Lane& L, float (&out)[2 * F::EPL]) {
   f32x4_t a[F::NT];
 #pragma unroll
   for (int nt = 0; nt < F::NT; ++nt) a[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -384,16 +528,16 @@ __device__ __forceinline__ void product(const typename F::TileRows (&X)[P], cons
 
 template <class F, int P>
 __device__ __forceinline__ void store_piece(unsigned char* out, int c, int row, int end, int stride, const Lane& L,
-                                            const float (&o)[8]) {
+                                            const float (&o)[2 * F::EPL]) {
   if (row < end)
     store_product_row<F, kStoreStreamed>(out + c * kRowBytes, row, RowAddr{stride, kRowBytes}, L, o);
 }
 
 template <class F, int P>
 __device__ __forceinline__ void store_zeros(unsigned char* out, int row, int end, int stride, const Lane& L) {
-  float z[8];
+  float z[2 * F::EPL];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) z[i] = 0.0f;
+  for (int i = 0; i < 2 * F::EPL; ++i) z[i] = 0.0f;
 #pragma unroll
   for (int c = 0; c < P; ++c) store_piece<F, P>(out, c, row, end, stride, L, z);
 }
@@ -406,24 +550,26 @@ __device__ __forceinline__ void plain_tile(const OwnRaw<P>& raw, bool live, floa
   own_mapped<F, P>(raw, live, x);
 #pragma unroll
   for (int q = 0; q < P; ++q) {
-    float o[8];
+    float o[2 * F::EPL];
     product<F, P>(x, images, q, P, L, o);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] *= inv;
+    for (int i = 0; i < 2 * F::EPL; ++i) o[i] *= inv;
     store_piece<F, P>(out, q, row, end, stride, L, o);
   }
 }
 
 // One tile of out = J (y rows) M^T, J the derivative of the map at the x rows (contraction over the
-// columns of M; `images`: the natural ones).  Returns mapped x . (y M^T) of the lane's row.
-template <class F, int P>
+// columns of M; `images`: the natural ones).  Returns (mapped x) . (y M^T) of the lane's row.
+// `y_used` may take the registers of y for the next tile.
+template <class F, int P, class Used>
 __device__ __forceinline__ float projected_tile(const OwnRaw<P>& x, const OwnRaw<P>& y, bool live, float inv,
                                                 const unsigned char* images, unsigned char* out, int row, int end,
-                                                int stride, const Lane& L, bool want_dot) {
-  float g[P][8];
+                                                int stride, const Lane& L, bool want_dot, Used&& y_used) {
+  float g[P][2 * F::EPL];
   {
     typename F::TileRows Y[P];
     own_rows<F, P>(y, Y);
+    y_used();
 #pragma unroll
     for (int p = 0; p < P; ++p) product<F, P>(Y, images, P * p, 1, L, g[p]);
   }
@@ -431,149 +577,138 @@ __device__ __forceinline__ float projected_tile(const OwnRaw<P>& x, const OwnRaw
   if (F::kMap != kMapElu1 || want_dot) {
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-      float f[8];
-      floats_of(x, p, f);
+      float f[2 * F::EPL];
+      own_values<F, P>(x, p, f);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < 2 * F::EPL; ++i)
         dot += (F::kMap == kMapElu1 ? (live ? elu1(f[i]) : 0.0f) : f[i] * inv) * g[p][i];
     }
     dot = row_sum_groups(dot, L);
   }
 #pragma unroll
   for (int p = 0; p < P; ++p) {
-    float f[8];
-    floats_of(x, p, f);
+    float f[2 * F::EPL];
+    own_values<F, P>(x, p, f);
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < 2 * F::EPL; ++i)
       g[p][i] = F::kMap == kMapElu1 ? g[p][i] * fminf(elu1(f[i]), 1.0f) : (g[p][i] - f[i] * inv * dot) * inv;
     store_piece<F, P>(out, p, row, end, stride, L, g[p]);
   }
   return dot;
 }
 
-struct Rows16 {  // the tiles of a wave: first, first + step, ... below end
+struct Range {
   int begin, end, stride;
 };
 
-template <class F, int P>
-__device__ __forceinline__ bool own_live(const uint8_t* keys, int row, int end) {
+// The images afresh for every tile: left alone the compiler reads the operands of all of them once, ahead
+// of the tile loop, into registers that it does not have.
+__device__ __forceinline__ const unsigned char* afresh(const unsigned char* images) {
+  int zero = 0;
+  asm volatile("" : "+s"(zero));
+  return images + zero;
+}
+
+__device__ __forceinline__ bool row_live(const uint8_t* keys, int row, int end) {
   return row < end && (keys == nullptr || keys[row] != 0);
 }
 
 // O, or dV alone.  `first`: the wave's first tile, already requested.
-template <class F, int P>
-__device__ __forceinline__ void apply_plain(const Buffers& X, const uint8_t* keys, const Rows16 r, float eps,
+template <class F, int P, int WAVES>
+__device__ __forceinline__ void apply_plain(const Buffers& X, const uint8_t* keys, const Range r, float eps,
                                             const unsigned char* images, unsigned char* out, const Lane& L,
                                             const OwnRaw<P>& first) {
-  constexpr int kStep = waves<P>() * TR;
+  constexpr int kStep = WAVES * TR;
   const RowAddr addr{r.stride, P * kRowBytes};
   OwnRaw<P> next = first;
-  bool next_live = own_live<F, P>(keys, r.begin + L.wave * TR + L.i16, r.end);
+  bool next_live = row_live(keys, r.begin + L.wave * TR + L.i16, r.end);
 #pragma unroll 1
   for (int row0 = r.begin + L.wave * TR; row0 < r.end; row0 += kStep) {
     const OwnRaw<P> cur = next;
+    const unsigned char* set = afresh(images);
     const bool live = next_live;
-    next_live = own_live<F, P>(keys, row0 + kStep + L.i16, r.end);
-    load_own<P>(next, L, X, addr, row0 + kStep, next_live);
     const int row = row0 + L.i16;
-    if (__builtin_amdgcn_ballot_w64(live) == 0) {
+    next_live = row_live(keys, row + kStep, r.end);
+    load_own<P>(next, L, X, addr, row0 + kStep, next_live);
+    if (keys != nullptr && __builtin_amdgcn_ballot_w64(live) == 0) {
       store_zeros<F, P>(out, row, r.end, r.stride, L);
       continue;
     }
-    plain_tile<F, P>(cur, live, own_factor<F, P>(cur, eps, live, L), images, out, row, r.end, r.stride, L);
+    plain_tile<F, P>(cur, live, own_factor<F, P>(cur, eps, live, L), set, out, row, r.end, r.stride, L);
   }
 }
 
-// dQ, or dK alone.  Returns this lane's share of sum_i x_i . (y_i M^T).
-template <class F, int P>
+// dQ, or dK alone (natural images; returns this lane's share of sum_i x_i . (y_i M^T)), or dK and dV (BOTH: from both
+// sets, K is read once).
+template <class F, int P, int WAVES, bool BOTH>
 __device__ __forceinline__ float apply_projected(const Buffers& X, const Buffers& Y, const uint8_t* keys,
-                                                 const Rows16 r, float eps, const unsigned char* images,
-                                                 unsigned char* out, const Lane& L, const OwnRaw<P>& first_x,
-                                                 const OwnRaw<P>& first_y, bool want_dot) {
-  constexpr int kStep = waves<P>() * TR;
+                                                 const Range r, float eps, const unsigned char* images,
+                                                 const unsigned char* transposed, unsigned char* out,
+                                                 unsigned char* out_plain, const Lane& L,
+                                                 const OwnRaw<P>& first_x, const OwnRaw<P>& first_y,
+                                                 bool want_dot) {
+  constexpr int kStep = WAVES * TR;
   const RowAddr addr{r.stride, P * kRowBytes};
   float dots = 0.0f;
-  OwnRaw<P> nx = first_x, ny = first_y;
-  bool next_live = own_live<F, P>(keys, r.begin + L.wave * TR + L.i16, r.end);
+  OwnRaw<P> nx = first_x, y = first_y;
+  bool next_live = row_live(keys, r.begin + L.wave * TR + L.i16, r.end);
 #pragma unroll 1
   for (int row0 = r.begin + L.wave * TR; row0 < r.end; row0 += kStep) {
-    const OwnRaw<P> x = nx, y = ny;
+    const OwnRaw<P> x = nx;
     const bool live = next_live;
-    next_live = own_live<F, P>(keys, row0 + kStep + L.i16, r.end);
+    next_live = row_live(keys, row0 + kStep + L.i16, r.end);
     load_own<P>(nx, L, X, addr, row0 + kStep, next_live);
-    load_own<P>(ny, L, Y, addr, row0 + kStep, next_live);
+    const auto next_y = [&] { load_own<P>(y, L, Y, addr, row0 + kStep, next_live); };
+    const OwnRaw<P> cur_y = y;
+    if (P == 2) next_y();  // (four pieces: once the registers are free)
     const int row = row0 + L.i16;
-    if (__builtin_amdgcn_ballot_w64(live) == 0) {
+    if (keys != nullptr && __builtin_amdgcn_ballot_w64(live) == 0) {
+      if (P == 4) next_y();
       store_zeros<F, P>(out, row, r.end, r.stride, L);
+      if (BOTH) store_zeros<F, P>(out_plain, row, r.end, r.stride, L);
       continue;
     }
     const float inv = own_factor<F, P>(x, eps, live, L);
-    const float dot = projected_tile<F, P>(x, y, live, inv, images, out, row, r.end, r.stride, L, want_dot);
+    if (BOTH) plain_tile<F, P>(x, live, inv, afresh(transposed), out_plain, row, r.end, r.stride, L);
+    const float dot = projected_tile<F, P>(x, cur_y, live, inv, afresh(images), out, row, r.end, r.stride, L, want_dot, [&] {
+      if (P == 4) next_y();
+    });
     if (L.g16 == 0) dots += dot;
   }
   return dots;
 }
 
-// dV and dK together, both image sets being there: K and V are read once.
-template <class F, int P>
-__device__ __forceinline__ void apply_both(const Buffers& K, const Buffers& V, const uint8_t* keys, const Rows16 r,
-                                           float eps, const unsigned char* transposed, const unsigned char* natural,
-                                           unsigned char* dV, unsigned char* dK, const Lane& L,
-                                           const OwnRaw<P>& first_k, const OwnRaw<P>& first_v) {
-  constexpr int kStep = waves<P>() * TR;
-  const RowAddr addr{r.stride, P * kRowBytes};
-  OwnRaw<P> nk = first_k, nv = first_v;
-  bool next_live = own_live<F, P>(keys, r.begin + L.wave * TR + L.i16, r.end);
-#pragma unroll 1
-  for (int row0 = r.begin + L.wave * TR; row0 < r.end; row0 += kStep) {
-    const OwnRaw<P> k = nk, v = nv;
-    const bool live = next_live;
-    next_live = own_live<F, P>(keys, row0 + kStep + L.i16, r.end);
-    load_own<P>(nk, L, K, addr, row0 + kStep, next_live);
-    load_own<P>(nv, L, V, addr, row0 + kStep, next_live);
-    const int row = row0 + L.i16;
-    if (__builtin_amdgcn_ballot_w64(live) == 0) {
-      store_zeros<F, P>(dV, row, r.end, r.stride, L);
-      store_zeros<F, P>(dK, row, r.end, r.stride, L);
-      continue;
-    }
-    const float inv = own_factor<F, P>(k, eps, live, L);
-    plain_tile<F, P>(k, live, inv, transposed, dV, row, r.end, r.stride, L);
-    projected_tile<F, P>(k, v, live, inv, natural, dK, row, r.end, r.stride, L, false);
-  }
-}
-
 // ---- one launch per direction ------------------------------------------------------------------------------
 
-template <class F, int P>
-__global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void fused_fwd_kernel(const Args a) {
-  typedef Lds<F, P> Map;
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void fused_fwd_kernel(const Args a) {
   constexpr int D = P * F::D;
   const Lane L;
   const int bh = blockIdx.x, N = a.N, stride = a.st.row.stride;
   const size_t base = a.st.slice_base(bh, a.H);
-  State<P> s;
-  {
-    const Buffers K(a.K + base, N, a.st.row), V(a.V + base, N, a.st.row);
-    state_walk<F, false>(s, K, V, stride, a.keys_of(bh), 0, N, a.eps, L);
-  }
-  // the first tile of Q travels while the images are made
+  const uint8_t* keys = a.keys_of(bh);
+  State<F, P> s;
   const Buffers Q(a.Q + base, N, a.st.row);
   OwnRaw<P> first;
-  load_own<P>(first, L, Q, a.st.row, L.wave * TR, L.wave * TR + L.i16 < N);
+  {
+    const Buffers K(a.K + base, N, a.st.row), V(a.V + base, N, a.st.row);
+    state_walk<F, P, WAVES, false>(s, K, V, stride, keys, walk_begin<P>(keys, N, L), N, a.eps, L, [&] {
+      load_own<P>(first, L, Q, a.st.row, L.wave * TR, L.wave * TR + L.i16 < N);
+    });
+  }
   state_images<F, P, false, true>(s, a.scale_of(bh), smem, L);
   if (a.kept != nullptr) state_rows<F, P>(s, a.kept + static_cast<size_t>(bh) * D * D, L);
   __syncthreads();
-  apply_plain<F, P>(Q, nullptr, Rows16{0, N, stride}, a.eps, smem, a.O + base, L, first);
+  apply_plain<F, P, WAVES>(Q, nullptr, Range{0, N, stride}, a.eps, smem, a.O + base, L, first);
 }
 
-template <class F, int P>
-__global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void fused_bwd_kernel(const Args a) {
-  typedef Lds<F, P> Map;
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void fused_bwd_kernel(const Args a) {
+  typedef Lds<F, P, WAVES> Map;
   const Lane L;
   // workgroups go to the XCDs round-robin: the two roles of a slice are eight apart, on one XCD
   const int bh = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);
-  const bool second = ((blockIdx.x >> 3) & 1) != 0;
+  const bool second = ((blockIdx.x >> 3) & 1) != 0;  // dS, dV, dK
   if (bh >= a.slices) return;
   const int N = a.N, stride = a.st.row.stride;
   const size_t base = a.st.slice_base(bh, a.H);
@@ -581,17 +716,19 @@ __global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void fused_bwd_ker
   const float scale = a.scale_of(bh);
   const Buffers Q(a.Q + base, N, a.st.row), K(a.K + base, N, a.st.row);
   const Buffers V(a.V + base, N, a.st.row), dO(a.dO + base, N, a.st.row);
-  const int row = L.wave * TR + L.i16;
-  const Rows16 all{0, N, stride};
-  State<P> s;
+  const Range all{0, N, stride};
+  const int row0 = L.wave * TR;
+  State<F, P> s;
   OwnRaw<P> fx, fy;
   if (!second) {
-    state_walk<F, true>(s, K, V, stride, keys, 0, N, a.eps, L);
-    load_own<P>(fx, L, Q, a.st.row, L.wave * TR, row < N);
-    load_own<P>(fy, L, dO, a.st.row, L.wave * TR, row < N);
+    state_walk<F, P, WAVES, true>(s, K, V, stride, keys, walk_begin<P>(keys, N, L), N, a.eps, L, [&] {
+      load_own<P>(fx, L, Q, a.st.row, row0, row0 + L.i16 < N);
+      load_own<P>(fy, L, dO, a.st.row, row0, row0 + L.i16 < N);
+    });
     state_images<F, P, true, true>(s, scale, smem, L);
     __syncthreads();
-    float dots = apply_projected<F, P>(Q, dO, nullptr, all, a.eps, smem, a.dQ + base, L, fx, fy, a.dlog != nullptr);
+    float dots = apply_projected<F, P, WAVES, false>(Q, dO, nullptr, all, a.eps, smem, nullptr, a.dQ + base, nullptr,
+                                                     L, fx, fy, a.dlog != nullptr);
     if (a.dlog != nullptr) {  // sum_i dO_i . O_i = sum_i qhat_i . (scale dO_i S^T), in a fixed order
       float* partial = reinterpret_cast<float*>(smem + Map::kWords);
       dots = wave_sum(dots);
@@ -599,31 +736,32 @@ __global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void fused_bwd_ker
       __syncthreads();
       if (threadIdx.x == 0) {
         float sum = 0.0f;
-        for (int w = 0; w < waves<P>(); ++w) sum += partial[w];
+        for (int w = 0; w < WAVES; ++w) sum += partial[w];
         a.dlog[bh] = sum;
       }
     }
     return;
   }
-  state_walk<F, false>(s, Q, dO, stride, nullptr, 0, N, a.eps, L);
-  const bool live = own_live<F, P>(keys, row, N);
-  load_own<P>(fx, L, K, a.st.row, L.wave * TR, live);
-  if (P == 2) {
-    load_own<P>(fy, L, V, a.st.row, L.wave * TR, live);
-    state_images<F, P, false, true>(s, scale, smem, L);
+  const bool live = row_live(keys, row0 + L.i16, N);
+  state_walk<F, P, WAVES, false>(s, Q, dO, stride, nullptr, 0, N, a.eps, L, [&] {
+    load_own<P>(fx, L, K, a.st.row, row0, live);
+    if (P == 2) load_own<P>(fy, L, V, a.st.row, row0, live);
+  });
+  state_images<F, P, false, true>(s, scale, smem, L);
+  if constexpr (P == 2) {
     state_images<F, P, false, false>(s, scale, smem + Map::kSet, L);
     __syncthreads();
-    apply_both<F, P>(K, V, keys, all, a.eps, smem, smem + Map::kSet, a.dV + base, a.dK + base, L, fx, fy);
+    apply_projected<F, P, WAVES, true>(K, V, keys, all, a.eps, smem + Map::kSet, smem, a.dK + base, a.dV + base, L,
+                                       fx, fy, false);
   } else {
-    state_images<F, P, false, true>(s, scale, smem, L);
     __syncthreads();
-    apply_plain<F, P>(K, keys, all, a.eps, smem, a.dV + base, L, fx);
-    load_own<P>(fx, L, K, a.st.row, L.wave * TR, live);
-    load_own<P>(fy, L, V, a.st.row, L.wave * TR, live);
+    apply_plain<F, P, WAVES>(K, keys, all, a.eps, smem, a.dV + base, L, fx);
+    load_own<P>(fx, L, K, a.st.row, row0, live);
+    load_own<P>(fy, L, V, a.st.row, row0, live);
     __syncthreads();  // nobody reads the transposed images any more
     state_images<F, P, false, false>(s, scale, smem, L);
     __syncthreads();
-    apply_projected<F, P>(K, V, keys, all, a.eps, smem, a.dK + base, L, fx, fy, false);
+    apply_projected<F, P, WAVES, false>(K, V, keys, all, a.eps, smem, nullptr, a.dK + base, nullptr, L, fx, fy, false);
   }
 }
 
@@ -631,8 +769,8 @@ __global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void fused_bwd_ker
 
 // grid (slices * splits, 1 or 2); blockIdx.y == 1 reduces (Q, dO) instead of (K, V) under the key mask.
 // Partial states: row-major D x D floats per workgroup, the second kind behind all of the first.
-template <class F, int P>
-__global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void state_kernel(const Args a, float* __restrict__ ws) {
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void state_kernel(const Args a, float* __restrict__ ws) {
   constexpr int D = P * F::D;
   const Lane L;
   const int split = blockIdx.x % a.splits, bh = blockIdx.x / a.splits;
@@ -641,16 +779,18 @@ __global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void state_kernel(
   const Buffers X((second ? a.Q : a.K) + base, a.N, a.st.row), Y((second ? a.dO : a.V) + base, a.N, a.st.row);
   const int begin = split * a.rows_per_split;
   const int end = a.N < begin + a.rows_per_split ? a.N : begin + a.rows_per_split;
-  State<P> s;
-  state_walk<F, false>(s, X, Y, a.st.row.stride, second ? nullptr : a.keys_of(bh), begin, end, a.eps, L);
+  State<F, P> s;
+  state_walk<F, P, WAVES, false>(s, X, Y, a.st.row.stride, second ? nullptr : a.keys_of(bh), begin, end, a.eps, L,
+                                  [] {});
   state_rows<F, P>(s, ws + (static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x) * D * D, L);
 }
 
 // The images of scale * M (M: a complete state in global memory, row-major D x D): block (p, q) at
-// P p + q, natural op[m][n] or transposed op[n][m] = M[p 32 + m][q 32 + n].
-template <class F, int P, bool TRANSPOSED>
+// P p + q, natural op[m][n] or transposed op[n][m] = M[p F::D + m][q F::D + n].
+template <class F, int P, int WAVES, bool TRANSPOSED>
 __device__ __forceinline__ void build_images(const float* __restrict__ M, float scale, unsigned char* images) {
-  constexpr int D = P * F::D, kThreads = 64 * waves<P>(), kPairs = D * D / 2, kBatch = 8;
+  constexpr int D = P * F::D, kThreads = 64 * WAVES, kPairs = D * D / 2;
+  constexpr int kBatch = kPairs / kThreads < 8 ? kPairs / kThreads : 8;  // whose loads travel together
   static_assert(kPairs % (kBatch * kThreads) == 0, "state size");
   for (int e0 = threadIdx.x; e0 < kPairs; e0 += kBatch * kThreads) {
     float v0[kBatch], v1[kBatch];
@@ -679,8 +819,8 @@ __device__ __forceinline__ void build_images(const float* __restrict__ M, float 
   }
 }
 
-template <class F, int P>
-__global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void apply_fwd_kernel(const Args a) {
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void apply_fwd_kernel(const Args a) {
   constexpr int D = P * F::D;
   const Lane L;
   const int split = blockIdx.x % a.splits, bh = blockIdx.x / a.splits;
@@ -691,14 +831,14 @@ __global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void apply_fwd_ker
   const Buffers Q(a.Q + base, a.N, a.st.row);
   OwnRaw<P> first;
   load_own<P>(first, L, Q, a.st.row, row0, row0 + L.i16 < end);
-  build_images<F, P, true>(a.states + static_cast<size_t>(bh) * D * D, a.scale_of(bh), smem);
+  build_images<F, P, WAVES, true>(a.states + static_cast<size_t>(bh) * D * D, a.scale_of(bh), smem);
   __syncthreads();
-  apply_plain<F, P>(Q, nullptr, Rows16{begin, end, a.st.row.stride}, a.eps, smem, a.O + base, L, first);
+  apply_plain<F, P, WAVES>(Q, nullptr, Range{begin, end, a.st.row.stride}, a.eps, smem, a.O + base, L, first);
 }
 
 // blockIdx.y: 0 dQ, 1 dV, 2 dK
-template <class F, int P>
-__global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void apply_bwd_kernel(const Args a) {
+template <class F, int P, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, WAVES == 4 ? 3 : 2) void apply_bwd_kernel(const Args a) {
   constexpr int D = P * F::D;
   const Lane L;
   const int split = blockIdx.x % a.splits, bh = blockIdx.x / a.splits, role = blockIdx.y;
@@ -706,22 +846,23 @@ __global__ __launch_bounds__(64 * waves<P>(), P == 2 ? 3 : 2) void apply_bwd_ker
   const int begin = split * a.rows_per_split;
   const int end = a.N < begin + a.rows_per_split ? a.N : begin + a.rows_per_split;
   const int row0 = begin + L.wave * TR;
-  const Rows16 rows{begin, end, a.st.row.stride};
+  const Range rows{begin, end, a.st.row.stride};
   const uint8_t* keys = role == 0 ? nullptr : a.keys_of(bh);
   const Buffers X((role == 0 ? a.Q : a.K) + base, a.N, a.st.row), Y((role == 0 ? a.dO : a.V) + base, a.N, a.st.row);
   const float* M = (role == 0 ? a.states : a.dstates) + static_cast<size_t>(bh) * D * D;
-  const bool live = own_live<F, P>(keys, row0 + L.i16, end);
+  const bool live = row_live(keys, row0 + L.i16, end);
   OwnRaw<P> fx, fy;
   load_own<P>(fx, L, X, a.st.row, row0, live);
   if (role == 1) {
-    build_images<F, P, true>(M, a.scale_of(bh), smem);
+    build_images<F, P, WAVES, true>(M, a.scale_of(bh), smem);
     __syncthreads();
-    apply_plain<F, P>(X, keys, rows, a.eps, smem, a.dV + base, L, fx);
+    apply_plain<F, P, WAVES>(X, keys, rows, a.eps, smem, a.dV + base, L, fx);
   } else {
     load_own<P>(fy, L, Y, a.st.row, row0, live);
-    build_images<F, P, false>(M, a.scale_of(bh), smem);
+    build_images<F, P, WAVES, false>(M, a.scale_of(bh), smem);
     __syncthreads();
-    apply_projected<F, P>(X, Y, keys, rows, a.eps, smem, (role == 0 ? a.dQ : a.dK) + base, L, fx, fy, false);
+    apply_projected<F, P, WAVES, false>(X, Y, keys, rows, a.eps, smem, nullptr, (role == 0 ? a.dQ : a.dK) + base,
+                                        nullptr, L, fx, fy, false);
   }
 }
 
@@ -748,8 +889,9 @@ Args make_args(const Problem& p, const Plan& plan) {
   a.dlog = p.dlog_scale;
   a.splits = plan.splits;
   a.rows_per_split = plan.rows_per_split;
-  a.st = Strides{p.stride_batch * 4, p.stride_head * 4,
-                 RowAddr{static_cast<int>(p.stride_row * 4), static_cast<int>(p.D * 4)}};
+  const long long e = p.elem_bytes();
+  a.st = Strides{p.stride_batch * e, p.stride_head * e,
+                 RowAddr{static_cast<int>(p.stride_row * e), static_cast<int>(p.D * e)}};
   return a;
 }
 
@@ -763,25 +905,39 @@ hipError_t launch(Kernel kernel, dim3 grid, int threads, int lds, const Problem&
 
 enum Kind { kFused, kStates, kApply };
 
-template <class F, int P>
+template <class F, int P, int WAVES>
 hipError_t run(Kind kind, const Problem& p, const Args& a, bool bwd) {
-  constexpr int threads = 64 * waves<P>(), lds = Lds<F, P>::kBytes;
-  static_assert(lds <= (P == 2 ? 160 * 1024 / 3 : 160 * 1024), "three workgroups per compute unit, or one");
+  constexpr int threads = 64 * WAVES, lds = Lds<F, P, WAVES>::kBytes;
+  static_assert(lds <= 160 * 1024 / (WAVES == 4 ? 3 : 1), "three workgroups per compute unit, or one");
   const unsigned slices = static_cast<unsigned>(a.slices);
   if (kind == kFused)
-    return bwd ? launch(fused_bwd_kernel<F, P>, dim3((slices + 7) / 8 * 16), threads, lds, p, a)
-               : launch(fused_fwd_kernel<F, P>, dim3(slices), threads, lds, p, a);
+    return bwd ? launch(fused_bwd_kernel<F, P, WAVES>, dim3((slices + 7) / 8 * 16), threads, lds, p, a)
+               : launch(fused_fwd_kernel<F, P, WAVES>, dim3(slices), threads, lds, p, a);
   const unsigned blocks = slices * a.splits;
-  if (kind == kStates) return launch(state_kernel<F, P>, dim3(blocks, bwd ? 2 : 1), threads, lds, p, a, p.workspace);
-  return bwd ? launch(apply_bwd_kernel<F, P>, dim3(blocks, 3), threads, lds, p, a)
-             : launch(apply_fwd_kernel<F, P>, dim3(blocks), threads, lds, p, a);
+  if (kind == kStates)
+    return launch(state_kernel<F, P, WAVES>, dim3(blocks, bwd ? 2 : 1), threads, lds, p, a, p.workspace);
+  return bwd ? launch(apply_bwd_kernel<F, P, WAVES>, dim3(blocks, 3), threads, lds, p, a)
+             : launch(apply_fwd_kernel<F, P, WAVES>, dim3(blocks), threads, lds, p, a);
+}
+
+template <class F, int P>
+hipError_t choose(Kind kind, const Problem& p, const Args& a, bool bwd) {
+  if constexpr (P == 4) {
+    return run<F, 4, 8>(kind, p, a, bwd);
+  } else {
+    // Eight waves where there is a compute unit for every workgroup (forward / backward, us, four and
+    // eight: 128 slices x 200 rows 15.8 / 20.3, 12.9 / 17.5; 8 slices 13.5 / 18.3, 10.5 / 15.1).
+    constexpr long kUnits = 256;
+    const bool few = static_cast<long>(a.slices) * a.splits * (bwd ? 2 : 1) <= kUnits;
+    return few ? run<F, 2, 8>(kind, p, a, bwd) : run<F, 2, 4>(kind, p, a, bwd);
+  }
 }
 
 hipError_t dispatch(Kind kind, const Problem& p, const Args& a, bool bwd) {
   typedef WithElu1<F32x32> Elu;
   if (p.feature_map == kMapElu1)
-    return p.D == 64 ? run<Elu, 2>(kind, p, a, bwd) : run<Elu, 4>(kind, p, a, bwd);
-  return p.D == 64 ? run<F32x32, 2>(kind, p, a, bwd) : run<F32x32, 4>(kind, p, a, bwd);
+    return p.D == 64 ? choose<Elu, 2>(kind, p, a, bwd) : choose<Elu, 4>(kind, p, a, bwd);
+  return p.D == 64 ? choose<F32x32, 2>(kind, p, a, bwd) : choose<F32x32, 4>(kind, p, a, bwd);
 }
 
 }  // namespace wide32
@@ -796,7 +952,7 @@ hipError_t launch_wide32_fused(const Problem& p, const Plan& plan, bool bwd) {
 }
 
 hipError_t launch_wide32_apply(const Problem& p, const Plan& plan, const float* states, const float* dstates,
-                               bool bwd) {
+                             bool bwd) {
   wide32::Args a = wide32::make_args(p, plan);
   a.states = states;
   a.dstates = dstates;
