@@ -13,6 +13,7 @@ captured into a graph the buffer is a fresh temporary from the graph's own pool 
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Tuple
 
@@ -110,14 +111,14 @@ def _check(status: int) -> None:
         raise CottenError(status, cotten_status_string(status))
 
 
+_DTYPE_CODES = {torch.float32: COTTEN_F32, torch.bfloat16: COTTEN_BF16, torch.float16: COTTEN_F16}
+
+
 def _dtype_code(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return COTTEN_F32
-    if t.dtype == torch.bfloat16:
-        return COTTEN_BF16
-    if t.dtype == torch.float16:
-        return COTTEN_F16
-    raise TypeError(f"unsupported I/O dtype {t.dtype}")
+    code = _DTYPE_CODES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported I/O dtype {t.dtype}")
+    return code
 
 
 def _prep(name: str, t: torch.Tensor, like: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -133,7 +134,7 @@ def _prep(name: str, t: torch.Tensor, like: Optional[torch.Tensor] = None) -> to
 def _mask_ptr(mask: Optional[torch.Tensor], B: int, N: int, dev) -> Optional[int]:
     if mask is None:
         return None
-    if mask.dtype != torch.uint8 or tuple(mask.shape) != (B, N) or not mask.is_contiguous() or mask.device != dev:
+    if mask.dtype != torch.uint8 or mask.shape != (B, N) or not mask.is_contiguous() or mask.device != dev:
         raise ValueError("mask must be a contiguous uint8 [B,N] tensor on the same device")
     return mask.data_ptr()
 
@@ -159,38 +160,42 @@ def _dims(Q: torch.Tensor, layout: str) -> Tuple[int, int, int, int]:
     return B, H, N, d
 
 
+_FEATURE_MAPS = {"cosine": COTTEN_MAP_COSINE, "elu1": COTTEN_MAP_ELU1}
+
+
 def _params(Q: torch.Tensor, scale, eps, workspace: Optional[torch.Tensor],
             slice_scale: Optional[torch.Tensor] = None,
             dlog_scale: Optional[torch.Tensor] = None, layout: str = "bhnd",
             causal: bool = False, saved_state: Optional[torch.Tensor] = None,
             feature_map: str = "cosine") -> CottenParams:
-    p = CottenParams()
-    p.causal = int(bool(causal))
-    if feature_map not in ("cosine", "elu1"):
+    fmap = _FEATURE_MAPS.get(feature_map)
+    if fmap is None:
         raise ValueError("feature_map must be 'cosine' or 'elu1'")
-    p.feature_map = COTTEN_MAP_ELU1 if feature_map == "elu1" else COTTEN_MAP_COSINE
-    B, H, _, d = _dims(Q, layout)
-    p.saved_state = _f32_vector("saved_state", saved_state, B * H * d * d, Q.device)
-    p.layout = COTTEN_BNHD if layout == "bnhd" else COTTEN_BHND
-    slices = B * H
-    p.slice_scale = _f32_vector("slice_scale", slice_scale, slices, Q.device)
-    p.dlog_scale = _f32_vector("dlog_scale", dlog_scale, slices, Q.device)
-    p.dtype = _dtype_code(Q)
-    p.scale = 0.0 if scale is None else float(scale)
-    p.eps = -1.0 if eps is None else float(eps)
+    kept = scales = dlog = space = None
+    if saved_state is not None or slice_scale is not None or dlog_scale is not None:
+        B, H, _, d = _dims(Q, layout)
+        kept = _f32_vector("saved_state", saved_state, B * H * d * d, Q.device)
+        scales = _f32_vector("slice_scale", slice_scale, B * H, Q.device)
+        dlog = _f32_vector("dlog_scale", dlog_scale, B * H, Q.device)
+    dtype = _dtype_code(Q)
+    space_bytes = 0
     if workspace is not None:
         if not workspace.is_cuda or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous GPU tensor")
-        p.workspace = workspace.data_ptr()
-        p.workspace_bytes = workspace.numel() * workspace.element_size()
-    else:
-        p.workspace = None
-        p.workspace_bytes = 0
-    return p
+        space = workspace.data_ptr()
+        space_bytes = workspace.numel() * workspace.element_size()
+    return CottenParams(dtype, 0.0 if scale is None else float(scale), -1.0 if eps is None else float(eps),
+                        space, space_bytes, scales, dlog, COTTEN_BNHD if layout == "bnhd" else COTTEN_BHND,
+                        1 if causal else 0, kept, fmap)
 
 
 _workspaces = {}    # (device index, stream handle) -> uint8 tensor
 _retired = []       # outgrown buffers: work already enqueued may still use them
+
+
+@functools.lru_cache(maxsize=1024)
+def _workspace_need(B: int, H: int, N: int, d: int, is_bwd: bool, dtype: int, causal: bool) -> int:
+    return cotten_attn_workspace_bytes_ex(B, H, N, d, is_bwd, dtype=dtype, causal=causal)
 
 
 def _workspace(Q: torch.Tensor, dims, is_bwd: bool, stream_handle: int,
@@ -199,7 +204,7 @@ def _workspace(Q: torch.Tensor, dims, is_bwd: bool, stream_handle: int,
     if given is not None:
         return given
     B, H, N, d = dims
-    need = cotten_attn_workspace_bytes_ex(B, H, N, d, is_bwd, dtype=_dtype_code(Q), causal=causal)
+    need = _workspace_need(B, H, N, d, is_bwd, _dtype_code(Q), bool(causal))
     if need == 0:
         return None
     with torch.cuda.device(Q.device):
@@ -216,11 +221,20 @@ def _workspace(Q: torch.Tensor, dims, is_bwd: bool, stream_handle: int,
 
 
 def _stream_handle(stream) -> int:
-    if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+    if stream is None:  # that of the current device
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
+
+
+def _on_device(device: torch.device, entry, *args) -> None:
+    """One call into the library with `device` current."""
+    if device.index == torch.cuda.current_device():
+        _check(entry(*args))
+    else:
+        with torch.cuda.device(device):
+            _check(entry(*args))
 
 
 def cotten_attn_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
@@ -239,16 +253,12 @@ def cotten_attn_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     lib = load_library()
     Q = _prep("Q", Q); K = _prep("K", K, Q); V = _prep("V", V, Q)
     B, H, N, d = _dims(Q, layout)
-    if O is None:
-        O = torch.empty_like(Q)
-    _prep("O", O, Q)
+    O = torch.empty_like(Q) if O is None else _prep("O", O, Q)
     handle = _stream_handle(stream)
     workspace = _workspace(Q, (B, H, N, d), False, handle, workspace, causal)
     prm = _params(Q, scale, eps, workspace, slice_scale, None, layout, causal, saved_state, feature_map)
-    with torch.cuda.device(Q.device):
-        _check(lib.cotten_attn_fwd_ex(Q.data_ptr(), K.data_ptr(), V.data_ptr(),
-                                      _mask_ptr(mask, B, N, Q.device), O.data_ptr(),
-                                      B, H, N, d, handle, ctypes.byref(prm)))
+    _on_device(Q.device, lib.cotten_attn_fwd_ex, Q.data_ptr(), K.data_ptr(), V.data_ptr(),
+               _mask_ptr(mask, B, N, Q.device), O.data_ptr(), B, H, N, d, handle, ctypes.byref(prm))
     return O
 
 
@@ -284,11 +294,8 @@ def cotten_attn_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     prm = _params(Q, scale, eps, workspace, slice_scale, dlog_scale, layout, causal, saved_state,
                   feature_map)
     entry = lib.cotten_attn_bwd_static if static_scratch else lib.cotten_attn_bwd_ex
-    with torch.cuda.device(Q.device):
-        _check(entry(Q.data_ptr(), K.data_ptr(), V.data_ptr(),
-                     _mask_ptr(mask, B, N, Q.device), dO.data_ptr(),
-                     dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(),
-                     B, H, N, d, handle, ctypes.byref(prm)))
+    _on_device(Q.device, entry, Q.data_ptr(), K.data_ptr(), V.data_ptr(), _mask_ptr(mask, B, N, Q.device),
+               dO.data_ptr(), dQ.data_ptr(), dK.data_ptr(), dV.data_ptr(), B, H, N, d, handle, ctypes.byref(prm))
     return dQ, dK, dV
 
 
