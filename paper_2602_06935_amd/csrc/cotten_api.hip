@@ -118,7 +118,7 @@ int run(bool bwd, const void* Q, const void* K, const void* V, const uint8_t* ma
   }
   cotten::Plan plan{};
   if (!causal)
-    plan = cotten::make_plan(B, H, N, d_h, prm->dtype, bwd, prm->feature_map == COTTEN_MAP_COSINE);
+    plan = cotten::make_plan(B, H, N, d_h, prm->dtype, bwd);
   const size_t need = sizeof(float) * (causal ? cotten::causal_workspace_floats(B, H, N, d_h, prm->dtype, bwd)
                                               : plan.workspace_floats);
   if (use_static_scratch) {

@@ -53,9 +53,7 @@ struct Plan {
   size_t workspace_floats;
 };
 
-// allow_resident = false keeps short 16-bit sequences off the kernels that hold a slice in LDS
-// (they implement the cosine map only); the workspace requirement is the same either way.
-Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, bool allow_resident = true);
+Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd);
 
 // Grants `kernel` `bytes` of dynamic LDS (kernels that use more than 64 KB must be granted it
 // before their first launch).  The attribute is set once per kernel and device: later calls

@@ -9,6 +9,10 @@
 // over the waves by tile; their epilogue runs in the layout the product comes out in, next to
 // the tile rows fetched from LDS in that same layout, and ends in 128-bit stores.
 //
+// Both feature maps (the rows of Q and K are mapped while they are staged); ELU + 1 on the streaming
+// kernels, which walk K, V twice, and here, fp16 d = 64, backward: 1024 slices x 197 rows 52.6 -> 44.2 us,
+// 32 x 100 11.8 -> 7.5.
+//
 //   forward    stage K, V, Q | barrier | 4 waves: S | barrier | wave w: O rows of tile w
 //   backward   see resident_bwd_kernel (dS is built while dQ is applied)
 #include "cotten_launch.h"
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(kThreads) void resident_fwd_kernel(const Args a) {
       if (mine) {
         float inv[2];
         if (__ballot(rk.live != 0) != 0)
-          stage<F, kXNormalized, true>(rk, L, a.eps, blk + kKt, blk + kVt, inv);
+          stage<F, mapped_mode<F>(), true>(rk, L, a.eps, blk + kKt, blk + kVt, inv, L.ch * 16 < a.st.row.bytes);
         else
           clear_tiles(L, blk + kKt, blk + kVt);
       }
@@ -243,7 +247,9 @@ __global__ __launch_bounds__(kThreads) void resident_fwd_kernel(const Args a) {
       }
       if (mine) {
         float inv[2];
-        stage<F, kXRaw, false>(rq, L, a.eps, blk + kQt, blk + kGt, inv);
+        // ELU + 1: phi(q) goes through the product, and 1/r is 1
+        stage<F, F::kMap == kMapElu1 ? kXFeature : kXRaw, false>(rq, L, a.eps, blk + kQt, blk + kGt, inv,
+                                                                 L.ch * 16 < a.st.row.bytes);
         publish_inv(invs, L, inv);
         fetch<false>(rq, rk, a, L, slice + stride, tile, keys);
         keys = key_rows(a, L, slice + 2 * stride, tile);
@@ -276,6 +282,7 @@ __global__ __launch_bounds__(kThreads) void resident_fwd_kernel(const Args a) {
 //                                                            khat is zero on masked rows)
 //   kind 2  dK = (h - khat (khat.h)) / r_k,  h = v W       (W = scale * dS, natural image;
 //                                                            1/r_k is zero on masked rows)
+// (ELU + 1: phi(q), phi(k) in place of the unit rows, dQ = g phi'(q), dK = h phi'(k))
 // Tiles without a valid key get zero rows of dK and dV without touching LDS.
 template <class F>
 __device__ __forceinline__ void apply_tile(const Lane& L, int kind, int t, int N,
@@ -297,7 +304,8 @@ __device__ __forceinline__ void apply_tile(const Lane& L, int kind, int t, int N
     if (kind != 1) {
       typename F::TileRows e;
       e.load(tb + (kind == 0 ? kQt : kKt), L);
-      project_rows<F, true>(p, e, invs[t * 2 * TR + (kind == 0 ? 0 : TR) + L.i16], L);
+      if (F::kMap == kMapElu1) feature_grad_rows<F>(p, e);
+      else project_rows<F, true>(p, e, invs[t * 2 * TR + (kind == 0 ? 0 : TR) + L.i16], L);
     }
   }
   if (row < N) store_product_row<F, kStoreStreamed>(dst, row, row_addr, L, p);
@@ -348,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void resident_bwd_kernel(const Args a) {
       const Lane L = L0.again();
       if (mine) {
         float inv[2];
-        stage<F, kXNormalized, true>(rq, L, a.eps, blk + kQt, blk + kGt, inv);
+        stage<F, mapped_mode<F>(), true>(rq, L, a.eps, blk + kQt, blk + kGt, inv, L.ch * 16 < a.st.row.bytes);
         publish_inv(invs + tile * 2 * TR, L, inv);
       }
       // Q, dO of the next slice are requested as soon as their registers are free
@@ -368,7 +376,7 @@ __global__ __launch_bounds__(kThreads) void resident_bwd_kernel(const Args a) {
         const bool any_key = __ballot(rk.live != 0) != 0;
         if (any_key) {
           float inv[2];
-          stage<F, kXNormalized, true>(rk, L, a.eps, blk + kKt, blk + kVt, inv);
+          stage<F, mapped_mode<F>(), true>(rk, L, a.eps, blk + kKt, blk + kVt, inv, L.ch * 16 < a.st.row.bytes);
           publish_inv(invs + tile * 2 * TR + TR, L, inv);
         } else {
           clear_tiles(L, blk + kKt, blk + kVt);
@@ -683,12 +691,16 @@ hipError_t launch_resident_causal(const Problem& p, bool bwd) {
   return p.dtype == 1 ? run_causal<Bf16x64>(p, bwd) : run_causal<F16x64>(p, bwd);
 }
 
-hipError_t launch_resident_fwd(const Problem& p) {
-  return p.dtype == 1 ? run<Bf16x64>(p, false) : run<F16x64>(p, false);
+namespace {
+hipError_t run_mapped(const Problem& p, bool bwd) {
+  if (p.feature_map == kMapElu1)
+    return p.dtype == 1 ? run<WithElu1<Bf16x64>>(p, bwd) : run<WithElu1<F16x64>>(p, bwd);
+  return p.dtype == 1 ? run<Bf16x64>(p, bwd) : run<F16x64>(p, bwd);
 }
+}  // namespace
 
-hipError_t launch_resident_bwd(const Problem& p) {
-  return p.dtype == 1 ? run<Bf16x64>(p, true) : run<F16x64>(p, true);
-}
+hipError_t launch_resident_fwd(const Problem& p) { return run_mapped(p, false); }
+
+hipError_t launch_resident_bwd(const Problem& p) { return run_mapped(p, true); }
 
 }  // namespace cotten

@@ -87,6 +87,17 @@ def test_elu_feature_map(oracle, dtype, B, H, N, d):
     assert rel_l2(to_f64(O_cos), ref_o) > 0.1
 
 
+@pytest.mark.parametrize("dtype,B,H,N,d", [
+    ("bf16", 3, 1, 16, 64), ("f16", 2, 2, 17, 64), ("bf16", 3, 1, 208, 64), ("f16", 2, 2, 209, 64),
+    ("f16", 65, 4, 197, 64),     # more slices than compute units: two per persistent workgroup
+    ("bf16", 70, 4, 160, 32), ("f16", 3, 3, 50, 16),
+])
+def test_elu_feature_map_slices_held_in_lds(oracle, dtype, B, H, N, d):
+    """Short 16-bit sequences, whose slices are held in LDS: ends of tiles, the longest sequence they
+    take and the first they do not, narrow rows (padding columns must stay zero: phi(0) = 1)."""
+    test_elu_feature_map(oracle, dtype, B, H, N, d)
+
+
 def test_elu_feature_map_layout_and_refusals(oracle):
     B, H, N, d = 4, 2, 90, 32
     Q, K, V, dO, mask = _inputs(31, "f32", B, H, N, d)
