@@ -166,7 +166,8 @@ __device__ __forceinline__ int first_live_tile(const uint8_t* __restrict__ m, in
 
 template <int P>
 __device__ __forceinline__ int walk_begin(const uint8_t* __restrict__ m, int N, const Lane& L) {
-  return P == 4 ? 0 : first_live_tile(m, N, L);
+  // (up to 64 rows every wave has its one tile requested at once, and looking first is a trip to memory)
+  return P == 4 || N <= 4 * TR ? 0 : first_live_tile(m, N, L);
 }
 
 // The walks: sum over the rows begin .. end-1 (those with a valid key, if `m` is given) of xhat^T y - or,
