@@ -88,7 +88,8 @@ typedef enum cotten_dtype {
   COTTEN_F16 = 2   /* IEEE half I/O, fp32 norms and accumulation (the mixed-precision mode
                       the paper trains in).  Results beyond +-65504 become Inf; the state
                       scale*S handed to the matrix cores is held in half as well, so
-                      |scale * S| must stay in range (it does for scale ~ 1/N)           */
+                      |scale * S| must stay in range (it does for scale ~ 1/N; the causal
+                      variant takes states of any size)                                  */
 } cotten_dtype;
 
 typedef enum cotten_layout {

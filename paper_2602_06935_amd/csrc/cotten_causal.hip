@@ -65,12 +65,13 @@ constexpr bool role_up(int role) { return role == kO || role == kDq; }  // ascen
 template <int P>
 constexpr bool separate_dv_dk() { return P == 2; }
 
-// LDS: [per wave: x tile, y tile, P pieces each][one flag per wave][one (forward) or two sets of
-// P x P operand images]
+// LDS: [per wave: x tile, y tile, P pieces each][one flag per wave][size of each state block][one
+// (forward) or two sets of P x P operand images]
 template <class F, int P, int WAVES>
 struct ScanLds {
   static constexpr int kWaveBytes = 2 * P * F::kTileBytes;
   static constexpr int kLive = WAVES * kWaveBytes;
+  static constexpr int kSizes = kLive + 8 * 4;
   static constexpr int kImages = kLive + 16 * 4;
   static constexpr int kSet = P * P * F::kImageBytes;
   static constexpr int bytes(bool bwd) { return kImages + (bwd && !separate_dv_dk<P>() ? 2 : 1) * kSet; }
@@ -139,6 +140,20 @@ __device__ __forceinline__ void stage_shared(const SharedRaw<P>& t, const Lane& 
   }
 }
 
+// States of any size in half operand images: an image holds 2^-e of the state and what comes out of a product
+// with it is multiplied by 2^e.  e = 0 while the state stays below 2^15 in magnitude (the usual
+// case: nothing is rounded differently then), otherwise what brings its largest value there.
+constexpr float kHalfTop = 32768.0f;
+struct HalfRange {
+  float factor, back;  // uniform, in scalar registers
+  __device__ __forceinline__ explicit HalfRange(float largest) {
+    const int exponent = (__builtin_amdgcn_readfirstlane(__float_as_int(largest)) >> 23) & 0xff;
+    const int e = exponent > 141 && exponent < 255 ? exponent - 141 : 0;  // 2^15 = 0.5 * 2^16, biased 142
+    factor = __int_as_float((127 - e) << 23);
+    back = __int_as_float((127 + e) << 23);
+  }
+};
+
 // What a wave carries of the state: one 32 x 32 block.  NATURAL / TRANSPOSED: which operand images
 // it keeps up to date.  The transposed one is written four values at a time from an accumulator that
 // holds the block as it is, the natural one likewise from one that holds it transposed (operands
@@ -177,31 +192,48 @@ struct Carried {
     if (kPlain) plain.mma(f);
     if (kSwapped) swapped.mma_swapped(f);
   }
-  __device__ __forceinline__ void write(unsigned char* natural, unsigned char* transposed, const Lane& L) const {
+  // The largest magnitude of the block, as far as it matters: 0 if it is below kHalfTop.
+  __device__ __forceinline__ float size() const {
+    const Acc& acc = kPlain ? plain : swapped;
+    float top = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) top = fmaxf(top, fabsf(acc.v[i]));
+    if (__builtin_amdgcn_ballot_w64(top >= kHalfTop) == 0) return 0.0f;
+#pragma unroll
+    for (int w = 1; w < 64; w <<= 1) top = fmaxf(top, __shfl_xor(top, w));
+    return top;
+  }
+  // the images of factor * state
+  __device__ __forceinline__ void write(unsigned char* natural, unsigned char* transposed, float factor,
+                                        const Lane& L) const {
     const int r0 = Acc::block_row0(block), c0 = Acc::block_col0(block), at = (p * P + q) * F::kImageBytes;
-    if (TRANSPOSED) plain.write_image(L, r0, c0, 1.0f, transposed + at);
-    if (kSwapped) swapped.write_image(L, c0, r0, 1.0f, natural + at);
+    if (TRANSPOSED) plain.write_image(L, r0, c0, factor, transposed + at);
+    if (kSwapped) swapped.write_image(L, c0, r0, factor, natural + at);
     if (kScatter) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           F::write_one_at(natural + at + F::image_offset(r0 + Acc::run_row(j, L) + i, c0 + Acc::run_col(L)),
-                          plain.v[4 * j + i]);
+                          plain.v[4 * j + i] * factor);
     }
   }
 };
 
-// out[piece] = sum_c X[piece c] W(first + c * step) over the images of a set
+// out[piece] = back * sum_c X[piece c] W(first + c * step) over the images of a set
 template <class F, int P>
 __device__ __forceinline__ void apply_set(const typename F::TileRows (&X)[P], const unsigned char* images,
-                                          int first, int step, const Lane& L, f32x4_t (&out)[F::NT]) {
+                                          int first, int step, float back, const Lane& L, f32x4_t (&out)[F::NT]) {
 #pragma unroll
   for (int c = 0; c < P; ++c) {
     typename F::Operand W;
     W.load(images + (first + c * step) * F::kImageBytes, L);
     if (c == 0) F::apply(X[c], W, out);
     else F::apply_onto(X[c], W, out);
+  }
+  if (!F::kFloatRange) {
+#pragma unroll
+    for (int nt = 0; nt < F::NT; ++nt) out[nt] *= back;
   }
 }
 
@@ -285,17 +317,26 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   unsigned char* natural = smem + Lds::kImages;
   unsigned char* transposed = smem + Lds::kImages + (ROLE == kDkDv ? Lds::kSet : 0);
   int* live = reinterpret_cast<int*>(smem + Lds::kLive);
+  float* sizes = reinterpret_cast<float*>(smem + Lds::kSizes);
 
   // the state blocks go to the waves with the fewest tile pairs
   typedef Carried<F, P, ROLE != kO && ROLE != kDv, ROLE != kDq && ROLE != kDk> State;
   const int duty = kUp ? wave : WAVES - 1 - wave;
   const bool on_duty = duty < State::kBlocks;
   State state(on_duty ? duty : 0);
+  const auto publish_size = [&] {
+    static_assert(F::kFloatRange || (State::kBlocks <= 8 && WAVES <= 8), "place for the sizes");
+    if (F::kFloatRange || !on_duty) return;
+    const float top = state.size();
+    if (L.lane == 0) sizes[duty] = top;
+  };
   bool have = false;  // the images stand for something (uniform)
   if (given != nullptr && (kUp ? segment > 0 : segment < a.segments - 1)) {
     have = true;
     if (on_duty)
       state.read(given + (static_cast<size_t>(bh) * a.segments + segment) * kState * kState, kState, L);
+    publish_size();
+    if (!F::kFloatRange) __syncthreads();
   }
 
   const auto tile_of = [&](int step) { return (kUp ? begin + step : begin - step) * WAVES + wave; };
@@ -354,7 +395,13 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
     const bool tile_live = __builtin_amdgcn_ballot_w64(shared.live != 0) != 0;
     if (tile_live) stage_shared<F, P>(shared, L, a.eps, mine);
     if (L.lane == 0) live[wave] = tile_live;
-    if (have && on_duty && applies(step)) state.write(natural, transposed, L);
+    float largest = 0.0f;  // of the state
+    if (!F::kFloatRange && have) {
+#pragma unroll
+      for (int b = 0; b < State::kBlocks; ++b) largest = fmaxf(largest, sizes[b]);
+    }
+    const HalfRange range(largest);
+    if (have && on_duty && applies(step)) state.write(natural, transposed, range.factor, L);
     TileRows x[P], y[P];
     own_rows<F, P>(nx, x);
     if (kTwoOwn) own_rows<F, P>(ny, y);
@@ -383,8 +430,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll
         for (int c = 0; c < P; ++c) {
           if (have) {
-            if (ROLE == kO) apply_set<F, P>(own, transposed, c, P, L, out[c]);
-            else apply_set<F, P>(own, natural, P * c, 1, L, out[c]);
+            if (ROLE == kO) apply_set<F, P>(own, transposed, c, P, range.back, L, out[c]);
+            else apply_set<F, P>(own, natural, P * c, 1, range.back, L, out[c]);
           } else {
 #pragma unroll
             for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -443,8 +490,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll
             for (int c = 0; c < P; ++c) {
               if (have) {
-                if (kind == 0) apply_set<F, P>(own, transposed, c, P, L, out[c]);
-                else apply_set<F, P>(own, natural, P * c, 1, L, out[c]);
+                if (kind == 0) apply_set<F, P>(own, transposed, c, P, range.back, L, out[c]);
+                else apply_set<F, P>(own, natural, P * c, 1, range.back, L, out[c]);
               } else {
 #pragma unroll
                 for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -494,6 +541,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll 2
         for (int u = 0; u < WAVES; ++u)
           if ((flags >> u) & 1) state.add(smem + u * Lds::kWaveBytes, L);
+        publish_size();
       }
     }
     __syncthreads();  // the tiles and images are written again next

@@ -96,6 +96,7 @@ typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 
 struct Bf16Elem {
+  static constexpr bool kFloatRange = true;  // (nearly) the exponents of a float
   typedef bf16x8_t v8;
   typedef bf16x4_t v4;
   static __device__ __forceinline__ float lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -126,6 +127,7 @@ struct Bf16Elem {
 };
 
 struct F16Elem {
+  static constexpr bool kFloatRange = false;
   typedef f16x8_t v8;
   typedef f16x4_t v4;
   static __device__ __forceinline__ float lo(uint32_t w) {
@@ -167,6 +169,7 @@ struct Half64 {
   typedef typename E::v8 v8_t;
   typedef typename E::v4 v4_t;
   static constexpr int D = 64, EPL = 8, NT = 4, kElemBytes = 2;
+  static constexpr bool kFloatRange = E::kFloatRange;
   // tiles in flight ahead of the one being processed, per pass (register budget permitting)
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 2, kDepthKV = 2, kDepthQAccum = 1;
   // keep-all-tiles-in-registers variants of the fused kernels: forward only (the backward
@@ -493,6 +496,7 @@ struct F32x32 {
   typedef float io_t;
   static constexpr int kMap = 0;
   static constexpr int D = 32, EPL = 4, NT = 2, kElemBytes = 4;
+  static constexpr bool kFloatRange = true;
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 3, kDepthKV = 2, kDepthQAccum = 2;
   static constexpr bool kShortFwd = true, kShortBwd = true;
   // A row of an LDS tile, or of an operand image: its 32 h pieces, its 32 m pieces, its 32 l pieces

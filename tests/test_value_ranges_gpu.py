@@ -1,0 +1,56 @@
+"""GPU parity where the values are of unusual size: states beyond the range of a half."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_06935_amd import binding
+from paper_2602_06935_amd.inputs import round_to_f16
+
+from gpu_util import F16_BAR, check_tensor, to_f64, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _causal(oracle, dtype, tensors, mask, scale, eps=1e-6):
+    """(results, oracle's results) of the causal variant: O, dQ, dK, dV."""
+    q, k, v, g = (to_gpu(x, dtype) for x in tensors)
+    m = torch.from_numpy(mask).cuda()
+    O = binding.cotten_attn_fwd(q, k, v, m, scale=scale, eps=eps, causal=True)
+    grads = binding.cotten_attn_bwd(q, k, v, m, g, scale=scale, eps=eps, causal=True)
+    torch.cuda.synchronize()
+    Q, K, V, dO = tensors
+    refs = (oracle.causal_fwd(Q, K, V, mask, scale=scale, eps=eps),
+            *oracle.causal_bwd(Q, K, V, dO, mask, scale=scale, eps=eps))
+    return [to_f64(t) for t in (O, *grads)], refs
+
+
+CAUSAL_F16 = [
+    (1030, 1, 100, 32),   # forward in two chunks of 64 rows
+    (300, 1, 200, 64),    # forward in two chunks, backward by tile pairs
+    (260, 1, 300, 64),    # one segment of three chunks
+    (2, 2, 600, 64),      # several segments, each walks what surrounds it
+    (1, 1, 1300, 64),     # states given
+]
+
+
+@pytest.mark.parametrize("B,H,N,d", CAUSAL_F16)
+@pytest.mark.parametrize("large", ["V", "dO"])
+def test_causal_half_states_beyond_its_range(oracle, B, H, N, d, large):
+    """fp16: |S| (|T|, the gradient's state) far above 65504 where |scale * S| is not: keys (queries) around
+    one direction, one large component of V (dO) throughout."""
+    print(f"[ranges] states of half {B} {H} {N} {d} {large}", flush=True)
+    rng = np.random.default_rng(61 + N)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
+    rows, values, other = (K, V, dO) if large == "V" else (Q, dO, V)
+    rows *= 0.25
+    rows[..., 3] += 4.0
+    values += 4200.0
+    other *= 0.02               # |dO . v| stays below 65504
+    tensors = [round_to_f16(x) for x in (Q, K, V, dO)]
+    mask = np.ones((B, N), np.uint8)
+    mask[B // 2, : N // 3] = 0
+    got, refs = _causal(oracle, "f16", tensors, mask, 1.0 / N)
+    state = (N - 1) * 0.9 * 4200
+    assert state > 4 * 65504 and np.abs(refs[0]).max() < 65504
+    for name, x, r in zip(("O", "dQ", "dK", "dV"), got, refs):
+        check_tensor(name, x, r, F16_BAR, few_terms=True)
