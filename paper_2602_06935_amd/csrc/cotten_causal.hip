@@ -490,8 +490,11 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll
             for (int c = 0; c < P; ++c) {
               if (have) {
-                if (kind == 0) apply_set<F, P>(own, transposed, c, P, range.back, L, out[c]);
-                else apply_set<F, P>(own, natural, P * c, 1, range.back, L, out[c]);
+                if (kind == 0) {
+                  apply_set<F, P>(own, transposed, c, P, F::kFloatRange ? 1.0f : range.back * inv_r, L, out[c]);
+                } else {
+                  apply_set<F, P>(own, natural, P * c, 1, range.back, L, out[c]);
+                }
               } else {
 #pragma unroll
                 for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -509,6 +512,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
                 query.load(tt + left + c * F::kTileBytes, L);
                 p = F::dots(query, own[c], p);
               }
+              if (kind == 0 && !F::kFloatRange) p *= inv_r;  // qhat . khat fits a half, qhat . k may not
               if (t == wave) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
@@ -518,7 +522,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
               for (int c = 0; c < P; ++c)
                 F::add_transposed_product(tt + right + c * F::kTileBytes, L, p, out[c]);
             }
-            const float factor = kind == 0 ? inv_r * scale : scale;
+            const float factor = kind == 0 && F::kFloatRange ? inv_r * scale : scale;
 #pragma unroll
             for (int c = 0; c < P; ++c) {
               product_rows<F>(out[c], o[c]);

@@ -1,4 +1,5 @@
-"""GPU parity where the values are of unusual size: states beyond the range of a half."""
+"""GPU parity where the values are of unusual size: states beyond the range of a half, keys far
+from length one."""
 import numpy as np
 import pytest
 import torch
@@ -53,4 +54,23 @@ def test_causal_half_states_beyond_its_range(oracle, B, H, N, d, large):
     state = (N - 1) * 0.9 * 4200
     assert state > 4 * 65504 and np.abs(refs[0]).max() < 65504
     for name, x, r in zip(("O", "dQ", "dK", "dV"), got, refs):
+        check_tensor(name, x, r, F16_BAR, few_terms=True)
+
+
+@pytest.mark.parametrize("B,H,N,d", [c for c in CAUSAL_F16 if c[2] != 200])
+@pytest.mark.parametrize("size", [2e-6, 1.0, 1.2e4])
+def test_causal_half_keys_of_any_size(oracle, B, H, N, d, size):
+    """fp16: the cosine map takes the length of a key out again, whatever it is."""
+    print(f"[ranges] keys of half {B} {H} {N} {d} {size}", flush=True)
+    rng = np.random.default_rng(62 + N)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
+    if size > 1:                # qhat . k above 65504
+        K = np.where(rng.random((B, H, N, 1)) < 0.5, 1.0, -1.0).astype(np.float32) + 0.1 * K
+        Q = 1.0 + 0.1 * Q
+    tensors = [round_to_f16(x) for x in (Q, K * np.float32(size), V, dO)]
+    mask = np.ones((B, N), np.uint8)
+    mask[B // 2, : N // 3] = 0
+    eps = 1e-14
+    got, refs = _causal(oracle, "f16", tensors, mask, 1.0, eps)
+    for name, x, r in zip(("O", "dV"), (got[0], got[3]), (refs[0], refs[3])):
         check_tensor(name, x, r, F16_BAR, few_terms=True)
