@@ -65,16 +65,29 @@ constexpr bool role_up(int role) { return role == kO || role == kDq; }  // ascen
 template <int P>
 constexpr bool separate_dv_dk() { return P == 2; }
 
+// An element of the carried state is a sum over all the rows before (after), and what a row gets from it
+// may be a small difference of such elements.  With 16-bit rows the state therefore has two operand
+// images, the second of what the first leaves off: 16 (bf16) and 22 bits, where the tile pairs
+// keep sums of 32 bits.  Keys and values with a common component that the queries do not see, bf16,
+// distance of O from a 64-bit evaluation, one image and two: N = 200 2.1e-2 and 4.5e-3 (tile pairs alone
+// 4.7e-3); N = 1001 6.3e-2 and 4.3e-3 (ordinary inputs 2.9e-3 and 2.5e-3).  Forward / backward, us, one and
+// two: bf16 256 slices x 1001 rows 31.7 / 75.2, 32.6 / 76.7; 64 x 1001 19.5 / 27.4, 19.9 / 28.3.
+template <class F>
+constexpr int state_images() { return F::kElemBytes == 2 ? 2 : 1; }
+
 // LDS: [per wave: x tile, y tile, P pieces each][one flag per wave][size of each state block][one
-// (forward) or two sets of P x P operand images]
+// (forward) or two sets of P x P operand images, each state_images() times]
 template <class F, int P, int WAVES>
 struct ScanLds {
   static constexpr int kWaveBytes = 2 * P * F::kTileBytes;
   static constexpr int kLive = WAVES * kWaveBytes;
   static constexpr int kSizes = kLive + 8 * 4;
   static constexpr int kImages = kLive + 16 * 4;
-  static constexpr int kSet = P * P * F::kImageBytes;
-  static constexpr int bytes(bool bwd) { return kImages + (bwd && !separate_dv_dk<P>() ? 2 : 1) * kSet; }
+  static constexpr int kSet = state_images<F>() * P * P * F::kImageBytes;
+  // `carried`: there is more than one chunk
+  static constexpr int bytes(bool bwd, bool carried) {
+    return kImages + (carried ? (bwd && !separate_dv_dk<P>() ? 2 : 1) * kSet : 0);
+  }
 };
 
 // A 16-row tile of a tensor pair on its way to LDS (load layout): piece [h][c] is bytes 128 c + 16 ch
@@ -157,8 +170,8 @@ struct HalfRange {
 // What a wave carries of the state: one 32 x 32 block.  NATURAL / TRANSPOSED: which operand images
 // it keeps up to date.  The transposed one is written four values at a time from an accumulator that
 // holds the block as it is, the natural one likewise from one that holds it transposed (operands
-// swapped).  Where both are kept, or in fp32, there is one accumulator (registers; matrix-core time)
-// and the natural image is written value by value (32 lanes write a run of one row).
+// swapped).  Where both are kept there is one accumulator (registers; matrix-core time) and the
+// natural image is written by pairs of columns: write_across().
 template <class F, int P, bool NATURAL, bool TRANSPOSED>
 struct Carried {
   typedef typename F::BlockAcc Acc;
@@ -206,16 +219,53 @@ struct Carried {
   // the images of factor * state
   __device__ __forceinline__ void write(unsigned char* natural, unsigned char* transposed, float factor,
                                         const Lane& L) const {
-    const int r0 = Acc::block_row0(block), c0 = Acc::block_col0(block), at = (p * P + q) * F::kImageBytes;
-    if (TRANSPOSED) plain.write_image(L, r0, c0, factor, transposed + at);
-    if (kSwapped) swapped.write_image(L, c0, r0, factor, natural + at);
-    if (kScatter) {
+    const int r0 = Acc::block_row0(block), c0 = Acc::block_col0(block);
+    Acc straight = plain, turned = swapped;  // (those that are not kept are not looked at)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+    for (int k = 0; k < state_images<F>(); ++k) {
+      const int at = (k * P * P + p * P + q) * F::kImageBytes;
+      const float f = k == 0 ? factor : 1.0f;
+      if (k > 0) {
+        if (kPlain) left_over(straight, factor);
+        if (kSwapped) left_over(turned, factor);
+      }
+      if (TRANSPOSED) straight.write_image(L, r0, c0, f, transposed + at);
+      if (kSwapped) turned.write_image(L, c0, r0, f, natural + at);
+      if (kScatter) write_across(straight, f, natural + at, r0, c0, L);
+    }
+  }
+  // The natural image from an accumulator that holds the block as it is: pairs of columns, the second from the
+  // neighbouring lane (even lanes write the first two rows of a run, odd lanes the last two).
+  static __device__ __forceinline__ void write_across(const Acc& acc, float factor, unsigned char* image, int r0, int c0,
+                                                      const Lane& L) {
+    const bool odd = (L.lane & 1) != 0;
+    Lane zero = L;
+    zero.set(0);
+    unsigned char* at = image + F::image_offset(r0 + Acc::run_row(0, L) + (odd ? 2 : 0), c0 + (Acc::run_col(L) & ~1));
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          F::write_one_at(natural + at + F::image_offset(r0 + Acc::run_row(j, L) + i, c0 + Acc::run_col(L)),
-                          plain.v[4 * j + i] * factor);
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const float first = acc.v[4 * j + i] * factor, second = acc.v[4 * j + 2 + i] * factor;
+        const float mine = odd ? second : first;
+        int sent = __builtin_bit_cast(int, odd ? first : second);  // (see quadrant_image)
+        asm volatile("" : "+v"(sent));
+        int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+        asm volatile("" : "+v"(got));
+        const float other = __builtin_bit_cast(float, got);
+        F::write_pair_at(at + F::image_offset(Acc::run_row(j, zero) + i, 0), odd ? other : mine, odd ? mine : other);
+      }
+  }
+  // what the image of factor * state leaves off
+  static __device__ __forceinline__ void left_over(Acc& acc, float factor) {
+    if constexpr (state_images<F>() > 1) {
+#pragma unroll
+      for (int i = 0; i < 16; i += 2) {
+        float v0 = acc.v[i] * factor, v1 = acc.v[i + 1] * factor;
+        F::left_over(v0, v1);
+        acc.v[i] = v0;
+        acc.v[i + 1] = v1;
+      }
     }
   }
 };
@@ -224,12 +274,23 @@ struct Carried {
 template <class F, int P>
 __device__ __forceinline__ void apply_set(const typename F::TileRows (&X)[P], const unsigned char* images,
                                           int first, int step, float back, const Lane& L, f32x4_t (&out)[F::NT]) {
+  if constexpr (state_images<F>() == 1) {
 #pragma unroll
-  for (int c = 0; c < P; ++c) {
-    typename F::Operand W;
-    W.load(images + (first + c * step) * F::kImageBytes, L);
-    if (c == 0) F::apply(X[c], W, out);
-    else F::apply_onto(X[c], W, out);
+    for (int c = 0; c < P; ++c) {
+      typename F::Operand W;
+      W.load(images + (first + c * step) * F::kImageBytes, L);
+      if (c == 0) F::apply(X[c], W, out);
+      else F::apply_onto(X[c], W, out);
+    }
+  } else {
+    static_assert(P == 1, "16-bit rows are one piece");
+#pragma unroll
+    for (int nt = 0; nt < F::NT; ++nt) {
+      out[nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < state_images<F>(); ++k)
+        out[nt] = F::apply_columns(X[0], images + k * F::kImageBytes, nt, L, out[nt]);
+    }
   }
   if (!F::kFloatRange) {
 #pragma unroll
@@ -295,7 +356,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   typedef typename F::TileRows TileRows;
   constexpr bool kUp = role_up(ROLE), kTwoOwn = ROLE != kO && ROLE != kDv;
   constexpr int kState = F::D * P;
-  const Lane L;
+  const Lane L0;
+  const Lane& L = L0;
   const int N = a.N, wave = L.wave;
   const int n_tiles = (N + TR - 1) / TR, chunks = (n_tiles + WAVES - 1) / WAVES;
   const size_t base = a.st.slice_base(bh, a.H);
@@ -392,6 +454,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   }
 #pragma unroll 1
   for (int step = 0; step < steps; ++step) {
+    const Lane L = P == 1 ? L0.again() : L0;  // (registers: see Lane::again)
     const bool tile_live = __builtin_amdgcn_ballot_w64(shared.live != 0) != 0;
     if (tile_live) stage_shared<F, P>(shared, L, a.eps, mine);
     if (L.lane == 0) live[wave] = tile_live;
@@ -477,6 +540,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 #pragma unroll
         for (int kind = 0; kind < 2; ++kind) {
           if (ROLE == (kind == 0 ? kDk : kDv)) continue;
+          const Lane L = P == 1 ? L0.again() : L0;  // (registers: see Lane::again)
           float o[P][2 * F::EPL];
 #pragma unroll
           for (int c = 0; c < P; ++c)
@@ -540,6 +604,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
       }
     }
     if (step + 1 < steps && flags != 0) {
+      const Lane L = P == 1 ? L0.again() : L0;  // (registers: see Lane::again)
       have = true;
       if (on_duty) {
 #pragma unroll 2
@@ -662,10 +727,10 @@ hipError_t run_scan(const Problem& p, bool bwd) {
     a.before = p.workspace;
     a.after = p.workspace + static_cast<size_t>(slices) * a.segments * side * side;
   }
-  const int lds = ScanLds<F, P, WAVES>::bytes(bwd);
+  const int lds = ScanLds<F, P, WAVES>::bytes(bwd, chunks > 1);
   const void* kern = bwd ? reinterpret_cast<const void*>(causal_scan_bwd_kernel<F, P, WAVES>)
                          : reinterpret_cast<const void*>(causal_scan_fwd_kernel<F, P, WAVES>);
-  const hipError_t err = grant_dynamic_lds(kern, lds);
+  const hipError_t err = grant_dynamic_lds(kern, ScanLds<F, P, WAVES>::bytes(bwd, true));
   if (err != hipSuccess) return err;
   const unsigned grid = static_cast<unsigned>(slices) * a.segments;
   if (bwd)
@@ -708,10 +773,11 @@ hipError_t launch_causal(const Problem& p, bool bwd) {
   //   N = 200: 256 slices 8.2 / 13.7, 9.5 / 18.2;  512: 13.9 / 26.9, 11.6 / 29.1;  4096: 100 / 161, 71 / 203
   //   N = 100: 512 slices 9.7 / 15.7, 7.4 / 17.2 (8.9 / 16.3);  4096: 62 / 103, 38 / 114 (35 / 96)
   //   N = 50:  256 slices 4.8 / 6.2, (4.5 / 8.0);  512: 7.8 / 10.6, (5.2 / 9.4);  4096: 48 / 76, (18 / 48)
+  // (The walk of these with one image per state.  With two, four waves: N = 100, 2048 slices, forward
+  // 22.0 -> 22.6; backward 49 -> 68, two workgroups per compute unit instead of four, resident 53.)
   const long slices = static_cast<long>(p.B) * p.H;
   const bool resident = causal_chunks(p.N) == 1 &&
-                        (bwd ? slices <= 256 || p.N > 128 || (p.N > 64 && slices < 1024)
-                             : slices <= 256 && p.N > 128);
+                        (bwd ? slices <= 256 || p.N > 64 : slices <= 256 && p.N > 128);
   if (resident) return launch_resident_causal(p, bwd);
   if (p.N <= 64 || (p.N <= 128 && slices >= 1024))
     return p.dtype == 1 ? run_scan<Bf16x64, 1, 4>(p, bwd) : run_scan<F16x64, 1, 4>(p, bwd);

@@ -344,6 +344,16 @@ struct Half64 {
       for (int ks = 0; ks < 2; ++ks) out[nt] = E::mfma16(W.frag[nt][ks], X.a[ks], out[nt]);
   }
 
+  // columns nt of such a product, the operand fetched on the way (8 registers of it instead of 32)
+  static __device__ __forceinline__ f32x4_t apply_columns(const TileRows& X, const unsigned char* image, int nt,
+                                                          const Lane& L, f32x4_t d) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+      d = E::mfma16(*reinterpret_cast<const v8_t*>(image + ((16 * nt + L.i16) * kImageStride + 8 * L.g16 + 32 * ks) * 2),
+                    X.a[ks], d);
+    return d;
+  }
+
   // Products of two 16-row tiles, for the kernels that work tile pair by tile pair:
   // dots(a, b) = X_a X_b^T: lane (j, g) gets rows 4g .. 4g+3 (rows of a) of column j (row of b).
   static __device__ __forceinline__ f32x4_t dots(const TileRows& a, const TileRows& b,
@@ -450,6 +460,12 @@ struct Half64 {
   }
   static __device__ __forceinline__ void write_one_at(unsigned char* at, float v) {
     *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(E::pack2(v, 0.0f));
+  }
+  // what rounding the pair to the element type leaves off
+  static __device__ __forceinline__ void left_over(float& v0, float& v1) {
+    const uint32_t w = E::pack2(v0, v1);
+    v0 -= E::lo(w);
+    v1 -= E::hi(w);
   }
   // element k of image row n
   static __device__ __forceinline__ float image_at(const unsigned char* image, int n, int k) {

@@ -1,13 +1,13 @@
 """GPU parity where the values are of unusual size: states beyond the range of a half, keys far
-from length one."""
+from length one, keys around a common direction."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2602_06935_amd import binding
-from paper_2602_06935_amd.inputs import round_to_f16
+from paper_2602_06935_amd.inputs import round_to_bf16, round_to_f16
 
-from gpu_util import F16_BAR, check_tensor, to_f64, to_gpu
+from gpu_util import F16_BAR, check_tensor, rel_l2, to_f64, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -74,3 +74,27 @@ def test_causal_half_keys_of_any_size(oracle, B, H, N, d, size):
     got, refs = _causal(oracle, "f16", tensors, mask, 1.0, eps)
     for name, x, r in zip(("O", "dV"), (got[0], got[3]), (refs[0], refs[3])):
         check_tensor(name, x, r, F16_BAR, few_terms=True)
+
+
+@pytest.mark.parametrize("B,H,N,d", [(300, 1, 200, 64), (300, 1, 140, 32), (1030, 1, 100, 64)])
+def test_causal_common_direction(oracle, B, H, N, d):
+    """bf16, up to 208 rows: keys and values with a strong common component that the queries do not see.
+    What reaches a query from far back is then small against the sums it is the difference of, and an
+    intermediate sum held in 16 bits (2^-9 of the sum, not of the result) is what such results show
+    (measured 2.1e-2; with sums of more bits 4.7e-3, the rounding of the unit rows: 2^-9 of them, twice
+    as large against the 0.45 of a key that the query sees).  Bound: twice that."""
+    print(f"[ranges] common direction {B} {H} {N} {d}", flush=True)
+    rng = np.random.default_rng(63 + N)
+    Q, K, V, dO = (0.5 * rng.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
+    c = rng.standard_normal(d).astype(np.float32)
+    K += c
+    V += rng.standard_normal(d).astype(np.float32)
+    dO += rng.standard_normal(d).astype(np.float32)
+    u = c / np.linalg.norm(c)
+    Q -= (Q @ u)[..., None] * u
+    tensors = [round_to_bf16(x) for x in (Q, K, V, dO)]
+    got, refs = _causal(oracle, "bf16", tensors, np.ones((B, N), np.uint8), 1.0 / N)
+    for name, x, r in zip(("O", "dQ", "dK", "dV"), got, refs):
+        e = rel_l2(x, r)
+        print(f"[ranges]   {name} {e:.2e}", flush=True)
+        assert e <= 1e-2, (name, e)
