@@ -312,7 +312,7 @@ __device__ __forceinline__ float own_inv(const typename F::TileRows (&x)[P], flo
   return inv_norm_or_zero(row_sum_groups(ss, L), eps, live);
 }
 
-// g <- (g - u (u.g)) / r over all pieces, from the raw rows x = r u:  g/r - x (x.g) / r^3
+// g <- (g - u (u.g)) / r over all pieces, from the raw rows x = r u:  (g - x (x.g) / r^2) / r
 template <class F, int P>
 __device__ __forceinline__ void project_own(float (&g)[P][2 * F::EPL], const typename F::TileRows (&x)[P],
                                             float inv_r, const Lane& L) {
@@ -324,14 +324,14 @@ __device__ __forceinline__ void project_own(float (&g)[P][2 * F::EPL], const typ
 #pragma unroll
     for (int i = 0; i < 2 * F::EPL; ++i) proj += f[i] * g[c][i];
   }
-  // one factor at a time: 1/r^3 alone leaves the fp32 range for rows next to zero
-  proj = row_sum_groups(proj, L) * inv_r * inv_r * inv_r;
+  // one factor at a time: 1/r^2 alone leaves the fp32 range for rows next to zero, and (x.g) / r^3 for long ones
+  proj = row_sum_groups(proj, L) * inv_r * inv_r;
 #pragma unroll
   for (int c = 0; c < P; ++c) {
     float f[2 * F::EPL];
     x[c].unpack(f);
 #pragma unroll
-    for (int i = 0; i < 2 * F::EPL; ++i) g[c][i] = g[c][i] * inv_r - f[i] * proj;
+    for (int i = 0; i < 2 * F::EPL; ++i) g[c][i] = (g[c][i] - f[i] * proj) * inv_r;
   }
 }
 

@@ -993,17 +993,17 @@ __device__ __forceinline__ void feature_grad_rows(float (&p)[2 * F::EPL],
   for (int c = 0; c < 2 * F::EPL; ++c) p[c] *= fminf(u[c], 1.0f);
 }
 
-// The same with the raw row x = r * u:  (p - u (u.p)) / r = p/r - x (x.p) / r^3.
+// The same with the raw row x = r * u:  (p - u (u.p)) / r = (p - x (x.p) / r^2) / r.
 template <class F>
 __device__ __forceinline__ void project_values(float (&p)[2 * F::EPL], const float (&x)[2 * F::EPL],
                                                float inv_r, const Lane& L) {
   float proj = 0.0f;
 #pragma unroll
   for (int c = 0; c < 2 * F::EPL; ++c) proj += x[c] * p[c];
-  // one factor at a time: 1/r^3 alone leaves the fp32 range for rows next to zero
-  proj = row_sum_groups(proj, L) * inv_r * inv_r * inv_r;
+  // one factor at a time: 1/r^2 alone leaves the fp32 range for rows next to zero, and (x.p) / r^3 for long ones
+  proj = row_sum_groups(proj, L) * inv_r * inv_r;
 #pragma unroll
-  for (int c = 0; c < 2 * F::EPL; ++c) p[c] = p[c] * inv_r - x[c] * proj;
+  for (int c = 0; c < 2 * F::EPL; ++c) p[c] = (p[c] - x[c] * proj) * inv_r;
 }
 template <class F>
 __device__ __forceinline__ void project_rows_raw(float (&p)[2 * F::EPL],

@@ -1,4 +1,4 @@
-"""GPU parity where the values are of unusual size: states beyond the range of a half, keys far
+"""GPU parity where the values are of unusual size: states beyond the range of a half, rows far
 from length one, keys around a common direction."""
 import numpy as np
 import pytest
@@ -7,7 +7,7 @@ import torch
 from paper_2602_06935_amd import binding
 from paper_2602_06935_amd.inputs import round_to_bf16, round_to_f16
 
-from gpu_util import F16_BAR, check_tensor, rel_l2, to_f64, to_gpu
+from gpu_util import F16_BAR, FP32_BAR, check_tensor, rel_l2, to_f64, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -98,3 +98,21 @@ def test_causal_common_direction(oracle, B, H, N, d):
         e = rel_l2(x, r)
         print(f"[ranges]   {name} {e:.2e}", flush=True)
         assert e <= 1e-2, (name, e)
+
+
+@pytest.mark.parametrize("B,H,N,d,causal", [
+    (2, 2, 70, 64, True), (150, 2, 100, 64, True), (2, 2, 300, 32, True), (3, 2, 100, 32, False), (2, 1, 1030, 32, False),
+])
+def test_projection_of_long_rows(oracle, B, H, N, d, causal):
+    """fp32: the part of a gradient along its own row is taken out of rows of length 1e18 too."""
+    print(f"[ranges] long rows {B} {H} {N} {d} {causal}", flush=True)
+    rng = np.random.default_rng(64 + N)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
+    Q, K, dO = Q * np.float32(1e17), K * np.float32(3e16), dO * np.float32(1e-8)
+    q, k, v, g = (to_gpu(x, "f32") for x in (Q, K, V, dO))
+    grads = binding.cotten_attn_bwd(q, k, v, None, g, scale=1.0 / N, causal=causal)
+    torch.cuda.synchronize()
+    mask = np.ones((B, N), np.uint8)
+    refs = (oracle.causal_bwd if causal else oracle.bwd)(Q, K, V, dO, mask, scale=1.0 / N)
+    for name, x, r in zip(("dQ", "dK", "dV"), grads, refs):
+        check_tensor(name, to_f64(x), r, FP32_BAR, few_terms=causal)
