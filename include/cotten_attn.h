@@ -45,8 +45,6 @@
  * pointers must be 16-byte aligned.  Outputs must not overlap inputs or each
  * other.  Masked K/V rows are never dereferenced into arithmetic: they may hold
  * anything, NaN and Inf included.
- * An infinity in a row that takes part: whatever it reaches is infinite or NaN; with fp32 I/O (whose
- * products are those of three 16-bit pieces per value) NaN.
  *
  * Arithmetic.  Row norms, the state and every accumulation are fp32 whatever
  * the I/O type (the paper keeps norms and partial sums in float32 under 16-bit

@@ -148,9 +148,24 @@ __device__ __forceinline__ void stage_shared(const SharedRaw<P>& t, const Lane& 
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[c][i] *= inv;
       F::put(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[c]);
-      F::put_raw(tiles + (P + c) * F::kTileBytes, L.r8 + 8 * h, L.ch, t.y[h][c]);
     }
   }
+  float top = 0.0f;
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+      float y[F::EPL];
+      F::unpack(t.y[h][c], y);
+      top = largest(y, top);
+    }
+  write_pieces<F>(top, [&](auto inf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+        F::template put_raw<decltype(inf)::value>(tiles + (P + c) * F::kTileBytes, L.r8 + 8 * h, L.ch, t.y[h][c]);
+  });
 }
 
 // States of any size in half operand images: an image holds 2^-e of the state and what comes out of a product
@@ -242,19 +257,27 @@ struct Carried {
     Lane zero = L;
     zero.set(0);
     unsigned char* at = image + F::image_offset(r0 + Acc::run_row(0, L) + (odd ? 2 : 0), c0 + (Acc::run_col(L) & ~1));
+    float top = 0.0f;
+    if (F::kPieces) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+      for (int i = 0; i < 16; ++i) top = fmaxf(top, fabsf(acc.v[i]));
+    }
+    write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const float first = acc.v[4 * j + i] * factor, second = acc.v[4 * j + 2 + i] * factor;
-        const float mine = odd ? second : first;
-        int sent = __builtin_bit_cast(int, odd ? first : second);  // (see quadrant_image)
-        asm volatile("" : "+v"(sent));
-        int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
-        asm volatile("" : "+v"(got));
-        const float other = __builtin_bit_cast(float, got);
-        F::write_pair_at(at + F::image_offset(Acc::run_row(j, zero) + i, 0), odd ? other : mine, odd ? mine : other);
-      }
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float first = acc.v[4 * j + i] * factor, second = acc.v[4 * j + 2 + i] * factor;
+          const float mine = odd ? second : first;
+          int sent = __builtin_bit_cast(int, odd ? first : second);  // (see quadrant_image)
+          asm volatile("" : "+v"(sent));
+          int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+          asm volatile("" : "+v"(got));
+          const float other = __builtin_bit_cast(float, got);
+          F::template write_pair_at<decltype(inf)::value>(at + F::image_offset(Acc::run_row(j, zero) + i, 0),
+                                                          odd ? other : mine, odd ? mine : other);
+        }
+    });
   }
   // what the image of factor * state leaves off
   static __device__ __forceinline__ void left_over(Acc& acc, float factor) {
@@ -466,8 +489,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
     const HalfRange range(largest);
     if (have && on_duty && applies(step)) state.write(natural, transposed, range.factor, L);
     TileRows x[P], y[P];
-    own_rows<F, P>(nx, x);
-    if (kTwoOwn) own_rows<F, P>(ny, y);
+    own_rows<F, P, false>(nx, x);
+    if (kTwoOwn) own_rows<F, P, true>(ny, y);
     const bool row_live = next_live;
     const int tile = tile_of(step);
     if (step + 1 < steps) {
@@ -519,7 +542,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
           }
 #pragma unroll
           for (int c = 0; c < P; ++c)
-            F::add_transposed_product(tu + ((ROLE == kO ? P : 0) + c) * F::kTileBytes, L, pt, out[c]);
+            F::template add_transposed_product<ROLE != kO>(tu + ((ROLE == kO ? P : 0) + c) * F::kTileBytes, L, pt, out[c]);
         }
         const float inv_r = own_inv<F, P>(x, a.eps, row_live, L);
         const float factor = ROLE == kO ? inv_r * scale : scale;
@@ -584,7 +607,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
               }
 #pragma unroll
               for (int c = 0; c < P; ++c)
-                F::add_transposed_product(tt + right + c * F::kTileBytes, L, p, out[c]);
+                if (kind == 0) F::add_transposed_product(tt + right + c * F::kTileBytes, L, p, out[c]);
+                else F::template add_transposed_product<true>(tt + right + c * F::kTileBytes, L, p, out[c]);
             }
             const float factor = kind == 0 && F::kFloatRange ? inv_r * scale : scale;
 #pragma unroll

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace cotten {
 namespace mfma {
 
@@ -169,7 +171,7 @@ struct Half64 {
   typedef typename E::v8 v8_t;
   typedef typename E::v4 v4_t;
   static constexpr int D = 64, EPL = 8, NT = 4, kElemBytes = 2;
-  static constexpr bool kFloatRange = E::kFloatRange;
+  static constexpr bool kFloatRange = E::kFloatRange, kPieces = false;
   // tiles in flight ahead of the one being processed, per pass (register budget permitting)
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 2, kDepthKV = 2, kDepthQAccum = 1;
   // keep-all-tiles-in-registers variants of the fused kernels: forward only (the backward
@@ -204,9 +206,11 @@ struct Half64 {
   }
 
   // the lane's EPL values (load layout: columns 8*ch ..) of tile row `row`
+  template <bool = false>
   static __device__ __forceinline__ void put(unsigned char* T, int row, int ch, const float (&f)[8]) {
     put_raw(T, row, ch, pack(f));
   }
+  template <bool = false>
   static __device__ __forceinline__ void put_raw(unsigned char* T, int row, int ch, u32x4_t r) {
     *reinterpret_cast<u32x4_t*>(T + row * kTileStride + ch * 16) = r;
   }
@@ -283,11 +287,13 @@ struct Half64 {
         a[ks] = *reinterpret_cast<const v8_t*>(T + L.i16 * kTileStride + (8 * L.g16 + 32 * ks) * 2);
     }
     // the two 16-byte pieces of the lane's row as 128-bit loads of global memory bring them
+    template <bool = false>
     __device__ __forceinline__ void set(u32x4_t r0, u32x4_t r1) {
       a[0] = __builtin_bit_cast(v8_t, r0);
       a[1] = __builtin_bit_cast(v8_t, r1);
     }
     // from the row's values: f[8j + i] is column 32j + 8*g16 + i
+    template <bool = false>
     __device__ __forceinline__ void set(const float (&f)[16]) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
@@ -367,6 +373,7 @@ struct Half64 {
   // operand, so P goes in without moving between lanes; X^T comes from the transposing LDS
   // read (lane i of a 16-lane group gets rows 4g .. 4g+3 of column out_col(nt, i/4) + i%4), so
   // the result lands in the product layout.
+  template <bool = false>
   static __device__ __forceinline__ void add_transposed_product(const unsigned char* T,
                                                                 const Lane& L, f32x4_t p,
                                                                 f32x4_t (&out)[4]) {
@@ -443,6 +450,7 @@ struct Half64 {
   };
 
   // two neighbouring image elements (k, k+1) of image row n
+  template <bool = false>
   static __device__ __forceinline__ void write_image_pair(unsigned char* image, int n, int k,
                                                           float v0, float v1) {
     *reinterpret_cast<uint32_t*>(image + (image_row(n) * kImageStride + k) * 2) = E::pack2(v0, v1);
@@ -452,14 +460,13 @@ struct Half64 {
   static __device__ __forceinline__ int image_offset(int n, int k) {
     return (image_row(n) * kImageStride + k) * 2;
   }
+  template <bool = false>
   static __device__ __forceinline__ void write_four_at(unsigned char* at, f32x4_t v) {
     *reinterpret_cast<u32x2_t*>(at) = u32x2_t{E::pack2(v[0], v[1]), E::pack2(v[2], v[3])};
   }
+  template <bool = false>
   static __device__ __forceinline__ void write_pair_at(unsigned char* at, float v0, float v1) {
     *reinterpret_cast<uint32_t*>(at) = E::pack2(v0, v1);
-  }
-  static __device__ __forceinline__ void write_one_at(unsigned char* at, float v) {
-    *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(E::pack2(v, 0.0f));
   }
   // what rounding the pair to the element type leaves off
   static __device__ __forceinline__ void left_over(float& v0, float& v1) {
@@ -488,7 +495,12 @@ typedef Half64<F16Elem> F16x64;
 // vector operations per pair of values cut.  Measured (a training step, us, fp32 products before and
 // this): 512 slices x 200 rows, d_h = 128 333 and 202 (with the kernels of cotten_wide32.hip), d_h = 32
 // 31.3 and 30.1; distance from a 64-bit evaluation 1.5e-7 ... 2.5e-7 and 1.1e-7 ... 1.5e-7.
-// An infinity has no such pieces: it comes out as NaN in every element it reaches.
+//
+// An infinity has no such pieces.  Its own are h = +-1, m = 0, l = +-inf: of the six products with a finite
+// y, l h' is the infinity of the right sign (NaN for y = 0) and the others are finite, and of those
+// with another infinity h l' and l h' are infinities of the same sign.  Rows that the cosine map divides by
+// their length need no such care (an infinity makes them NaN); the others are looked over for one
+// (one operation per pair of values) and cut again if there is one: write_pieces().
 struct Pieces {
   bf16x8_t h, m, l;  // of eight values
 };
@@ -497,8 +509,48 @@ __device__ __forceinline__ void split_pair(float a, float b, uint32_t& h, uint32
   h = __builtin_amdgcn_perm(ub, ua, 0x07060302);  // the upper halves
   const float ra = a - __uint_as_float(ua & 0xffff0000u), rb = b - __uint_as_float(ub & 0xffff0000u);
   m = pack_bf16(ra, rb);
+  asm("" : "+v"(m));  // (otherwise one of the pair is converted a second time for the next line)
   const float sa = ra - Bf16Elem::lo(m), sb = rb - Bf16Elem::hi(m);
   l = __builtin_amdgcn_perm(__float_as_uint(sb), __float_as_uint(sa), 0x07060302);
+}
+// n values, value i in half i % 2 of word i / 2.  INF: some may be infinite.
+template <bool INF, int N>
+__device__ __forceinline__ void split(const float (&v)[N], uint32_t (&h)[N / 2], uint32_t (&m)[N / 2],
+                                      uint32_t (&l)[N / 2]) {
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) {
+    split_pair(v[2 * i], v[2 * i + 1], h[i], m[i], l[i]);
+    if (INF) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t half = 0xffffu << (16 * j), word = __float_as_uint(v[2 * i + j]), sign = word & 0x80000000u;
+        if ((word & 0x7fffffffu) != 0x7f800000u) continue;
+        h[i] = (h[i] & ~half) | (sign | 0x3f800000u) >> (16 - 16 * j);
+        m[i] &= ~half;
+        l[i] = (l[i] & ~half) | word >> (16 - 16 * j);
+      }
+    }
+  }
+}
+template <int N>
+__device__ __forceinline__ float largest(const float (&v)[N], float so_far = 0.0f) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) so_far = fmaxf(so_far, fabsf(v[i]));  // (NaN is passed over)
+  return so_far;
+}
+__device__ __forceinline__ float largest(f32x4_t v, float so_far = 0.0f) {
+  const float f[4] = {v[0], v[1], v[2], v[3]};
+  return largest(f, so_far);
+}
+// write(std::false_type): values to where a product reads them, infinities not thought of.  `largest`: the
+// largest magnitude of what the lane writes; if a lane of the wave has an infinity, write(std::true_type) follows.
+// (Formats without pieces write once.)
+template <class F, class Write>
+__device__ __forceinline__ void write_pieces(float largest, Write&& write) {
+  write(std::false_type{});
+  if constexpr (F::kPieces) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(largest == __builtin_inff()) != 0, 0)) write(std::true_type{});
+  }
 }
 // the two values back, exactly
 __device__ __forceinline__ float whole_lo(uint32_t h, uint32_t m, uint32_t l) {
@@ -512,7 +564,7 @@ struct F32x32 {
   typedef float io_t;
   static constexpr int kMap = 0;
   static constexpr int D = 32, EPL = 4, NT = 2, kElemBytes = 4;
-  static constexpr bool kFloatRange = true;
+  static constexpr bool kFloatRange = true, kPieces = true;
   static constexpr int kDepthState = 3, kDepthFwd = 3, kDepthQ = 3, kDepthKV = 2, kDepthQAccum = 2;
   static constexpr bool kShortFwd = true, kShortBwd = true;
   // A row of an LDS tile, or of an operand image: its 32 h pieces, its 32 m pieces, its 32 l pieces
@@ -544,25 +596,24 @@ struct F32x32 {
   }
 
   // four neighbouring places (multiples of four) of a plane row
-  static __device__ __forceinline__ void write_four(unsigned char* at, float a, float b, float c, float d) {
-    u32x2_t h, m, l;
-    uint32_t ph, pm, pl;
-    split_pair(a, b, ph, pm, pl);
-    h[0] = ph, m[0] = pm, l[0] = pl;
-    split_pair(c, d, ph, pm, pl);
-    h[1] = ph, m[1] = pm, l[1] = pl;
-    *reinterpret_cast<u32x2_t*>(at) = h;
-    *reinterpret_cast<u32x2_t*>(at + kPlane) = m;
-    *reinterpret_cast<u32x2_t*>(at + 2 * kPlane) = l;
+  template <bool INF>
+  static __device__ __forceinline__ void write_four(unsigned char* at, const float (&f)[4]) {
+    uint32_t h[2], m[2], l[2];
+    split<INF>(f, h, m, l);
+    *reinterpret_cast<u32x2_t*>(at) = u32x2_t{h[0], h[1]};
+    *reinterpret_cast<u32x2_t*>(at + kPlane) = u32x2_t{m[0], m[1]};
+    *reinterpret_cast<u32x2_t*>(at + 2 * kPlane) = u32x2_t{l[0], l[1]};
   }
   // the lane's EPL values (load layout: columns 4*ch ..) of tile row `row`
+  template <bool INF = false>
   static __device__ __forceinline__ void put(unsigned char* T, int row, int ch, const float (&f)[4]) {
-    write_four(T + row * kTileStride + 16 * (ch & 3) + 8 * (ch >> 2), f[0], f[1], f[2], f[3]);
+    write_four<INF>(T + row * kTileStride + 16 * (ch & 3) + 8 * (ch >> 2), f);
   }
+  template <bool INF = false>
   static __device__ __forceinline__ void put_raw(unsigned char* T, int row, int ch, u32x4_t r) {
     float f[4];
     unpack(r, f);
-    put(T, row, ch, f);
+    put<INF>(T, row, ch, f);
   }
 
   static __device__ __forceinline__ f32x16_t mfma32(const Pieces& a, const Pieces& b, f32x16_t v) {
@@ -646,17 +697,15 @@ struct F32x32 {
       a.l = *reinterpret_cast<const bf16x8_t*>(p + 2 * kPlane);
     }
     // from the row's values: f[4j + i] is column 16j + 4*g16 + i
+    template <bool INF = false>
     __device__ __forceinline__ void set(const float (&f)[8]) {
-      u32x4_t h, m, l;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        uint32_t ph, pm, pl;
-        split_pair(f[2 * i], f[2 * i + 1], ph, pm, pl);
-        h[i] = ph, m[i] = pm, l[i] = pl;
-      }
-      a = Pieces{__builtin_bit_cast(bf16x8_t, h), __builtin_bit_cast(bf16x8_t, m),
-                 __builtin_bit_cast(bf16x8_t, l)};
+      uint32_t h[4], m[4], l[4];
+      split<INF>(f, h, m, l);
+      a = Pieces{__builtin_bit_cast(bf16x8_t, (u32x4_t{h[0], h[1], h[2], h[3]})),
+                 __builtin_bit_cast(bf16x8_t, (u32x4_t{m[0], m[1], m[2], m[3]})),
+                 __builtin_bit_cast(bf16x8_t, (u32x4_t{l[0], l[1], l[2], l[3]}))};
     }
+    template <bool INF = false>
     __device__ __forceinline__ void set(u32x4_t r0, u32x4_t r1) {
       float f[8];
 #pragma unroll
@@ -664,7 +713,7 @@ struct F32x32 {
         f[i] = __uint_as_float(r0[i]);
         f[4 + i] = __uint_as_float(r1[i]);
       }
-      set(f);
+      set<INF>(f);
     }
     __device__ __forceinline__ void unpack(float (&f)[8]) const {
       const u32x4_t h = __builtin_bit_cast(u32x4_t, a.h), m = __builtin_bit_cast(u32x4_t, a.m),
@@ -703,18 +752,16 @@ struct F32x32 {
   }
   // out += X^T P (see Half64).  The contraction runs over 16 rows where a 16x16x32 product takes 32:
   // the two halves of its depth carry two products of pieces at a time, three instead of six.
+  template <bool INF = false>
   static __device__ __forceinline__ void add_transposed_product(const unsigned char* T,
                                                                 const Lane& L, f32x4_t p,
                                                                 f32x4_t (&out)[2]) {
-    u32x2_t h, m, l;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      uint32_t ph, pm, pl;
-      split_pair(p[2 * i], p[2 * i + 1], ph, pm, pl);
-      h[i] = ph, m[i] = pm, l[i] = pl;
-    }
-    const bf16x4_t bh = __builtin_bit_cast(bf16x4_t, h), bm = __builtin_bit_cast(bf16x4_t, m),
-                   bl = __builtin_bit_cast(bf16x4_t, l);
+    const float f[4] = {p[0], p[1], p[2], p[3]};
+    uint32_t h[2], m[2], l[2];
+    split<false>(f, h, m, l);
+    if (INF && __builtin_expect(__builtin_amdgcn_ballot_w64(largest(f) == __builtin_inff()) != 0, 0)) split<true>(f, h, m, l);
+    const bf16x4_t bh = __builtin_bit_cast(bf16x4_t, (u32x2_t{h[0], h[1]})), bm = __builtin_bit_cast(bf16x4_t, (u32x2_t{m[0], m[1]})),
+                   bl = __builtin_bit_cast(bf16x4_t, (u32x2_t{l[0], l[1]}));
     const bf16x8_t hh = both(bh, bh), mm = both(bm, bm), hl = both(bh, bl);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
@@ -749,37 +796,41 @@ struct F32x32 {
     static __device__ __forceinline__ int run_col(const Lane& L) { return F32x32::run_col(L); }
     __device__ __forceinline__ void write_image(const Lane& L, int r0, int c0, float scale,
                                                 unsigned char* image) const {
+      float top = 0.0f;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        write_four_at(image + image_offset(c0 + run_col(L), r0 + run_row(j, L)), quad(v, j) * scale);
+        top = largest(quad(v, j) * scale, top);
+      write_pieces<F32x32>(top, [&](auto inf) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          write_four_at<decltype(inf)::value>(image + image_offset(c0 + run_col(L), r0 + run_row(j, L)), quad(v, j) * scale);
+      });
     }
     static __device__ __forceinline__ int block_row0(int) { return 0; }
     static __device__ __forceinline__ int block_col0(int) { return 0; }
   };
 
+  template <bool INF = false>
   static __device__ __forceinline__ void write_image_pair(unsigned char* image, int n, int k,
                                                           float v0, float v1) {
-    write_pair_at(image + image_offset(n, k), v0, v1);
+    write_pair_at<INF>(image + image_offset(n, k), v0, v1);
   }
   static __device__ __forceinline__ int image_offset(int n, int k) {
     return n * kImageStride + place(k) * 2;
   }
+  template <bool INF = false>
   static __device__ __forceinline__ void write_four_at(unsigned char* at, f32x4_t v) {
-    write_four(at, v[0], v[1], v[2], v[3]);
+    const float f[4] = {v[0], v[1], v[2], v[3]};
+    write_four<INF>(at, f);
   }
+  template <bool INF = false>
   static __device__ __forceinline__ void write_pair_at(unsigned char* at, float v0, float v1) {
-    uint32_t h, m, l;
-    split_pair(v0, v1, h, m, l);
-    *reinterpret_cast<uint32_t*>(at) = h;
-    *reinterpret_cast<uint32_t*>(at + kPlane) = m;
-    *reinterpret_cast<uint32_t*>(at + 2 * kPlane) = l;
-  }
-  static __device__ __forceinline__ void write_one_at(unsigned char* at, float v) {
-    uint32_t h, m, l;
-    split_pair(v, 0.0f, h, m, l);
-    *reinterpret_cast<uint16_t*>(at) = static_cast<uint16_t>(h);
-    *reinterpret_cast<uint16_t*>(at + kPlane) = static_cast<uint16_t>(m);
-    *reinterpret_cast<uint16_t*>(at + 2 * kPlane) = static_cast<uint16_t>(l);
+    const float f[2] = {v0, v1};
+    uint32_t h[1], m[1], l[1];
+    split<INF>(f, h, m, l);
+    *reinterpret_cast<uint32_t*>(at) = h[0];
+    *reinterpret_cast<uint32_t*>(at + kPlane) = m[0];
+    *reinterpret_cast<uint32_t*>(at + 2 * kPlane) = l[0];
   }
   static __device__ __forceinline__ float image_at(const unsigned char* image, int n, int k) {
     const uint16_t* p = reinterpret_cast<const uint16_t*>(image + image_offset(n, k));
@@ -906,32 +957,44 @@ constexpr int mapped_mode() {
 template <class F, int XMODE, bool USE_Y>
 __device__ __forceinline__ void stage(const Raw& r, const Lane& L, float eps, unsigned char* Xt,
                                       unsigned char* Yt, float (&inv)[2], bool cols = true) {
+  float mapped[2][F::EPL], top = 0.0f;  // (top: of what may be infinite)
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    float f[F::EPL];
+    float(&f)[F::EPL] = mapped[h];
     F::unpack(r.x[h], f);
+    const bool live = ((r.live >> h) & 1) != 0;
     if (XMODE == kXFeature) {
-      const bool live = ((r.live >> h) & 1) != 0;
       inv[h] = live ? 1.0f : 0.0f;
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[i] = (live && cols) ? elu1(f[i]) : 0.0f;
-      F::put(Xt, L.r8 + 8 * h, L.ch, f);
-      if (USE_Y) F::put_raw(Yt, L.r8 + 8 * h, L.ch, r.y[h]);
-      continue;
-    }
-    float ss = 0.0f;
+      top = largest(f, top);
+    } else {
+      float ss = 0.0f;
 #pragma unroll
-    for (int i = 0; i < F::EPL; ++i) ss += f[i] * f[i];
-    inv[h] = inv_norm_or_zero(row_sum8(ss), eps, (r.live >> h) & 1);
-    if (XMODE == kXNormalized) {
+      for (int i = 0; i < F::EPL; ++i) ss += f[i] * f[i];
+      inv[h] = inv_norm_or_zero(row_sum8(ss), eps, live);
+      if (XMODE == kXNormalized) {
 #pragma unroll
-      for (int i = 0; i < F::EPL; ++i) f[i] *= inv[h];
-      F::put(Xt, L.r8 + 8 * h, L.ch, f);
-    } else if (XMODE == kXRaw) {
-      F::put_raw(Xt, L.r8 + 8 * h, L.ch, r.x[h]);
+        for (int i = 0; i < F::EPL; ++i) f[i] *= inv[h];
+      }
     }
-    if (USE_Y) F::put_raw(Yt, L.r8 + 8 * h, L.ch, r.y[h]);
+    if (USE_Y) {
+      float y[F::EPL];
+      F::unpack(r.y[h], y);
+      top = largest(y, top);
+    }
   }
+  write_pieces<F>(top, [&](auto inf) {
+    constexpr bool kInf = decltype(inf)::value;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int row = L.r8 + 8 * h;
+      if (XMODE == kXFeature) F::template put<kInf>(Xt, row, L.ch, mapped[h]);
+      if (XMODE == kXNormalized && !kInf) F::put(Xt, row, L.ch, mapped[h]);
+      if (XMODE == kXRaw && !kInf) F::put_raw(Xt, row, L.ch, r.x[h]);
+      if (USE_Y) F::template put_raw<kInf>(Yt, row, L.ch, r.y[h]);
+    }
+  });
 }
 
 // ---- epilogues in the product layout ------------------------------------------------------
@@ -1091,10 +1154,23 @@ __device__ __forceinline__ void own_values(const OwnRaw<P>& t, int c, float (&f)
   }
 }
 
-template <class F, int P>
+// (INF: rows that the cosine map does not divide by their length)
+template <class F, int P, bool INF>
 __device__ __forceinline__ void own_rows(const OwnRaw<P>& t, typename F::TileRows (&x)[P]) {
+  float top = 0.0f;
+  if (F::kPieces && INF) {
 #pragma unroll
-  for (int c = 0; c < P; ++c) x[c].set(t.r[c][0], t.r[c][1]);
+    for (int c = 0; c < P; ++c) {
+      float f[2 * F::EPL];
+      own_values<F, P>(t, c, f);
+      top = largest(f, top);
+    }
+  }
+  write_pieces<F>(top, [&](auto inf) {
+    if (decltype(inf)::value && !INF) return;
+#pragma unroll
+    for (int c = 0; c < P; ++c) x[c].template set<decltype(inf)::value>(t.r[c][0], t.r[c][1]);
+  });
 }
 
 // ---- states into operand images --------------------------------------------------------------
@@ -1114,27 +1190,35 @@ __device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned ch
   zero.set(0);
   unsigned char* at = image + (NATURAL ? F::image_offset(lane_row + (odd ? 2 : 0), lane_col & ~1)
                                        : F::image_offset(lane_col, lane_row));
+  float top = 0.0f;
+  if (F::kPieces) {
 #pragma unroll
-  for (int g = 0; g < F::Acc::kGroups; ++g) {
-    const f32x4_t v = get(g) * scale;
-    const int row = F::Acc::group_row(g, zero), col = F::Acc::group_col(g, zero);  // the group's part
-    if (!NATURAL) {
-      F::write_four_at(at + F::image_offset(col, row), v);
-    } else {
-      // The lane sends what its neighbour wants (the choice is made on the sending side: a
-      // choice between two values received from the neighbour would be evaluated over there).
+    for (int g = 0; g < F::Acc::kGroups; ++g) top = largest(get(g) * scale, top);
+  }
+  write_pieces<F>(top, [&](auto inf) {
+    constexpr bool kInf = decltype(inf)::value;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const float mine = odd ? v[2 + i] : v[i];
-        int sent = __builtin_bit_cast(int, odd ? v[i] : v[2 + i]);
-        asm volatile("" : "+v"(sent));
-        int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
-        asm volatile("" : "+v"(got));
-        const float other = __builtin_bit_cast(float, got);
-        F::write_pair_at(at + F::image_offset(row + i, col), odd ? other : mine, odd ? mine : other);
+    for (int g = 0; g < F::Acc::kGroups; ++g) {
+      const f32x4_t v = get(g) * scale;
+      const int row = F::Acc::group_row(g, zero), col = F::Acc::group_col(g, zero);  // the group's part
+      if (!NATURAL) {
+        F::template write_four_at<kInf>(at + F::image_offset(col, row), v);
+      } else {
+        // The lane sends what its neighbour wants (the choice is made on the sending side: a
+        // choice between two values received from the neighbour would be evaluated over there).
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const float mine = odd ? v[2 + i] : v[i];
+          int sent = __builtin_bit_cast(int, odd ? v[i] : v[2 + i]);
+          asm volatile("" : "+v"(sent));
+          int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+          asm volatile("" : "+v"(got));
+          const float other = __builtin_bit_cast(float, got);
+          F::template write_pair_at<kInf>(at + F::image_offset(row + i, col), odd ? other : mine, odd ? mine : other);
+        }
       }
     }
-  }
+  });
 }
 
 }  // namespace mfma

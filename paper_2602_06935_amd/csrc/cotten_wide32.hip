@@ -108,34 +108,54 @@ __device__ __forceinline__ void load_half(Half16<P>& t, const Lane& L, const Buf
 template <class F, int P>
 __device__ __forceinline__ void stage_mapped(const Half16<P>& t, int bits, const Lane& L, float eps,
                                              unsigned char* tiles) {
+  float f[2][P][F::EPL], top = 0.0f;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const bool live = ((bits >> h) & 1) != 0;
-    float f[P][F::EPL];
     float ss = 0.0f;
 #pragma unroll
     for (int c = 0; c < P; ++c) {
-      F::unpack(t.r[h][c], f[c]);
+      F::unpack(t.r[h][c], f[h][c]);
 #pragma unroll
-      for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
+      for (int i = 0; i < F::EPL; ++i) ss += f[h][c][i] * f[h][c][i];
     }
     const float inv = F::kMap == kMapElu1 ? 1.0f : inv_norm_or_zero(row_sum8(ss), eps, live);
 #pragma unroll
     for (int c = 0; c < P; ++c) {
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i)
-        f[c][i] = F::kMap == kMapElu1 ? (live ? elu1(f[c][i]) : 0.0f) : f[c][i] * inv;
-      F::put(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[c]);
+        f[h][c][i] = F::kMap == kMapElu1 ? (live ? elu1(f[h][c][i]) : 0.0f) : f[h][c][i] * inv;
+      if (F::kMap == kMapElu1) top = largest(f[h][c], top);
     }
   }
+  write_pieces<F>(top, [&](auto inf) {
+    if (decltype(inf)::value && F::kMap != kMapElu1) return;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+        F::template put<decltype(inf)::value>(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[h][c]);
+  });
 }
 
 template <class F, int P>
 __device__ __forceinline__ void stage_plain(const Half16<P>& t, const Lane& L, unsigned char* tiles) {
+  float top = 0.0f;
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int c = 0; c < P; ++c) F::put_raw(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, t.r[h][c]);
+    for (int c = 0; c < P; ++c) {
+      float f[F::EPL];
+      F::unpack(t.r[h][c], f);
+      top = largest(f, top);
+    }
+  write_pieces<F>(top, [&](auto inf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+        F::template put_raw<decltype(inf)::value>(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, t.r[h][c]);
+  });
 }
 
 // The blocks of the complete state that a wave ends up with: block j is piece p of the left rows
@@ -369,8 +389,15 @@ __device__ __forceinline__ void walk_quadrants(State<F, 4>& out, const Buffers& 
       const bool any = __builtin_amdgcn_ballot_w64(on) != 0;
       if (L.lane == 0) live_halves[4 * buffer + L.wave] = any;
     }
+    float top = 0.0f;
 #pragma unroll
-    for (int c = 0; c < P; ++c) F::put(mine + buffer * kBuffer + c * F::kTileBytes, row & 15, L.ch, f[c]);
+    for (int c = 0; c < P; ++c) top = largest(f[c], top);
+    if (F::kMap != kMapElu1 && part == 0) top = 0.0f;
+    write_pieces<F>(top, [&](auto inf) {
+#pragma unroll
+      for (int c = 0; c < P; ++c)
+        F::template put<decltype(inf)::value>(mine + buffer * kBuffer + c * F::kTileBytes, row & 15, L.ch, f[c]);
+    });
   };
   bool next_live = row_at(begin + 2 * kRound);
 #pragma unroll
@@ -498,7 +525,7 @@ __device__ __forceinline__ float own_factor(const OwnRaw<P>& t, float eps, bool 
 template <class F, int P>
 __device__ __forceinline__ void own_mapped(const OwnRaw<P>& t, bool live, typename F::TileRows (&x)[P]) {
   if (F::kMap != kMapElu1) {
-    own_rows<F, P>(t, x);
+    own_rows<F, P, false>(t, x);
     return;
   }
 #pragma unroll
@@ -507,7 +534,7 @@ __device__ __forceinline__ void own_mapped(const OwnRaw<P>& t, bool live, typena
     own_values<F, P>(t, c, f);
 #pragma unroll
     for (int i = 0; i < 2 * F::EPL; ++i) f[i] = live ? elu1(f[i]) : 0.0f;
-    x[c].set(f);
+    write_pieces<F>(largest(f), [&](auto inf) { x[c].template set<decltype(inf)::value>(f); });
   }
 }
 
@@ -569,7 +596,7 @@ __device__ __forceinline__ float projected_tile(const OwnRaw<P>& x, const OwnRaw
   float g[P][2 * F::EPL];
   {
     typename F::TileRows Y[P];
-    own_rows<F, P>(y, Y);
+    own_rows<F, P, true>(y, Y);
     y_used();
 #pragma unroll
     for (int p = 0; p < P; ++p) product<F, P>(Y, images, P * p, 1, L, g[p]);
@@ -808,15 +835,17 @@ __device__ __forceinline__ void build_images(const float* __restrict__ M, float 
         v1[j] = v.y;
       }
     }
+    write_pieces<F>(largest(v0, largest(v1)) * scale, [&](auto inf) {
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const int e = e0 + j * kThreads;
-      const int m = TRANSPOSED ? 2 * (e / D) : e / (D / 2);
-      const int n = TRANSPOSED ? e % D : 2 * (e % (D / 2));
-      unsigned char* image = images + (P * (m / F::D) + n / F::D) * F::kImageBytes;
-      if (TRANSPOSED) F::write_image_pair(image, n % F::D, m % F::D, v0[j] * scale, v1[j] * scale);
-      else F::write_image_pair(image, m % F::D, n % F::D, v0[j] * scale, v1[j] * scale);
-    }
+      for (int j = 0; j < kBatch; ++j) {
+        const int e = e0 + j * kThreads;
+        const int m = TRANSPOSED ? 2 * (e / D) : e / (D / 2);
+        const int n = TRANSPOSED ? e % D : 2 * (e % (D / 2));
+        unsigned char* image = images + (P * (m / F::D) + n / F::D) * F::kImageBytes;
+        if (TRANSPOSED) F::template write_image_pair<decltype(inf)::value>(image, n % F::D, m % F::D, v0[j] * scale, v1[j] * scale);
+        else F::template write_image_pair<decltype(inf)::value>(image, m % F::D, n % F::D, v0[j] * scale, v1[j] * scale);
+      }
+    });
   }
 }
 

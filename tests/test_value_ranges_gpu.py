@@ -1,5 +1,5 @@
-"""GPU parity where the values are of unusual size: states beyond the range of a half, rows far
-from length one, keys around a common direction."""
+"""GPU parity where the values are of unusual size: states beyond the range of a half, rows far from
+length one, keys around a common direction, infinities."""
 import numpy as np
 import pytest
 import torch
@@ -116,3 +116,50 @@ def test_projection_of_long_rows(oracle, B, H, N, d, causal):
     refs = (oracle.causal_bwd if causal else oracle.bwd)(Q, K, V, dO, mask, scale=1.0 / N)
     for name, x, r in zip(("dQ", "dK", "dV"), grads, refs):
         check_tensor(name, to_f64(x), r, FP32_BAR, few_terms=causal)
+
+
+INFINITE = [
+    (2, 2, 50, 32, 0), (300, 1, 300, 32, 0), (2, 1, 1030, 32, 0),
+    (3, 2, 70, 64, 0), (150, 2, 100, 64, 0), (2, 1, 700, 64, 0), (3, 1, 100, 128, 0), (2, 1, 700, 128, 0),
+    (3, 2, 200, 64, 1), (150, 2, 100, 64, 1), (3, 2, 100, 32, 1), (2, 1, 2100, 32, 1),
+]
+
+
+@pytest.mark.parametrize("feature_map", ["cosine", "elu1"])
+@pytest.mark.parametrize("B,H,N,d,causal", INFINITE)
+def test_fp32_infinities(B, H, N, d, causal, feature_map):
+    """fp32: an infinite value gives infinities of its sign where all it meets has one sign, and leaves what
+    it does not meet alone: one component of V (of dO) infinite in one row, rows of Q and K positive."""
+    if causal and feature_map == "elu1":
+        pytest.skip("no causal variant of this map")
+    print(f"[ranges] infinities {B} {H} {N} {d} {causal} {feature_map}", flush=True)
+    rng = np.random.default_rng(65 + N)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
+    Q, K = np.abs(Q) + 0.1, np.abs(K) + 0.1
+    at, up, down = N // 2, 1, d - 2
+    kw = dict(scale=1.0 / N, causal=bool(causal), feature_map=feature_map)
+    q, k = to_gpu(Q, "f32"), to_gpu(K, "f32")
+    m = torch.ones(B, N, dtype=torch.uint8, device="cuda")
+    if N > 64:
+        m[:, :3] = 0
+    def run(V, dO):
+        v, g = to_gpu(V, "f32"), to_gpu(dO, "f32")
+        O = binding.cotten_attn_fwd(q, k, v, m, **kw)
+        dV = binding.cotten_attn_bwd(q, k, v, m, g, **kw)[2]
+        torch.cuda.synchronize()
+        return O.cpu().numpy(), dV.cpu().numpy()
+    O0, dV0 = run(V, dO)
+    Vi, gi = V.copy(), dO.copy()
+    Vi[0, 0, at, up], Vi[0, 0, at, down] = np.inf, -np.inf
+    gi[0, 0, at, up], gi[0, 0, at, down] = np.inf, -np.inf
+    O, dV = run(Vi, gi)
+    for got, plain, sees in ((O, O0, slice(at + (15 if causal else -at), None)),
+                             (dV, dV0, slice(None, at - 15) if causal else slice(None))):
+        valid = m.cpu().numpy()[0] != 0 if got is dV else np.ones(N, bool)
+        rows = np.zeros(N, bool)
+        rows[sees] = True
+        assert np.all(got[0, 0, rows & valid, up] == np.inf)
+        assert np.all(got[0, 0, rows & valid, down] == -np.inf)
+        rest = np.ones(got.shape, bool)
+        rest[0, 0, :, [up, down]] = False
+        assert np.array_equal(got[rest], plain[rest])
