@@ -186,13 +186,30 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
     // and has the sum read back: no fewer than 256 rows per workgroup, and a sequence is not cut
     // at all once there is a workgroup per compute unit without it.
     plan.path = Plan::kGeneric;
-    // 16-bit rows: one workgroup per compute unit and kind, of eight waves (512 instead of 256, forward /
-    // backward: 32 slices x 3000 rows 40.4 / 80.5 us against 36.5 / 78.9, 128 x 600 38.7 / 73.1 against
-    // 33.0 / 69.1); fp32 rows, where the matrix products weigh more: 64 x 4096, d = 64, 65.3 / 152 against
-    // 68.6 / 159.
-    constexpr long kBlock = 64;
-    const long kTarget = dtype == 0 ? 512 : 256;
-    splits = BH >= 256 ? 1 : (kTarget + BH - 1) / BH;
+    constexpr long kBlock = 64, kUnits = 256;
+    if (BH >= kUnits) {
+      splits = 1;
+    } else if (dtype == 0) {
+      // fp32 rows, where the matrix products weigh more: two workgroups per compute unit (64 x 4096, d = 64,
+      // forward / backward 65.3 / 152 us; one 68.6 / 159)
+      splits = (2 * kUnits + BH - 1) / BH;
+    } else if (2 * BH > kUnits) {
+      // 16-bit rows, bf16 d = 128, forward / backward, us.  More than half as many slices as compute units: whole
+      // (a workgroup of eight waves each), or from a length on in three parts (of four waves, two per
+      // compute unit).  Whole, two, three parts:  130 x 600 24.5 / 67, 35 / 70, 37 / 77;  140 x 1200 54 / 148,
+      // 61 / 128, 56 / 130;  140 x 4096 173 / 515, 176 / 397, 140 / 356;  180 x 1600 73 / 209, 87 / 199, 88 / 199;
+      // 200 x 2400 110 / 327, 131 / 328, 133 / 311;  200 x 4096 185 / 554, 197 / 514, 196 / 490;
+      // 255 x 4000 199 / 585, 219 / 598, 221 / 602.
+      splits = N >= (is_bwd ? 20 : 50) * (BH - 100) ? 3 : 1;
+    } else {
+      // No more workgroups than compute units, of eight waves - or, for long sequences, and for those of 2048 rows
+      // where that leaves a fifth of the chip idle, twice as many, of four.  At most 256 and 512 workgroups:
+      // 64 x 3000 53 / 137, 60 / 143;  100 x 600 28 / 56, 34 / 61;  100 x 3000 86 / 216, 81 / 204;  80 x 3000 67 / 166,
+      // 68 / 171;  80 x 6000 116 / 311, 115 / 302;  100 x 6000 154 / 420, 139 / 370;  128 x 6000 172 / 458, 167 / 467.
+      // (One workgroup more than compute units costs: 100 x 600 in three parts 34 / 61, in two 28 / 56.)
+      splits = kUnits / BH;
+      if (N >= 4096 || (N >= 2048 && 5 * splits * BH < 4 * kUnits)) splits = 2 * kUnits / BH;
+    }
     const long max_splits = (N + 255) / 256;
     if (splits > max_splits) splits = max_splits;
     if (splits < 1) splits = 1;

@@ -121,6 +121,22 @@ def test_workspace_rules(lib):
                                       16, 4, 4096, 64, None, ctypes.byref(p)) == -5
 
 
+@pytest.mark.parametrize("slices,N,fwd,bwd", [
+    (256, 8192, 1, 1), (255, 3099, 1, 1), (255, 3100, 1, 3), (255, 7749, 1, 3), (255, 7750, 3, 3),
+    (129, 579, 1, 1), (129, 580, 1, 3), (129, 1449, 1, 3), (129, 1450, 3, 3),
+    (128, 600, 2, 2), (128, 4095, 2, 2), (128, 4096, 4, 4),        # whole or in parts of at least 256 rows
+    (100, 2047, 2, 2), (100, 2048, 5, 5), (103, 2048, 2, 2), (85, 512, 2, 2), (64, 1100, 4, 4), (1, 600, 3, 3),
+])
+def test_wide_row_splits(lib, slices, N, fwd, bwd):
+    """Into how many parts the sequences of 16-bit d_h = 128 rows are cut, as their workspaces tell: one d x d
+    state (backward: two) per part, and the sum of more than one."""
+    for is_bwd, parts in ((False, fwd), (True, bwd)):
+        states = 0 if parts == 1 else (parts + 1) * (2 if is_bwd else 1)
+        for dtype in (binding.COTTEN_BF16, binding.COTTEN_F16):
+            assert binding.cotten_attn_workspace_bytes(slices, 1, N, 128, dtype, is_bwd) == \
+                slices * states * 128 * 128 * 4, (is_bwd, parts)
+
+
 def test_causal_workspace_rules(lib):
     """The causal variant passes one d x d state per 208-row chunk and slice through the
     workspace (two in the backward call) once a sequence has more than one chunk; the sizing

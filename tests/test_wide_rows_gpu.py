@@ -51,9 +51,11 @@ def _inputs(seed, dtype, B, H, N, d):
     ("f16", 2, 2, 600, 128),        # three launches, workgroups of eight waves, fp16
     ("bf16", 257, 1, 40, 128),      # forward with two slices per workgroup, the last one alone
     ("f32", 129, 3, 90, 64),
-    ("bf16", 100, 2, 600, 128),     # three launches, workgroups of four waves (600 of them)
-    ("f32", 100, 2, 600, 64),
+    ("bf16", 100, 2, 600, 128),     # one launch per direction, tiles streamed
+    ("f32", 100, 2, 600, 64),       # three launches, workgroups of four waves (600 of them)
     ("f16", 100, 2, 600, 128),
+    ("bf16", 129, 1, 1450, 128),    # three launches, workgroups of four waves, in both directions
+    ("f16", 43, 3, 580, 128),       # in the backward
 ])
 def test_wide_rows_parity(oracle, dtype, B, H, N, d):
     print(f"[wide rows] {dtype} B={B} H={H} N={N} d={d}", flush=True)
