@@ -3,9 +3,10 @@ kernels for 256- and 512-byte rows change shape - one row, ends of tiles (16), o
 state walk (64), more tiles than waves (4 and 8), slices in groups of eight, sequences cut over
 several workgroups - with values over many powers of two.
 
-Whole-tensor bound 1e-6: a product of two values as six products of their pieces is within 2^-23
-(1.2e-7) of it, and the fp32 sums that follow (N, then d_h terms, then one rounding per result) add a few
-units of 2^-24 on random inputs; a missing or misplaced piece would show as 2^-16 or more."""
+Bound per slice 1e-6: a product of two values as six products of their pieces is within 2^-22 (2.4e-7) of it
+at worst (each value cut to 8 bits, then rounded to 8 more: the first remainder is below 2^-7 of the value, the
+second below 2^-16), and the fp32 sums that follow (N, then d_h terms, then one rounding per result) add a
+few units of 2^-24 on random inputs; a missing or misplaced piece would show as 2^-16 or more."""
 from __future__ import annotations
 
 import numpy as np
@@ -33,7 +34,8 @@ def test_fp32_pieces(oracle, B, H, N, d, feature_map):
     if feature_map == "cosine":
         for x in (Q, K):                     # the map takes the scale of a row out again
             x *= np.exp2(rng.integers(-8, 9, (B, H, N, 1))).astype(np.float32)
-        V *= np.exp2(rng.integers(-30, 31, (B, H, 1, 1))).astype(np.float32)
+        if B * H < 20:                       # (larger cases are held tensor by tensor)
+            V *= np.exp2(rng.integers(-30, 31, (B, H, 1, 1))).astype(np.float32)
     mask = (np.arange(N)[None, :] >= rng.integers(0, N, B)[:, None]).astype(np.uint8)
     if B > 1:
         mask[1] = rng.random(N) < 0.5
@@ -56,16 +58,21 @@ def test_fp32_pieces(oracle, B, H, N, d, feature_map):
         refs = oracle.elu_bwd(Q, K, V, dO, mask, scale=0.25)
     assert all(torch.equal(a, b) for a, b in zip(grads, again))
     for name, got, ref in zip(("O", "dQ", "dK", "dV"), (O, *grads), (ref_o, *refs)):
-        for b in range(B):                   # V differs by powers of two between slices
-            for h in range(H):
-                e = rel_l2(to_f64(got)[b, h], ref[b, h]) if B * H < 20 else 0.0
-                # a slice with one key or one row may consist of a cosine near zero
-                assert e <= (1e-6 if N >= 16 and mask[b].sum() > 8 else FP32_BAR) or not ref[b, h].any(), (name, b, h, e)
+        if B * H >= 20:
+            check_tensor(name, to_f64(got), ref, FP32_BAR)
+        else:
+            for b in range(B):               # V differs by powers of two between slices
+                for h in range(H):
+                    g, r = to_f64(got)[b, h], ref[b, h]
+                    if not r.any():          # no valid key
+                        assert not g.any(), (name, b, h)
+                        continue
+                    e = rel_l2(g, r)
+                    # a slice with one key or one row may consist of a cosine near zero
+                    assert e <= (1e-6 if N >= 16 and mask[b].sum() > 8 else FP32_BAR), (name, b, h, e)
         dead = np.broadcast_to((mask == 0)[:, None, :, None], ref.shape)
         if name in ("dK", "dV"):
             assert np.all(to_f64(got)[dead] == 0.0)
-    if B * H >= 20:
-        check_tensor("O", to_f64(O), ref_o, FP32_BAR)
     ref_dlog = (dO.astype(np.float64) * ref_o).sum(axis=(2, 3))
     size = np.sqrt(((dO.astype(np.float64) * ref_o) ** 2).sum(axis=(2, 3)))  # sums with cancellation
     assert np.all(np.abs(dlog.double().cpu().numpy() - ref_dlog) <= 1e-5 * np.maximum(size, np.abs(ref_dlog)))

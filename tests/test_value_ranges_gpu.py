@@ -82,7 +82,8 @@ def test_causal_common_direction(oracle, B, H, N, d):
     What reaches a query from far back is then small against the sums it is the difference of, and an
     intermediate sum held in 16 bits (2^-9 of the sum, not of the result) is what such results show
     (measured 2.1e-2; with sums of more bits 4.7e-3, the rounding of the unit rows: 2^-9 of them, twice
-    as large against the 0.45 of a key that the query sees).  Bound: twice that."""
+    as large against the 0.45 of a key that the query sees).  Bound: twice that, of the whole tensor (the rounding
+    of the unit rows alone moves single rows of dV by up to 6e-2)."""
     print(f"[ranges] common direction {B} {H} {N} {d}", flush=True)
     rng = np.random.default_rng(63 + N)
     Q, K, V, dO = (0.5 * rng.standard_normal((B, H, N, d)).astype(np.float32) for _ in range(4))
