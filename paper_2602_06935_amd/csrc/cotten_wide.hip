@@ -35,32 +35,28 @@ using namespace mfma;
 // Every kernel exists for workgroups of 4 and of 8 waves (template parameter WAVES): 4 when there
 // are workgroups enough to put two on every compute unit, 8 when there are not.
 //
-// Template parameter P: the 128-byte pieces of a row (2).
+constexpr int P = 2;                     // 128-byte pieces of a row
 constexpr int kHalfBytes = kRowBytes;    // one piece of a row
 
 // A 16-row tile of a tensor pair in the load layout: piece [h][c] is bytes 128 c + 16 ch .. + 15 of
 // row r8 + 8 h.  `live` bit h: the row takes part.
-template <int P>
-struct WideRawT {
+struct WideRaw {
   u32x4_t x[2][P], y[2][P];
   int live;
 };
-typedef WideRawT<2> WideRaw;
 
 // The two tensors of a pass as buffer resources over one slice (see Src in cotten_mfma_core.h:
 // lanes whose row does not take part get zeros and cause no traffic).
-template <int P>
-struct WideSrcT {
+struct WideSrc {
   __amdgpu_buffer_rsrc_t x, y;
   int stride;
-  __device__ __forceinline__ WideSrcT(const unsigned char* X, const unsigned char* Y, int N, int stride_bytes)
+  __device__ __forceinline__ WideSrc(const unsigned char* X, const unsigned char* Y, int N, int stride_bytes)
       : stride(stride_bytes) {
     const int bytes = (N - 1) * stride + P * kHalfBytes;
     x = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(X), 0, bytes, 0x00020000);
     y = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Y), 0, bytes, 0x00020000);
   }
 };
-typedef WideSrcT<2> WideSrc;
 
 // Bit h: row row0 + r8 + 8 h is below `limit` and, if a mask is given, a valid key.
 __device__ __forceinline__ int row_bits(const uint8_t* __restrict__ mask, int row0, int limit,
@@ -74,8 +70,8 @@ __device__ __forceinline__ int row_bits(const uint8_t* __restrict__ mask, int ro
   return bits;
 }
 
-template <bool USE_Y, int P>
-__device__ __forceinline__ void load_wide(WideRawT<P>& r, const Lane& L, const WideSrcT<P>& src, int row0,
+template <bool USE_Y>
+__device__ __forceinline__ void load_wide(WideRaw& r, const Lane& L, const WideSrc& src, int row0,
                                           int bits) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -97,8 +93,8 @@ __device__ __forceinline__ void load_wide(WideRawT<P>& r, const Lane& L, const W
 // the format (XMODE, see stage() in cotten_mfma_core.h).
 // inv[h] = 1/r of row r8 + 8 h (0 for a row that does not take part; with the element-wise map 1
 // for a row that does, and a row that does not is written as zeros explicitly: phi(0) is not 0).
-template <class F, int XMODE, bool USE_Y, int P>
-__device__ __forceinline__ void stage_wide(const WideRawT<P>& r, const Lane& L, float eps,
+template <class F, int XMODE, bool USE_Y>
+__device__ __forceinline__ void stage_wide(const WideRaw& r, const Lane& L, float eps,
                                            unsigned char* tiles, float (&inv)[2]) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
@@ -158,12 +154,11 @@ __device__ __forceinline__ float inv_by_row(float* slot, const Lane& L, const fl
 
 // No row of the tile takes part (all of them masked or beyond the sequence): the wave can write
 // the zeros such rows come out as without computing them.
-template <int P>
-__device__ __forceinline__ bool tile_dead(const WideRawT<P>& r) {
+__device__ __forceinline__ bool tile_dead(const WideRaw& r) {
   return __builtin_amdgcn_ballot_w64(r.live != 0) == 0;
 }
 
-template <class F, int P = 2>
+template <class F>
 __device__ __forceinline__ void store_zero_rows(unsigned char* out, int row0, int r_end, int stride,
                                                 const Lane& L) {
   float z[2 * F::EPL];
@@ -184,16 +179,16 @@ extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 // grid (slices * splits, 1 or 2): blockIdx.y == 1 reduces (Q, dO) to sum_i qhat_i^T dO_i instead
 // of (K, V) under the key mask.  Partial states: row-major D x D floats per workgroup, the second
 // kind `second_offset` floats behind the first.
-// The P x P blocks of the state are dealt to the waves 0-3 of a group, P*P/4 consecutive ones
-// each (block i = piece i / P of x against piece i % P of y); with 8 waves two groups share the
-// tiles of a round and their sums meet at the end.
-template <class F, int WAVES, int P>
+// Each of the waves 0-3 of a group has one of the four blocks of the state (block i = piece i / P of x
+// against piece i % P of y); with 8 waves two groups share the tiles of a round and their sums
+// meet at the end.
+template <class F, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
     const unsigned char* __restrict__ Q, const unsigned char* __restrict__ K,
     const unsigned char* __restrict__ V, const unsigned char* __restrict__ dO,
     const uint8_t* __restrict__ mask, float* __restrict__ ws, int H, int N, int splits,
     int rows_per_split, size_t second_offset, float eps, Strides st) {
-  constexpr int Dh = F::D, D = P * Dh, kRoundRows = WAVES * TR, kBlocks = P * P / 4;
+  constexpr int Dh = F::D, D = P * Dh, kRoundRows = WAVES * TR;
   constexpr int kSetBytes = 2 * P * kTileBytes;  // the tiles one wave stages per round
   static_assert(WAVES == 4 || WAVES == 8, "one or two groups of four waves");
   unsigned char* round = smem;  // WAVES x [x pieces | y pieces]
@@ -201,19 +196,18 @@ __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
   const int split = blockIdx.x % splits, bh = blockIdx.x / splits;
   const bool second = blockIdx.y == 1;
   const size_t base = st.slice_base(bh, H);
-  const WideSrcT<P> src((second ? Q : K) + base, (second ? dO : V) + base, N, st.row.stride);
+  const WideSrc src((second ? Q : K) + base, (second ? dO : V) + base, N, st.row.stride);
   const uint8_t* __restrict__ m =
       (second || mask == nullptr) ? nullptr : mask + static_cast<size_t>(bh / H) * N;
   const int r_begin = split * rows_per_split;
   const int r_end = N < r_begin + rows_per_split ? N : r_begin + rows_per_split;
-  // this wave's blocks of the state, and (8 waves) which four tiles of a round it adds up
+  // this wave's block of the state, and (8 waves) which four tiles of a round it adds up
   const int quadrant = L.wave & 3, part = L.wave >> 2;
   unsigned char* mine = round + L.wave * kSetBytes;
 
-  typename F::Acc acc[kBlocks];
-#pragma unroll
-  for (int j = 0; j < kBlocks; ++j) acc[j].zero();
-  WideRawT<P> cur;
+  typename F::Acc acc;
+  acc.zero();
+  WideRaw cur;
   load_wide<true>(cur, L, src, r_begin + L.wave * TR, row_bits(m, r_begin + L.wave * TR, r_end, L));
   int next_bits = row_bits(m, r_begin + kRoundRows + L.wave * TR, r_end, L);
   for (int r0 = r_begin; r0 < r_end; r0 += kRoundRows) {
@@ -226,23 +220,17 @@ __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const unsigned char* tile = round + (4 * part + t) * kSetBytes;
-#pragma unroll
-      for (int j = 0; j < kBlocks; ++j) {
-        const int block = quadrant * kBlocks + j;
-        acc[j].mfma(tile + (block / P) * kTileBytes, tile + (P + block % P) * kTileBytes, L);
-      }
+      acc.mfma(tile + (quadrant / P) * kTileBytes, tile + (P + quadrant % P) * kTileBytes, L);
     }
     __syncthreads();  // the round's tiles are overwritten next
   }
   // 8 waves: the two sums of a block meet in LDS (the round buffer is free), in a fixed order
-  f32x4_t* meet = reinterpret_cast<f32x4_t*>(round) + quadrant * kBlocks * F::Acc::kGroups * 64 + L.lane;
-  static_assert(4 * kBlocks * F::Acc::kGroups * 64 * 16 <= 8 * kSetBytes, "the sums fit the round buffer");
+  f32x4_t* meet = reinterpret_cast<f32x4_t*>(round) + quadrant * F::Acc::kGroups * 64 + L.lane;
+  static_assert(4 * F::Acc::kGroups * 64 * 16 <= 8 * kSetBytes, "the sums fit the round buffer");
   if (WAVES == 8) {
     if (part == 1) {
 #pragma unroll
-      for (int j = 0; j < kBlocks; ++j)
-#pragma unroll
-        for (int g = 0; g < F::Acc::kGroups; ++g) meet[(j * F::Acc::kGroups + g) * 64] = acc[j].group(g);
+      for (int g = 0; g < F::Acc::kGroups; ++g) meet[g * 64] = acc.group(g);
     }
     __syncthreads();
     if (part == 1) return;
@@ -250,17 +238,13 @@ __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
   float* __restrict__ out =
       ws + (second ? second_offset : 0) + static_cast<size_t>(blockIdx.x) * D * D;
 #pragma unroll
-  for (int j = 0; j < kBlocks; ++j) {
-    const int block = quadrant * kBlocks + j;
+  for (int g = 0; g < F::Acc::kGroups; ++g) {
+    f32x4_t v = acc.group(g);
+    if (WAVES == 8) v += meet[g * 64];
+    const int row = (quadrant / P) * Dh + F::Acc::group_row(g, L);
+    const int col = (quadrant % P) * Dh + F::Acc::group_col(g, L);
 #pragma unroll
-    for (int g = 0; g < F::Acc::kGroups; ++g) {
-      f32x4_t v = acc[j].group(g);
-      if (WAVES == 8) v += meet[(j * F::Acc::kGroups + g) * 64];
-      const int row = (block / P) * Dh + F::Acc::group_row(g, L);
-      const int col = (block % P) * Dh + F::Acc::group_col(g, L);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[(row + i) * D + col] = v[i];
-    }
+    for (int i = 0; i < 4; ++i) out[(row + i) * D + col] = v[i];
   }
 }
 
@@ -270,7 +254,7 @@ __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
 // image (p, q) at images + (P p + q) * F::kImageBytes:
 //   natural     op[m][n] = M[p Dh + m][q Dh + n]     for products that contract over n
 //   transposed  op[n][m] = M[p Dh + m][q Dh + n]     for products that contract over m
-template <class F, int WAVES, bool TRANSPOSED, int P>
+template <class F, int WAVES, bool TRANSPOSED>
 __device__ __forceinline__ void build_images(const float* __restrict__ M, float scale,
                                              unsigned char* images) {
   constexpr int Dh = F::D, D = P * Dh, kThreads = 64 * WAVES;
@@ -309,7 +293,7 @@ __device__ __forceinline__ void build_images(const float* __restrict__ M, float 
 // 4 x 32 registers for the 16-bit formats with P = 2), or fetched from the images for every
 // product (the backward roles share one kernel and do better at two waves per SIMD than with
 // the operands held at one).
-template <class F, bool HOLD, int P = 2>
+template <class F, bool HOLD>
 struct Quadrants {
   typename F::Operand held[HOLD ? P * P : 1];
   const unsigned char* images;
@@ -352,7 +336,7 @@ struct ApplyArgs {
 };
 
 // LDS of the apply kernels: [P x P images][per wave: 2 P tiles, 16 floats]
-template <class F, int WAVES, int P = 2>
+template <class F, int WAVES>
 struct ApplyLds {
   static constexpr int kImages = 0;
   static constexpr int kWave = P * P * F::kImageBytes;
@@ -362,12 +346,12 @@ struct ApplyLds {
 
 // out rows = (x rows) M / r, contraction over the rows of M:  O = scale qhat S,  dV = scale khat dS.
 // One tile of the plain role: `cur` staged raw into the wave's tile set, out rows = x W / r.
-template <class F, bool HOLD, int P>
-__device__ __forceinline__ void plain_tile(const Quadrants<F, HOLD, P>& W, const WideRawT<P>& cur, int row0,
+template <class F, bool HOLD>
+__device__ __forceinline__ void plain_tile(const Quadrants<F, HOLD>& W, const WideRaw& cur, int row0,
                                            int r_end, unsigned char* out, int stride, float eps,
                                            unsigned char* tiles, const Lane& L) {
   if (tile_dead(cur)) {
-    store_zero_rows<F, P>(out, row0, r_end, stride, L);
+    store_zero_rows<F>(out, row0, r_end, stride, L);
     return;
   }
   float* inv_slot = reinterpret_cast<float*>(tiles + 2 * P * kTileBytes);
@@ -392,46 +376,46 @@ __device__ __forceinline__ void plain_tile(const Quadrants<F, HOLD, P>& W, const
 
 // `images`: the transposed block images of scale * M; `tiles`: this wave's tile set.
 // The wave's first tile: requested here, or (REQUESTED) by the caller with request_first_tile.
-template <int WAVES, int P>
-__device__ __forceinline__ void request_first_tile(WideRawT<P>& cur, const ApplyArgs& a, const Lane& L) {
-  const WideSrcT<P> src(a.X, a.X, a.N, a.stride);
+template <int WAVES>
+__device__ __forceinline__ void request_first_tile(WideRaw& cur, const ApplyArgs& a, const Lane& L) {
+  const WideSrc src(a.X, a.X, a.N, a.stride);
   const int row0 = a.r_begin + L.wave * TR;
   load_wide<false>(cur, L, src, row0, row_bits(a.mask, row0, a.r_end, L));
 }
 
-template <class F, int WAVES, bool HOLD, bool REQUESTED = false, int P = 2>
+template <class F, int WAVES, bool HOLD, bool REQUESTED = false>
 __device__ __forceinline__ void plain_tiles(const ApplyArgs& a, const unsigned char* images,
                                             unsigned char* tiles, const Lane& L,
-                                            const WideRawT<P>* first = nullptr) {
+                                            const WideRaw* first = nullptr) {
   constexpr int kRoundRows = WAVES * TR;  // rows between two tiles of a wave
-  const Quadrants<F, HOLD, P> W(images, L);
-  const WideSrcT<P> src(a.X, a.X, a.N, a.stride);
+  const Quadrants<F, HOLD> W(images, L);
+  const WideSrc src(a.X, a.X, a.N, a.stride);
   int row0 = a.r_begin + L.wave * TR;
-  WideRawT<P> cur;
+  WideRaw cur;
   if (REQUESTED) cur = *first;
   else request_first_tile<WAVES>(cur, a, L);
   int next_bits = row_bits(a.mask, row0 + kRoundRows, a.r_end, L);
   for (; row0 < a.r_end; row0 += kRoundRows) {
-    const WideRawT<P> tile = cur;
+    const WideRaw tile = cur;
     load_wide<false>(cur, L, src, row0 + kRoundRows, next_bits);
     next_bits = row_bits(a.mask, row0 + 2 * kRoundRows, a.r_end, L);
     plain_tile<F, HOLD>(W, tile, row0, a.r_end, a.out, a.stride, a.eps, tiles, L);
   }
 }
 
-template <class F, int WAVES, bool HOLD, int P>
+template <class F, int WAVES, bool HOLD>
 __device__ __forceinline__ void plain_role(const ApplyArgs& a) {
   const Lane L;
-  unsigned char* images = smem + ApplyLds<F, WAVES, P>::kImages;
-  unsigned char* tiles = smem + ApplyLds<F, WAVES, P>::kWave + L.wave * ApplyLds<F, WAVES, P>::kWaveBytes;
-  build_images<F, WAVES, true, P>(a.state, a.scale, images);
+  unsigned char* images = smem + ApplyLds<F, WAVES>::kImages;
+  unsigned char* tiles = smem + ApplyLds<F, WAVES>::kWave + L.wave * ApplyLds<F, WAVES>::kWaveBytes;
+  build_images<F, WAVES, true>(a.state, a.scale, images);
   __syncthreads();
-  plain_tiles<F, WAVES, HOLD, false, P>(a, images, tiles, L);
+  plain_tiles<F, WAVES, HOLD, false>(a, images, tiles, L);
 }
 
 // The row epilogue of dQ and dK over all pieces of a row, E holding the mapped rows (xhat, or
 // phi(x)):  cosine map  g <- (g - xhat (xhat . g)) / r;   ELU + 1  g <- g * phi'(x), phi' = min(phi, 1).
-template <class F, int P>
+template <class F>
 __device__ __forceinline__ void finish_projected(float (&g)[P][2 * F::EPL], typename F::TileRows (&E)[P],
                                                  float inv_r, const Lane& L) {
   if (F::kMap == kMapElu1) {
@@ -461,22 +445,22 @@ __device__ __forceinline__ void finish_projected(float (&g)[P][2 * F::EPL], type
 // out rows = (g - xhat (xhat . g)) / r with g = (y rows) M^T, contraction over the columns of M:
 //   dQ from (Q, dO) and scale S;   dK from (K, V) and scale dS (masked rows come out as zeros).
 // `images`: the natural block images of scale * M.
-template <class F, int WAVES, int P = 2>
+template <class F, int WAVES>
 __device__ __forceinline__ void projected_tiles(const ApplyArgs& a, const unsigned char* images,
                                                 unsigned char* tiles, const Lane& L) {
   constexpr int kRoundRows = WAVES * TR;
   float* inv_slot = reinterpret_cast<float*>(tiles + 2 * P * kTileBytes);
-  const Quadrants<F, false, P> W(images, L);
-  const WideSrcT<P> src(a.X, a.Y, a.N, a.stride);
+  const Quadrants<F, false> W(images, L);
+  const WideSrc src(a.X, a.Y, a.N, a.stride);
   int row0 = a.r_begin + L.wave * TR;
-  WideRawT<P> cur;
+  WideRaw cur;
   load_wide<true>(cur, L, src, row0, row_bits(a.mask, row0, a.r_end, L));
   int next_bits = row_bits(a.mask, row0 + kRoundRows, a.r_end, L);
   for (; row0 < a.r_end; row0 += kRoundRows) {
     if (tile_dead(cur)) {  // nothing was fetched: zeros
       load_wide<true>(cur, L, src, row0 + kRoundRows, next_bits);
       next_bits = row_bits(a.mask, row0 + 2 * kRoundRows, a.r_end, L);
-      store_zero_rows<F, P>(a.out, row0, a.r_end, a.stride, L);
+      store_zero_rows<F>(a.out, row0, a.r_end, a.stride, L);
       continue;
     }
     float inv[2];
@@ -504,14 +488,14 @@ __device__ __forceinline__ void projected_tiles(const ApplyArgs& a, const unsign
   }
 }
 
-template <class F, int WAVES, int P>
+template <class F, int WAVES>
 __device__ __forceinline__ void projected_role(const ApplyArgs& a) {
   const Lane L;
-  unsigned char* images = smem + ApplyLds<F, WAVES, P>::kImages;
-  unsigned char* tiles = smem + ApplyLds<F, WAVES, P>::kWave + L.wave * ApplyLds<F, WAVES, P>::kWaveBytes;
-  build_images<F, WAVES, false, P>(a.state, a.scale, images);
+  unsigned char* images = smem + ApplyLds<F, WAVES>::kImages;
+  unsigned char* tiles = smem + ApplyLds<F, WAVES>::kWave + L.wave * ApplyLds<F, WAVES>::kWaveBytes;
+  build_images<F, WAVES, false>(a.state, a.scale, images);
   __syncthreads();
-  projected_tiles<F, WAVES, P>(a, images, tiles, L);
+  projected_tiles<F, WAVES>(a, images, tiles, L);
 }
 
 struct LaunchArgs {
@@ -544,7 +528,7 @@ __device__ __forceinline__ ApplyArgs role_args(const LaunchArgs& a) {
   return r;
 }
 
-template <class F, int WAVES, int P>
+template <class F, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void wide_fwd_kernel(const LaunchArgs a) {
   constexpr int D = P * F::D;
   const int bh = blockIdx.x / a.splits;
@@ -554,11 +538,11 @@ __global__ __launch_bounds__(64 * WAVES) void wide_fwd_kernel(const LaunchArgs a
   r.mask = nullptr;  // queries are not masked
   r.state = a.states + static_cast<size_t>(bh) * D * D;
   r.out = a.O + base;
-  plain_role<F, WAVES, true, P>(r);  // operands held in registers
+  plain_role<F, WAVES, true>(r);  // operands held in registers
 }
 
 // blockIdx.y: 0 dQ, 1 dV, 2 dK
-template <class F, int WAVES, int P>
+template <class F, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void wide_bwd_kernel(const LaunchArgs a) {
   constexpr int D = P * F::D;
   const int bh = blockIdx.x / a.splits;
@@ -571,20 +555,20 @@ __global__ __launch_bounds__(64 * WAVES) void wide_bwd_kernel(const LaunchArgs a
     r.mask = nullptr;
     r.state = a.states + static_cast<size_t>(bh) * D * D;
     r.out = a.dQ + base;
-    projected_role<F, WAVES, P>(r);
+    projected_role<F, WAVES>(r);
   } else if (blockIdx.y == 1) {
     r.X = a.K + base;
     r.mask = keys;
     r.state = a.dstates + static_cast<size_t>(bh) * D * D;
     r.out = a.dV + base;
-    plain_role<F, WAVES, false, P>(r);
+    plain_role<F, WAVES, false>(r);
   } else {
     r.X = a.K + base;
     r.Y = a.V + base;
     r.mask = keys;
     r.state = a.dstates + static_cast<size_t>(bh) * D * D;
     r.out = a.dK + base;
-    projected_role<F, WAVES, P>(r);
+    projected_role<F, WAVES>(r);
   }
 }
 
@@ -1060,22 +1044,22 @@ LaunchArgs launch_args(const Problem& p, const Plan& plan, const float* states, 
 // Workgroups of 8 waves (the whole LDS of a compute unit at their disposal) when the launch has
 // no more workgroups than there are compute units, of 4 waves (two per compute unit) otherwise.
 constexpr int kUnits = 256;
-template <int WAVES, int P = 2>
+template <int WAVES>
 constexpr int max_lds_bytes() {
   return WAVES == 8 ? 160 * 1024 : 80 * 1024;
 }
 
-template <class F, int WAVES, int P>
+template <class F, int WAVES>
 hipError_t states_w(const Problem& p, const Plan& plan, bool bwd) {
   constexpr int D = P * F::D;
   constexpr int lds = WAVES * 2 * P * kTileBytes;
-  static_assert(lds <= max_lds_bytes<WAVES, P>(), "round buffer");
+  static_assert(lds <= max_lds_bytes<WAVES>(), "round buffer");
   const unsigned blocks = static_cast<unsigned>(p.B) * p.H * plan.splits;
   const size_t second = static_cast<size_t>(blocks) * D * D;
-  const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(wide_state_kernel<F, WAVES, P>),
-                                           max_lds_bytes<WAVES, P>());
+  const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(wide_state_kernel<F, WAVES>),
+                                           max_lds_bytes<WAVES>());
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((wide_state_kernel<F, WAVES, P>), dim3(blocks, bwd ? 2 : 1), dim3(64 * WAVES), lds,
+  hipLaunchKernelGGL((wide_state_kernel<F, WAVES>), dim3(blocks, bwd ? 2 : 1), dim3(64 * WAVES), lds,
                      p.stream, static_cast<const unsigned char*>(p.Q),
                      static_cast<const unsigned char*>(p.K), static_cast<const unsigned char*>(p.V),
                      static_cast<const unsigned char*>(p.dO), p.mask, p.workspace, p.H, p.N,
@@ -1083,20 +1067,20 @@ hipError_t states_w(const Problem& p, const Plan& plan, bool bwd) {
   return hipGetLastError();
 }
 
-template <class F, int WAVES, int P>
+template <class F, int WAVES>
 hipError_t apply_w(const Problem& p, const Plan& plan, const float* st, const float* dst, bool bwd) {
-  constexpr int lds = ApplyLds<F, WAVES, P>::kBytes;
-  static_assert(lds <= max_lds_bytes<WAVES, P>(), "images and tiles");
+  constexpr int lds = ApplyLds<F, WAVES>::kBytes;
+  static_assert(lds <= max_lds_bytes<WAVES>(), "images and tiles");
   const LaunchArgs a = launch_args(p, plan, st, dst);
   const unsigned blocks = static_cast<unsigned>(p.B) * p.H * plan.splits;
-  const void* kern = bwd ? reinterpret_cast<const void*>(wide_bwd_kernel<F, WAVES, P>)
-                         : reinterpret_cast<const void*>(wide_fwd_kernel<F, WAVES, P>);
-  const hipError_t err = grant_dynamic_lds(kern, max_lds_bytes<WAVES, P>());
+  const void* kern = bwd ? reinterpret_cast<const void*>(wide_bwd_kernel<F, WAVES>)
+                         : reinterpret_cast<const void*>(wide_fwd_kernel<F, WAVES>);
+  const hipError_t err = grant_dynamic_lds(kern, max_lds_bytes<WAVES>());
   if (err != hipSuccess) return err;
   if (bwd)
-    hipLaunchKernelGGL((wide_bwd_kernel<F, WAVES, P>), dim3(blocks, 3), dim3(64 * WAVES), lds, p.stream, a);
+    hipLaunchKernelGGL((wide_bwd_kernel<F, WAVES>), dim3(blocks, 3), dim3(64 * WAVES), lds, p.stream, a);
   else
-    hipLaunchKernelGGL((wide_fwd_kernel<F, WAVES, P>), dim3(blocks), dim3(64 * WAVES), lds, p.stream, a);
+    hipLaunchKernelGGL((wide_fwd_kernel<F, WAVES>), dim3(blocks), dim3(64 * WAVES), lds, p.stream, a);
   return hipGetLastError();
 }
 
@@ -1105,16 +1089,16 @@ inline bool few_workgroups(const Problem& p, const Plan& plan, int kinds) {
   return static_cast<long>(p.B) * p.H * plan.splits * kinds <= kUnits;
 }
 
-template <class F, int P>
+template <class F>
 hipError_t states(const Problem& p, const Plan& plan, bool bwd) {
-  return few_workgroups(p, plan, bwd ? 2 : 1) ? states_w<F, 8, P>(p, plan, bwd)
-                                              : states_w<F, 4, P>(p, plan, bwd);
+  return few_workgroups(p, plan, bwd ? 2 : 1) ? states_w<F, 8>(p, plan, bwd)
+                                              : states_w<F, 4>(p, plan, bwd);
 }
 
-template <class F, int P>
+template <class F>
 hipError_t apply(const Problem& p, const Plan& plan, const float* st, const float* dst, bool bwd) {
-  return few_workgroups(p, plan, bwd ? 3 : 1) ? apply_w<F, 8, 2>(p, plan, st, dst, bwd)
-                                              : apply_w<F, 4, 2>(p, plan, st, dst, bwd);
+  return few_workgroups(p, plan, bwd ? 3 : 1) ? apply_w<F, 8>(p, plan, st, dst, bwd)
+                                              : apply_w<F, 4>(p, plan, st, dst, bwd);
 }
 
 template <class F>
@@ -1171,7 +1155,7 @@ hipError_t for_format(const Problem& p, Fn fn) {
 
 hipError_t launch_wide_states(const Problem& p, const Plan& plan, bool bwd) {
   if (p.dtype == 0) return launch_wide32_states(p, plan, bwd);
-  return for_format(p, [&](auto f) { return wide::states<decltype(f), 2>(p, plan, bwd); });
+  return for_format(p, [&](auto f) { return wide::states<decltype(f)>(p, plan, bwd); });
 }
 
 // One launch per direction whenever the sequence is not cut - except, with 16-bit rows, a backward
@@ -1191,7 +1175,7 @@ hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd) {
 hipError_t launch_wide_apply(const Problem& p, const Plan& plan, const float* states,
                              const float* dstates, bool bwd) {
   if (p.dtype == 0) return launch_wide32_apply(p, plan, states, dstates, bwd);
-  return for_format(p, [&](auto f) { return wide::apply<decltype(f), 2>(p, plan, states, dstates, bwd); });
+  return for_format(p, [&](auto f) { return wide::apply<decltype(f)>(p, plan, states, dstates, bwd); });
 }
 
 }  // namespace cotten
