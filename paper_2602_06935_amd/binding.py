@@ -220,9 +220,15 @@ def _workspace(Q: torch.Tensor, dims, is_bwd: bool, stream_handle: int,
         return ws
 
 
+# Handle of the current stream of a device: straight from torch's extension module where that has it (no
+# Stream object is made).
+_current_stream_handle = getattr(torch._C, "_cuda_getCurrentRawStream",
+                                 lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:  # that of the current device
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _current_stream_handle(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
