@@ -33,7 +33,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-MFMA_PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0, "f16": 2500.0}   # dense, published
+# dense, published; an fp32 product is six products of bf16 pieces (cotten_mfma_core.h)
+MFMA_PEAK_TFLOPS = {"f32": 2500.0 / 6, "bf16": 2500.0, "f16": 2500.0}
 HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 ROTATE_BYTES = 640 << 20       # rotate over at least this many bytes of tensors
 SETTLE_SECONDS = 0.3           # untimed replays before the timed ones
@@ -305,7 +306,7 @@ def roofline_block(w, db, res):
                                            / ((res["fwd_us"] + res["bwd_us"]) * 1e-6) / 1e9 / HBM_PEAK_GBS)},
         # the contractions run on the matrix cores: algorithmic flops / time against the dense
         # peak, and the share of SIMD cycles the matrix cores were busy (hardware counter)
-        "matrix_cores": {"achieved": round(mfma_tflops, 2), "peak": MFMA_PEAK_TFLOPS[w.dtype],
+        "matrix_cores": {"achieved": round(mfma_tflops, 2), "peak": round(MFMA_PEAK_TFLOPS[w.dtype], 1),
                          "unit": "TFLOP/s", "frac": r4(mfma_tflops / MFMA_PEAK_TFLOPS[w.dtype]),
                          "busy_pct_counter": prof["mfma_busy_pct"]},
     }

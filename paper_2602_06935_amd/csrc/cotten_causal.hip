@@ -21,12 +21,16 @@
 // (`apply`), its update one 32 x 32 block per wave.  What a wave needs of its own rows it loads
 // straight in the layout of the products; only the rows that other waves read go through LDS.
 //
-// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 16 / 30, where a scan on the vector
-// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 32 / 77, where 208-row
-// chunks joined by states in memory took 60 / 105 (three launches, 13 * 14 / 2 tile pairs per chunk
+// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 15 / 32, where a scan on the vector
+// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 33 / 77, where 208-row
+// chunks joined by states in memory took 56 / 101 (three launches, 13 * 14 / 2 tile pairs per chunk
 // instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - memory, at about 3.7 TB/s (the two roles of
 // the backward each read all they need) with one chunk of loads in flight per wave; fp32 - latency:
 // with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is.
+//
+// 16-bit results differ from those of 208-row chunks in the places where sums are rounded, by about as much
+// as either differs from a 64-bit evaluation (bf16, 256 x 1001 rows: 3e-3; from 64 bits 2.9e-3 ... 3.3e-3
+// there, 2.5e-3 here: the state in two images, dV from raw keys).
 #include "cotten_launch.h"
 #include "cotten_mfma_core.h"
 
@@ -789,6 +793,10 @@ hipError_t launch_causal(const Problem& p, bool bwd) {
     if (p.dtype != 0 || p.D != 64) return hipErrorInvalidValue;
     return run_scan<F32x32, 2, 4>(p, bwd);
   }
+  // fp32, a slice of at most 208 rows held in LDS whole (with fp32 products) and the walk, forward / backward, us,
+  // d = 32:  8 slices x 200 rows 9.7 / 19.8, 7.7 / 9.8;  256 x 200 12.5 / 26.6, 11.8 / 20.5;  2048 x 200
+  // 70 / 149, 42 / 113;  64 x 50 4.1 / 6.1, 4.1 / 6.1;  512 x 50 8.7 / 12.7, 5.6 / 10.3;  512 x 128 13.9 / 26.3,
+  // 10.6 / 20.8
   if (p.dtype == 0) return run_scan<F32x32, 1, 4>(p, bwd);
   // 16-bit rows.  The walk reads what its two backward roles share twice; a slice of at most 208
   // rows held in LDS is read once and wins as long as its workgroups (one per compute unit) do

@@ -6,11 +6,11 @@
 // wave-private LDS tile, from which the matrix cores are fed:
 //   state products  S += Xhat^T Y  (contraction over rows; Xhat normalised in fp32 registers
 //                   before it is written to the tile)
-//                   bf16: 32x32x16 MFMA, operands fetched with the transposing LDS read
-//                   fp32: 32x32x2 MFMA, one LDS dword per lane and step
+//                   32x32x16 MFMA, operands fetched with the transposing LDS read
 //   apply products  T = X W        (contraction over columns; X raw, the 1/r of each row is
 //                   applied to the result; W held in registers)
-//                   bf16: 16x16x32 MFMA      fp32: 16x16x4 MFMA
+//                   16x16x32 MFMA
+// (fp32: each product as six of bf16 pieces, see Pieces in cotten_mfma_core.h.)
 // Products are computed transposed, which leaves every lane with runs of neighbouring
 // columns of one tile row; the epilogue (projection off the unit row, 1/r, masking) runs in
 // fp32 in that layout, next to the tile rows fetched from LDS in the same arrangement, and

@@ -490,8 +490,8 @@ typedef Half64<F16Elem> F16x64;
 // upper half of the word, m the remainder rounded to bf16, l what is left, which fits), and a
 // product of two values is the sum of the six products of pieces that reach its 24 bits,
 //     h h' + (h m' + m h') + (h l' + l h' + m m'),
-// each exact, accumulated in fp32.  What is left out (m l', l m', l l') is below 2^-24 of the product
-// and of either sign.  Six products at 16 times the rate: 2.7 times the fp32 matrix rate, for 11
+// each exact, accumulated in fp32.  What is left out (m l', l m', l l') is below 2^-22 of the product (m below
+// 2^-7 of its value, l below 2^-16) and of either sign.  Six products at 16 times the rate: 2.7 times the fp32 matrix rate, for 11
 // vector operations per pair of values cut.  Measured (a training step, us, fp32 products before and
 // this): 512 slices x 200 rows, d_h = 128 333 and 202 (with the kernels of cotten_wide32.hip), d_h = 32
 // 31.3 and 30.1; distance from a 64-bit evaluation 1.5e-7 ... 2.5e-7 and 1.1e-7 ... 1.5e-7.

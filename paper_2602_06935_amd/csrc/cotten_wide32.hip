@@ -11,8 +11,8 @@
 //                       meet at the end
 //   P = 2, eight waves  (few workgroups) rounds of 128 rows, a wave adds the tiles of its half of the
 //                       workgroup to one block, the two sums of a block meet at the end
-//   P = 4, eight waves  rounds of 64 rows, a wave adds two of the four tiles of a round to a quadrant
-//                       of 2 x 2 blocks, the two sums of a quadrant meet at the end
+//   P = 4, eight waves  rounds of 32 rows in two buffers, a wave adds one of the two tiles of a round to a
+//                       quadrant of 2 x 2 blocks, the two sums of a quadrant meet at the end
 // Apply: a wave loads its own rows straight in the layout of the products (no LDS), the state is
 // read from operand images that lie over the tiles of the walk.
 //
@@ -37,7 +37,7 @@ extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 template <class F, int P, int WAVES>
 struct Lds {
   static constexpr int kPair = 2 * P * F::kTileBytes;   // [x pieces | y pieces] of 16 rows
-  static constexpr int kPairs = P == 2 ? WAVES : 4;     // one per wave; P = 4: a round of 64 rows
+  static constexpr int kPairs = P == 2 ? WAVES : 4;     // one per wave; P = 4: two rounds of 32 rows
   static constexpr int kTiles = kPairs * kPair;
   static constexpr int kSet = P * P * F::kImageBytes;
   static constexpr int kSets = P == 2 ? 2 : 1;          // image sets there is room for
