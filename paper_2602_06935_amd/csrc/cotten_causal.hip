@@ -544,9 +544,11 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
             for (int v = 0; v < 4; ++v)
               if (4 * L.g16 + v > L.i16) pt[v] = 0.0f;
           }
+          // (khat . q is infinite in rows only that 1/r makes NaN anyway)
+          const typename F::Weights w = F::template weights<ROLE != kO>(pt);
 #pragma unroll
           for (int c = 0; c < P; ++c)
-            F::template add_transposed_product<ROLE != kO>(tu + ((ROLE == kO ? P : 0) + c) * F::kTileBytes, L, pt, out[c]);
+            F::add_transposed_product(tu + ((ROLE == kO ? P : 0) + c) * F::kTileBytes, L, w, out[c]);
         }
         const float inv_r = own_inv<F, P>(x, a.eps, row_live, L);
         const float factor = ROLE == kO ? inv_r * scale : scale;
@@ -609,10 +611,9 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
                 for (int v = 0; v < 4; ++v)
                   if (L.i16 > 4 * L.g16 + v) p[v] = 0.0f;
               }
+              const typename F::Weights w = kind == 0 ? F::weights(p) : F::template weights<true>(p);
 #pragma unroll
-              for (int c = 0; c < P; ++c)
-                if (kind == 0) F::add_transposed_product(tt + right + c * F::kTileBytes, L, p, out[c]);
-                else F::template add_transposed_product<true>(tt + right + c * F::kTileBytes, L, p, out[c]);
+              for (int c = 0; c < P; ++c) F::add_transposed_product(tt + right + c * F::kTileBytes, L, w, out[c]);
             }
             const float factor = kind == 0 && F::kFloatRange ? inv_r * scale : scale;
 #pragma unroll

@@ -373,16 +373,19 @@ struct Half64 {
   // operand, so P goes in without moving between lanes; X^T comes from the transposing LDS
   // read (lane i of a 16-lane group gets rows 4g .. 4g+3 of column out_col(nt, i/4) + i%4), so
   // the result lands in the product layout.
+  typedef v4_t Weights;
   template <bool = false>
+  static __device__ __forceinline__ Weights weights(f32x4_t p) {
+    return E::pack4(p);
+  }
   static __device__ __forceinline__ void add_transposed_product(const unsigned char* T,
-                                                                const Lane& L, f32x4_t p,
+                                                                const Lane& L, const Weights& p,
                                                                 f32x4_t (&out)[4]) {
-    const v4_t pb = E::pack4(p);
 #pragma unroll
     for (int nt = 0; nt < 4; ++nt)
       out[nt] = E::mfma_k16(E::read_tr(T + (4 * L.g16 + (L.i16 >> 2)) * kTileStride +
                                        out_col(nt, L.i16 & 3) * 2),
-                            pb, out[nt]);
+                            p, out[nt]);
   }
 
   // One 32x32 block of a state, accumulated by one wave over LDS-resident tiles
@@ -752,17 +755,23 @@ struct F32x32 {
   }
   // out += X^T P (see Half64).  The contraction runs over 16 rows where a 16x16x32 product takes 32:
   // the two halves of its depth carry two products of pieces at a time, three instead of six.
+  // INF: P may hold infinities.
+  struct Weights {
+    bf16x8_t hh, mm, hl;
+  };
   template <bool INF = false>
-  static __device__ __forceinline__ void add_transposed_product(const unsigned char* T,
-                                                                const Lane& L, f32x4_t p,
-                                                                f32x4_t (&out)[2]) {
+  static __device__ __forceinline__ Weights weights(f32x4_t p) {
     const float f[4] = {p[0], p[1], p[2], p[3]};
     uint32_t h[2], m[2], l[2];
     split<false>(f, h, m, l);
     if (INF && __builtin_expect(__builtin_amdgcn_ballot_w64(largest(f) == __builtin_inff()) != 0, 0)) split<true>(f, h, m, l);
     const bf16x4_t bh = __builtin_bit_cast(bf16x4_t, (u32x2_t{h[0], h[1]})), bm = __builtin_bit_cast(bf16x4_t, (u32x2_t{m[0], m[1]})),
                    bl = __builtin_bit_cast(bf16x4_t, (u32x2_t{l[0], l[1]}));
-    const bf16x8_t hh = both(bh, bh), mm = both(bm, bm), hl = both(bh, bl);
+    return Weights{both(bh, bh), both(bm, bm), both(bh, bl)};
+  }
+  static __device__ __forceinline__ void add_transposed_product(const unsigned char* T,
+                                                                const Lane& L, const Weights& p,
+                                                                f32x4_t (&out)[2]) {
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
       const unsigned char* at =
@@ -770,9 +779,9 @@ struct F32x32 {
       const bf16x4_t xh = Bf16Elem::read_tr(at), xm = Bf16Elem::read_tr(at + kPlane),
                      xl = Bf16Elem::read_tr(at + 2 * kPlane);
       const bf16x8_t xhm = both(xh, xm);
-      out[nt] = Bf16Elem::mfma16(both(xl, xh), hl, out[nt]);  // l h' + h l'
-      out[nt] = Bf16Elem::mfma16(xhm, mm, out[nt]);           // h m' + m m'
-      out[nt] = Bf16Elem::mfma16(xhm, hh, out[nt]);           // h h' + m h'
+      out[nt] = Bf16Elem::mfma16(both(xl, xh), p.hl, out[nt]);  // l h' + h l'
+      out[nt] = Bf16Elem::mfma16(xhm, p.mm, out[nt]);           // h m' + m m'
+      out[nt] = Bf16Elem::mfma16(xhm, p.hh, out[nt]);           // h h' + m h'
     }
   }
   // The state as the one 32 x 32 block it is (see Half64::BlockAcc).

@@ -476,7 +476,7 @@ __global__ __launch_bounds__(kThreads) void causal_fwd_kernel(const Args a) {
       for (int v = 0; v < 4; ++v)
         if (4 * L.g16 + v > L.i16) pt[v] = 0.0f;
     }
-    F::add_transposed_product(ub + kVt, L, pt, out);
+    F::add_transposed_product(ub + kVt, L, F::weights(pt), out);
   }
   float o[2 * F::EPL];
   product_rows<F>(out, o);
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
         for (int v = 0; v < 4; ++v)
           if (4 * L.g16 + v > L.i16) gt[v] = 0.0f;
       }
-      F::add_transposed_product(ub + kKt, L, gt, acc);
+      F::add_transposed_product(ub + kKt, L, F::weights(gt), acc);
     }
     float g[2 * F::EPL];
     product_rows<F>(acc, g);
@@ -571,8 +571,8 @@ __global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
           for (int v = 0; v < 4; ++v)
             if (L.i16 > 4 * L.g16 + v) p[v] = gg[v] = 0.0f;
         }
-        F::add_transposed_product(tb + kGt, L, p, av);
-        F::add_transposed_product(tb + kQt, L, gg, ah);
+        F::add_transposed_product(tb + kGt, L, F::weights(p), av);
+        F::add_transposed_product(tb + kQt, L, F::weights(gg), ah);
       }
       product_rows<F>(av, dv);
       product_rows<F>(ah, dk);
