@@ -220,8 +220,8 @@ def _workspace(Q: torch.Tensor, dims, is_bwd: bool, stream_handle: int,
         return ws
 
 
-# Handle of the current stream of a device: straight from torch's extension module where that has it (no
-# Stream object is made).
+# Handle of the current stream of a device: straight from torch's extension module where that has it (0.1 us; a
+# Stream object, made for its handle, 2.9).
 _current_stream_handle = getattr(torch._C, "_cuda_getCurrentRawStream",
                                  lambda device: torch.cuda.current_stream(device).cuda_stream)
 
