@@ -107,7 +107,7 @@ __device__ __forceinline__ void stage_wide(const WideRaw& r, const Lane& L, floa
       for (int c = 0; c < P; ++c) {
         F::unpack(r.x[h][c], f[c]);
 #pragma unroll
-        for (int i = 0; i < F::EPL; ++i) f[c][i] = live ? elu1(f[c][i]) : 0.0f;
+        for (int i = 0; i < F::EPL; ++i) f[c][i] = elu1_or_zero(f[c][i], live);
         *reinterpret_cast<u32x4_t*>(tiles + c * kTileBytes + off) = F::pack(f[c]);
         if (USE_Y) *reinterpret_cast<u32x4_t*>(tiles + (P + c) * kTileBytes + off) = r.y[h][c];
       }

@@ -108,33 +108,38 @@ __device__ __forceinline__ void load_half(Half16<P>& t, const Lane& L, const Buf
 template <class F, int P>
 __device__ __forceinline__ void stage_mapped(const Half16<P>& t, int bits, const Lane& L, float eps,
                                              unsigned char* tiles) {
-  float f[2][P][F::EPL], top = 0.0f;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const bool live = ((bits >> h) & 1) != 0;
-    float ss = 0.0f;
-#pragma unroll
-    for (int c = 0; c < P; ++c) {
-      F::unpack(t.r[h][c], f[h][c]);
-#pragma unroll
-      for (int i = 0; i < F::EPL; ++i) ss += f[h][c][i] * f[h][c][i];
-    }
-    const float inv = F::kMap == kMapElu1 ? 1.0f : inv_norm_or_zero(row_sum8(ss), eps, live);
-#pragma unroll
-    for (int c = 0; c < P; ++c) {
-#pragma unroll
-      for (int i = 0; i < F::EPL; ++i)
-        f[h][c][i] = F::kMap == kMapElu1 ? (live ? elu1(f[h][c][i]) : 0.0f) : f[h][c][i] * inv;
-      if (F::kMap == kMapElu1) top = largest(f[h][c], top);
-    }
-  }
-  write_pieces<F>(top, [&](auto inf) {
-    if (decltype(inf)::value && F::kMap != kMapElu1) return;
+  float top = 0.0f;  // (phi(x) is infinite where x is)
+  if (F::kMap == kMapElu1) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int c = 0; c < P; ++c)
-        F::template put<decltype(inf)::value>(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[h][c]);
+      for (int c = 0; c < P; ++c) {
+        float f[F::EPL];
+        F::unpack(t.r[h][c], f);
+        top = largest(f, top);
+      }
+  }
+  write_pieces<F>(top, [&](auto inf) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bool live = ((bits >> h) & 1) != 0;
+      float f[P][F::EPL];
+      float ss = 0.0f;
+#pragma unroll
+      for (int c = 0; c < P; ++c) {
+        F::unpack(t.r[h][c], f[c]);
+#pragma unroll
+        for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
+      }
+      const float inv = F::kMap == kMapElu1 ? 1.0f : inv_norm_or_zero(row_sum8(ss), eps, live);
+#pragma unroll
+      for (int c = 0; c < P; ++c) {
+#pragma unroll
+        for (int i = 0; i < F::EPL; ++i)
+          f[c][i] = F::kMap == kMapElu1 ? elu1_or_zero(f[c][i], live) : f[c][i] * inv;
+        F::template put<decltype(inf)::value>(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[c]);
+      }
+    }
   });
 }
 
@@ -385,7 +390,7 @@ __device__ __forceinline__ void walk_quadrants(State<F, 4>& out, const Buffers& 
       for (int c = 0; c < P; ++c)
 #pragma unroll
         for (int i = 0; i < F::EPL; ++i)
-          f[c][i] = F::kMap == kMapElu1 ? (on ? elu1(f[c][i]) : 0.0f) : f[c][i] * inv;
+          f[c][i] = F::kMap == kMapElu1 ? elu1_or_zero(f[c][i], on) : f[c][i] * inv;
       const bool any = __builtin_amdgcn_ballot_w64(on) != 0;
       if (L.lane == 0) live_halves[4 * buffer + L.wave] = any;
     }
@@ -533,7 +538,7 @@ __device__ __forceinline__ void own_mapped(const OwnRaw<P>& t, bool live, typena
     float f[2 * F::EPL];
     own_values<F, P>(t, c, f);
 #pragma unroll
-    for (int i = 0; i < 2 * F::EPL; ++i) f[i] = live ? elu1(f[i]) : 0.0f;
+    for (int i = 0; i < 2 * F::EPL; ++i) f[i] = elu1_or_zero(f[i], live);
     write_pieces<F>(largest(f), [&](auto inf) { x[c].template set<decltype(inf)::value>(f); });
   }
 }
@@ -609,7 +614,7 @@ __device__ __forceinline__ float projected_tile(const OwnRaw<P>& x, const OwnRaw
       own_values<F, P>(x, p, f);
 #pragma unroll
       for (int i = 0; i < 2 * F::EPL; ++i)
-        dot += (F::kMap == kMapElu1 ? (live ? elu1(f[i]) : 0.0f) : f[i] * inv) * g[p][i];
+        dot += (F::kMap == kMapElu1 ? elu1_or_zero(f[i], live) : f[i] * inv) * g[p][i];
     }
     dot = row_sum_groups(dot, L);
   }
