@@ -136,37 +136,35 @@ __device__ __forceinline__ void load_shared(SharedRaw<P>& t, const Lane& L, cons
 template <class F, int P>
 __device__ __forceinline__ void stage_shared(const SharedRaw<P>& t, const Lane& L, float eps,
                                              unsigned char* tiles) {
-  float top = 0.0f;  // of y
-  if (F::kPieces) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    float f[P][F::EPL];
+    float ss = 0.0f;
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+      F::unpack(t.x[h][c], f[c]);
+#pragma unroll
+      for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
+    }
+    const float inv = inv_norm_or_zero(row_sum8(ss), eps, ((t.live >> h) & 1) != 0);
+#pragma unroll
+    for (int c = 0; c < P; ++c) {
+#pragma unroll
+      for (int i = 0; i < F::EPL; ++i) f[c][i] *= inv;
+      F::put(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[c]);
+      if (!F::kPieces) F::put_raw(tiles + (P + c) * F::kTileBytes, L.r8 + 8 * h, L.ch, t.y[h][c]);
+    }
+  }
+  if (!F::kPieces) return;
+  float top = 0.0f;
+#pragma unroll
+  for (int c = 0; c < P; ++c) top = F::largest_raw(t.y[0][c], F::largest_raw(t.y[1][c], top));
+  write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int c = 0; c < P; ++c) {
-        float y[F::EPL];
-        F::unpack(t.y[h][c], y);
-        top = largest(y, top);
-      }
-  }
-  write_pieces<F>(top, [&](auto inf) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float f[P][F::EPL];
-      float ss = 0.0f;
-#pragma unroll
-      for (int c = 0; c < P; ++c) {
-        F::unpack(t.x[h][c], f[c]);
-#pragma unroll
-        for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
-      }
-      const float inv = inv_norm_or_zero(row_sum8(ss), eps, ((t.live >> h) & 1) != 0);
-#pragma unroll
-      for (int c = 0; c < P; ++c) {
-#pragma unroll
-        for (int i = 0; i < F::EPL; ++i) f[c][i] *= inv;
-        F::put(tiles + c * F::kTileBytes, L.r8 + 8 * h, L.ch, f[c]);
+      for (int c = 0; c < P; ++c)
         F::template put_raw<decltype(inf)::value>(tiles + (P + c) * F::kTileBytes, L.r8 + 8 * h, L.ch, t.y[h][c]);
-      }
-    }
   });
 }
 

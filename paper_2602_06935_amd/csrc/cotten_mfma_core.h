@@ -205,6 +205,7 @@ struct Half64 {
     return r;
   }
 
+  static __device__ __forceinline__ float largest_raw(u32x4_t, float = 0.0f) { return 0.0f; }  // (no need to look)
   // the lane's EPL values (load layout: columns 8*ch ..) of tile row `row`
   template <bool = false>
   static __device__ __forceinline__ void put(unsigned char* T, int row, int ch, const float (&f)[8]) {
@@ -600,6 +601,11 @@ struct F32x32 {
     return r;
   }
 
+  static __device__ __forceinline__ float largest_raw(u32x4_t r, float so_far = 0.0f) {
+    float f[4];
+    unpack(r, f);
+    return largest(f, so_far);
+  }
   // four neighbouring places (multiples of four) of a plane row
   template <bool INF>
   static __device__ __forceinline__ void write_four(unsigned char* at, const float (&f)[4]) {
@@ -973,46 +979,50 @@ constexpr int mapped_mode() {
 template <class F, int XMODE, bool USE_Y>
 __device__ __forceinline__ void stage(const Raw& r, const Lane& L, float eps, unsigned char* Xt,
                                       unsigned char* Yt, float (&inv)[2], bool cols = true) {
-  float top = 0.0f;  // of what may be infinite (phi(x) is where x is)
-  if (F::kPieces) {
+  // one row: x (INF: phi(x) may be infinite), y
+  const auto stage_x = [&](int h, auto inf) {
+    float f[F::EPL];
+    F::unpack(r.x[h], f);
+    const int row = L.r8 + 8 * h;
+    if (XMODE == kXFeature) {
+      const bool live = ((r.live >> h) & 1) != 0, on = live & cols;
+      inv[h] = live ? 1.0f : 0.0f;
+#pragma unroll
+      for (int i = 0; i < F::EPL; ++i) f[i] = elu1_or_zero(f[i], on);
+      F::template put<decltype(inf)::value>(Xt, row, L.ch, f);
+      return;
+    }
+    float ss = 0.0f;
+#pragma unroll
+    for (int i = 0; i < F::EPL; ++i) ss += f[i] * f[i];
+    inv[h] = inv_norm_or_zero(row_sum8(ss), eps, (r.live >> h) & 1);
+    if (XMODE == kXNormalized) {
+#pragma unroll
+      for (int i = 0; i < F::EPL; ++i) f[i] *= inv[h];
+      F::put(Xt, row, L.ch, f);
+    } else if (XMODE == kXRaw) {
+      F::put_raw(Xt, row, L.ch, r.x[h]);
+    }
+  };
+  const auto stage_y = [&](int h, auto inf) {
+    if (USE_Y) F::template put_raw<decltype(inf)::value>(Yt, L.r8 + 8 * h, L.ch, r.y[h]);
+  };
+  if constexpr (!F::kPieces) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      float f[F::EPL];
-      F::unpack(r.x[h], f);
-      if (XMODE == kXFeature) top = largest(f, top);
-      F::unpack(r.y[h], f);
-      if (USE_Y) top = largest(f, top);
+      stage_x(h, std::false_type{});
+      stage_y(h, std::false_type{});
     }
+    return;
   }
-  write_pieces<F>(top, [&](auto inf) {
-    constexpr bool kInf = decltype(inf)::value;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      float f[F::EPL];
-      F::unpack(r.x[h], f);
-      const int row = L.r8 + 8 * h;
-      if (XMODE == kXFeature) {
-        const bool live = ((r.live >> h) & 1) != 0, on = live & cols;
-        inv[h] = live ? 1.0f : 0.0f;
-#pragma unroll
-        for (int i = 0; i < F::EPL; ++i) f[i] = elu1_or_zero(f[i], on);
-        F::template put<kInf>(Xt, row, L.ch, f);
-        if (USE_Y) F::template put_raw<kInf>(Yt, row, L.ch, r.y[h]);
-        continue;
-      }
-      float ss = 0.0f;
-#pragma unroll
-      for (int i = 0; i < F::EPL; ++i) ss += f[i] * f[i];
-      inv[h] = inv_norm_or_zero(row_sum8(ss), eps, (r.live >> h) & 1);
-      if (XMODE == kXNormalized) {
-#pragma unroll
-        for (int i = 0; i < F::EPL; ++i) f[i] *= inv[h];
-        F::put(Xt, row, L.ch, f);
-      } else if (XMODE == kXRaw) {
-        F::put_raw(Xt, row, L.ch, r.x[h]);
-      }
-      if (USE_Y) F::template put_raw<kInf>(Yt, row, L.ch, r.y[h]);
-    }
+  // (y is looked at behind x: it may still be on its way)
+  write_pieces<F>(XMODE == kXFeature ? F::largest_raw(r.x[0], F::largest_raw(r.x[1])) : 0.0f, [&](auto inf) {
+    stage_x(0, inf);
+    stage_x(1, inf);
+  });
+  write_pieces<F>(USE_Y ? F::largest_raw(r.y[0], F::largest_raw(r.y[1])) : 0.0f, [&](auto inf) {
+    stage_y(0, inf);
+    stage_y(1, inf);
   });
 }
 

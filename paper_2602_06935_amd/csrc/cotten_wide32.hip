@@ -111,13 +111,7 @@ __device__ __forceinline__ void stage_mapped(const Half16<P>& t, int bits, const
   float top = 0.0f;  // (phi(x) is infinite where x is)
   if (F::kMap == kMapElu1) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int c = 0; c < P; ++c) {
-        float f[F::EPL];
-        F::unpack(t.r[h][c], f);
-        top = largest(f, top);
-      }
+    for (int c = 0; c < P; ++c) top = F::largest_raw(t.r[0][c], F::largest_raw(t.r[1][c], top));
   }
   write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
@@ -147,13 +141,7 @@ template <class F, int P>
 __device__ __forceinline__ void stage_plain(const Half16<P>& t, const Lane& L, unsigned char* tiles) {
   float top = 0.0f;
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int c = 0; c < P; ++c) {
-      float f[F::EPL];
-      F::unpack(t.r[h][c], f);
-      top = largest(f, top);
-    }
+  for (int c = 0; c < P; ++c) top = F::largest_raw(t.r[0][c], F::largest_raw(t.r[1][c], top));
   write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
