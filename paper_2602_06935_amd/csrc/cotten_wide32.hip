@@ -383,9 +383,10 @@ __device__ __forceinline__ void walk_quadrants(State<F, 4>& out, const Buffers& 
       if (L.lane == 0) live_halves[4 * buffer + L.wave] = any;
     }
     float top = 0.0f;
+    if (F::kMap == kMapElu1 || part == 1) {
 #pragma unroll
-    for (int c = 0; c < P; ++c) top = largest(f[c], top);
-    if (F::kMap != kMapElu1 && part == 0) top = 0.0f;
+      for (int c = 0; c < P; ++c) top = largest(f[c], top);
+    }
     write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
       for (int c = 0; c < P; ++c)
@@ -521,14 +522,19 @@ __device__ __forceinline__ void own_mapped(const OwnRaw<P>& t, bool live, typena
     own_rows<F, P, false>(t, x);
     return;
   }
+  float top = 0.0f;  // (phi(x) is infinite where x is)
 #pragma unroll
-  for (int c = 0; c < P; ++c) {
-    float f[2 * F::EPL];
-    own_values<F, P>(t, c, f);
+  for (int c = 0; c < P; ++c) top = F::largest_raw(t.r[c][0], F::largest_raw(t.r[c][1], top));
+  write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
-    for (int i = 0; i < 2 * F::EPL; ++i) f[i] = elu1_or_zero(f[i], live);
-    write_pieces<F>(largest(f), [&](auto inf) { x[c].template set<decltype(inf)::value>(f); });
-  }
+    for (int c = 0; c < P; ++c) {
+      float f[2 * F::EPL];
+      own_values<F, P>(t, c, f);
+#pragma unroll
+      for (int i = 0; i < 2 * F::EPL; ++i) f[i] = elu1_or_zero(f[i], live);
+      x[c].template set<decltype(inf)::value>(f);
+    }
+  });
 }
 
 // out = sum_c X[c] W(first + c * step)
