@@ -84,6 +84,10 @@ hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd);
 // The same three for fp32 rows (cotten_wide32.hip); the functions above hand over to them.
 hipError_t launch_wide32_states(const Problem& p, const Plan& plan, bool bwd);
 hipError_t launch_wide32_fused(const Problem& p, const Plan& plan, bool bwd);
+// Sequences that are not cut, every wave the owner of 32 columns of the results (cotten_columns.hip), where
+// there are slices enough for that.
+bool columns_apply(const Problem& p, bool bwd);
+hipError_t launch_columns(const Problem& p, bool bwd);
 hipError_t launch_wide32_apply(const Problem& p, const Plan& plan, const float* states,
                                const float* dstates, bool bwd);
 

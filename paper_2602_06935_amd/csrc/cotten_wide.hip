@@ -1168,6 +1168,7 @@ bool wide_fused_applies(int dtype, int B, int H, int splits, bool bwd) {
 
 hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd) {
   if (!wide_fused_applies(p.dtype, p.B, p.H, plan.splits, bwd)) return hipErrorInvalidValue;
+  if (columns_apply(p, bwd)) return launch_columns(p, bwd);
   if (p.dtype == 0) return launch_wide32_fused(p, plan, bwd);
   return for_format(p, [&](auto f) { return wide::fused<decltype(f)>(p, plan, bwd); });
 }

@@ -1,0 +1,113 @@
+"""Kernels whose waves own 32 columns of the results (fp32 d_h = 128 with more slices than a launch of
+other kernels has workgroups): against the fp64 oracle at the edges of their tiles (16 rows) and rounds (16
+rows of K and V or 32 of Q in the forward, 32 in the backward), with histories that start anywhere in a round,
+holes and sequences without a valid key; the kept state, per-slice scales, d loss / d log(scale), both layouts.
+The bound is that of the other fp32 kernels (1e-5: the products of pieces leave out 2^-22, the sums add units of
+2^-24)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_06935_amd import binding
+from tests.gpu_util import FP32_BAR, check_tensor, rel_l2, to_f64, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+def _mask(rng, B, N):
+    mask = (np.arange(N)[None, :] >= rng.integers(0, N, B)[:, None]).astype(np.uint8)
+    mask[1] = 0
+    mask[2] = rng.random(N) < 0.3
+    mask[2, -1] = 1
+    mask[3] = 1
+    mask[4] = 0
+    mask[4, 0] = 1
+    return mask
+
+
+@pytest.mark.parametrize("B,H,N", [
+    (260, 1, 1), (130, 1, 15), (260, 1, 16), (130, 2, 17), (260, 1, 31), (260, 1, 32), (87, 3, 33), (150, 1, 63),
+    (130, 2, 65), (129, 1, 200), (130, 2, 513), (64, 4, 600),
+])
+@pytest.mark.parametrize("feature_map", ["cosine", "elu1"])
+def test_columns(oracle, B, H, N, feature_map):
+    if feature_map == "elu1" and N > 100:
+        pytest.skip("one map is enough at this size")
+    print(f"[columns] B={B} H={H} N={N} {feature_map}", flush=True)
+    rng = np.random.default_rng(2100 + N + B)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, 128)).astype(np.float32) for _ in range(4))
+    mask = _mask(rng, B, N)
+    tq, tk, tv, tg = (to_gpu(x, "f32") for x in (Q, K, V, dO))
+    tm = torch.from_numpy(mask).cuda()
+    opts = dict(scale=0.25, eps=1e-6, feature_map=feature_map)
+    state, dlog = torch.zeros(B, H, 128, 128, device="cuda"), torch.zeros(B, H, device="cuda")
+    O = binding.cotten_attn_fwd(tq, tk, tv, tm, saved_state=state, **opts)
+    grads = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, dlog_scale=dlog, **opts)
+    again = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, **opts)
+    sw = lambda t: t.permute(0, 2, 1, 3).contiguous()
+    other = binding.cotten_attn_bwd(sw(tq), sw(tk), sw(tv), tm, sw(tg), layout="bnhd", **opts)
+    O2 = binding.cotten_attn_fwd(sw(tq), sw(tk), sw(tv), tm, layout="bnhd", **opts)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) and torch.equal(sw(a), c) for a, b, c in zip(grads, again, other))
+    assert torch.equal(sw(O), O2)
+    if feature_map == "cosine":
+        ref_o, refs = oracle.fwd_linear(Q, K, V, mask, scale=0.25), oracle.bwd(Q, K, V, dO, mask, scale=0.25)
+        assert rel_l2(state.double().cpu().numpy(), oracle.state(K, V, mask)) <= FP32_BAR
+    else:
+        ref_o, refs = oracle.elu_fwd(Q, K, V, mask, scale=0.25), oracle.elu_bwd(Q, K, V, dO, mask, scale=0.25)
+    for name, got, ref in zip(("O", "dQ", "dK", "dV"), (O, *grads), (ref_o, *refs)):
+        check_tensor(name, to_f64(got), ref, FP32_BAR, few_terms=True)  # (histories of one key are among them)
+        if name in ("dK", "dV"):
+            assert np.all(to_f64(got)[np.broadcast_to((mask == 0)[:, None, :, None], ref.shape)] == 0.0)
+    ref_dlog = (dO.astype(np.float64) * ref_o).sum(axis=(2, 3))
+    size = np.sqrt(((dO.astype(np.float64) * ref_o) ** 2).sum(axis=(2, 3)))  # sums with cancellation
+    assert np.all(np.abs(dlog.double().cpu().numpy() - ref_dlog) <= 1e-5 * np.maximum(size, np.abs(ref_dlog)))
+
+
+def test_columns_scales_and_masked_rows(oracle):
+    """Per-slice scales; masked rows may hold anything."""
+    B, H, N = 140, 2, 75
+    rng = np.random.default_rng(77)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, 128)).astype(np.float32) for _ in range(4))
+    mask = _mask(rng, B, N)
+    tq, tk, tv, tg = (to_gpu(x, "f32") for x in (Q, K, V, dO))
+    tm = torch.from_numpy(mask).cuda()
+    ss = torch.rand(B, H, device="cuda") * 0.05 + 0.01
+    run = lambda k, v: (binding.cotten_attn_fwd(tq, k, v, tm, slice_scale=ss),
+                        *binding.cotten_attn_bwd(tq, k, v, tm, tg, slice_scale=ss))
+    plain = run(tk, tv)
+    dead = (tm == 0)[:, None, :, None].expand_as(tk)
+    garbage = run(tk.masked_fill(dead, float("nan")), tv.masked_fill(dead, float("inf")))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(plain, garbage))
+    unit = (oracle.fwd_linear(Q, K, V, mask, scale=1.0), *oracle.bwd(Q, K, V, dO, mask, scale=1.0))
+    s64 = ss.double().cpu().numpy()[:, :, None, None]
+    for name, got, ref in zip(("O", "dQ", "dK", "dV"), plain, unit):  # (every result is linear in the scale)
+        check_tensor(name, to_f64(got), ref * s64, FP32_BAR, few_terms=True)
+
+
+def test_columns_infinities():
+    """A component of V (of dO) that is infinite in one row: infinities of its sign in that column of O (dV), everything
+    else as without it, bit for bit."""
+    B, H, N, at, up, down = 260, 1, 50, 25, 1, 126
+    rng = np.random.default_rng(65)
+    Q, K, V, dO = (rng.standard_normal((B, H, N, 128)).astype(np.float32) for _ in range(4))
+    q, k = to_gpu(np.abs(Q) + 0.1, "f32"), to_gpu(np.abs(K) + 0.1, "f32")
+
+    def run(V, dO):
+        v, g = to_gpu(V, "f32"), to_gpu(dO, "f32")
+        O = binding.cotten_attn_fwd(q, k, v, None, scale=1.0 / N)
+        dV = binding.cotten_attn_bwd(q, k, v, None, g, scale=1.0 / N)[2]
+        torch.cuda.synchronize()
+        return O.cpu().numpy(), dV.cpu().numpy()
+
+    plain = run(V, dO)
+    for x in (V, dO):
+        x[0, 0, at, up], x[0, 0, at, down] = np.inf, -np.inf
+    for got, was in zip(run(V, dO), plain):
+        assert np.all(got[0, 0, :, up] == np.inf) and np.all(got[0, 0, :, down] == -np.inf)
+        rest = np.ones(got.shape, bool)
+        rest[0, 0, :, [up, down]] = False
+        assert np.array_equal(got[rest], was[rest])
