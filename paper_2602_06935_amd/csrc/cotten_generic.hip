@@ -136,17 +136,47 @@ void launch_reduce_states(const float* partial, float* reduced, int splits, int 
                      total);
 }
 
+namespace {
+
+// Workgroups per slice of a sequence that is cut (rows of up to 128 bytes).  The slices are dealt to the eight XCDs, and
+// with them all their workgroups: what has to fit is `per_xcd` * splits on 32 compute units.  In 16 bits every workgroup
+// of an apply launch gathers a partial state of 16 KB per split, as much as 128 rows of a tensor: that many splits and
+// no more than about sqrt(N / 7) (or ten), and one workgroup per compute unit, two where a workgroup would have more than 600 rows
+// or the slices are too many to fill one well.  Partial states of fp32 rows are a quarter of that: two workgroups per compute
+// unit, or three where these fill it better.  Forward / backward, us, against as many splits as make 512 workgroups in all:
+//   bf16 d = 64:  4 x 4096, 16 splits 13.8 / 26.8 (64: 29.4 / 56.3);  8 x 1500, 12: 11.7 / 21.4 (24: 12.5 / 22.5);  20 x 1500, 8: 13.2 /
+//   24.6 (24: 23.5 / 45.9);  24 x 4096, 10: 18.7 / 40.0 (22: 28.3 / 57.3);  40 x 4096, 12: 25.5 / 49.6, 6: 24.0 / 51.6 (13: 30.8 / 65.3);
+//   64 x 2000, 4: 19.8 / 40.9 (8: 20.9 / 43.3);  64 x 4096, 4: 37 / 67, 8: 34 / 71;  100 x 2500, 4: 34.7 / 65.5 (6: 37.1 / 80.7);
+//   240 x 4096, 2: 108 / 241 (3: 117 / 267)
+//   fp32 d = 32:  4 x 4096, 32: 11.1 / 19.9 (64: 12.9 / 23.4);  60 x 3333, 8: 24.6 / 53.6 (9: 26.7 / 57.2);  90 x 4096, 8: 49.2 / 98.4 (6:
+//   53.6 / 107);  180 x 4096, 4: 85 / 188 (3: 94 / 213)
+long split_count(long BH, long N, int dtype) {
+  constexpr long kXcds = 8, kUnits = 32;  // and compute units of an XCD
+  const long per_xcd = (BH + kXcds - 1) / kXcds, one = kUnits / per_xcd, two = 2 * kUnits / per_xcd, three = 3 * kUnits / per_xcd;
+  long splits;
+  if (dtype != 0) {
+    splits = per_xcd > 8 || N > 600 * one ? two : one;
+    long most = 10;
+    while (7 * (most + 1) * (most + 1) <= N) ++most;
+    if (splits > most) splits = most;
+  } else if (per_xcd <= 2) {
+    splits = one;
+  } else {
+    splits = 200 * three > 318 * two ? three : two;  // (fills 6 % more)
+  }
+  return splits < 2 ? 2 : splits;
+}
+
+}  // namespace
+
 Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
   const long BH = static_cast<long>(B) * H;
   const size_t nstates = is_bwd ? 2 : 1;
   Plan plan;
   long splits, rows;
   if (mfma_supports(dtype, D)) {
-    // One workgroup per slice while that fills the chip or the slice is short; otherwise
-    // cut the sequence so that about 512 workgroups exist, two per compute unit (measured at
-    // N = 4096 with 64 slices: 256 workgroups 0.67 G tokens/s, 512: 0.71 G, 768 and 1024: 0.58 G
-    // - a second workgroup covers the fixed work of the first, more only add fixed work), in
-    // blocks of 64 rows.
+    // One workgroup per slice and launch while that fills enough of the chip or the slice is short; otherwise the
+    // sequence is cut, in blocks of 64 rows (split_count).
     constexpr long kFusedMaxN = 2048, kBlock = 64;
     // 16-bit sequences that fit LDS go to the resident kernels - except the forward of the
     // longer ones when there are many slices, where the fused kernel that keeps its tiles in
@@ -164,7 +194,13 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
     // (measured at N = 3000 ... 4096: the backward from 256 slices on, the forward from 512).
     constexpr long kFusedLongMaxN = 16384;  // key flags of the slice must fit LDS
     const bool fused_long = N <= kFusedLongMaxN && BH >= (is_bwd ? 256 : 512);
-    if ((N <= kFusedMaxN && (BH >= 256 || N <= 256)) || fused_long) {
+    // One launch against two or three, forward / backward, us, whole and cut: bf16 d = 64: 40 x 320 rows 9.8 / 18.6, 10.4 / 18.4;
+    // 64 x 420 11.7 / 23.6, 11.5 / 21.4;  100 x 420 12.0 / 24.2, 14.5 / 26.8;  100 x 600 15.5 / 30.5, 15.4 / 30.9;  130 x 900 21.3 / 44.3,
+    // 20.0 / 42.3;  160 x 900 22.6 / 45.3, 21.4 / 45.5;  160 x 1300 34 / 65, 26 / 55;  200 x 1300 35 / 65, 38 / 67;  200 x 2000 51 / 105,
+    // 54 / 111.  fp32 d = 32: 100 x 260 10.4 / 19.3, 10.4 / 18.6;  130 x 320 10.8 / 20.3, 11.5 / 21.1;  160 x 420 13.8 / 26.0, 13.4 /
+    // 26.4;  200 x 600 19.0 / 35.0, 18.6 / 36.1;  250 x 600 20.1 / 36.9, 20.5 / 41.7;  250 x 900 27.5 / 55.9, 26.5 / 55.0.
+    const long enough = dtype != 0 ? (N / 5 - 10 < 170 ? N / 5 - 10 : 170) : (N / 4 + 40 < 256 ? N / 4 + 40 : 256);
+    if ((N <= kFusedMaxN && (BH >= enough || N <= 256)) || fused_long) {
       plan.path = Plan::kFused;
       plan.splits = 1;
       plan.rows_per_split = N;
@@ -172,7 +208,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
       return plan;
     }
     plan.path = Plan::kSplit;
-    splits = (512 + BH - 1) / BH;
+    splits = split_count(BH, N, dtype);
     const long by_len = (N + kFusedMaxN - 1) / kFusedMaxN;
     if (splits < by_len) splits = by_len;
     const long max_splits = (N + kBlock - 1) / kBlock;

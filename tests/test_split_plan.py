@@ -1,0 +1,60 @@
+"""Where sequences of rows of up to 128 bytes are cut, and into how many workgroups: the rule on the host (through the
+workspace a call asks for: one state per slice and workgroup, two in the backward, none where a call is one launch),
+and parity on both sides of its lines."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_06935_amd import binding
+from tests.gpu_util import bar_for, check_tensor, to_f64, to_gpu
+
+F32, BF16, F16 = binding.COTTEN_F32, binding.COTTEN_BF16, binding.COTTEN_F16
+
+
+def _splits(slices, N, dtype, bwd):
+    side = 32 if dtype == F32 else 64
+    need = binding.cotten_attn_workspace_bytes(slices, 1, N, side, dtype, bwd)
+    states = need // (slices * side * side * 4 * (2 if bwd else 1))
+    assert states * slices * side * side * 4 * (2 if bwd else 1) == need
+    return states
+
+
+@pytest.mark.parametrize("slices,N,dtype,splits", [
+    # 16 bits: whole from N / 5 - 10 slices on, at most 170 of them
+    (39, 250, BF16, 0), (53, 320, BF16, 3), (54, 320, BF16, 0), (109, 600, F16, 4), (110, 600, F16, 0),
+    (169, 2048, BF16, 2), (170, 2048, BF16, 0), (170, 2049, BF16, 2),
+    # a workgroup per compute unit of the XCD, no more than sqrt(N / 7) (or ten), blocks of 64 rows
+    (1, 300, BF16, 5), (8, 600, BF16, 10), (8, 1500, BF16, 12), (8, 4096, BF16, 22), (9, 4096, BF16, 16),
+    (24, 4096, BF16, 10), (32, 2000, F16, 8), (64, 2000, BF16, 4),
+    # two where a workgroup would have more than 600 rows, or there are more than eight slices per XCD
+    (64, 4096, BF16, 8), (72, 4096, BF16, 7), (100, 2500, BF16, 4), (128, 4096, F16, 4),
+    # fp32: two, or three where these fill it better
+    (7, 4096, F32, 32), (16, 4096, F32, 16), (64, 4096, F32, 8), (96, 4096, F32, 8), (180, 4096, F32, 4),
+    (200, 4096, F32, 2), (119, 320, F32, 3), (120, 320, F32, 0), (255, 864, F32, 2),
+])
+def test_split_rule(slices, N, dtype, splits):
+    assert _splits(slices, N, dtype, True) == splits
+    assert _splits(slices, N, dtype, False) == splits
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,slices,N", [
+    ("bf16", 53, 320), ("bf16", 54, 320), ("f16", 170, 1029), ("bf16", 169, 1029), ("bf16", 9, 1531), ("f16", 3, 2300),
+    ("f32", 120, 320), ("f32", 96, 1100), ("f32", 7, 2049),
+])
+def test_both_sides_of_the_split_rule(oracle, dtype, slices, N):
+    print(f"[split plan] {dtype} {slices} x {N}", flush=True)
+    d = 32 if dtype == "f32" else 64
+    rng = np.random.default_rng(3000 + N + slices)
+    Q, K, V, dO = (to_f64(to_gpu(rng.standard_normal((slices, 1, N, d)), dtype)).astype(np.float32) for _ in range(4))
+    mask = (np.arange(N)[None, :] >= rng.integers(0, N, slices)[:, None]).astype(np.uint8)
+    tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
+    tm = torch.from_numpy(mask).cuda()
+    O = binding.cotten_attn_fwd(tq, tk, tv, tm)
+    grads = binding.cotten_attn_bwd(tq, tk, tv, tm, tg)
+    torch.cuda.synchronize()
+    refs = (oracle.fwd_linear(Q, K, V, mask), *oracle.bwd(Q, K, V, dO, mask))
+    for name, got, ref in zip(("O", "dQ", "dK", "dV"), (O, *grads), refs):
+        check_tensor(name, to_f64(got), ref, bar_for(dtype))
