@@ -47,7 +47,6 @@ template <>
 struct Cols<F32x32> {
   typedef F32x32 F;
   typedef Pieces Frag;
-  static constexpr int kPerPiece = 1;  // groups of 32 columns in a 128-byte piece
   static __device__ __forceinline__ Frag rows(const unsigned char* tiles, int group, const Lane& L) {
     return F::rows_operand(tiles + group * F::kTileBytes, L);
   }
@@ -98,11 +97,34 @@ struct Cols<F32x32> {
   static __device__ __forceinline__ int run_row(int j, const Lane& L) { return F::run_row(j, L); }
   static __device__ __forceinline__ int run_col(const Lane& L) { return F::run_col(L); }
 };
+template <class E>
+struct Cols<Half64<E>> {
+  typedef Half64<E> F;
+  typedef typename F::v8_t Frag;
+  static __device__ __forceinline__ Frag rows(const unsigned char* tiles, int group, const Lane& L) {
+    return F::rows_operand(tiles + (group >> 1) * F::kTileBytes, L, 32 * (group & 1));
+  }
+  static __device__ __forceinline__ Frag own(const unsigned char* tiles, int group, const Lane& L) {
+    return *reinterpret_cast<const Frag*>(tiles + (group >> 1) * F::kTileBytes + L.i16 * F::kTileStride + 64 * (group & 1) + 16 * L.g16);
+  }
+  static __device__ __forceinline__ void values(const Frag& x, float (&f)[8]) { F::unpack(__builtin_bit_cast(u32x4_t, x), f); }
+  template <bool>
+  static __device__ __forceinline__ Frag cut(const float (&f)[8]) { return __builtin_bit_cast(Frag, F::pack(f)); }
+  static __device__ __forceinline__ int column(int g16, int e) { return 8 * g16 + e; }
+  static __device__ __forceinline__ int place(int nt, int i16) { return 8 * (i16 >> 2) + 4 * nt + (i16 & 3); }
+  static __device__ __forceinline__ void mfma16(const Frag (&w)[2], const Frag& x, f32x4_t (&out)[2]) {
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) out[nt] = E::mfma16(w[nt], x, out[nt]);
+  }
+  static __device__ __forceinline__ f32x16_t mfma32(const Frag& a, const Frag& b, f32x16_t c) { return E::mfma32(a, b, c); }
+  static __device__ __forceinline__ int run_row(int j, const Lane& L) { return F::BlockAcc::run_row(j, L); }
+  static __device__ __forceinline__ int run_col(const Lane& L) { return F::BlockAcc::run_col(L); }
+};
 template <class Base>
 struct Cols<WithElu1<Base>> : Cols<Base> {};
 
-// A workgroup has one wave per group of 32 columns, or two: then a round has two tiles of x and of y, and the waves
-// of a group share its work (`part`).
+// A workgroup has one, two or four waves per group of 32 columns: a round has as many tiles of x and of y, and the
+// waves of a group share its work (`part`).
 template <class F, int P, int WAVES>
 struct Lds {
   static constexpr int D = P * F::D, kGroups = D / 32, kParts = WAVES / kGroups;
@@ -115,7 +137,7 @@ struct Lds {
   static constexpr int kDots = kFactors + 2 * 2 * kRound * 4;          // [buffer][group][row of a round]
   static constexpr int kLive = kDots + 2 * kGroups * kRound * 4;       // [buffer][wave]
   static constexpr int kBytes = kLive + 2 * WAVES * 4;
-  static_assert(kGroups == 4 && (kParts == 1 || kParts == 2), "shape");
+  static_assert(kGroups == 4 && (kParts == 1 || kParts == 2 || kParts == 4), "shape");
 };
 
 struct Args {
@@ -139,7 +161,7 @@ struct Args {
 // What becomes of the rows of a round on their way to LDS, and who brings them there (eight rows of a tensor at a time).
 enum Stage {
   kMapped,  // x: xhat or phi(x), the first half of the waves;  y as it is, the second half
-  kRaw,     // x as it is (phi(x) under ELU + 1) and y as it is; with two waves per group the first of them, one of each
+  kRaw,     // x as it is (phi(x) under ELU + 1) and y as it is, both the first half of the waves
   kRawX,    // x alone, all waves: twice as many rows
 };
 
@@ -148,7 +170,7 @@ enum Stage {
 template <class F, int P, int WAVES, int STAGE>
 struct Walk {
   typedef Lds<F, P, WAVES> Map;
-  static constexpr bool kBoth = STAGE == kRaw && Map::kParts == 2;  // a wave brings x and y, or nothing
+  static constexpr bool kBoth = STAGE == kRaw;  // a wave brings x and y, or nothing
   static constexpr int kRows = STAGE == kRawX ? 2 * Map::kRound : Map::kRound, kUnits = kBoth ? 2 : 1;
   __amdgpu_buffer_rsrc_t src[kUnits];
   const uint8_t* mask;
@@ -282,8 +304,8 @@ __device__ __forceinline__ void rounds(W& walk, int begin, int end, float eps, c
 
 // ---- states -----------------------------------------------------------------------------------------
 
-// The wave's blocks of a state: columns 32 p .. of x against 32 (q0 + j) .. of y.  The products of a round are summed up on
-// their own, small ones first, and then added to what there is: few roundings at its size.
+// The wave's blocks of a state: columns 32 p .. of x against 32 (q0 + j) .. of y.  fp32: the products of
+// a round are summed up on their own, small ones first, and then added to what there is: few roundings at its size.
 template <class F, int P, int WAVES>
 struct State {
   typedef Lds<F, P, WAVES> Map;
@@ -300,6 +322,19 @@ struct State {
   __device__ __forceinline__ void add(int buffer, const Lane& L) {
     constexpr int T = Map::kParts;
     const unsigned char* tiles = smem + buffer * Map::kBuffer;
+    if constexpr (!F::kPieces) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const typename C::Frag x = C::rows(tiles + t * Map::kPair, p, L);
+#pragma unroll
+        for (int j = 0; j < kBlocks; ++j) v[j] = C::mfma32(x, C::rows(tiles + t * Map::kPair + Map::kY, q0 + j, L), v[j]);
+      }
+    } else {
+      add_pieces(tiles, L);
+    }
+  }
+  __device__ __forceinline__ void add_pieces(const unsigned char* tiles, const Lane& L) {
+    constexpr int T = Map::kParts;
     f32x16_t sum[kBlocks];
     typename C::Large x_large[T], y_large[T][kBlocks];
 #pragma unroll
@@ -370,7 +405,7 @@ struct Weights {
       for (int nt = 0; nt < 2; ++nt) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) f[ks][nt][e] *= scale;
-        top = largest(f[ks][nt], top);
+        if (F::kPieces) top = largest(f[ks][nt], top);
       }
     write_pieces<F>(top, [&](auto inf) {
 #pragma unroll
@@ -407,7 +442,13 @@ template <class F>
 __device__ __forceinline__ void store_columns(unsigned char* out, int group, int row, int end, int stride, const Lane& L,
                                               const float (&o)[8]) {
   if (row >= end) return;
-  store_product_row<F, kStoreStreamed>(out + group * kRowBytes, row, RowAddr{stride, kRowBytes}, L, o);
+  if constexpr (F::kPieces) {
+    store_product_row<F, kStoreStreamed>(out + group * kRowBytes, row, RowAddr{stride, kRowBytes}, L, o);
+  } else {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(out, 0, 0x7fffffff, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(F::pack(o), r, static_cast<uint32_t>(row) * stride + 64 * group + 16 * L.g16, 0,
+                                           kStoreStreamed);
+  }
 }
 
 // Rows first .. last-1 of a result that are zeros.
@@ -490,11 +531,11 @@ __device__ __forceinline__ void key_state(State<F, P, WAVES>& s, const Args& a, 
   }, [](int, int) {});
 }
 
-template <class F, int P>
-__global__ __launch_bounds__(256, 2) void columns_fwd_kernel(const Args a) {
-  constexpr int WAVES = 4;
+template <class F, int P, int WAVES, int PER_SIMD>
+__global__ __launch_bounds__(64 * WAVES, PER_SIMD) void columns_fwd_kernel(const Args a) {
   typedef Lds<F, P, WAVES> Map;
   const Lane L;
+  const int group = L.wave % Map::kGroups, part = L.wave / Map::kGroups;
   const int bh = blockIdx.x, N = a.N;
   const size_t base = a.st.slice_base(bh, a.H);
   const uint8_t* keys = a.mask == nullptr ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * N;
@@ -512,26 +553,29 @@ __global__ __launch_bounds__(256, 2) void columns_fwd_kernel(const Args a) {
           *reinterpret_cast<const f32x4_t*>(reinterpret_cast<const float*>(smem) + 4 * e / D * Map::kLd + 4 * e % D);
   }
   Weights<F, P, WAVES> W;
-  W.load(L.wave, scale, false, L);
+  W.load(group, scale, false, L);
   __syncthreads();
   rounds<WAVES>(q, 0, N, a.eps, L, [&](int buffer, int row0) {
     const float* factors = reinterpret_cast<const float*>(smem + Map::kFactors) + 2 * Map::kRound * buffer;
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
+    for (int i = 0; i < 2; ++i) {
+      const int t = part + i * Map::kParts;
       if (row0 + t * TR >= N) continue;
       float o[8];
       W.apply(smem + buffer * Map::kBuffer + t * Map::kY, L, o);
       const float inv = factors[t * TR + L.i16];
 #pragma unroll
       for (int e = 0; e < 8; ++e) o[e] *= inv;
-      store_columns<F>(a.O + base, L.wave, row0 + t * TR + L.i16, N, a.st.row.stride, L, o);
+      store_columns<F>(a.O + base, group, row0 + t * TR + L.i16, N, a.st.row.stride, L, o);
     }
   }, [](int, int) {});
 }
 
-template <class F, int P>
-__global__ __launch_bounds__(512, 2) void columns_bwd_kernel(const Args a) {
-  constexpr int WAVES = 8;
+// DLOG: <S, dS> from the accumulators of both, which 16-bit rows take for the gradient of the scale; fp32 rows sum up the
+// dot products of the rows.
+template <class F, int P, int WAVES, int PER_SIMD, bool DLOG>
+__global__ __launch_bounds__(64 * WAVES, PER_SIMD) void columns_bwd_kernel(const Args a) {
+  constexpr int kShare = Lds<F, P, WAVES>::kParts / 2;  // waves of a group that share dV (dK)
   typedef Lds<F, P, WAVES> Map;
   typedef Cols<F> C;
   const Lane L;
@@ -541,7 +585,7 @@ __global__ __launch_bounds__(512, 2) void columns_bwd_kernel(const Args a) {
   const float scale = a.slice_scale != nullptr ? a.slice_scale[bh] : a.scale;
   const int group = L.wave % Map::kGroups, part = L.wave / Map::kGroups;
   const int begin = first_live_tile(keys, N, L);
-  const bool want_dots = F::kMap != kMapElu1 || a.dlog != nullptr;
+  const bool want_dots = F::kMap != kMapElu1 || (F::kPieces && a.dlog != nullptr);
   float* all_dots = reinterpret_cast<float*>(smem + Map::kDots);
   const auto dots_of = [&](int buffer, int g) { return all_dots + (buffer * Map::kGroups + g) * Map::kRound; };
   const auto row_dot = [&](int buffer, int row) {
@@ -579,53 +623,66 @@ __global__ __launch_bounds__(512, 2) void columns_bwd_kernel(const Args a) {
       finish<F>(t, dot);
       store_columns<F>(a.dQ + base, group, row, N, stride, L, t.g);
     });
-    if (a.dlog != nullptr) {  // sum_i dO_i . O_i = sum_i qhat_i . (scale dO_i S^T), in a fixed order
-      __syncthreads();
-      if (group == 0) {
-        const float sum = wave_sum(L.g16 == 0 ? dlog : 0.0f);
-        if (L.lane == 0) all_dots[part] = sum;
+    if (F::kPieces ? a.dlog != nullptr : DLOG) {  // in a fixed order
+      float sum = 0.0f;
+      if constexpr (F::kPieces) {  // sum_i dO_i . O_i = sum_i qhat_i . (scale dO_i S^T)
+        sum = group == 0 && L.g16 == 0 ? dlog : 0.0f;
+      } else {
+#pragma unroll
+        for (int j = 0; j < State<F, P, WAVES>::kBlocks; ++j)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) sum += s.v[j][i] * ds.v[j][i];
       }
+      sum = wave_sum(sum);
       __syncthreads();
-      if (threadIdx.x == 0) a.dlog[bh] = all_dots[0] + all_dots[1];
+      if (L.lane == 0) all_dots[L.wave] = sum;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        float total = 0.0f;
+        for (int w = 0; w < WAVES; ++w) total += all_dots[w];
+        a.dlog[bh] = F::kPieces ? total : total * scale;
+      }
     }
   }
-  {  // dV = scale khat dS (part 0, which also stages the rows) and dK from scale v dS^T (part 1)
+  {  // dV = scale khat dS (the first half of the waves, which also stage the rows) and dK from scale v dS^T (the others)
+    const bool plain = part < kShare;
+    const int first = plain ? part : part - kShare;
     Walk<F, P, WAVES, kRaw> kv(a.K + base, a.V + base, N, a.st.row, keys, L);
     kv.start(begin, L);
     publish(ds, L);
-    W.load(group, scale, part == 1, L);
+    W.load(group, scale, !plain, L);
     __syncthreads();
     Projected t[2];
     rounds<WAVES>(kv, begin, N, a.eps, L, [&](int buffer, int row0) {
       const unsigned char* tiles = smem + buffer * Map::kBuffer;
-      if (part == 0) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          float o[8];
-          W.apply(tiles + i * Map::kPair, L, o);
-          const float inv = factor_of(buffer, i * TR + L.i16);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = inv < 0.0f ? 0.0f : o[e] * inv;
-          store_columns<F>(a.dV + base, group, row0 + i * TR + L.i16, N, stride, L, o);
-        }
-        return;
-      }
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        W.apply(tiles + i * Map::kPair + Map::kY, L, t[i].g);
-        C::values(C::own(tiles + i * Map::kPair, group, L), t[i].x);
-        t[i].inv = factor_of(buffer, i * TR + L.i16);
+        const int at = (first + i * kShare) * TR;  // row of the round
+        const unsigned char* pair = tiles + at / TR * Map::kPair;
+        const float inv = factor_of(buffer, at + L.i16);
+        if (plain) {
+          float o[8];
+          W.apply(pair, L, o);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = inv < 0.0f ? 0.0f : o[e] * inv;
+          store_columns<F>(a.dV + base, group, row0 + at + L.i16, N, stride, L, o);
+          continue;
+        }
+        W.apply(pair + Map::kY, L, t[i].g);
+        C::values(C::own(pair, group, L), t[i].x);
+        t[i].inv = inv;
         if (F::kMap == kMapElu1) continue;
 #pragma unroll
         for (int e = 0; e < 8; ++e) t[i].x[e] *= t[i].inv;  // (below zero: the row's results are dropped)
-        publish_dot(t[i], dots_of(buffer, group) + i * TR, L);
+        publish_dot(t[i], dots_of(buffer, group) + at, L);
       }
     }, [&](int buffer, int row0) {
-      if (part == 0) return;
+      if (plain) return;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        finish<F>(t[i], F::kMap != kMapElu1 ? row_dot(buffer, i * TR + L.i16) : 0.0f);
-        store_columns<F>(a.dK + base, group, row0 + i * TR + L.i16, N, stride, L, t[i].g);
+        const int at = (first + i * kShare) * TR;
+        finish<F>(t[i], F::kMap != kMapElu1 ? row_dot(buffer, at + L.i16) : 0.0f);
+        store_columns<F>(a.dK + base, group, row0 + at + L.i16, N, stride, L, t[i].g);
       }
     });
   }
@@ -635,21 +692,37 @@ __global__ __launch_bounds__(512, 2) void columns_bwd_kernel(const Args a) {
 
 // ---- host side -------------------------------------------------------------------------------------------
 
-template <class F, int P>
-hipError_t run(const Problem& p, const Args& a, bool bwd) {
-  constexpr int lds_fwd = Lds<F, P, 4>::kBytes, lds_bwd = Lds<F, P, 8>::kBytes;
-  static_assert(lds_fwd <= 80 * 1024 && lds_bwd <= 160 * 1024, "two workgroups per compute unit, and one");
-  const dim3 grid(static_cast<unsigned>(p.B) * p.H);
-  if (bwd) {
-    const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(columns_bwd_kernel<F, P>), lds_bwd);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((columns_bwd_kernel<F, P>), grid, dim3(512), lds_bwd, p.stream, a);
-  } else {
-    const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(columns_fwd_kernel<F, P>), lds_fwd);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((columns_fwd_kernel<F, P>), grid, dim3(256), lds_fwd, p.stream, a);
-  }
+constexpr long kUnits = 256;
+
+template <class Kernel>
+hipError_t launch(Kernel kernel, int waves, int lds, const Problem& p, const Args& a) {
+  const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
+  if (err != hipSuccess) return err;
+  hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(p.B) * p.H), dim3(64 * waves), lds, p.stream, a);
   return hipGetLastError();
+}
+
+hipError_t run32(const Problem& p, const Args& a, bool bwd) {
+  const auto go = [&](auto f) {
+    typedef decltype(f) F;
+    constexpr int lds_fwd = Lds<F, 4, 4>::kBytes, lds_bwd = Lds<F, 4, 8>::kBytes;
+    static_assert(lds_fwd <= 80 * 1024 && lds_bwd <= 160 * 1024, "two workgroups per compute unit, and one");
+    return bwd ? launch(columns_bwd_kernel<F, 4, 8, 2, false>, 8, lds_bwd, p, a)
+               : launch(columns_fwd_kernel<F, 4, 4, 2>, 4, lds_fwd, p, a);
+  };
+  return p.feature_map == kMapElu1 ? go(WithElu1<F32x32>{}) : go(F32x32{});
+}
+
+// 16-bit rows, backward: eight waves, two workgroups per compute unit, where there are more slices than units, sixteen
+// otherwise and where the accumulators of S are kept for <S, dS> (registers).  bf16 d_h = 128, sixteen and eight, us:
+// 256 x 400 47.7, 58.2;  300 x 300 61.8, 51.4;  512 x 300 77.9, 65.6;  512 x 500 120, 115;  700 x 500 162, 165.
+template <class F>
+hipError_t run16(const Problem& p, const Args& a) {
+  constexpr int lds8 = Lds<F, 2, 8>::kBytes, lds16 = Lds<F, 2, 16>::kBytes;
+  static_assert(lds8 <= 80 * 1024 && lds16 <= 160 * 1024, "two workgroups per compute unit, and one");
+  if (a.dlog != nullptr) return launch(columns_bwd_kernel<F, 2, 16, 4, true>, 16, lds16, p, a);
+  if (static_cast<long>(p.B) * p.H > kUnits) return launch(columns_bwd_kernel<F, 2, 8, 4, false>, 8, lds8, p, a);
+  return launch(columns_bwd_kernel<F, 2, 16, 4, false>, 16, lds16, p, a);
 }
 
 }  // namespace columns
@@ -660,10 +733,15 @@ hipError_t run(const Problem& p, const Args& a, bool bwd) {
 // those and these):  128 slices x 200 rows 26.6 / 39.7, 36.5 / 58.8;  192: 30.2 / 73.4, 40.2 / 60.6;  256: 33.4 / 76.8, 41.5 /
 // 62.3;  300: 50.0 / 104, 48.0 / 104;  512: 60.4 / 155, 53.0 / 123;  512 x 100 36.5 / 95.9, 31.6 / 77.3;  512 x 20 19.9 / 61.6, 11.6 /
 // 32.8;  512 x 700 163 / 415, 164 / 368;  256 x 1000 118 / 283, 181 / 277.
+// 16-bit rows of 256 bytes, backward: against the kernels of cotten_wide.hip, which keep the tiles of up to 256 rows in
+// registers and walk longer sequences three times (us, those and these):  1024 slices x 200 rows 94.6, 99.6;  100 x 300 31.5,
+// 34.2;  180 x 300 34.8, 36.2;  180 x 400 45.3, 43.8;  256 x 300 38.2, 37.2;  512 x 300 85.0, 65.6;  512 x 400 117, 87;  256 x 800 130, 96;
+// 200 x 1800 255, 192.  (Their forward stays: 512 x 400 37, 39.)
 bool columns_apply(const Problem& p, bool bwd) {
-  constexpr long kUnits = 256;
   const long slices = static_cast<long>(p.B) * p.H;
-  return p.dtype == 0 && p.D == 128 && slices * (bwd ? 2 : 1) > kUnits;
+  if (p.D != 128) return false;
+  if (p.dtype != 0) return bwd && (p.N > 384 || (p.N > 256 && slices >= columns::kUnits));
+  return slices * (bwd ? 2 : 1) > columns::kUnits;
 }
 
 hipError_t launch_columns(const Problem& p, bool bwd) {
@@ -688,7 +766,10 @@ hipError_t launch_columns(const Problem& p, bool bwd) {
   const long long e = p.elem_bytes();
   a.st = Strides{p.stride_batch * e, p.stride_head * e,
                  RowAddr{static_cast<int>(p.stride_row * e), static_cast<int>(p.D * e)}};
-  return p.feature_map == kMapElu1 ? run<WithElu1<F32x32>, 4>(p, a, bwd) : run<F32x32, 4>(p, a, bwd);
+  if (p.dtype == 0) return run32(p, a, bwd);
+  if (!bwd) return hipErrorInvalidValue;
+  if (p.feature_map == kMapElu1) return p.dtype == 1 ? run16<WithElu1<Bf16x64>>(p, a) : run16<WithElu1<F16x64>>(p, a);
+  return p.dtype == 1 ? run16<Bf16x64>(p, a) : run16<F16x64>(p, a);
 }
 
 }  // namespace cotten

@@ -167,13 +167,65 @@ long split_count(long BH, long N, int dtype) {
   return splits < 2 ? 2 : splits;
 }
 
+constexpr long kUnits = 256;  // compute units
+
+// Wide rows: parts of a sequence for fewer slices than compute units.  A part costs a d x d state (64 KB at d = 128) written,
+// summed up and read back, and two launches more; whole sequences take one launch per direction (16-bit backward over
+// fewer than 86 slices: three).  Forward / backward, us.
+
+// 16-bit rows, as many parts as bound the workspace of a call: what sequences were cut into before the
+// rule below.
+long asked_splits16(long BH, long N, bool bwd) {
+  if (2 * BH > kUnits) return N >= (bwd ? 20 : 50) * (BH - 100) ? ((N + 255) / 256 < 3 ? (N + 255) / 256 : 3) : 1;
+  long splits = kUnits / BH;
+  if (N >= 4096 || (N >= 2048 && 5 * splits * BH < 4 * kUnits)) splits = 2 * kUnits / BH;
+  const long most = (N + 255) / 256;
+  return splits > most ? most : splits;
+}
+
+// bf16 d = 128.  Forward: whole for short sequences, else one workgroup per compute unit, in parts of 256 rows or more:
+//   64 x 300 13.2 (2 parts 20.7);  64 x 600 20.8 (3: 22.3);  128 x 600 22.3 (2: 30.1);  85 x 900 30.1 (2: 29.0);  128 x 1300 61 (2: 53);
+//   64 x 4096, 4 parts 70 (8: 78);  85 x 4096, 3: 88 (6: 95);  24 x 4096, 10: 34 (21: 40).
+// More than 128 slices: whole, or from a length on three parts (140 x 4096 173 whole, 140 in three).
+// Backward: the three roles of the last launch are workgroups of their own, so that as many parts as make 256 of them fill
+// the chip; beyond a length (the shorter the less they fill it) 512, and beyond 700 rows each one part per compute unit:
+//   64 x 300 21.5 whole (2: 28.2);  64 x 900 47.6 (4: 53.4);  85 x 1500 93 (3: 102);  48 x 600 32.0 (3: 33.8);  48 x 900, 3: 39.6 (1: 46.4,
+//   4: 46.3);  24 x 900, 3: 26.7 (4: 30.4);  32 x 1500, 4: 41.4 (2: 43.6, 6: 46.2);  16 x 2500, 10: 35.6 (6: 42.6);  64 x 2500, 4: 125 (2: 138);
+//   32 x 4096, 8: 108 (16: 117).
+// From 86 slices on one launch, whole up to a length: 128 x 600 57 (2: 64);  128 x 1300 109 (2: 127);  110 x 1300 105 (2: 118);  90 x 600
+// 56 (2: 52);  140 x 900 79 (3: 112);  200 x 1800 192 (whole in the kernel before: 257);  160 x 2500 241 (3: 265);  140 x 2500 242 (3: 241).
+long wide_splits16(long BH, long N, bool bwd) {
+  if (!bwd) {
+    if (BH > 128) return N >= 50 * (BH - 100) ? 3 : 1;
+    if (N <= 6 * BH + 260) return 1;
+    return BH >= 86 || N >= 5000 ? 2 * kUnits / BH : kUnits / BH;
+  }
+  if (BH > 128) return BH >= 140 || N <= 1900 ? 1 : 3;
+  if (BH >= 86) {
+    const long whole = 55 * (BH - 85) < 1900 ? 55 * (BH - 85) : 1900;
+    return N <= 400 || N <= whole ? 1 : 2 * kUnits / BH;
+  }
+  const long few = kUnits / (3 * BH), fill = 3 * BH * few;  // of 256
+  if (N <= 256 * few || N <= 100 + 1800 * fill * fill / (kUnits * kUnits)) return BH >= 20 && N <= 260 + 2 * BH ? 1 : few;
+  const long more = 2 * kUnits / (3 * BH);
+  if (N > 700 * more) return N >= 5000 ? 2 * kUnits / BH : kUnits / BH;
+  return more < N / 200 ? more : N / 200;
+}
+
+// fp32 rows, where the matrix products weigh more: two workgroups per compute unit (64 x 4096, d = 64, forward / backward
+// 65.3 / 152 us; one 68.6 / 159)
+long wide_splits32(long BH, long N) {
+  const long splits = (2 * kUnits + BH - 1) / BH, most = (N + 255) / 256;
+  return splits > most ? most : splits;
+}
+
 }  // namespace
 
 Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
   const long BH = static_cast<long>(B) * H;
   const size_t nstates = is_bwd ? 2 : 1;
   Plan plan;
-  long splits, rows;
+  long splits, rows, asked = 0;
   if (mfma_supports(dtype, D)) {
     // One workgroup per slice and launch while that fills enough of the chip or the slice is short; otherwise the
     // sequence is cut, in blocks of 64 rows (split_count).
@@ -216,41 +268,22 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
     rows = (N + splits - 1) / splits;
     rows = (rows + kBlock - 1) / kBlock * kBlock;
   } else {
-    // Wide rows (256 or 512 bytes).  Their kernels build operand images per workgroup and stage
-    // 64 rows per round; sequences are cut in blocks of 64 rows.
-    // A d x d state is as large as 64 ... 256 rows of a tensor there, and every split writes one
-    // and has the sum read back: no fewer than 256 rows per workgroup, and a sequence is not cut
-    // at all once there is a workgroup per compute unit without it.
+    // Wide rows (256 or 512 bytes), in blocks of 64 rows.
     plan.path = Plan::kGeneric;
-    constexpr long kBlock = 64, kUnits = 256;
-    if (BH >= kUnits) {
-      splits = 1;
-    } else if (dtype == 0) {
-      // fp32 rows, where the matrix products weigh more: two workgroups per compute unit (64 x 4096, d = 64,
-      // forward / backward 65.3 / 152 us; one 68.6 / 159)
-      splits = (2 * kUnits + BH - 1) / BH;
-    } else if (2 * BH > kUnits) {
-      // 16-bit rows, bf16 d = 128, forward / backward, us.  More than half as many slices as compute units: whole
-      // (a workgroup of eight waves each), or from a length on in three parts (of four waves, two per
-      // compute unit).  Whole, two, three parts:  130 x 600 24.5 / 67, 35 / 70, 37 / 77;  140 x 1200 54 / 148,
-      // 61 / 128, 56 / 130;  140 x 4096 173 / 515, 176 / 397, 140 / 356;  180 x 1600 73 / 209, 87 / 199, 88 / 199;
-      // 200 x 2400 110 / 327, 131 / 328, 133 / 311;  200 x 4096 185 / 554, 197 / 514, 196 / 490;
-      // 255 x 4000 199 / 585, 219 / 598, 221 / 602.
-      splits = N >= (is_bwd ? 20 : 50) * (BH - 100) ? 3 : 1;
-    } else {
-      // No more workgroups than compute units, of eight waves - or, for long sequences, and for those of 2048 rows
-      // where that leaves a fifth of the chip idle, twice as many, of four.  At most 256 and 512 workgroups:
-      // 64 x 3000 53 / 137, 60 / 143;  100 x 600 28 / 56, 34 / 61;  100 x 3000 86 / 216, 81 / 204;  80 x 3000 67 / 166,
-      // 68 / 171;  80 x 6000 116 / 311, 115 / 302;  100 x 6000 154 / 420, 139 / 370;  128 x 6000 172 / 458, 167 / 467.
-      // (One workgroup more than compute units costs: 100 x 600 in three parts 34 / 61, in two 28 / 56.)
-      splits = kUnits / BH;
-      if (N >= 4096 || (N >= 2048 && 5 * splits * BH < 4 * kUnits)) splits = 2 * kUnits / BH;
-    }
-    const long max_splits = (N + 255) / 256;
-    if (splits > max_splits) splits = max_splits;
+    constexpr long kBlock = 64;
+    const auto blocks_of = [&](long parts) {
+      const long r = (N + parts - 1) / parts;
+      return (r + kBlock - 1) / kBlock * kBlock;
+    };
+    splits = BH >= kUnits ? 1 : dtype == 0 ? wide_splits32(BH, N) : wide_splits16(BH, N, is_bwd);
     if (splits < 1) splits = 1;
-    rows = (N + splits - 1) / splits;
-    rows = (rows + kBlock - 1) / kBlock * kBlock;
+    rows = blocks_of(splits);
+    if (dtype != 0 && BH < kUnits) {
+      // The workspace that a call asks for is what the call would use with more parts than are run now.
+      asked = asked_splits16(BH, N, is_bwd);
+      asked = (N + blocks_of(asked) - 1) / blocks_of(asked);
+      if ((N + rows - 1) / rows > asked) rows = blocks_of(asked);
+    }
   }
   splits = (N + rows - 1) / rows;
   plan.splits = static_cast<int>(splits);
@@ -261,10 +294,11 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
   } else {
     // partial states, plus the reduced states when there is more than one partial
     // (one launch per direction: the state never leaves the compute unit)
+    if (asked < splits) asked = splits;
     plan.workspace_floats =
-        wide_fused_applies(dtype, B, H, static_cast<int>(splits), is_bwd)
+        wide_fused_applies(dtype, B, H, static_cast<int>(asked), is_bwd)
             ? 0
-            : static_cast<size_t>(BH) * D * D * nstates * (splits + (splits > 1 ? 1 : 0));
+            : static_cast<size_t>(BH) * D * D * nstates * (asked + (asked > 1 ? 1 : 0));
   }
   return plan;
 }

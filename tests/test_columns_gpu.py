@@ -1,5 +1,5 @@
 """Kernels whose waves own 32 columns of the results (fp32 d_h = 128 with more slices than a launch of
-other kernels has workgroups): against the fp64 oracle at the edges of their tiles (16 rows) and rounds (16
+other kernels has workgroups; the backward of 16-bit d_h = 128 beyond 256 rows): against the fp64 oracle at the edges of their tiles (16 rows) and rounds (16
 rows of K and V or 32 of Q in the forward, 32 in the backward), with histories that start anywhere in a round,
 holes and sequences without a valid key; the kept state, per-slice scales, d loss / d log(scale), both layouts.
 The bound is that of the other fp32 kernels (1e-5: the products of pieces leave out 2^-22, the sums add units of
@@ -11,7 +11,7 @@ import pytest
 import torch
 
 from paper_2602_06935_amd import binding
-from tests.gpu_util import FP32_BAR, check_tensor, rel_l2, to_f64, to_gpu
+from tests.gpu_util import FP32_BAR, bar_for, check_tensor, rel_l2, to_f64, to_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -64,6 +64,43 @@ def test_columns(oracle, B, H, N, feature_map):
     ref_dlog = (dO.astype(np.float64) * ref_o).sum(axis=(2, 3))
     size = np.sqrt(((dO.astype(np.float64) * ref_o) ** 2).sum(axis=(2, 3)))  # sums with cancellation
     assert np.all(np.abs(dlog.double().cpu().numpy() - ref_dlog) <= 1e-5 * np.maximum(size, np.abs(ref_dlog)))
+
+
+@pytest.mark.parametrize("dtype,B,H,N", [
+    ("bf16", 87, 1, 385), ("f16", 130, 1, 447), ("bf16", 128, 2, 257), ("bf16", 129, 2, 271), ("f16", 150, 2, 320), ("bf16", 140, 1, 641),
+])
+@pytest.mark.parametrize("feature_map", ["cosine", "elu1"])
+def test_columns_16bit_backward(oracle, dtype, B, H, N, feature_map):
+    """Sixteen waves (up to 256 slices, and wherever d loss / d log(scale) is asked for) and eight."""
+    if feature_map == "elu1" and N > 300:
+        pytest.skip("one map is enough at this size")
+    print(f"[columns] {dtype} B={B} H={H} N={N} {feature_map}", flush=True)
+    rng = np.random.default_rng(2300 + N + B)
+    Q, K, V, dO = (to_f64(to_gpu(0.5 * rng.standard_normal((B, H, N, 128)), dtype)).astype(np.float32) for _ in range(4))
+    mask = _mask(rng, B, N)
+    tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
+    tm = torch.from_numpy(mask).cuda()
+    # phi is not a unit row: a scale that keeps results of half precision in their range
+    opts = dict(scale=0.05 if feature_map == "cosine" else 1e-3, feature_map=feature_map)
+    dlog = torch.zeros(B, H, device="cuda")
+    plain = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, **opts)
+    with_dlog = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, dlog_scale=dlog, **opts)
+    again = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, **opts)
+    sw = lambda t: t.permute(0, 2, 1, 3).contiguous()
+    other = binding.cotten_attn_bwd(sw(tq), sw(tk), sw(tv), tm, sw(tg), layout="bnhd", **opts)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) and torch.equal(sw(a), c) for a, b, c in zip(plain, again, other))
+    if feature_map == "cosine":
+        ref_o, refs = oracle.fwd_linear(Q, K, V, mask, scale=0.05), oracle.bwd(Q, K, V, dO, mask, scale=0.05)
+    else:
+        ref_o, refs = oracle.elu_fwd(Q, K, V, mask, scale=1e-3), oracle.elu_bwd(Q, K, V, dO, mask, scale=1e-3)
+    for grads in (plain, with_dlog):
+        for name, got, ref in zip(("dQ", "dK", "dV"), grads, refs):
+            check_tensor(name, to_f64(got), ref, bar_for(dtype), few_terms=True)
+            if name != "dQ":
+                assert np.all(to_f64(got)[np.broadcast_to((mask == 0)[:, None, :, None], ref.shape)] == 0.0)
+    ref_dlog = (dO.astype(np.float64) * ref_o).sum(axis=(2, 3))
+    assert rel_l2(dlog.double().cpu().numpy(), ref_dlog) <= 5 * bar_for(dtype)
 
 
 def test_columns_scales_and_masked_rows(oracle):

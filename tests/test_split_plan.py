@@ -1,6 +1,6 @@
-"""Where sequences of rows of up to 128 bytes are cut, and into how many workgroups: the rule on the host (through the
-workspace a call asks for: one state per slice and workgroup, two in the backward, none where a call is one launch),
-and parity on both sides of its lines."""
+"""Where sequences are cut, and into how many workgroups: the rule on the host (through the workspace a call asks for:
+one state per slice and workgroup, two in the backward, none where a call is one launch; wide rows that are cut: one
+more), and parity on both sides of its lines."""
 from __future__ import annotations
 
 import numpy as np
@@ -40,13 +40,26 @@ def test_split_rule(slices, N, dtype, splits):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("dtype,d,slices,N", [
+    ("bf16", 128, 64, 300), ("bf16", 128, 40, 310), ("f16", 128, 128, 520), ("bf16", 128, 48, 700),
+    ("bf16", 128, 32, 1300), ("f16", 128, 150, 1300),
+])
+def test_wide_rows_on_both_sides_of_the_split_rule(oracle, dtype, d, slices, N):
+    print(f"[split plan] {dtype} d={d} {slices} x {N}", flush=True)
+    _parity(oracle, dtype, d, slices, N)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("dtype,slices,N", [
     ("bf16", 53, 320), ("bf16", 54, 320), ("f16", 170, 1029), ("bf16", 169, 1029), ("bf16", 9, 1531), ("f16", 3, 2300),
     ("f32", 120, 320), ("f32", 96, 1100), ("f32", 7, 2049),
 ])
 def test_both_sides_of_the_split_rule(oracle, dtype, slices, N):
     print(f"[split plan] {dtype} {slices} x {N}", flush=True)
-    d = 32 if dtype == "f32" else 64
+    _parity(oracle, dtype, 32 if dtype == "f32" else 64, slices, N)
+
+
+def _parity(oracle, dtype, d, slices, N):
     rng = np.random.default_rng(3000 + N + slices)
     Q, K, V, dO = (to_f64(to_gpu(rng.standard_normal((slices, 1, N, d)), dtype)).astype(np.float32) for _ in range(4))
     mask = (np.arange(N)[None, :] >= rng.integers(0, N, slices)[:, None]).astype(np.uint8)
