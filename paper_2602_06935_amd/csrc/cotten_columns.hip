@@ -83,14 +83,8 @@ struct Cols<F32x32> {
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) out[nt] = Bf16Elem::mfma16(w[nt].h, x.h, out[nt]);
   }
-  // a product of two operands in two steps: all but the largest of its terms, and that
-  static __device__ __forceinline__ f32x16_t mfma32_small(const Frag& a, const Frag& b, f32x16_t c) {
-    c = Bf16Elem::mfma32(a.l, b.h, c);
-    c = Bf16Elem::mfma32(a.h, b.l, c);
-    c = Bf16Elem::mfma32(a.m, b.m, c);
-    c = Bf16Elem::mfma32(a.m, b.h, c);
-    return Bf16Elem::mfma32(a.h, b.m, c);
-  }
+  // a product of two operands in two steps (see F32x32): what the second needs of an operand is its largest piece
+  static __device__ __forceinline__ f32x16_t mfma32_small(const Frag& a, const Frag& b, f32x16_t c) { return F::mfma32_small(a, b, c); }
   typedef bf16x8_t Large;
   static __device__ __forceinline__ Large large(const Frag& a) { return a.h; }
   static __device__ __forceinline__ f32x16_t mfma32_large(Large a, Large b, f32x16_t c) { return Bf16Elem::mfma32(a, b, c); }

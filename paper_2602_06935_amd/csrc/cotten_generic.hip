@@ -12,7 +12,8 @@ constexpr int kThreads = 256;
 // Sums the partial states of every slice in split order (fixed order => results do
 // not depend on scheduling).  One thread per four state elements; the loads of kAhead splits travel
 // together.  Bound by the reads of the partials, out of the memory-side cache (one float per
-// thread, one split at a time: forward of 8 slices x 3000 rows, 16-bit d = 128, 22.9 us against 20.6).
+// thread, one split at a time: forward of 8 slices x 3000 rows, 16-bit d = 128, 22.9 us against 20.6).  The splits of a
+// batch are summed before they join the sum: with one chain over 63 splits its roundings were most of the error.
 __global__ __launch_bounds__(kThreads) void reduce_states_kernel(
     const float4* __restrict__ partial, float4* __restrict__ reduced, int splits, int quads,
     size_t total) {
@@ -28,13 +29,17 @@ __global__ __launch_bounds__(kThreads) void reduce_states_kernel(
     for (int i = 0; i < kAhead; ++i)
       v[i] = p0 + i < splits ? src[static_cast<size_t>(p0 + i) * quads] : float4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i)
+    for (int i = 1; i < kAhead; ++i)
       if (p0 + i < splits) {
-        s.x += v[i].x;
-        s.y += v[i].y;
-        s.z += v[i].z;
-        s.w += v[i].w;
+        v[0].x += v[i].x;
+        v[0].y += v[i].y;
+        v[0].z += v[i].z;
+        v[0].w += v[i].w;
       }
+    s.x += v[0].x;
+    s.y += v[0].y;
+    s.z += v[0].z;
+    s.w += v[0].w;
   }
   reduced[e] = s;
 }
@@ -173,8 +178,7 @@ constexpr long kUnits = 256;  // compute units
 // summed up and read back, and two launches more; whole sequences take one launch per direction (16-bit backward over
 // fewer than 86 slices: three).  Forward / backward, us.
 
-// 16-bit rows, as many parts as bound the workspace of a call: what sequences were cut into before the
-// rule below.
+// 16-bit rows, as many parts as bound the workspace of a call: what sequences were cut into before the rule below.
 long asked_splits16(long BH, long N, bool bwd) {
   if (2 * BH > kUnits) return N >= (bwd ? 20 : 50) * (BH - 100) ? ((N + 255) / 256 < 3 ? (N + 255) / 256 : 3) : 1;
   long splits = kUnits / BH;
@@ -212,11 +216,35 @@ long wide_splits16(long BH, long N, bool bwd) {
   return more < N / 200 ? more : N / 200;
 }
 
-// fp32 rows, where the matrix products weigh more: two workgroups per compute unit (64 x 4096, d = 64, forward / backward
-// 65.3 / 152 us; one 68.6 / 159)
-long wide_splits32(long BH, long N) {
-  const long splits = (2 * kUnits + BH - 1) / BH, most = (N + 255) / 256;
-  return splits > most ? most : splits;
+// fp32 rows, one workgroup of eight waves per compute unit (d = 128), or up to three of four (d = 64).
+// d = 128:  forward 250 x 300 41.9 whole (2 parts 72);  200 x 1000 110 (2: 140);  128 x 1000, 2: 82 (4: 95);  64 x 1800, 4: 80 (8: 93);
+//   4 x 1000, 16: 20.6 (4: 33);  1 x 16000, 63: 40 (42: 49);  backward 128 x 1000 168 whole (4: 227);  250 x 600 174 (2: 246);  90 x 1800 248
+//   (6: 256);  64 x 1800, 2: 174 (7: 217);  4 x 6000, 19: 52 (32: 55);  8 x 6000, 16: 80 (10: 85);  16 x 4000, 8: 108 (5: 123, 16: 115);
+//   32 x 4000, 4: 191 (5: 200);  32 x 6000, 8: 269 (4: 278).
+// d = 64:  forward 250 x 600 38 whole (2: 45);  150 x 1800, 3: 74 (4: 81);  90 x 3500, 8: 81 (6: 90);  64 x 1800, 4: 36 (7: 37);  10 x 1000,
+//   8: 13.7 (4: 17.4);  64 x 320 16.5 (3: 15.7);  80 x 320 16.7 (3: 17.1);  64 x 4000, 8: 68 (4: 73, 9: 73);  197 x 1916, 3: 95 (2: 106);  32 x 6000, 16: 53 (24: 54,
+//   8: 56);  backward 128 x 1000 73 whole (4: 87);  250 x 600 86 (2: 109);  200 x 1800, 3: 211 (1: 220);  32 x 1000, 8: 27 (4: 29);
+//   64 x 1800, 4: 73 (7: 82);  64 x 3500, 11: 143 (4: 147);  20 x 1000, 4: 21.2 (8: 22.4);  4 x 4000, 21: 21 (32: 23);  8 x 8000, 32: 42
+//   (16: 49).
+long wide_splits32(long BH, long N, int D, bool bwd) {
+  if (N <= 256) return 1;  // (calls of this length need no workspace)
+  // workgroups per slice: one per compute unit in all, two, three, and those of a launch of three roles
+  const long one = kUnits / BH, two = 2 * kUnits / BH, three = 3 * kUnits / BH, few = BH >= 86 ? 1 : kUnits / (3 * BH);
+  // 64 rows or more each, and 256 where the partial states would be more than 48
+  const long long_parts = (N + 255) / 256, most = N <= 48 * 64 ? (N + 63) / 64 : long_parts < 48 ? 48 : long_parts;
+  const auto up_to = [](long parts, long limit) { return parts < limit ? parts : limit; };
+  if (D == 128) {
+    if (!bwd) return one == 2 && N <= 330 ? 1 : up_to(one, most);
+    if (BH >= 86) return 1;
+    return up_to(N * BH > 180000 ? one : N > 450 * few ? one / 2 : few, most);
+  }
+  if (!bwd) {
+    if (N > (one == 1 ? 1300 * BH / kUnits : 550 * one)) return up_to(one == 1 || 200 * three > 318 * two ? three : two, long_parts);
+    return N <= 200 + 2 * BH ? 1 : up_to(one, most);
+  }
+  if (N <= (BH > 128 ? 8 * BH : BH >= 86 ? 1100 + 60 * (BH - 86) : few == 1 ? 420 : 0)) return 1;
+  if (BH >= 86 || N > 600 * (N > 250 * few ? one : few)) return up_to(three, long_parts);
+  return up_to(N > 250 * few ? one : few, most);
 }
 
 }  // namespace
@@ -275,7 +303,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
       const long r = (N + parts - 1) / parts;
       return (r + kBlock - 1) / kBlock * kBlock;
     };
-    splits = BH >= kUnits ? 1 : dtype == 0 ? wide_splits32(BH, N) : wide_splits16(BH, N, is_bwd);
+    splits = BH >= kUnits ? 1 : dtype == 0 ? wide_splits32(BH, N, D, is_bwd) : wide_splits16(BH, N, is_bwd);
     if (splits < 1) splits = 1;
     rows = blocks_of(splits);
     if (dtype != 0 && BH < kUnits) {

@@ -48,25 +48,33 @@ bool mfma_supports(int dtype, int D) {
 
 int mfma_state_dim(int dtype) { return dtype == 0 ? F32x32::D : Bf16x64::D; }
 
-hipError_t launch_mfma_fwd(const Problem& p, const Plan& plan) {
-  if (p.feature_map == kMapElu1)
-    return p.dtype == 1   ? stream4::run_fwd<WithElu1<Bf16x64>>(p, plan)
-           : p.dtype == 2 ? stream4::run_fwd<WithElu1<F16x64>>(p, plan)
-                          : stream4::run_fwd<WithElu1<F32x32>>(p, plan);
-  return p.dtype == 1   ? stream4::run_fwd<Bf16x64>(p, plan)
-         : p.dtype == 2 ? stream4::run_fwd<F16x64>(p, plan)
-                        : stream4::run_fwd<F32x32>(p, plan);
+namespace {
+// fp32: states summed apart (F32x32Apart) where a call has at most a slice per compute unit, as every call that is
+// cut has, and more tiles than the registers keep.
+constexpr long kUnits = 256;
+bool sums_apart(const Problem& p, const Plan& plan, bool bwd) {
+  return plan.path == Plan::kSplit ||
+         (static_cast<long>(p.B) * p.H <= kUnits && !stream4::keeps_tiles<F32x32>(p.N, bwd));
 }
 
-hipError_t launch_mfma_bwd(const Problem& p, const Plan& plan) {
-  if (p.feature_map == kMapElu1)
-    return p.dtype == 1   ? stream4::run_bwd<WithElu1<Bf16x64>>(p, plan)
-           : p.dtype == 2 ? stream4::run_bwd<WithElu1<F16x64>>(p, plan)
-                          : stream4::run_bwd<WithElu1<F32x32>>(p, plan);
-  return p.dtype == 1   ? stream4::run_bwd<Bf16x64>(p, plan)
-         : p.dtype == 2 ? stream4::run_bwd<F16x64>(p, plan)
-                        : stream4::run_bwd<F32x32>(p, plan);
+template <class F>
+hipError_t run(const Problem& p, const Plan& plan, bool bwd) {
+  return bwd ? stream4::run_bwd<F>(p, plan) : stream4::run_fwd<F>(p, plan);
 }
+template <class F>
+hipError_t run_mapped(const Problem& p, const Plan& plan, bool bwd) {
+  return p.feature_map == kMapElu1 ? run<WithElu1<F>>(p, plan, bwd) : run<F>(p, plan, bwd);
+}
+hipError_t run_typed(const Problem& p, const Plan& plan, bool bwd) {
+  if (p.dtype == 1) return run_mapped<Bf16x64>(p, plan, bwd);
+  if (p.dtype == 2) return run_mapped<F16x64>(p, plan, bwd);
+  return sums_apart(p, plan, bwd) ? run_mapped<F32x32Apart>(p, plan, bwd) : run_mapped<F32x32>(p, plan, bwd);
+}
+}  // namespace
+
+hipError_t launch_mfma_fwd(const Problem& p, const Plan& plan) { return run_typed(p, plan, false); }
+
+hipError_t launch_mfma_bwd(const Problem& p, const Plan& plan) { return run_typed(p, plan, true); }
 
 hipError_t launch_chunk_states(const Problem& p, int chunk_tiles, int chunks, bool with_queries) {
   return p.dtype == 1   ? stream4::run_chunk_states<Bf16x64>(p, chunk_tiles, chunks, with_queries)

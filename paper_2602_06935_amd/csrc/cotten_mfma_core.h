@@ -568,6 +568,7 @@ __device__ __forceinline__ float whole_hi(uint32_t h, uint32_t m, uint32_t l) {
 
 struct F32x32 {
   typedef float io_t;
+  static constexpr bool kApart = false;
   static constexpr int kMap = 0;
   static constexpr int D = 32, EPL = 4, NT = 2, kElemBytes = 4;
   static constexpr bool kFloatRange = true, kPieces = true;
@@ -635,6 +636,19 @@ struct F32x32 {
     v = Bf16Elem::mfma32(a.h, b.m, v);
     return Bf16Elem::mfma32(a.h, b.h, v);
   }
+  // The same in two steps: all but the largest of the six products, and that one.  A sum over many tiles that takes the
+  // small ones by themselves is rounded once per tile at its own size instead of six times.  (A tile's products from zero,
+  // then added: the matrix instruction rounds off more beside a small addend, dK 1 x 16000 x 128 3.5e-7 against 1.9e-7.)
+  static __device__ __forceinline__ f32x16_t mfma32_small(const Pieces& a, const Pieces& b, f32x16_t v) {
+    v = Bf16Elem::mfma32(a.l, b.h, v);
+    v = Bf16Elem::mfma32(a.h, b.l, v);
+    v = Bf16Elem::mfma32(a.m, b.m, v);
+    v = Bf16Elem::mfma32(a.m, b.h, v);
+    return Bf16Elem::mfma32(a.h, b.m, v);
+  }
+  static __device__ __forceinline__ f32x16_t mfma32_large(const Pieces& a, const Pieces& b, f32x16_t v) {
+    return Bf16Elem::mfma32(a.h, b.h, v);
+  }
   static __device__ __forceinline__ f32x4_t mfma16(const Pieces& a, const Pieces& b, f32x4_t v) {
     v = Bf16Elem::mfma16(a.l, b.h, v);
     v = Bf16Elem::mfma16(a.h, b.l, v);
@@ -671,8 +685,10 @@ struct F32x32 {
     // += (X tile)^T (Y tile)
     __device__ __forceinline__ void mfma(const unsigned char* Xt, const unsigned char* Yt,
                                          const Lane& L) {
-      v = mfma32(rows_operand(Xt, L), rows_operand(Yt, L), v);
+      add(rows_operand(Xt, L), rows_operand(Yt, L));
     }
+    __device__ __forceinline__ void add(const Pieces& a, const Pieces& b) { v = mfma32(a, b, v); }
+    __device__ __forceinline__ void add_lean(const Pieces& a, const Pieces& b) { v = mfma32(a, b, v); }
     __device__ __forceinline__ f32x4_t group(int g) const { return quad(v, g); }
     __device__ __forceinline__ void add_group(int g, f32x4_t x) {
 #pragma unroll
@@ -852,6 +868,43 @@ struct F32x32 {
     const uint16_t* p = reinterpret_cast<const uint16_t*>(image + image_offset(n, k));
     return whole_lo(p[0], p[kPlane / 2], p[kPlane]);
   }
+};
+
+// The same rows, with states whose small products are summed apart from the large one, for the sums that run over whole
+// sequences or long parts of them (error of dK against float64, 64 slices x 3500 rows, d_h = 128: 3.7e-7 without, 2.1e-7
+// with).  Where three or more workgroups share a compute unit the registers cost time (419 slices x 736 rows, d_h = 32,
+// backward 71.1 us without, 72.7 with): those keep the plain format.
+struct F32x32Apart : F32x32 {
+  static constexpr bool kApart = true;
+  // (one tile ahead while two states' worth of accumulators are live: three waves per SIMD instead of two, split
+  // backward 90 slices x 2000 rows, d_h = 32, 48.3 -> 44.4 us)
+  static constexpr int kDepthQAccum = 1;
+  struct Acc : F32x32::Acc {
+    f32x16_t small;  // the sum of the small products
+    __device__ __forceinline__ void zero() {
+      F32x32::Acc::zero();
+#pragma unroll
+      for (int i = 0; i < 16; ++i) small[i] = 0.0f;
+    }
+    __device__ __forceinline__ void mfma(const unsigned char* Xt, const unsigned char* Yt, const Lane& L) {
+      add(rows_operand(Xt, L), rows_operand(Yt, L));
+    }
+    __device__ __forceinline__ void add(const Pieces& a, const Pieces& b) {
+      small = mfma32_small(a, b, small);
+      v = mfma32_large(a, b, v);
+    }
+    // without a second accumulator: the tile's small products first, by themselves
+    __device__ __forceinline__ void add_lean(const Pieces& a, const Pieces& b) {
+      f32x16_t t;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) t[i] = 0.0f;
+      t = mfma32_small(a, b, t);
+      v = mfma32_large(a, b, v);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) v[i] += t[i];
+    }
+    __device__ __forceinline__ f32x4_t group(int g) const { return quad(v, g) + quad(small, g); }
+  };
 };
 
 // What a format does to the rows of Q and K before they enter the products:

@@ -21,6 +21,8 @@
 //   S from (K, V), then dQ;      dS from (Q, dO), then dV and dK
 // A cut one takes three launches: partial states into the caller's workspace, their sum in split
 // order (reduce_states_kernel), apply (backward: three roles).
+#include <type_traits>
+
 #include "cotten_launch.h"
 #include "cotten_mfma_core.h"
 
@@ -200,8 +202,12 @@ __device__ __forceinline__ void walk_shared(State<F, 2>& out, const Buffers& X, 
   unsigned char* mine = smem + L.wave * Map::kPair;
   int* live_tiles = reinterpret_cast<int*>(smem + Map::kWords);
   const int left = (SWAPPED ? P + p : p) * F::kTileBytes, right = (SWAPPED ? q : P + q) * F::kTileBytes;
+  // a sum over more than eight tiles is a sum of sums over eight (two rounds of the wave's four): error of dK against
+  // float64, 100 slices x 1500 rows, 2.0e-7 as one sum
   typename F::Acc& acc = out.v[0];
+  typename F::Acc sums;
   acc.zero();
+  sums.zero();
   out.p = p;
   out.q0 = q;
   out.here = group == 0;
@@ -210,6 +216,7 @@ __device__ __forceinline__ void walk_shared(State<F, 2>& out, const Buffers& X, 
   int bits = row_bits(m, row0, end, L), next_bits = row_bits(m, row0 + kRound, end, L);
   load_half(x, L, X, stride, row0, bits);
   load_half(y, L, Y, stride, row0, bits);
+  bool odd = false;
 #pragma unroll 1
   for (int r0 = begin; r0 < end; r0 += kRound, row0 += kRound) {
     const bool live = __builtin_amdgcn_ballot_w64(bits != 0) != 0;
@@ -233,7 +240,18 @@ __device__ __forceinline__ void walk_shared(State<F, 2>& out, const Buffers& X, 
         const unsigned char* pair = smem + (4 * group + t) * Map::kPair;
         acc.mfma(pair + left, pair + right, L);
       }
+    if (F::kApart && odd) {
+#pragma unroll
+      for (int g = 0; g < F::Acc::kGroups; ++g) sums.add_group(g, acc.group(g));
+      acc.zero();
+    }
+    odd = !odd;
     __syncthreads();  // the tiles are overwritten next
+  }
+  if (F::kApart) {
+#pragma unroll
+    for (int g = 0; g < F::Acc::kGroups; ++g) sums.add_group(g, acc.group(g));
+    acc = sums;
   }
   request();
   {  // first group's sum + second group's sum
@@ -289,8 +307,8 @@ __device__ __forceinline__ void walk_private(State<F, 2>& out, const Buffers& X,
 #pragma unroll
       for (int q = 0; q < P; ++q) {
         const Pieces r = F::rows_operand(right + q * F::kTileBytes, L);
-        acc[0][q].v = F::mfma32(l0, r, acc[0][q].v);
-        acc[1][q].v = F::mfma32(l1, r, acc[1][q].v);
+        acc[0][q].add_lean(l0, r);
+        acc[1][q].add_lean(l1, r);
       }
       wave_lds_fence();
     }
@@ -425,8 +443,8 @@ __device__ __forceinline__ void walk_quadrants(State<F, 4>& out, const Buffers& 
 #pragma unroll
           for (int b = 0; b < 2; ++b) {
             const Pieces y = F::rows_operand(at + right + b * F::kTileBytes, L);
-            acc[0][b].v = F::mfma32(l0, y, acc[0][b].v);
-            acc[1][b].v = F::mfma32(l1, y, acc[1][b].v);
+            acc[0][b].add(l0, y);
+            acc[1][b].add(l1, y);
           }
         }
         if (part == 1) advance();
@@ -949,24 +967,24 @@ hipError_t run(Kind kind, const Problem& p, const Args& a, bool bwd) {
              : launch(apply_fwd_kernel<F, P, WAVES>, dim3(blocks), threads, lds, p, a);
 }
 
-template <class F, int P>
+template <bool ELU>
 hipError_t choose(Kind kind, const Problem& p, const Args& a, bool bwd) {
-  if constexpr (P == 4) {
-    return run<F, 4, 8>(kind, p, a, bwd);
-  } else {
-    // Eight waves where there is a compute unit for every workgroup (forward / backward, us, four and
-    // eight: 128 slices x 200 rows 15.8 / 20.3, 12.9 / 17.5; 8 slices 13.5 / 18.3, 10.5 / 15.1).
-    constexpr long kUnits = 256;
-    const bool few = static_cast<long>(a.slices) * a.splits * (bwd ? 2 : 1) <= kUnits;
-    return few ? run<F, 2, 8>(kind, p, a, bwd) : run<F, 2, 4>(kind, p, a, bwd);
-  }
+  typedef typename std::conditional<ELU, WithElu1<F32x32>, F32x32>::type F;
+  typedef typename std::conditional<ELU, WithElu1<F32x32Apart>, F32x32Apart>::type Apart;
+  if (p.D == 128) return run<Apart, 4, 8>(kind, p, a, bwd);
+  // Eight waves where there is a compute unit for every workgroup (forward / backward, us, four and
+  // eight: 128 slices x 200 rows 15.8 / 20.3, 12.9 / 17.5; 8 slices 13.5 / 18.3, 10.5 / 15.1).
+  constexpr long kUnits = 256;
+  const bool few = static_cast<long>(a.slices) * a.splits * (bwd ? 2 : 1) <= kUnits;
+  // Sequences, or parts of them, of more than 256 rows are summed apart.  (Shorter ones have no need, and it costs time: 4
+  // slices x 200 rows 10.6 / 14.8 plain, 11.0 / 15.2.  Nor do they where there are more slices than compute units.)
+  if (a.rows_per_split <= 256) return few ? run<F, 2, 8>(kind, p, a, bwd) : run<F, 2, 4>(kind, p, a, bwd);
+  if (few) return run<Apart, 2, 8>(kind, p, a, bwd);
+  return a.slices <= kUnits ? run<Apart, 2, 4>(kind, p, a, bwd) : run<F, 2, 4>(kind, p, a, bwd);
 }
 
 hipError_t dispatch(Kind kind, const Problem& p, const Args& a, bool bwd) {
-  typedef WithElu1<F32x32> Elu;
-  if (p.feature_map == kMapElu1)
-    return p.D == 64 ? choose<Elu, 2>(kind, p, a, bwd) : choose<Elu, 4>(kind, p, a, bwd);
-  return p.D == 64 ? choose<F32x32, 2>(kind, p, a, bwd) : choose<F32x32, 4>(kind, p, a, bwd);
+  return p.feature_map == kMapElu1 ? choose<true>(kind, p, a, bwd) : choose<false>(kind, p, a, bwd);
 }
 
 }  // namespace wide32

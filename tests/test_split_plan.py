@@ -39,9 +39,25 @@ def test_split_rule(slices, N, dtype, splits):
     assert _splits(slices, N, dtype, False) == splits
 
 
+@pytest.mark.parametrize("slices,N,d,fwd,bwd", [
+    # forward: a workgroup per compute unit; backward: as many as three roles leave room for, 256 or 384 in all
+    (1, 256, 128, 1, 1), (1, 257, 128, 5, 5), (4, 1000, 128, 16, 16), (10, 3500, 128, 19, 8), (20, 1800, 128, 10, 4), (32, 901, 128, 8, 4), (64, 300, 128, 3, 1),
+    (64, 1800, 128, 4, 2), (86, 331, 128, 2, 1), (128, 330, 128, 1, 1), (128, 2000, 128, 2, 1), (129, 256, 128, 1, 1), (255, 4000, 128, 1, 1),
+    # two pieces per row: up to three workgroups per compute unit
+    (1, 3500, 64, 28, 28), (20, 1000, 64, 8, 4), (32, 1000, 64, 8, 8), (64, 328, 64, 1, 1), (64, 420, 64, 4, 1), (64, 1800, 64, 4, 4), (90, 3500, 64, 8, 8),
+    (128, 1000, 64, 2, 1), (150, 1800, 64, 5, 5), (200, 1600, 64, 3, 1), (250, 1200, 64, 1, 1),
+])
+def test_wide_fp32_split_rule(slices, N, d, fwd, bwd):
+    for is_bwd, parts in ((False, fwd), (True, bwd)):
+        need = binding.cotten_attn_workspace_bytes(slices, 1, N, d, F32, is_bwd)
+        states = 0 if parts == 1 else (parts + 1) * (2 if is_bwd else 1)
+        assert need == slices * states * d * d * 4, (is_bwd, need / (slices * d * d * 4))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d,slices,N", [
-    ("bf16", 128, 64, 300), ("bf16", 128, 40, 310), ("f16", 128, 128, 520), ("bf16", 128, 48, 700),
+    ("f32", 128, 4, 257), ("f32", 128, 86, 340), ("f32", 128, 150, 290), ("f32", 64, 20, 333), ("f32", 64, 64, 421),
+    ("f32", 64, 150, 1300), ("f32", 64, 200, 310), ("bf16", 128, 64, 300), ("bf16", 128, 40, 310), ("f16", 128, 128, 520), ("bf16", 128, 48, 700),
     ("bf16", 128, 32, 1300), ("f16", 128, 150, 1300),
 ])
 def test_wide_rows_on_both_sides_of_the_split_rule(oracle, dtype, d, slices, N):
