@@ -21,12 +21,14 @@
 // (`apply`), its update one 32 x 32 block per wave.  What a wave needs of its own rows it loads
 // straight in the layout of the products; only the rows that other waves read go through LDS.
 //
-// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 15 / 32, where a scan on the vector
-// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 33 / 77, where 208-row
+// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 13.5 / 30.7, where a scan on the vector
+// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 29 / 75, where 208-row
 // chunks joined by states in memory took 56 / 101 (three launches, 13 * 14 / 2 tile pairs per chunk
-// instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - memory, at about 3.7 TB/s (the two roles of
-// the backward each read all they need) with one chunk of loads in flight per wave; fp32 - latency:
-// with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is.
+// instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - memory, the forward at about 4 TB/s with two chunks of loads in
+// flight per wave (with one, and the bytes of the key mask waited for before the loads of their rows, 32.4; 64 x 1001
+// rows 20.0, now 16.8), the backward at 3.8 (its two roles each read all they need) with one: it has no registers for
+// more; fp32 - latency: with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is (mask bytes
+// ahead: 32 x 2048 rows, d = 64, forward 79 -> 71.6;  1024 x 200 backward 150 -> 145;  8 x 200 backward 12.5, now 12.9).
 //
 // 16-bit results differ from those of 208-row chunks in the places where sums are rounded, by about as much
 // as either differs from a 64-bit evaluation (bf16, 256 x 1001 rows: 3e-3; from 64 bits 2.9e-3 ... 3.3e-3
@@ -102,16 +104,21 @@ struct SharedRaw {
   int live;
 };
 
-// Bit h: row row0 + r8 + 8 h exists and, if a mask is given, is a valid key.
-__device__ __forceinline__ int row_bits(const uint8_t* __restrict__ mask, int row0, int N, const Lane& L) {
-  int bits = 0;
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int row = row0 + L.r8 + 8 * h;
-    if (row < N) bits |= static_cast<int>(mask == nullptr || mask[row] != 0) << h;
+// The key mask of a sequence; without one every row of it takes part.  Its bytes are requested a chunk before the rows that
+// they decide on, and tested when those are requested: a wait for them would be one for every load before them.
+struct Keys {
+  __amdgpu_buffer_rsrc_t r;
+  int N;
+  bool all;
+  __device__ __forceinline__ Keys(const uint8_t* mask, int n)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(mask), 0, mask == nullptr ? 0 : n, 0x00020000)),
+        N(n), all(mask == nullptr) {}
+  // (rows outside the sequence lie outside the buffer: zero, no traffic)
+  __device__ __forceinline__ unsigned request(int row) const {
+    return __builtin_amdgcn_raw_buffer_load_b8(r, row, 0, 0);
   }
-  return bits;
-}
+  __device__ __forceinline__ bool test(unsigned byte, int row) const { return all ? row < N : byte != 0; }
+};
 
 template <int P>
 __device__ __forceinline__ void load_shared(SharedRaw<P>& t, const Lane& L, const Buffers& X, const Buffers& Y,
@@ -386,7 +393,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   const size_t base = a.st.slice_base(bh, a.H);
   const RowAddr addr = a.st.row;
   const uint8_t* keys = a.mask == nullptr ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * N;
-  const uint8_t* shared_mask = kUp ? keys : nullptr;
+  const Keys shared_keys(kUp ? keys : nullptr, N), own_keys(kUp ? nullptr : keys, N);
   const float scale = a.scales != nullptr ? a.scales[bh] : a.scale;
   const Buffers sx((kUp ? a.K : a.Q) + base, N, addr), sy((kUp ? a.V : a.dO) + base, N, addr);
   const Buffers ox((kUp ? a.Q : a.K) + base, N, addr), oy((ROLE == kDq ? a.dO : a.V) + base, N, addr);
@@ -426,21 +433,61 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
 
   const auto tile_of = [&](int step) { return (kUp ? begin + step : begin - step) * WAVES + wave; };
   const auto applies = [&](int step) { return kUp ? begin + step >= first : begin - step < last; };
-  const auto own_live = [&](int tile) {
-    const int row = tile * TR + L.i16;
-    return row < N && (kUp || keys == nullptr || keys[row] != 0);
+  // (the backward of fp32 rows of one piece is at the registers of four waves per SIMD: its keys are read where they
+  // are needed, 512 slices x 128 rows 18.2 us against 21.0)
+  constexpr bool kKeysAhead = ROLE == kO || F::kElemBytes == 2 || P == 2;
+  struct KeyBytes {
+    unsigned of[2];
   };
-
-  SharedRaw<P> shared;
-  OwnRaw<P> nx, ny;
-  bool next_live = false;
+  const auto request_keys = [&](int step) {
+    const int row0 = tile_of(step) * TR;
+    KeyBytes b = {{0u, 0u}};
+    if (kUp) {
+      b.of[0] = shared_keys.request(row0 + L.r8);
+      b.of[1] = shared_keys.request(row0 + L.r8 + 8);
+    } else {
+      b.of[0] = own_keys.request(row0 + L.i16);
+    }
+    return b;
+  };
+  // the rows of a chunk on their way
+  struct Ahead {
+    SharedRaw<P> shared;
+    OwnRaw<P> nx, ny;
+    bool live;
+  };
+  const auto request = [&](Ahead& t, int step, const KeyBytes& b, const Lane& L) {
+    const int row0 = tile_of(step) * TR, row = row0 + L.r8;
+    int bits = 0;
+    if (kUp) {
+      const KeyBytes k = kKeysAhead ? b : request_keys(step);
+      bits = static_cast<int>(shared_keys.test(k.of[0], row)) | static_cast<int>(shared_keys.test(k.of[1], row + 8)) << 1;
+    } else {
+      bits = static_cast<int>(row < N) | static_cast<int>(row + 8 < N) << 1;
+    }
+    load_shared<P>(t.shared, L, sx, sy, addr, row0, bits);
+    if (applies(step)) {
+      if (kUp) t.live = row0 + L.i16 < N;
+      else t.live = own_keys.test((kKeysAhead ? b : request_keys(step)).of[0], row0 + L.i16);
+      load_own<P>(t.nx, L, ox, addr, row0, t.live);
+      if (kTwoOwn) load_own<P>(t.ny, L, oy, addr, row0, t.live);
+    }
+  };
+  // The forward of 16-bit rows, which has the registers for it, keeps two chunks on their way, the others one.  (A
+  // walk of two chunks requests the second when the first has come: both at once would come together.)
+  constexpr int kAhead = ROLE == kO && F::kElemBytes == 2 ? 2 : 1;
+  const bool late = kAhead == 2 && steps == 2;
+  Ahead ahead[kAhead];
+  KeyBytes next_keys = {{0u, 0u}};
   {
-    const int row0 = tile_of(0) * TR;
-    load_shared<P>(shared, L, sx, sy, addr, row0, row_bits(shared_mask, row0, N, L));
-    if (applies(0)) {
-      next_live = own_live(tile_of(0));
-      load_own<P>(nx, L, ox, addr, row0, next_live);
-      if (kTwoOwn) load_own<P>(ny, L, oy, addr, row0, next_live);
+    KeyBytes b[kAhead];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) b[i] = kKeysAhead ? request_keys(i) : KeyBytes{{0u, 0u}};
+    if (kKeysAhead && steps > (late ? 1 : kAhead)) next_keys = request_keys(late ? 1 : kAhead);
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      ahead[i].live = false;
+      if (i == 0 || (i < steps && !late)) request(ahead[i], i, b[i], L);
     }
   }
   if (!kUp && keys != nullptr && steps > 4) {
@@ -475,9 +522,9 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
       if (ROLE != kDv) store_own<F, P>(a.dK + base, t * TR + L.i16, N, addr, L, zeros);
     }
   }
-#pragma unroll 1
-  for (int step = 0; step < steps; ++step) {
+  const auto walk = [&](int step, Ahead& now) {
     const Lane L = P == 1 ? L0.again() : L0;  // (registers: see Lane::again)
+    SharedRaw<P>& shared = now.shared;
     const bool tile_live = __builtin_amdgcn_ballot_w64(shared.live != 0) != 0;
     if (tile_live) stage_shared<F, P>(shared, L, a.eps, mine);
     if (L.lane == 0) live[wave] = tile_live;
@@ -489,18 +536,16 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
     const HalfRange range(largest);
     if (have && on_duty && applies(step)) state.write(natural, transposed, range.factor, L);
     TileRows x[P], y[P];
-    own_rows<F, P, false>(nx, x);
-    if (kTwoOwn) own_rows<F, P, true>(ny, y);
-    const bool row_live = next_live;
+    own_rows<F, P, false>(now.nx, x);
+    if (kTwoOwn) own_rows<F, P, true>(now.ny, y);
+    const bool row_live = now.live;
     const int tile = tile_of(step);
-    if (step + 1 < steps) {
-      const int row0 = tile_of(step + 1) * TR;
-      load_shared<P>(shared, L, sx, sy, addr, row0, row_bits(shared_mask, row0, N, L));
-      if (applies(step + 1)) {
-        next_live = own_live(tile_of(step + 1));
-        load_own<P>(nx, L, ox, addr, row0, next_live);
-        if (kTwoOwn) load_own<P>(ny, L, oy, addr, row0, next_live);
-      }
+    const KeyBytes bytes = next_keys;
+    if (kKeysAhead) next_keys = request_keys(step + kAhead + 1);  // (a branch here would wait: 64 x 4096 rows backward 98 -> 105)
+    if (late) {
+      if (step == 0) request(ahead[kAhead - 1], 1, bytes, L);
+    } else if (step + kAhead < steps) {
+      request(now, step + kAhead, bytes, L);
     }
     __syncthreads();
     int flags = 0;  // bit u: tile u of the chunk has rows that take part
@@ -639,6 +684,12 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
       }
     }
     __syncthreads();  // the tiles and images are written again next
+  };
+#pragma unroll 1
+  for (int step = 0; step < steps; step += kAhead) {
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+      if (i == 0 || step + i < steps) walk(step + i, ahead[i]);
   }
 }
 

@@ -174,6 +174,32 @@ def test_causal_walk(oracle, dtype, B, H, N, d):
     assert torch.equal(sw(O), O3) and all(torch.equal(sw(a), c) for a, c in zip(grads, grads3))
 
 
+@pytest.mark.parametrize("dtype,B,H,d", [("bf16", 260, 1, 64), ("f16", 130, 2, 16), ("f32", 257, 2, 32), ("f32", 130, 2, 64)])
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5])
+def test_causal_walk_of_few_chunks(oracle, dtype, B, H, d, chunks):
+    """Walks of one segment with each number of chunks on their way at the start, the last chunk of a single row or whole,
+    with a key mask and without one: forwards and backwards against the oracle on the first and last sequences."""
+    rows = 64 if dtype == "f32" else 128
+    for N in (rows * (chunks - 1) + 1, rows * chunks):
+        print(f"[causal] few chunks {dtype} B={B} H={H} N={N} d={d}", flush=True)
+        Q, K, V, dO, mask = _inputs(5200 + N + d, dtype, B, H, N, d)
+        mask[-1] = 0
+        mask[-1, N - 1:] = 1                  # the last sequence: one valid key, in the last chunk
+        tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
+        pick = [0, B - 1]
+        for m in (mask, None):
+            tm = None if m is None else torch.from_numpy(m).cuda()
+            out = (binding.cotten_attn_fwd(tq, tk, tv, tm, scale=0.2, causal=True),
+                   *binding.cotten_attn_bwd(tq, tk, tv, tm, tg, scale=0.2, causal=True))
+            few = [np.ascontiguousarray(x[pick]) for x in (Q, K, V, dO)]
+            fm = np.ones((2, N), np.uint8) if m is None else np.ascontiguousarray(m[pick])
+            ref = (oracle.causal_fwd(*few[:3], fm, scale=0.2), *oracle.causal_bwd(*few, fm, scale=0.2))
+            for n, g, r in zip(("O", "dQ", "dK", "dV"), out, ref):
+                check_tensor(n, to_f64(g[pick]), r, bar_for(dtype), few_terms=True)
+            if m is not None:
+                assert (out[2][-1, :, :N - 1] == 0).all() and (out[3][-1, :, :N - 1] == 0).all()
+
+
 def test_causal_chunks_layout_scales_workspace(oracle):
     """[B,N,H,d] layout and per-slice scales over several chunks; the caller's own workspace;
     a workspace that is too small is refused."""
