@@ -61,8 +61,8 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd);
 // is always granted the same size.
 hipError_t grant_dynamic_lds(const void* kernel, int bytes);
 
-// reduced[s][e] = partial[s][0][e] + partial[s][1][e] + ... in split order, for `slices`
-// slices of dd floats each.
+// reduced[s][e] = partial[s][0][e] + partial[s][1][e] + ... in split order, eight at a time, for
+// `slices` slices of dd floats each.
 void launch_reduce_states(const float* partial, float* reduced, int splits, int dd, size_t slices,
                           hipStream_t stream);
 
@@ -84,12 +84,12 @@ hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd);
 // The same three for fp32 rows (cotten_wide32.hip); the functions above hand over to them.
 hipError_t launch_wide32_states(const Problem& p, const Plan& plan, bool bwd);
 hipError_t launch_wide32_fused(const Problem& p, const Plan& plan, bool bwd);
-// Sequences that are not cut, every wave the owner of 32 columns of the results (cotten_columns.hip), where
-// there are slices enough for that.
-bool columns_apply(const Problem& p, bool bwd);
-hipError_t launch_columns(const Problem& p, bool bwd);
 hipError_t launch_wide32_apply(const Problem& p, const Plan& plan, const float* states,
                                const float* dstates, bool bwd);
+// Sequences that are not cut, every wave the owner of some columns of the results (cotten_columns.hip): fp32 d_h = 128 where
+// there are slices enough, the 16-bit backward of longer sequences.  launch_wide_fused hands over to it.
+bool columns_apply(const Problem& p, bool bwd);
+hipError_t launch_columns(const Problem& p, bool bwd);
 
 // MFMA path: bf16 or fp16 I/O with d_h = 64 and fp32 I/O with d_h = 32 (128-byte rows), and
 // the half-width shapes (16-bit d_h = 32, fp32 d_h = 16) zero-padded onto the same kernels.

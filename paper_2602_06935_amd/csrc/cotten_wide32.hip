@@ -16,8 +16,8 @@
 // Apply: a wave loads its own rows straight in the layout of the products (no LDS), the state is
 // read from operand images that lie over the tiles of the walk.
 //
-// A sequence that is not cut takes one launch per direction and the state never leaves the compute
-// unit; the backward has two roles, side by side on one XCD, each of which reads all four tensors:
+// A sequence that is not cut takes one launch per direction (d_h = 128: up to 256 slices, in the backward 128; more go to
+// cotten_columns.hip) and the state never leaves the compute unit; the backward has two roles, side by side on one XCD, each of which reads all four tensors:
 //   S from (K, V), then dQ;      dS from (Q, dO), then dV and dK
 // A cut one takes three launches: partial states into the caller's workspace, their sum in split
 // order (reduce_states_kernel), apply (backward: three roles).
