@@ -247,17 +247,32 @@ long wide_splits32(long BH, long N, int D, bool bwd) {
   return up_to(N > 250 * few ? one : few, most);
 }
 
+// fp32 rows: the fewest parts that a call's workspace may be sized for, those of 512 workgroups in all, of 64 rows or more
+// (wide rows: 256).  Calls used to be cut into these; what asks for more now still runs in a workspace of that size.
+long least_splits32(long BH, long N, bool wide) {
+  const long long_parts = (N + 2047) / 2048, wanted = (2 * kUnits + BH - 1) / BH;
+  const long most = wide ? (N + 255) / 256 : (N + 63) / 64;
+  const long splits = !wide && wanted < long_parts ? long_parts : wanted;
+  return splits < most ? splits : most;
+}
+
 }  // namespace
 
-Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
+Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given) {
   const long BH = static_cast<long>(B) * H;
   const size_t nstates = is_bwd ? 2 : 1;
   Plan plan;
+  constexpr long kBlock = 64;  // rows
+  const auto blocks_of = [&](long parts) {
+    const long r = (N + parts - 1) / parts;
+    return (r + kBlock - 1) / kBlock * kBlock;
+  };
+  const auto parts_of = [&](long r) { return (N + r - 1) / r; };
   long splits, rows, asked = 0;
   if (mfma_supports(dtype, D)) {
     // One workgroup per slice and launch while that fills enough of the chip or the slice is short; otherwise the
     // sequence is cut, in blocks of 64 rows (split_count).
-    constexpr long kFusedMaxN = 2048, kBlock = 64;
+    constexpr long kFusedMaxN = 2048;
     // 16-bit sequences that fit LDS go to the resident kernels - except the forward of the
     // longer ones when there are many slices, where the fused kernel that keeps its tiles in
     // registers is faster (N = 208, 512 slices: 9.6 against 10.2 us; the resident kernel wins
@@ -293,27 +308,28 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd) {
     if (splits < by_len) splits = by_len;
     const long max_splits = (N + kBlock - 1) / kBlock;
     if (splits > max_splits) splits = max_splits;
-    rows = (N + splits - 1) / splits;
-    rows = (rows + kBlock - 1) / kBlock * kBlock;
+    rows = blocks_of(splits);
   } else {
     // Wide rows (256 or 512 bytes), in blocks of 64 rows.
     plan.path = Plan::kGeneric;
-    constexpr long kBlock = 64;
-    const auto blocks_of = [&](long parts) {
-      const long r = (N + parts - 1) / parts;
-      return (r + kBlock - 1) / kBlock * kBlock;
-    };
     splits = BH >= kUnits ? 1 : dtype == 0 ? wide_splits32(BH, N, D, is_bwd) : wide_splits16(BH, N, is_bwd);
     if (splits < 1) splits = 1;
     rows = blocks_of(splits);
     if (dtype != 0 && BH < kUnits) {
       // The workspace that a call asks for is what the call would use with more parts than are run now.
       asked = asked_splits16(BH, N, is_bwd);
-      asked = (N + blocks_of(asked) - 1) / blocks_of(asked);
-      if ((N + rows - 1) / rows > asked) rows = blocks_of(asked);
+      asked = parts_of(blocks_of(asked));
+      if (parts_of(rows) > asked) rows = blocks_of(asked);
     }
   }
-  splits = (N + rows - 1) / rows;
+  if (dtype == 0) {  // a smaller workspace than is asked for: as many parts as it holds
+    const bool wide = plan.path == Plan::kGeneric;
+    const size_t side = wide ? D : mfma_state_dim(dtype), part = static_cast<size_t>(BH) * side * side * nstates;
+    const long sum = wide ? 1 : 0;  // (wide rows: and their sum)
+    const long held = given / part > static_cast<size_t>(N) ? N : static_cast<long>(given / part) - sum;
+    if (parts_of(rows) > held && held >= parts_of(blocks_of(least_splits32(BH, N, wide)))) rows = blocks_of(held);
+  }
+  splits = parts_of(rows);
   plan.splits = static_cast<int>(splits);
   plan.rows_per_split = static_cast<int>(rows);
   if (plan.path == Plan::kSplit) {

@@ -3,6 +3,8 @@ one state per slice and workgroup, two in the backward, none where a call is one
 more), and parity on both sides of its lines."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -54,6 +56,43 @@ def test_wide_fp32_split_rule(slices, N, d, fwd, bwd):
         assert need == slices * states * d * d * 4, (is_bwd, need / (slices * d * d * 4))
 
 
+# fp32 shapes that ask for more parts than 512 workgroups in all make, and those: (d, slices, N, parts)
+FEWER_PARTS = [(128, 4, 700, 3), (64, 1, 1100, 5), (128, 12, 600, 3), (64, 8, 1000, 4), (32, 81, 453, 4), (16, 81, 453, 4), (32, 129, 2050, 4)]
+
+
+def _least_bytes(d, slices, parts, is_bwd):
+    side, states = (32, parts) if d <= 32 else (d, parts + 1)
+    return slices * states * side * side * 4 * (2 if is_bwd else 1)
+
+
+@pytest.mark.parametrize("d,slices,N,parts", FEWER_PARTS)
+def test_fp32_workspace_smaller_than_asked_for(d, slices, N, parts):
+    """Refused, on the host, below the states of as many parts as make 512 workgroups."""
+    lib = binding.load_library()
+    ptrs = (0x1000, 0x2000, 0x3000, None, 0x4000, 0x5000, 0x6000, 0x7000)
+    for is_bwd in (False, True):
+        least = _least_bytes(d, slices, parts, is_bwd)
+        p = binding.CottenParams(F32, 0.0, -1.0, 0x10000, least - 4)
+        if is_bwd:
+            assert lib.cotten_attn_bwd_ex(*ptrs, slices, 1, N, d, None, ctypes.byref(p)) == -6
+        else:
+            assert lib.cotten_attn_fwd_ex(*ptrs[:5], slices, 1, N, d, None, ctypes.byref(p)) == -6
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,slices,N,parts", FEWER_PARTS)
+def test_fp32_runs_in_fewer_parts(oracle, d, slices, N, parts):
+    """What was refused above runs from that size on, and writes nothing behind it."""
+    print(f"[split plan] fewer parts d={d} {slices} x {N}", flush=True)
+    bytes_of = [_least_bytes(d, slices, parts, is_bwd) for is_bwd in (False, True)]
+    asked = [binding.cotten_attn_workspace_bytes(slices, 1, N, d, F32, is_bwd) for is_bwd in (False, True)]
+    assert any(a > b for a, b in zip(asked, bytes_of))
+    tail = 4096
+    whole = [torch.full((b + tail,), 0xA5, dtype=torch.uint8, device="cuda") for b in bytes_of]
+    _parity(oracle, "f32", d, slices, N, [w[:b] for w, b in zip(whole, bytes_of)])
+    assert all((w[b:] == 0xA5).all() for w, b in zip(whole, bytes_of))
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d,slices,N", [
     ("f32", 128, 4, 257), ("f32", 128, 86, 340), ("f32", 128, 150, 290), ("f32", 64, 20, 333), ("f32", 64, 64, 421),
@@ -75,14 +114,14 @@ def test_both_sides_of_the_split_rule(oracle, dtype, slices, N):
     _parity(oracle, dtype, 32 if dtype == "f32" else 64, slices, N)
 
 
-def _parity(oracle, dtype, d, slices, N):
+def _parity(oracle, dtype, d, slices, N, workspaces=(None, None)):
     rng = np.random.default_rng(3000 + N + slices)
     Q, K, V, dO = (to_f64(to_gpu(rng.standard_normal((slices, 1, N, d)), dtype)).astype(np.float32) for _ in range(4))
     mask = (np.arange(N)[None, :] >= rng.integers(0, N, slices)[:, None]).astype(np.uint8)
     tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
     tm = torch.from_numpy(mask).cuda()
-    O = binding.cotten_attn_fwd(tq, tk, tv, tm)
-    grads = binding.cotten_attn_bwd(tq, tk, tv, tm, tg)
+    O = binding.cotten_attn_fwd(tq, tk, tv, tm, workspace=workspaces[0])
+    grads = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, workspace=workspaces[1])
     torch.cuda.synchronize()
     refs = (oracle.fwd_linear(Q, K, V, mask), *oracle.bwd(Q, K, V, dO, mask))
     for name, got, ref in zip(("O", "dQ", "dK", "dV"), (O, *grads), refs):
