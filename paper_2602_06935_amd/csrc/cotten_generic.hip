@@ -178,17 +178,12 @@ constexpr long kUnits = 256;  // compute units
 // summed up and read back, and two launches more; whole sequences take one launch per direction (16-bit backward over
 // fewer than 86 slices: three).  Forward / backward, us.
 
-// 16-bit rows, as many parts as bound the workspace of a call: what sequences were cut into before the rule below.
-long asked_splits16(long BH, long N, bool bwd) {
-  if (2 * BH > kUnits) return N >= (bwd ? 20 : 50) * (BH - 100) ? ((N + 255) / 256 < 3 ? (N + 255) / 256 : 3) : 1;
-  long splits = kUnits / BH;
-  if (N >= 4096 || (N >= 2048 && 5 * splits * BH < 4 * kUnits)) splits = 2 * kUnits / BH;
-  const long most = (N + 255) / 256;
-  return splits > most ? most : splits;
-}
-
-// bf16 d = 128.  Forward: whole for short sequences, else one workgroup per compute unit, in parts of 256 rows or more:
-//   64 x 300 13.2 (2 parts 20.7);  64 x 600 20.8 (3: 22.3);  128 x 600 22.3 (2: 30.1);  85 x 900 30.1 (2: 29.0);  128 x 1300 61 (2: 53);
+// bf16 d = 128.  Up to 128 slices: parts of 256 rows or more, one workgroup per compute unit, two for sequences of 4096 rows, and
+// of 2048 where one leaves a fifth of the chip idle:
+//   100 x 600 28 / 56 (3 parts, more workgroups than units: 34 / 61);  100 x 3000, 5: 81 / 204 (2: 86 / 216);  64 x 3000, 4: 53 / 137
+//   (8: 60 / 143);  128 x 6000, 4: 167 / 467 (2: 172 / 458).
+// Forward: whole for short sequences:
+//   64 x 300 13.2 (2 parts 20.7);  64 x 600 20.8 (3: 22.3);  128 x 600 22.3 (2: 30.1);  85 x 800, 3: 28.4 (1: 29.7, 2: 28.8);  128 x 1300 61 (2: 53);
 //   64 x 4096, 4 parts 70 (8: 78);  85 x 4096, 3: 88 (6: 95);  24 x 4096, 10: 34 (21: 40).
 // More than 128 slices: whole, or from a length on three parts (140 x 4096 173 whole, 140 in three).
 // Backward: the three roles of the last launch are workgroups of their own, so that as many parts as make 256 of them fill
@@ -199,21 +194,31 @@ long asked_splits16(long BH, long N, bool bwd) {
 // From 86 slices on one launch, whole up to a length: 128 x 600 57 (2: 64);  128 x 1300 109 (2: 127);  110 x 1300 105 (2: 118);  90 x 600
 // 56 (2: 52);  140 x 900 79 (3: 112);  200 x 1800 192 (whole in the kernel before: 257);  160 x 2500 241 (3: 265);  140 x 2500 242 (3: 241).
 long wide_splits16(long BH, long N, bool bwd) {
-  if (!bwd) {
-    if (BH > 128) return N >= 50 * (BH - 100) ? 3 : 1;
-    if (N <= 6 * BH + 260) return 1;
-    return BH >= 86 || N >= 5000 ? 2 * kUnits / BH : kUnits / BH;
+  if (BH > 128) {
+    if (bwd) return BH >= 140 || N <= 1900 ? 1 : 3;
+    return N >= 50 * (BH - 100) ? 3 : 1;
   }
-  if (BH > 128) return BH >= 140 || N <= 1900 ? 1 : 3;
+  const long one = kUnits / BH, two = 2 * kUnits / BH;
+  const bool crowded = N >= 4096 || (N >= 2048 && 5 * one * BH < 4 * kUnits);
+  const long long_parts = (N + 255) / 256, most = (crowded ? two : one) < long_parts ? (crowded ? two : one) : long_parts;
+  if (!bwd) {
+    if (N <= 6 * BH + 260) return 1;
+    return BH >= 86 || N >= 5000 || one > most ? most : one;
+  }
   if (BH >= 86) {
     const long whole = 55 * (BH - 85) < 1900 ? 55 * (BH - 85) : 1900;
-    return N <= 400 || N <= whole ? 1 : 2 * kUnits / BH;
+    return N <= 400 || N <= whole ? 1 : most;
   }
   const long few = kUnits / (3 * BH), fill = 3 * BH * few;  // of 256
-  if (N <= 256 * few || N <= 100 + 1800 * fill * fill / (kUnits * kUnits)) return BH >= 20 && N <= 260 + 2 * BH ? 1 : few;
-  const long more = 2 * kUnits / (3 * BH);
-  if (N > 700 * more) return N >= 5000 ? 2 * kUnits / BH : kUnits / BH;
-  return more < N / 200 ? more : N / 200;
+  long parts;
+  if (N <= 256 * few || N <= 100 + 1800 * fill * fill / (kUnits * kUnits)) {
+    parts = BH >= 20 && N <= 260 + 2 * BH ? 1 : few;
+  } else {
+    const long more = 2 * kUnits / (3 * BH);
+    if (N > 700 * more) parts = N >= 5000 ? two : one;
+    else parts = more < N / 200 ? more : N / 200;
+  }
+  return parts < most ? parts : most;
 }
 
 // fp32 rows, one workgroup of eight waves per compute unit (d = 128), or up to three of four (d = 64).
@@ -268,7 +273,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
     return (r + kBlock - 1) / kBlock * kBlock;
   };
   const auto parts_of = [&](long r) { return (N + r - 1) / r; };
-  long splits, rows, asked = 0;
+  long splits, rows;
   if (mfma_supports(dtype, D)) {
     // One workgroup per slice and launch while that fills enough of the chip or the slice is short; otherwise the
     // sequence is cut, in blocks of 64 rows (split_count).
@@ -315,12 +320,6 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
     splits = BH >= kUnits ? 1 : dtype == 0 ? wide_splits32(BH, N, D, is_bwd) : wide_splits16(BH, N, is_bwd);
     if (splits < 1) splits = 1;
     rows = blocks_of(splits);
-    if (dtype != 0 && BH < kUnits) {
-      // The workspace that a call asks for is what the call would use with more parts than are run now.
-      asked = asked_splits16(BH, N, is_bwd);
-      asked = parts_of(blocks_of(asked));
-      if (parts_of(rows) > asked) rows = blocks_of(asked);
-    }
   }
   if (dtype == 0) {  // a smaller workspace than is asked for: as many parts as it holds
     const bool wide = plan.path == Plan::kGeneric;
@@ -338,11 +337,10 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
   } else {
     // partial states, plus the reduced states when there is more than one partial
     // (one launch per direction: the state never leaves the compute unit)
-    if (asked < splits) asked = splits;
     plan.workspace_floats =
-        wide_fused_applies(dtype, B, H, static_cast<int>(asked), is_bwd)
+        wide_fused_applies(dtype, B, H, static_cast<int>(splits), is_bwd)
             ? 0
-            : static_cast<size_t>(BH) * D * D * nstates * (asked + (asked > 1 ? 1 : 0));
+            : static_cast<size_t>(BH) * D * D * nstates * (splits + (splits > 1 ? 1 : 0));
   }
   return plan;
 }

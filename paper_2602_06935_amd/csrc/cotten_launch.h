@@ -41,7 +41,7 @@ struct Problem {
 //                          or partial states, reduction and apply via the workspace
 //   splits      : workgroups per slice in the state-reduction kernel; each reduces
 //                 `rows_per_split` consecutive rows to one partial d x d state
-//   workspace   : floats.  kGeneric: partial states [nstates][B*H*splits][D*D], followed, when
+//   workspace   : floats, 0 where a call is one launch.  kGeneric: partial states [nstates][B*H*splits][D*D], followed, when
 //                 splits > 1, by the reduced states [nstates][B*H][D*D].  kSplit: partial
 //                 states [nstates][B*H][splits][D*D]; every consumer workgroup sums the
 //                 partials of its slice itself, in split order
@@ -79,8 +79,8 @@ bool wide_supports(int dtype, int D);
 hipError_t launch_wide_states(const Problem& p, const Plan& plan, bool bwd);
 hipError_t launch_wide_apply(const Problem& p, const Plan& plan, const float* states,
                              const float* dstates, bool bwd);
-// Sequences that are not cut (wide_fused_applies): one launch per direction, the state stays in
-// LDS, no workspace; the forward writes p.saved_state, the backward p.dlog_scale, when given.
+// Sequences that are not cut (wide_fused_applies): one launch per direction and no workspace, the state stays
+// on the compute unit; the forward writes p.saved_state, the backward p.dlog_scale, when given.
 bool wide_fused_applies(int dtype, int B, int H, int splits, bool bwd);
 hipError_t launch_wide_fused(const Problem& p, const Plan& plan, bool bwd);
 // The same three for fp32 rows (cotten_wide32.hip); the functions above hand over to them.

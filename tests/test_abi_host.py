@@ -122,19 +122,29 @@ def test_workspace_rules(lib):
 
 
 @pytest.mark.parametrize("slices,N,fwd,bwd", [
-    (256, 8192, 1, 1), (255, 3099, 1, 1), (255, 3100, 1, 3), (255, 7749, 1, 3), (255, 7750, 3, 3),
-    (129, 579, 1, 1), (129, 580, 1, 3), (129, 1449, 1, 3), (129, 1450, 3, 3),
-    (128, 600, 2, 2), (128, 4095, 2, 2), (128, 4096, 4, 4),        # whole or in parts of at least 256 rows
-    (100, 2047, 2, 2), (100, 2048, 5, 5), (103, 2048, 2, 2), (85, 512, 2, 2), (64, 1100, 4, 4), (1, 600, 3, 3),
+    (256, 8192, 1, 1), (255, 7749, 1, 1), (255, 7750, 3, 1), (140, 1999, 1, 1), (140, 2000, 3, 1),
+    (139, 1900, 1, 1), (139, 1901, 1, 3), (129, 1449, 1, 1), (129, 1450, 3, 1),
+    (128, 1028, 1, 1), (128, 1029, 2, 1), (128, 1901, 2, 2), (128, 4095, 2, 2), (128, 4096, 4, 4),
+    (100, 400, 1, 1), (100, 860, 1, 2), (100, 2047, 2, 2), (100, 2048, 5, 5), (103, 2048, 2, 2),
+    (85, 770, 1, 1), (85, 771, 3, 1), (64, 1400, 4, 2), (64, 1401, 4, 4), (46, 2100, 5, 3), (46, 2101, 5, 5),
+    (20, 300, 1, 1), (20, 301, 1, 2), (7, 582, 3, 3), (1, 270, 2, 2), (1, 600, 3, 3),
 ])
 def test_wide_row_splits(lib, slices, N, fwd, bwd):
     """Into how many parts the sequences of 16-bit d_h = 128 rows are cut, as their workspaces tell: one d x d
-    state (backward: two) per part, and the sum of more than one."""
+    state (backward: two) per part, and the sum of more than one; none where a call is one launch (a whole sequence, in the
+    backward from 86 slices on)."""
     for is_bwd, parts in ((False, fwd), (True, bwd)):
-        states = 0 if parts == 1 else (parts + 1) * (2 if is_bwd else 1)
+        one_launch = parts == 1 and (slices >= 86 or not is_bwd)
+        states = 0 if one_launch else (parts + (parts > 1)) * (2 if is_bwd else 1)
         for dtype in (binding.COTTEN_BF16, binding.COTTEN_F16):
             assert binding.cotten_attn_workspace_bytes(slices, 1, N, 128, dtype, is_bwd) == \
                 slices * states * 128 * 128 * 4, (is_bwd, parts)
+
+
+def test_wide_rows_in_one_launch_need_no_workspace(lib):
+    """Nor does cotten_attn_bwd_static refuse them: 255 x 4092 rows of 16-bit d_h = 128 are one launch."""
+    for slices, N, is_bwd in ((255, 4092, True), (128, 1024, False), (140, 4096, True)):
+        assert binding.cotten_attn_workspace_bytes(slices, 1, N, 128, binding.COTTEN_BF16, is_bwd) == 0
 
 
 def test_causal_workspace_rules(lib):
