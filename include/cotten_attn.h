@@ -58,13 +58,18 @@
  * Workspace.  Long sequences are split over several workgroups per slice; the
  * partial d_h x d_h states travel through a workspace of
  * cotten_attn_workspace_bytes(...) bytes (0 when a shape needs none: every
- * sequence of at most 256 rows, and longer ones when B*H fills the device).  The
+ * sequence of at most 256 rows, except in the backward over fewer than 86 slices of
+ * 16-bit d_h = 128, and longer ones when B*H fills the device).  The size of a shape may
+ * change from one version of the library to the next: ask for it.  The
  * library never allocates, frees or synchronises: the caller brings the
  * workspace through cotten_params (its contents need no initialisation and mean
  * nothing afterwards; calls that share one must be ordered on one stream).  A
  * call whose shape needs a workspace and has none - params->workspace NULL, or
  * one of the plain entry points, which carry no params - returns
- * COTTEN_ERR_WORKSPACE_TOO_SMALL and enqueues nothing.
+ * COTTEN_ERR_WORKSPACE_TOO_SMALL and enqueues nothing.  fp32 calls also run, slower, in less
+ * than they ask for: cut into as many parts as the workspace holds the states of, two
+ * or more (results agree to fp32 rounding of the states), and, where about a third of the
+ * compute units or more work on uncut sequences, whole without one.
  *
  * Errors.  Every entry point returns a cotten_status; 0 is success, negative
  * values are listed below.  Argument validation happens on the host before any
@@ -118,7 +123,8 @@ typedef enum cotten_status {
   COTTEN_ERR_BAD_DTYPE = -4,            /* dtype is not a cotten_dtype                  */
   COTTEN_ERR_MISALIGNED = -5,           /* a tensor or workspace pointer not 16-B aligned */
   COTTEN_ERR_WORKSPACE_TOO_SMALL = -6,  /* the shape needs a workspace and params->workspace is
-                                           NULL or params->workspace_bytes is too small  */
+                                           NULL or params->workspace_bytes is too small
+                                           (see Workspace, above)                        */
   COTTEN_ERR_BAD_PARAM = -7,            /* params->scale or params->eps is NaN or Inf, or
                                            an option combination that is not available   */
   COTTEN_ERR_LAUNCH = -8,               /* the HIP runtime refused a launch             */
@@ -188,14 +194,14 @@ int cotten_attn_bwd_ex(const void* Q, const void* K, const void* V, const uint8_
 
 /* For callers that cannot allocate device memory and so cannot bring a workspace: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The same
- * operation, arguments and results (bit for bit) as cotten_attn_bwd_ex, except that the
- * partial states of long sequences go through a scratch array that is part of the library
+ * operation, arguments and results (bit for bit) as cotten_attn_bwd_ex with a workspace of
+ * COTTEN_STATIC_SCRATCH_BYTES, except that the partial states of long sequences go through a scratch array that is part of the library
  * image (a file-scope __device__ array of COTTEN_STATIC_SCRATCH_BYTES bytes; every GPU the
  * library runs on holds its own copy until the process ends) instead of params->workspace,
  * which is ignored together with params->workspace_bytes.  The call allocates, frees and
  * synchronises nothing.  A call that needs more scratch than the array holds
- * (cotten_attn_workspace_bytes(..., is_bwd = 1) > COTTEN_STATIC_SCRATCH_BYTES) returns
- * COTTEN_ERR_STATIC_SCRATCH and enqueues nothing; 32 MiB covers, for instance, 64 slices of
+ * (cotten_attn_workspace_bytes(..., is_bwd = 1) > COTTEN_STATIC_SCRATCH_BYTES; fp32: than it
+ * also runs in, see Workspace) returns COTTEN_ERR_STATIC_SCRATCH and enqueues nothing; 32 MiB covers, for instance, 64 slices of
  * 4096 rows at d_h = 64 (16 MiB) and every shape that needs no workspace at all.  All calls on
  * one GPU share that GPU's array, which keeps the last call's contents (every element a
  * call reads it has written before, so nothing needs clearing): calls on the same GPU must be
@@ -218,7 +224,7 @@ int cotten_normaliser_fwd(const float* m, const int32_t* n, float* slice_scale, 
 int cotten_normaliser_bwd(const float* dlog_scale, const int32_t* n, float* dm, int B, int H,
                           int N, void* stream);
 
-/* Bytes of workspace the given call would use (pure host arithmetic; 0 for an
+/* Bytes of workspace the given call would use if it has them (pure host arithmetic; 0 for an
  * unsupported shape).  Grows like B*H*d_h^2 times the number of sequence splits,
  * never like N*d_h or N^2: the method keeps only the d_h x d_h state ("Memory and
  * Compute Complexity"). */

@@ -119,7 +119,9 @@ int run(bool bwd, const void* Q, const void* K, const void* V, const uint8_t* ma
   cotten::Plan plan{};
   if (!causal)
     plan = cotten::make_plan(B, H, N, d_h, prm->dtype, bwd,
-                             use_static_scratch || prm->workspace == nullptr ? SIZE_MAX : prm->workspace_bytes / sizeof(float));
+                             (use_static_scratch          ? COTTEN_STATIC_SCRATCH_BYTES
+                              : prm->workspace != nullptr ? prm->workspace_bytes
+                                                          : 0) / sizeof(float));
   const size_t need = sizeof(float) * (causal ? cotten::causal_workspace_floats(B, H, N, d_h, prm->dtype, bwd)
                                               : plan.workspace_floats);
   if (use_static_scratch) {

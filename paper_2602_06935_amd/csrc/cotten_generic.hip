@@ -226,6 +226,12 @@ long wide_splits16(long BH, long N, bool bwd) {
 //   4 x 1000, 16: 20.6 (4: 33);  1 x 16000, 63: 40 (42: 49);  backward 128 x 1000 168 whole (4: 227);  250 x 600 174 (2: 246);  90 x 1800 248
 //   (6: 256);  64 x 1800, 2: 174 (7: 217);  4 x 6000, 19: 52 (32: 55);  8 x 6000, 16: 80 (10: 85);  16 x 4000, 8: 108 (5: 123, 16: 115);
 //   32 x 4000, 4: 191 (5: 200);  32 x 6000, 8: 269 (4: 278).
+//   More than half as many slices as compute units, beyond a length, and other counts that leave much of the chip idle (whole or in few parts):
+//   forward 129 x 1700, 3: 145 (1: 167, 4: 153);  150 x 3000, 3: 242 (1: 285);  170 x 4096, 3: 334 (1: 384);  180 x 1700 171 (3: 186);
+//   92 x 2500, 5: 137 (2: 160);  100 x 4096, 5: 208 (2: 223);  backward 129 x 950, 3: 195 (1: 228);  129 x 3000, 3: 498 (1: 709);  150 x 1150,
+//   3: 249 (1: 266);  170 x 3000, 3: 625 (1: 733);  180 x 2040, 3: 469 (1: 500);  192 x 1700 424 (3: 428);  92 x 3000, 5: 365 (1: 392);
+//   100 x 2040 267 (5: 285);  72 x 1700, 3: 183 (1: 218);  85 x 950 128 (3: 132);  85 x 1400, 3: 179 (1: 189);  46 x 330, 2: 47.6 (1: 51.3);
+//   58 x 400 56.5 (2: 57.2);  46 x 1700, 5: 129 (2: 138);  58 x 2500, 4: 213 (2: 224);  64 x 1700, 2: 160 (4: 168);  36 x 3000, 7: 162 (3: 180).
 // d = 64:  forward 250 x 600 38 whole (2: 45);  150 x 1800, 3: 74 (4: 81);  90 x 3500, 8: 81 (6: 90);  64 x 1800, 4: 36 (7: 37);  10 x 1000,
 //   8: 13.7 (4: 17.4);  64 x 320 16.5 (3: 15.7);  80 x 320 16.7 (3: 17.1);  64 x 4000, 8: 68 (4: 73, 9: 73);  197 x 1916, 3: 95 (2: 106);  32 x 6000, 16: 53 (24: 54,
 //   8: 56);  backward 128 x 1000 73 whole (4: 87);  250 x 600 86 (2: 109);  200 x 1800, 3: 211 (1: 220);  32 x 1000, 8: 27 (4: 29);
@@ -239,9 +245,15 @@ long wide_splits32(long BH, long N, int D, bool bwd) {
   const long long_parts = (N + 255) / 256, most = N <= 48 * 64 ? (N + 63) / 64 : long_parts < 48 ? 48 : long_parts;
   const auto up_to = [](long parts, long limit) { return parts < limit ? parts : limit; };
   if (D == 128) {
-    if (!bwd) return one == 2 && N <= 330 ? 1 : up_to(one, most);
-    if (BH >= 86) return 1;
-    return up_to(N * BH > 180000 ? one : N > 450 * few ? one / 2 : few, most);
+    if (!bwd) {
+      if (BH > 128) return BH <= 170 && N > 1400 ? 3 : 1;
+      return one == 2 && N <= 330 ? 1 : up_to(two == 5 && N > 2000 ? two : one, most);
+    }
+    if (BH > 128) return BH <= 192 && N > 700 + 12 * (BH - 129) ? 3 : 1;
+    if (BH >= 86) return two == 5 && N > 125 * BH - 9100 ? two : 1;
+    if (BH > 64) return N > 1000 ? one : 1;
+    if (BH > 42) return N > 100 * BH - 3500 ? one : N > (BH <= 56 ? 300 : 450) ? 2 : 1;
+    return up_to(N * BH > 180000 || (BH > 32 && N > 2400) ? one : N > 450 * few ? one / 2 : few, most);
   }
   if (!bwd) {
     if (N > (one == 1 ? 1300 * BH / kUnits : 550 * one)) return up_to(one == 1 || 200 * three > 318 * two ? three : two, long_parts);
@@ -252,13 +264,11 @@ long wide_splits32(long BH, long N, int D, bool bwd) {
   return up_to(N > 250 * few ? one : few, most);
 }
 
-// fp32 rows: the fewest parts that a call's workspace may be sized for, those of 512 workgroups in all, of 64 rows or more
-// (wide rows: 256).  Calls used to be cut into these; what asks for more now still runs in a workspace of that size.
-long least_splits32(long BH, long N, bool wide) {
-  const long long_parts = (N + 2047) / 2048, wanted = (2 * kUnits + BH - 1) / BH;
-  const long most = wide ? (N + 255) / 256 : (N + 63) / 64;
-  const long splits = !wide && wanted < long_parts ? long_parts : wanted;
-  return splits < most ? splits : most;
+// fp32 rows: calls that are cut for speed but run whole, in one launch, where there is no workspace.
+bool whole_without_workspace32(long BH, long N, int D, bool bwd) {
+  if (D < 128) return false;
+  if (!bwd) return BH > 128;
+  return BH > 85 || (BH > 64 ? N * BH <= 180000 : BH > 42 && N <= 450);
 }
 
 }  // namespace
@@ -267,7 +277,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
   const long BH = static_cast<long>(B) * H;
   const size_t nstates = is_bwd ? 2 : 1;
   Plan plan;
-  constexpr long kBlock = 64;  // rows
+  constexpr long kBlock = 64, kMostRows = 2048;  // of a workgroup, up to 128 bytes each: their key flags
   const auto blocks_of = [&](long parts) {
     const long r = (N + parts - 1) / parts;
     return (r + kBlock - 1) / kBlock * kBlock;
@@ -277,7 +287,6 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
   if (mfma_supports(dtype, D)) {
     // One workgroup per slice and launch while that fills enough of the chip or the slice is short; otherwise the
     // sequence is cut, in blocks of 64 rows (split_count).
-    constexpr long kFusedMaxN = 2048;
     // 16-bit sequences that fit LDS go to the resident kernels - except the forward of the
     // longer ones when there are many slices, where the fused kernel that keeps its tiles in
     // registers is faster (N = 208, 512 slices: 9.6 against 10.2 us; the resident kernel wins
@@ -300,7 +309,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
     // 54 / 111.  fp32 d = 32: 100 x 260 10.4 / 19.3, 10.4 / 18.6;  130 x 320 10.8 / 20.3, 11.5 / 21.1;  160 x 420 13.8 / 26.0, 13.4 /
     // 26.4;  200 x 600 19.0 / 35.0, 18.6 / 36.1;  250 x 600 20.1 / 36.9, 20.5 / 41.7;  250 x 900 27.5 / 55.9, 26.5 / 55.0.
     const long enough = dtype != 0 ? (N / 5 - 10 < 170 ? N / 5 - 10 : 170) : (N / 4 + 40 < 256 ? N / 4 + 40 : 256);
-    if ((N <= kFusedMaxN && (BH >= enough || N <= 256)) || fused_long) {
+    if ((N <= kMostRows && (BH >= enough || N <= 256)) || fused_long) {
       plan.path = Plan::kFused;
       plan.splits = 1;
       plan.rows_per_split = N;
@@ -309,7 +318,7 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
     }
     plan.path = Plan::kSplit;
     splits = split_count(BH, N, dtype);
-    const long by_len = (N + kFusedMaxN - 1) / kFusedMaxN;
+    const long by_len = (N + kMostRows - 1) / kMostRows;
     if (splits < by_len) splits = by_len;
     const long max_splits = (N + kBlock - 1) / kBlock;
     if (splits > max_splits) splits = max_splits;
@@ -321,12 +330,16 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
     if (splits < 1) splits = 1;
     rows = blocks_of(splits);
   }
-  if (dtype == 0) {  // a smaller workspace than is asked for: as many parts as it holds
+  if (dtype == 0 && parts_of(rows) > 1) {  // a smaller workspace than is asked for: as many parts as it holds
     const bool wide = plan.path == Plan::kGeneric;
     const size_t side = wide ? D : mfma_state_dim(dtype), part = static_cast<size_t>(BH) * side * side * nstates;
     const long sum = wide ? 1 : 0;  // (wide rows: and their sum)
     const long held = given / part > static_cast<size_t>(N) ? N : static_cast<long>(given / part) - sum;
-    if (parts_of(rows) > held && held >= parts_of(blocks_of(least_splits32(BH, N, wide)))) rows = blocks_of(held);
+    const long least = wide || N <= 2 * kMostRows ? 2 : parts_of(kMostRows);
+    if (parts_of(rows) > held) {
+      if (held >= least) rows = blocks_of(held);
+      else if (whole_without_workspace32(BH, N, D, is_bwd)) rows = blocks_of(1);
+    }
   }
   splits = parts_of(rows);
   plan.splits = static_cast<int>(splits);

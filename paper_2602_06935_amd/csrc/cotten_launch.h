@@ -53,8 +53,8 @@ struct Plan {
   size_t workspace_floats;
 };
 
-// `given`: floats of the workspace that there is (without it: what the call asks for).  fp32 calls are cut into fewer parts
-// where it is smaller, down to a size from which on a call is refused (workspace_floats > given).
+// `given`: floats of the workspace that there is (without it: what the call asks for).  fp32 calls are cut into fewer parts where
+// it is smaller, some of them run whole without one; where neither can be, workspace_floats > given.
 Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given = SIZE_MAX);
 
 // Grants `kernel` `bytes` of dynamic LDS (kernels that use more than 64 KB must be granted it

@@ -44,6 +44,9 @@ def test_split_rule(slices, N, dtype, splits):
 @pytest.mark.parametrize("slices,N,d,fwd,bwd", [
     # forward: a workgroup per compute unit; backward: as many as three roles leave room for, 256 or 384 in all
     (1, 256, 128, 1, 1), (1, 257, 128, 5, 5), (4, 1000, 128, 16, 16), (10, 3500, 128, 19, 8), (20, 1800, 128, 10, 4), (32, 901, 128, 8, 4), (64, 300, 128, 3, 1),
+    (46, 300, 128, 5, 1), (46, 301, 128, 5, 2), (46, 1101, 128, 5, 5), (56, 301, 128, 3, 2), (57, 450, 128, 4, 1), (36, 2400, 128, 7, 3), (36, 2401, 128, 7, 7),
+    (72, 1000, 128, 3, 1), (72, 1001, 128, 3, 3), (92, 2000, 128, 2, 1), (92, 2401, 128, 5, 5), (103, 4000, 128, 2, 1),
+    (129, 700, 128, 1, 1), (129, 701, 128, 1, 3), (170, 1400, 128, 1, 3), (170, 1401, 128, 3, 3), (171, 1401, 128, 1, 3), (193, 4000, 128, 1, 1),
     (64, 1800, 128, 4, 2), (86, 331, 128, 2, 1), (128, 330, 128, 1, 1), (128, 2000, 128, 2, 1), (129, 256, 128, 1, 1), (255, 4000, 128, 1, 1),
     # two pieces per row: up to three workgroups per compute unit
     (1, 3500, 64, 28, 28), (20, 1000, 64, 8, 4), (32, 1000, 64, 8, 8), (64, 328, 64, 1, 1), (64, 420, 64, 4, 1), (64, 1800, 64, 4, 4), (90, 3500, 64, 8, 8),
@@ -56,46 +59,63 @@ def test_wide_fp32_split_rule(slices, N, d, fwd, bwd):
         assert need == slices * states * d * d * 4, (is_bwd, need / (slices * d * d * 4))
 
 
-# fp32 shapes that ask for more parts than 512 workgroups in all make, and those: (d, slices, N, parts)
-FEWER_PARTS = [(128, 4, 700, 3), (64, 1, 1100, 5), (128, 12, 600, 3), (64, 8, 1000, 4), (32, 81, 453, 4), (16, 81, 453, 4), (32, 129, 2050, 4)]
+# fp32 shapes that are cut in both directions, and a number of parts that they also run in: (d, slices, N, fewest, parts)
+FEWER_PARTS = [(128, 4, 700, 2, 3), (64, 1, 1100, 2, 5), (128, 12, 600, 2, 3), (64, 8, 1000, 2, 4), (32, 81, 453, 2, 4), (16, 81, 453, 2, 3),
+               (32, 129, 4100, 3, 4)]
+# shapes that are cut where there is a workspace and run whole without one: (d, slices, N, fwd, bwd)
+WHOLE_WITHOUT = [(128, 129, 1401, 3, 3), (128, 192, 1457, 1, 3), (128, 170, 1401, 3, 3)]
 
 
-def _least_bytes(d, slices, parts, is_bwd):
+def _bytes(d, slices, parts, is_bwd):
     side, states = (32, parts) if d <= 32 else (d, parts + 1)
     return slices * states * side * side * 4 * (2 if is_bwd else 1)
 
 
-@pytest.mark.parametrize("d,slices,N,parts", FEWER_PARTS)
-def test_fp32_workspace_smaller_than_asked_for(d, slices, N, parts):
-    """Refused, on the host, below the states of as many parts as make 512 workgroups."""
+@pytest.mark.parametrize("d,slices,N,fewest,parts", FEWER_PARTS)
+def test_fp32_workspace_smaller_than_asked_for(d, slices, N, fewest, parts):
+    """Refused, on the host, below the states of two parts (of rows of 128 bytes: of parts of 2048 rows), and without one."""
     lib = binding.load_library()
     ptrs = (0x1000, 0x2000, 0x3000, None, 0x4000, 0x5000, 0x6000, 0x7000)
     for is_bwd in (False, True):
-        least = _least_bytes(d, slices, parts, is_bwd)
-        p = binding.CottenParams(F32, 0.0, -1.0, 0x10000, least - 4)
-        if is_bwd:
-            assert lib.cotten_attn_bwd_ex(*ptrs, slices, 1, N, d, None, ctypes.byref(p)) == -6
-        else:
-            assert lib.cotten_attn_fwd_ex(*ptrs[:5], slices, 1, N, d, None, ctypes.byref(p)) == -6
+        for space, size in ((0x10000, _bytes(d, slices, fewest, is_bwd) - 4), (None, 0)):
+            p = binding.CottenParams(F32, 0.0, -1.0, space, size)
+            if is_bwd:
+                assert lib.cotten_attn_bwd_ex(*ptrs, slices, 1, N, d, None, ctypes.byref(p)) == -6
+            else:
+                assert lib.cotten_attn_fwd_ex(*ptrs[:5], slices, 1, N, d, None, ctypes.byref(p)) == -6
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,slices,N,parts", FEWER_PARTS)
-def test_fp32_runs_in_fewer_parts(oracle, d, slices, N, parts):
+@pytest.mark.parametrize("d,slices,N,fewest,parts", FEWER_PARTS)
+def test_fp32_runs_in_fewer_parts(oracle, d, slices, N, fewest, parts):
     """What was refused above runs from that size on, and writes nothing behind it."""
-    print(f"[split plan] fewer parts d={d} {slices} x {N}", flush=True)
-    bytes_of = [_least_bytes(d, slices, parts, is_bwd) for is_bwd in (False, True)]
-    asked = [binding.cotten_attn_workspace_bytes(slices, 1, N, d, F32, is_bwd) for is_bwd in (False, True)]
-    assert any(a > b for a, b in zip(asked, bytes_of))
+    for n in (fewest, parts):
+        print(f"[split plan] fewer parts d={d} {slices} x {N} in {n}", flush=True)
+        sizes = [_bytes(d, slices, n, is_bwd) for is_bwd in (False, True)]
+        assert all(binding.cotten_attn_workspace_bytes(slices, 1, N, d, F32, x) > sizes[x] for x in (False, True))
+        _parity_in(oracle, d, slices, N, sizes)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,slices,N,fwd,bwd", WHOLE_WITHOUT)
+def test_fp32_runs_whole_without_a_workspace(oracle, d, slices, N, fwd, bwd):
+    print(f"[split plan] whole d={d} {slices} x {N}", flush=True)
+    for is_bwd, parts in ((False, fwd), (True, bwd)):
+        asked = binding.cotten_attn_workspace_bytes(slices, 1, N, d, F32, is_bwd)
+        assert asked == (0 if parts == 1 else _bytes(d, slices, parts, is_bwd))
+    _parity_in(oracle, d, slices, N, (16, 16))
+
+
+def _parity_in(oracle, d, slices, N, sizes):
     tail = 4096
-    whole = [torch.full((b + tail,), 0xA5, dtype=torch.uint8, device="cuda") for b in bytes_of]
-    _parity(oracle, "f32", d, slices, N, [w[:b] for w, b in zip(whole, bytes_of)])
-    assert all((w[b:] == 0xA5).all() for w, b in zip(whole, bytes_of))
+    whole = [torch.full((b + tail,), 0xA5, dtype=torch.uint8, device="cuda") for b in sizes]
+    _parity(oracle, "f32", d, slices, N, [w[:b] for w, b in zip(whole, sizes)])
+    assert all((w[b:] == 0xA5).all() for w, b in zip(whole, sizes))
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d,slices,N", [
-    ("f32", 128, 4, 257), ("f32", 128, 86, 340), ("f32", 128, 150, 290), ("f32", 64, 20, 333), ("f32", 64, 64, 421),
+    ("f32", 128, 4, 257), ("f32", 128, 86, 340), ("f32", 128, 150, 290), ("f32", 128, 46, 310), ("f32", 128, 72, 1001), ("f32", 128, 92, 2420), ("f32", 128, 131, 1450), ("f32", 64, 20, 333), ("f32", 64, 64, 421),
     ("f32", 64, 150, 1300), ("f32", 64, 200, 310), ("bf16", 128, 64, 300), ("bf16", 128, 40, 310), ("f16", 128, 128, 520), ("bf16", 128, 48, 700),
     ("bf16", 128, 32, 1300), ("f16", 128, 150, 1300),
 ])
