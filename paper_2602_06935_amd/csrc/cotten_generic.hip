@@ -236,7 +236,9 @@ long wide_splits16(long BH, long N, bool bwd) {
 //   8: 13.7 (4: 17.4);  64 x 320 16.5 (3: 15.7);  80 x 320 16.7 (3: 17.1);  64 x 4000, 8: 68 (4: 73, 9: 73);  197 x 1916, 3: 95 (2: 106);  32 x 6000, 16: 53 (24: 54,
 //   8: 56);  backward 128 x 1000 73 whole (4: 87);  250 x 600 86 (2: 109);  200 x 1800, 3: 211 (1: 220);  32 x 1000, 8: 27 (4: 29);
 //   64 x 1800, 4: 73 (7: 82);  64 x 3500, 11: 143 (4: 147);  20 x 1000, 4: 21.2 (8: 22.4);  4 x 4000, 21: 21 (32: 23);  8 x 8000, 32: 42
-//   (16: 49).
+//   (16: 49);  just over half as many slices as units, 129 x 680, 2: 59 (1: 65);  140 x 950, 2: 91 (1: 104);  150 x 800, 2: 73 (1: 79);  129 x 800, 2:
+//   62.5 (1: 60.4);  140 x 560 53.7 (2: 54.2);  160 x 950 99 (2: 101).  (The forward of 32 x 3600 is faster in 15 parts of 256 rows, 33 to 39, but
+//   these are not summed apart: error 1.8e-7 against 1.5e-7.)
 long wide_splits32(long BH, long N, int D, bool bwd) {
   if (N <= 256) return 1;  // (calls of this length need no workspace)
   // workgroups per slice: one per compute unit in all, two, three, and those of a launch of three roles
@@ -259,6 +261,7 @@ long wide_splits32(long BH, long N, int D, bool bwd) {
     if (N > (one == 1 ? 1300 * BH / kUnits : 550 * one)) return up_to(one == 1 || 200 * three > 318 * two ? three : two, long_parts);
     return N <= 200 + 2 * BH ? 1 : up_to(one, most);
   }
+  if (BH > 128 && BH <= 150 && N > 600 && N <= 8 * BH) return 2;
   if (N <= (BH > 128 ? 8 * BH : BH >= 86 ? 1100 + 60 * (BH - 86) : few == 1 ? 420 : 0)) return 1;
   if (BH >= 86 || N > 600 * (N > 250 * few ? one : few)) return up_to(three, long_parts);
   return up_to(N > 250 * few ? one : few, most);
@@ -266,7 +269,7 @@ long wide_splits32(long BH, long N, int D, bool bwd) {
 
 // fp32 rows: calls that are cut for speed but run whole, in one launch, where there is no workspace.
 bool whole_without_workspace32(long BH, long N, int D, bool bwd) {
-  if (D < 128) return false;
+  if (D < 128) return D == 64 && bwd && BH > 128 && N <= 8 * BH;
   if (!bwd) return BH > 128;
   return BH > 85 || (BH > 64 ? N * BH <= 180000 : BH > 42 && N <= 450);
 }
