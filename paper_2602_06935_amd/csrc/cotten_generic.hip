@@ -311,8 +311,12 @@ Plan make_plan(int B, int H, int N, int D, int dtype, bool is_bwd, size_t given)
     // 20.0 / 42.3;  160 x 900 22.6 / 45.3, 21.4 / 45.5;  160 x 1300 34 / 65, 26 / 55;  200 x 1300 35 / 65, 38 / 67;  200 x 2000 51 / 105,
     // 54 / 111.  fp32 d = 32: 100 x 260 10.4 / 19.3, 10.4 / 18.6;  130 x 320 10.8 / 20.3, 11.5 / 21.1;  160 x 420 13.8 / 26.0, 13.4 /
     // 26.4;  200 x 600 19.0 / 35.0, 18.6 / 36.1;  250 x 600 20.1 / 36.9, 20.5 / 41.7;  250 x 900 27.5 / 55.9, 26.5 / 55.0.
-    const long enough = dtype != 0 ? (N / 5 - 10 < 170 ? N / 5 - 10 : 170) : (N / 4 + 40 < 256 ? N / 4 + 40 : 256);
-    if ((N <= kMostRows && (BH >= enough || N <= 256)) || fused_long) {
+    // fp32, beyond 320 rows and up to 168 slices (three workgroups of each on two per compute unit):  128 x 330, 3 parts: 11.1 / 20.6, whole 11.7 /
+    // 22.1;  160 x 470, 3: 13.5 / 25.6, whole 14.2 / 28.1;  170 x 470, 2: 14.1 / 28.6, whole 14.3 / 28.0.  (Whole also there, without a workspace for two.)
+    const auto at_most = [](long x, long limit) { return x < limit ? x : limit; };
+    const long enough = dtype != 0 ? at_most(N / 5 - 10, 170) : at_most(N / 4 + 40, 256);
+    const bool three = dtype == 0 && N > 320 && BH <= 168 && given / 2 >= nstates * BH * mfma_state_dim(dtype) * mfma_state_dim(dtype);
+    if ((N <= kMostRows && ((BH >= enough && !three) || N <= 256)) || fused_long) {
       plan.path = Plan::kFused;
       plan.splits = 1;
       plan.rows_per_split = N;

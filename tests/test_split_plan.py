@@ -34,7 +34,7 @@ def _splits(slices, N, dtype, bwd):
     (64, 4096, BF16, 8), (72, 4096, BF16, 7), (100, 2500, BF16, 4), (128, 4096, F16, 4),
     # fp32: two, or three where these fill it better
     (7, 4096, F32, 32), (16, 4096, F32, 16), (64, 4096, F32, 8), (96, 4096, F32, 8), (180, 4096, F32, 4),
-    (200, 4096, F32, 2), (119, 320, F32, 3), (120, 320, F32, 0), (255, 864, F32, 2),
+    (200, 4096, F32, 2), (119, 320, F32, 3), (120, 320, F32, 0), (128, 321, F32, 3), (168, 470, F32, 3), (169, 470, F32, 0), (255, 864, F32, 2),
 ])
 def test_split_rule(slices, N, dtype, splits):
     assert _splits(slices, N, dtype, True) == splits
@@ -64,7 +64,7 @@ def test_wide_fp32_split_rule(slices, N, d, fwd, bwd):
 FEWER_PARTS = [(128, 4, 700, 2, 3), (64, 1, 1100, 2, 5), (128, 12, 600, 2, 3), (64, 8, 1000, 2, 4), (32, 81, 453, 2, 4), (16, 81, 453, 2, 3),
                (32, 129, 4100, 3, 4)]
 # shapes that are cut where there is a workspace and run whole without one: (d, slices, N, fwd, bwd)
-WHOLE_WITHOUT = [(128, 129, 1401, 3, 3), (128, 192, 1457, 1, 3), (128, 170, 1401, 3, 3), (64, 129, 601, 1, 2)]
+WHOLE_WITHOUT = [(128, 129, 1401, 3, 3), (128, 192, 1457, 1, 3), (128, 170, 1401, 3, 3), (64, 129, 601, 1, 2), (32, 168, 321, 3, 3), (16, 168, 440, 3, 3)]
 
 
 def _bytes(d, slices, parts, is_bwd):
@@ -128,7 +128,7 @@ def test_wide_rows_on_both_sides_of_the_split_rule(oracle, dtype, d, slices, N):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,slices,N", [
     ("bf16", 53, 320), ("bf16", 54, 320), ("f16", 170, 1029), ("bf16", 169, 1029), ("bf16", 9, 1531), ("f16", 3, 2300),
-    ("f32", 120, 320), ("f32", 96, 1100), ("f32", 7, 2049),
+    ("f32", 120, 320), ("f32", 168, 321), ("f32", 96, 1100), ("f32", 7, 2049),
 ])
 def test_both_sides_of_the_split_rule(oracle, dtype, slices, N):
     print(f"[split plan] {dtype} {slices} x {N}", flush=True)
