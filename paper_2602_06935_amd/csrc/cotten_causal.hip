@@ -434,7 +434,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   const auto tile_of = [&](int step) { return (kUp ? begin + step : begin - step) * WAVES + wave; };
   const auto applies = [&](int step) { return kUp ? begin + step >= first : begin - step < last; };
   // (the backward of fp32 rows of one piece is at the registers of four waves per SIMD: its keys are read where they
-  // are needed, 512 slices x 128 rows 18.2 us against 21.0)
+  // are needed, 512 slices x 128 rows 18.2 us against 21.0, and where there is a mask: 512 x 400 rows 56.4, through an empty buffer 57.4)
   constexpr bool kKeysAhead = ROLE == kO || F::kElemBytes == 2 || P == 2;
   struct KeyBytes {
     unsigned of[2];
@@ -459,36 +459,40 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   const auto request = [&](Ahead& t, int step, const KeyBytes& b, const Lane& L) {
     const int row0 = tile_of(step) * TR, row = row0 + L.r8;
     int bits = 0;
-    if (kUp) {
-      const KeyBytes k = kKeysAhead ? b : request_keys(step);
-      bits = static_cast<int>(shared_keys.test(k.of[0], row)) | static_cast<int>(shared_keys.test(k.of[1], row + 8)) << 1;
-    } else {
+    if (!kUp) {
       bits = static_cast<int>(row < N) | static_cast<int>(row + 8 < N) << 1;
+    } else if (kKeysAhead) {
+      bits = static_cast<int>(shared_keys.test(b.of[0], row)) | static_cast<int>(shared_keys.test(b.of[1], row + 8)) << 1;
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (row + 8 * h < N) bits |= static_cast<int>(keys == nullptr || keys[row + 8 * h] != 0) << h;
     }
     load_shared<P>(t.shared, L, sx, sy, addr, row0, bits);
     if (applies(step)) {
-      if (kUp) t.live = row0 + L.i16 < N;
-      else t.live = own_keys.test((kKeysAhead ? b : request_keys(step)).of[0], row0 + L.i16);
+      const int own = row0 + L.i16;
+      if (kUp) t.live = own < N;
+      else if (kKeysAhead) t.live = own_keys.test(b.of[0], own);
+      else t.live = own < N && (keys == nullptr || keys[own] != 0);
       load_own<P>(t.nx, L, ox, addr, row0, t.live);
       if (kTwoOwn) load_own<P>(t.ny, L, oy, addr, row0, t.live);
     }
   };
-  // The forward of 16-bit rows, which has the registers for it, keeps two chunks on their way, the others one.  (A
-  // walk of two chunks requests the second when the first has come: both at once would come together.)
+  // The forward of 16-bit rows, which has the registers for it, keeps two chunks on their way, the others one.  The second is
+  // requested when the first has come: both at once would come together (bf16 d = 64, both at once and this, us: 256 x 1001 rows, padded, 31.0,
+  // 29.6;  without a mask 256 x 600 24.0, 22.7;  1024 x 378 45.5, 44.5;  one chunk on its way 32.9, 22.3 and 41.9).
   constexpr int kAhead = ROLE == kO && F::kElemBytes == 2 ? 2 : 1;
-  const bool late = kAhead == 2 && steps == 2;
   Ahead ahead[kAhead];
-  KeyBytes next_keys = {{0u, 0u}};
+  KeyBytes next_keys = {{0u, 0u}}, second_keys;
   {
     KeyBytes b[kAhead];
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) b[i] = kKeysAhead ? request_keys(i) : KeyBytes{{0u, 0u}};
-    if (kKeysAhead && steps > (late ? 1 : kAhead)) next_keys = request_keys(late ? 1 : kAhead);
+    if (kKeysAhead) next_keys = request_keys(kAhead);
+    second_keys = b[kAhead - 1];
 #pragma unroll
-    for (int i = 0; i < kAhead; ++i) {
-      ahead[i].live = false;
-      if (i == 0 || (i < steps && !late)) request(ahead[i], i, b[i], L);
-    }
+    for (int i = 0; i < kAhead; ++i) ahead[i].live = false;
+    request(ahead[0], 0, b[0], L);
   }
   if (!kUp && keys != nullptr && steps > 4) {
     // Chunks below the first valid key of the segment get zeros and are not walked.  (Looking for it
@@ -542,11 +546,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
     const int tile = tile_of(step);
     const KeyBytes bytes = next_keys;
     if (kKeysAhead) next_keys = request_keys(step + kAhead + 1);  // (a branch here would wait: 64 x 4096 rows backward 98 -> 105)
-    if (late) {
-      if (step == 0) request(ahead[kAhead - 1], 1, bytes, L);
-    } else if (step + kAhead < steps) {
-      request(now, step + kAhead, bytes, L);
-    }
+    if (kAhead == 2 && step == 0 && steps > 1) request(ahead[kAhead - 1], 1, second_keys, L);
+    if (step + kAhead < steps) request(now, step + kAhead, bytes, L);
     __syncthreads();
     int flags = 0;  // bit u: tile u of the chunk has rows that take part
 #pragma unroll
