@@ -85,11 +85,14 @@ def test_columns_16bit_backward(oracle, dtype, B, H, N, feature_map):
     dlog = torch.zeros(B, H, device="cuda")
     plain = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, **opts)
     with_dlog = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, dlog_scale=dlog, **opts)
-    again = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, **opts)
     sw = lambda t: t.permute(0, 2, 1, 3).contiguous()
-    other = binding.cotten_attn_bwd(sw(tq), sw(tk), sw(tv), tm, sw(tg), layout="bnhd", **opts)
+    for first, kw in ((plain, {}), (with_dlog, dict(dlog_scale=torch.zeros_like(dlog)))):
+        again = binding.cotten_attn_bwd(tq, tk, tv, tm, tg, **kw, **opts)
+        assert not kw or torch.equal(kw["dlog_scale"], dlog)
+        other = binding.cotten_attn_bwd(sw(tq), sw(tk), sw(tv), tm, sw(tg), layout="bnhd", **kw, **opts)
+        assert not kw or torch.equal(kw["dlog_scale"], dlog)
+        assert all(torch.equal(a, b) and torch.equal(sw(a), c) for a, b, c in zip(first, again, other))
     torch.cuda.synchronize()
-    assert all(torch.equal(a, b) and torch.equal(sw(a), c) for a, b, c in zip(plain, again, other))
     if feature_map == "cosine":
         ref_o, refs = oracle.fwd_linear(Q, K, V, mask, scale=0.05), oracle.bwd(Q, K, V, dO, mask, scale=0.05)
     else:
@@ -103,26 +106,50 @@ def test_columns_16bit_backward(oracle, dtype, B, H, N, feature_map):
     assert rel_l2(dlog.double().cpu().numpy(), ref_dlog) <= 5 * bar_for(dtype)
 
 
-def test_columns_scales_and_masked_rows(oracle):
-    """Per-slice scales; masked rows may hold anything."""
-    B, H, N = 140, 2, 75
+@pytest.mark.parametrize("dtype,B,H,N", [("f32", 140, 2, 75), ("bf16", 65, 2, 400), ("f16", 130, 1, 389), ("bf16", 150, 2, 300), ("f16", 300, 1, 261)])
+def test_columns_scales_and_masked_rows(oracle, dtype, B, H, N):
+    """Per-slice scales, with the gradient of their logarithms; masked rows may hold anything."""
+    print(f"[columns] scales {dtype} B={B} H={H} N={N}", flush=True)
     rng = np.random.default_rng(77)
-    Q, K, V, dO = (rng.standard_normal((B, H, N, 128)).astype(np.float32) for _ in range(4))
+    Q, K, V, dO = (to_f64(to_gpu(rng.standard_normal((B, H, N, 128)).astype(np.float32), dtype)).astype(np.float32) for _ in range(4))
     mask = _mask(rng, B, N)
-    tq, tk, tv, tg = (to_gpu(x, "f32") for x in (Q, K, V, dO))
+    tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
     tm = torch.from_numpy(mask).cuda()
     ss = torch.rand(B, H, device="cuda") * 0.05 + 0.01
-    run = lambda k, v: (binding.cotten_attn_fwd(tq, k, v, tm, slice_scale=ss),
-                        *binding.cotten_attn_bwd(tq, k, v, tm, tg, slice_scale=ss))
+
+    def run(k, v):
+        dlog = torch.zeros(B, H, device="cuda")
+        return (binding.cotten_attn_fwd(tq, k, v, tm, slice_scale=ss),
+                *binding.cotten_attn_bwd(tq, k, v, tm, tg, slice_scale=ss),
+                *binding.cotten_attn_bwd(tq, k, v, tm, tg, slice_scale=ss, dlog_scale=dlog), dlog)
+
     plain = run(tk, tv)
     dead = (tm == 0)[:, None, :, None].expand_as(tk)
     garbage = run(tk.masked_fill(dead, float("nan")), tv.masked_fill(dead, float("inf")))
     torch.cuda.synchronize()
     assert all(torch.equal(a, b) for a, b in zip(plain, garbage))
-    unit = (oracle.fwd_linear(Q, K, V, mask, scale=1.0), *oracle.bwd(Q, K, V, dO, mask, scale=1.0))
+    unit_o, unit = oracle.fwd_linear(Q, K, V, mask, scale=1.0), oracle.bwd(Q, K, V, dO, mask, scale=1.0)
     s64 = ss.double().cpu().numpy()[:, :, None, None]
-    for name, got, ref in zip(("O", "dQ", "dK", "dV"), plain, unit):  # (every result is linear in the scale)
-        check_tensor(name, to_f64(got), ref * s64, FP32_BAR, few_terms=True)
+    for name, got, ref in zip(("O", "dQ", "dK", "dV", "dQ", "dK", "dV"), plain, (unit_o, *unit, *unit)):  # (every result is linear in the scale)
+        check_tensor(name, to_f64(got), ref * s64, bar_for(dtype), few_terms=True)
+    ref_dlog = (dO.astype(np.float64) * unit_o * s64).sum(axis=(2, 3))
+    assert rel_l2(plain[-1].double().cpu().numpy(), ref_dlog) <= 5 * bar_for(dtype)  # (sums with cancellation)
+
+
+@pytest.mark.parametrize("dtype,B,H,N", [("f32", 130, 2, 77), ("bf16", 44, 2, 401), ("f16", 260, 1, 270)])
+def test_columns_without_a_mask(oracle, dtype, B, H, N):
+    print(f"[columns] no mask {dtype} B={B} H={H} N={N}", flush=True)
+    rng = np.random.default_rng(78)
+    Q, K, V, dO = (to_f64(to_gpu(rng.standard_normal((B, H, N, 128)).astype(np.float32), dtype)).astype(np.float32) for _ in range(4))
+    tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
+    ones = np.ones((B, N), np.uint8)
+    got = (binding.cotten_attn_fwd(tq, tk, tv, None), *binding.cotten_attn_bwd(tq, tk, tv, None, tg))
+    with_ones = (binding.cotten_attn_fwd(tq, tk, tv, torch.from_numpy(ones).cuda()),
+                 *binding.cotten_attn_bwd(tq, tk, tv, torch.from_numpy(ones).cuda(), tg))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(got, with_ones))
+    for name, x, ref in zip(("O", "dQ", "dK", "dV"), got, (oracle.fwd_linear(Q, K, V, ones), *oracle.bwd(Q, K, V, dO, ones))):
+        check_tensor(name, to_f64(x), ref, bar_for(dtype))
 
 
 def test_columns_infinities():
