@@ -726,7 +726,10 @@ hipError_t run16(const Problem& p, const Args& a) {
 // and compute unit; they stay where these fit the chip at once, and these kernels take over from there (forward / backward, us,
 // those and these):  128 slices x 200 rows 26.6 / 39.7, 36.5 / 58.8;  192: 30.2 / 73.4, 40.2 / 60.6;  256: 33.4 / 76.8, 41.5 /
 // 62.3;  300: 50.0 / 104, 48.0 / 104;  512: 60.4 / 155, 53.0 / 123;  512 x 100 36.5 / 95.9, 31.6 / 77.3;  512 x 20 19.9 / 61.6, 11.6 /
-// 32.8;  512 x 700 163 / 415, 164 / 368;  256 x 1000 118 / 283, 181 / 277.
+// 32.8;  512 x 700 163 / 415, 164 / 368;  256 x 1000 118 / 283, 181 / 277.  Forwards of longer sequences stay there, one
+// workgroup per compute unit in rounds of 256:  280 x 300 57.5, 61.7;  280 x 700 121, 136;  512 x 300 65.1, 65.5;  519 x 700 193, 218;  640 x 500
+// 158, 173 - but 900 x 300 132, 127, and 900 x 400 171, 164.  (Errors against float64 1.9e-7, here 2.1e-7.)  Backwards of 258 ... 384 slices and more
+// than 256 rows are faster there too, 280 x 400 159, 170, 280 x 1000 390, 416, but less exact, dK of 300 x 1000 2.2e-7, 2.1e-7: not them.
 // 16-bit rows of 256 bytes, backward: against the kernels of cotten_wide.hip, which keep the tiles of up to 256 rows in
 // registers and walk longer sequences three times (us, those and these):  1024 slices x 200 rows 94.6, 99.6;  100 x 300 31.5,
 // 34.2;  180 x 300 34.8, 36.2;  180 x 400 45.3, 43.8;  256 x 300 38.2, 37.2;  512 x 300 85.0, 65.6;  512 x 400 117, 87;  256 x 800 130, 96;
@@ -735,7 +738,8 @@ bool columns_apply(const Problem& p, bool bwd) {
   const long slices = static_cast<long>(p.B) * p.H;
   if (p.D != 128) return false;
   if (p.dtype != 0) return bwd && (p.N > 384 || (p.N > 256 && slices >= columns::kUnits));
-  return slices * (bwd ? 2 : 1) > columns::kUnits;
+  if (bwd) return 2 * slices > columns::kUnits;
+  return slices > columns::kUnits && (p.N <= 256 || (slices - 1) / columns::kUnits == 3);
 }
 
 hipError_t launch_columns(const Problem& p, bool bwd) {

@@ -29,7 +29,7 @@ def _mask(rng, B, N):
 
 @pytest.mark.parametrize("B,H,N", [
     (260, 1, 1), (130, 1, 15), (260, 1, 16), (130, 2, 17), (260, 1, 31), (260, 1, 32), (87, 3, 33), (150, 1, 63),
-    (130, 2, 65), (129, 1, 200), (130, 2, 513), (64, 4, 600),
+    (130, 2, 65), (129, 1, 200), (130, 2, 513), (64, 4, 600), (130, 2, 256), (130, 2, 257), (193, 4, 259),
 ])
 @pytest.mark.parametrize("feature_map", ["cosine", "elu1"])
 def test_columns(oracle, B, H, N, feature_map):
