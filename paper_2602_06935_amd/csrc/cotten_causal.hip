@@ -380,7 +380,8 @@ __device__ __forceinline__ void store_own(unsigned char* dst, int row, int N, Ro
 //   carried so far into the operand images, request everything of the next chunk         B
 //   own rows: carried state, then the tile pairs; epilogue, stores.  Then the waves with the
 //   fewest pairs add the chunk to the carried state, one 32 x 32 block each              B
-template <class F, int P, int WAVES, int ROLE>
+// UNMASKED: the kernel is for calls without a mask: nothing is requested for one, and one chunk of rows is on its way.
+template <class F, int P, int WAVES, int ROLE, bool UNMASKED>
 __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment) {
   typedef ScanLds<F, P, WAVES> Lds;
   typedef typename F::TileRows TileRows;
@@ -392,7 +393,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   const int n_tiles = (N + TR - 1) / TR, chunks = (n_tiles + WAVES - 1) / WAVES;
   const size_t base = a.st.slice_base(bh, a.H);
   const RowAddr addr = a.st.row;
-  const uint8_t* keys = a.mask == nullptr ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * N;
+  const uint8_t* keys = UNMASKED || a.mask == nullptr ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * N;
   const Keys shared_keys(kUp ? keys : nullptr, N), own_keys(kUp ? nullptr : keys, N);
   const float scale = a.scales != nullptr ? a.scales[bh] : a.scale;
   const Buffers sx((kUp ? a.K : a.Q) + base, N, addr), sy((kUp ? a.V : a.dO) + base, N, addr);
@@ -435,7 +436,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   const auto applies = [&](int step) { return kUp ? begin + step >= first : begin - step < last; };
   // (the backward of fp32 rows of one piece is at the registers of four waves per SIMD: its keys are read where they
   // are needed, 512 slices x 128 rows 18.2 us against 21.0, and where there is a mask: 512 x 400 rows 56.4, through an empty buffer 57.4)
-  constexpr bool kKeysAhead = ROLE == kO || F::kElemBytes == 2 || P == 2;
+  constexpr bool kKeysAhead = !UNMASKED && (ROLE == kO || F::kElemBytes == 2 || P == 2);
   struct KeyBytes {
     unsigned of[2];
   };
@@ -478,10 +479,10 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
       if (kTwoOwn) load_own<P>(t.ny, L, oy, addr, row0, t.live);
     }
   };
-  // The forward of 16-bit rows, which has the registers for it, keeps two chunks on their way, the others one.  The second is
-  // requested when the first has come: both at once would come together (bf16 d = 64, both at once and this, us: 256 x 1001 rows, padded, 31.0,
-  // 29.6;  without a mask 256 x 600 24.0, 22.7;  1024 x 378 45.5, 44.5;  one chunk on its way 32.9, 22.3 and 41.9).
-  constexpr int kAhead = ROLE == kO && F::kElemBytes == 2 ? 2 : 1;
+  // The forward of 16-bit rows, which has the registers for it, keeps two chunks on their way where the mask decides on the rows, the others
+  // one.  The second is requested when the first has come: both at once would come together (bf16 d = 64, 256 x 1001 rows, padded: one 33.2 us, two
+  // at once 31.8, this 30.3).
+  constexpr int kAhead = !UNMASKED && ROLE == kO && F::kElemBytes == 2 ? 2 : 1;
   Ahead ahead[kAhead];
   KeyBytes next_keys = {{0u, 0u}}, second_keys;
   {
@@ -694,18 +695,19 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   }
 }
 
-template <class F, int P, int WAVES>
+template <class F, int P, int WAVES, bool UNMASKED>
 __global__ __launch_bounds__(64 * WAVES, P == 1 ? 4 : 2) void causal_scan_fwd_kernel(const Args a) {
-  scan_segment<F, P, WAVES, kO>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+  scan_segment<F, P, WAVES, kO, UNMASKED>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
 }
 
 // blockIdx.y == 0: dQ.   blockIdx.y == 1: dK and dV, or (1, 2) dV, dK.
-template <class F, int P, int WAVES>
+template <class F, int P, int WAVES, bool UNMASKED>
 __global__ __launch_bounds__(64 * WAVES, P == 1 ? 4 : 2) void causal_scan_bwd_kernel(const Args a) {
-  if (blockIdx.y == 0) scan_segment<F, P, WAVES, kDq>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
-  else if constexpr (!separate_dv_dk<P>()) scan_segment<F, P, WAVES, kDkDv>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
-  else if (blockIdx.y == 1) scan_segment<F, P, WAVES, kDv>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
-  else scan_segment<F, P, WAVES, kDk>(a, blockIdx.x / a.segments, blockIdx.x % a.segments);
+  const int bh = blockIdx.x / a.segments, segment = blockIdx.x % a.segments;
+  if (blockIdx.y == 0) scan_segment<F, P, WAVES, kDq, UNMASKED>(a, bh, segment);
+  else if constexpr (!separate_dv_dk<P>()) scan_segment<F, P, WAVES, kDkDv, UNMASKED>(a, bh, segment);
+  else if (blockIdx.y == 1) scan_segment<F, P, WAVES, kDv, UNMASKED>(a, bh, segment);
+  else scan_segment<F, P, WAVES, kDk, UNMASKED>(a, bh, segment);
 }
 
 constexpr int kThreads = 256;
@@ -805,16 +807,22 @@ hipError_t run_scan(const Problem& p, bool bwd) {
     a.after = p.workspace + static_cast<size_t>(slices) * a.segments * side * side;
   }
   const int lds = ScanLds<F, P, WAVES>::bytes(bwd, chunks > 1);
-  const void* kern = bwd ? reinterpret_cast<const void*>(causal_scan_bwd_kernel<F, P, WAVES>)
-                         : reinterpret_cast<const void*>(causal_scan_fwd_kernel<F, P, WAVES>);
-  const hipError_t err = grant_dynamic_lds(kern, ScanLds<F, P, WAVES>::bytes(bwd, true));
-  if (err != hipSuccess) return err;
-  const unsigned grid = static_cast<unsigned>(slices) * a.segments;
-  if (bwd)
-    hipLaunchKernelGGL((causal_scan_bwd_kernel<F, P, WAVES>), dim3(grid, separate_dv_dk<P>() ? 3 : 2), dim3(64 * WAVES), lds, p.stream, a);
-  else
-    hipLaunchKernelGGL((causal_scan_fwd_kernel<F, P, WAVES>), dim3(grid), dim3(64 * WAVES), lds, p.stream, a);
-  return hipGetLastError();
+  const dim3 grid(static_cast<unsigned>(slices) * a.segments, bwd ? (separate_dv_dk<P>() ? 3 : 2) : 1);
+  const auto launch = [&](auto kernel) {
+    const hipError_t err =
+        grant_dynamic_lds(reinterpret_cast<const void*>(kernel), ScanLds<F, P, WAVES>::bytes(bwd, true));
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), lds, p.stream, a);
+    return hipGetLastError();
+  };
+  // Calls without a mask have kernels of their own where that gains (bytes of an empty buffer, us, and none): bf16 d = 64, forward 256 x 600 22.7,
+  // 21.5; 128 x 318 10.3, 9.4; backward 21.7, 20.6; 256 x 1001 79.4, 80.5;  fp32 d = 64, backward 8 x 200 13.3, 12.9; 128 x 200 31.9, 31.5.  Not the
+  // fp32 forward (8 x 2800 87.8, 91.6) nor fp32 d = 32 (backward 64 x 820 37.9, 43.7).
+  if constexpr (F::kElemBytes == 2 || P == 2)
+    if (p.mask == nullptr && bwd) return launch(causal_scan_bwd_kernel<F, P, WAVES, true>);
+  if constexpr (F::kElemBytes == 2)
+    if (p.mask == nullptr && !bwd) return launch(causal_scan_fwd_kernel<F, P, WAVES, true>);
+  return bwd ? launch(causal_scan_bwd_kernel<F, P, WAVES, false>) : launch(causal_scan_fwd_kernel<F, P, WAVES, false>);
 }
 
 }  // namespace
