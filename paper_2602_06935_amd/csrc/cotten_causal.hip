@@ -481,8 +481,8 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
   };
   // The forward of 16-bit rows, which has the registers for it, keeps two chunks on their way where the mask decides on the rows, the others
   // one.  The second is requested when the first has come: both at once would come together (bf16 d = 64, 256 x 1001 rows, padded: one 33.2 us, two
-  // at once 31.8, this 30.3).
-  constexpr int kAhead = !UNMASKED && ROLE == kO && F::kElemBytes == 2 ? 2 : 1;
+  // at once 31.8, this 30.3).  Workgroups of four waves, which walk one chunk or two, keep one (bf16, 1024 x 50: two 6.3, one 6.0).
+  constexpr int kAhead = !UNMASKED && ROLE == kO && F::kElemBytes == 2 && WAVES == 8 ? 2 : 1;
   Ahead ahead[kAhead];
   KeyBytes next_keys = {{0u, 0u}}, second_keys;
   {
