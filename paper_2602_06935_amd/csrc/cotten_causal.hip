@@ -21,14 +21,15 @@
 // (`apply`), its update one 32 x 32 block per wave.  What a wave needs of its own rows it loads
 // straight in the layout of the products; only the rows that other waves read go through LDS.
 //
-// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 13.5 / 30.7, where a scan on the vector
-// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 29 / 75, where 208-row
+// Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 13.4 / 30.6, where a scan on the vector
+// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 30 / 73, where 208-row
 // chunks joined by states in memory took 56 / 101 (three launches, 13 * 14 / 2 tile pairs per chunk
-// instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - memory, the forward at about 4 TB/s with two chunks of loads in
-// flight per wave (with one, and the bytes of the key mask waited for before the loads of their rows, 32.4; 64 x 1001
-// rows 20.0, now 16.8), the backward at 3.8 (its two roles each read all they need) with one: it has no registers for
-// more; fp32 - latency: with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is (mask bytes
-// ahead: 32 x 2048 rows, d = 64, forward 79 -> 71.6;  1024 x 200 backward 150 -> 145;  8 x 200 backward 12.5, now 12.9).
+// instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - the forward by memory, at about 4 TB/s with two chunks of loads in
+// flight per wave (with one, and the bytes of the key mask waited for before the loads of their rows, 33.2; 64 x 1001
+// rows 20.3, now 17.1), the backward by waits, with one: 249 MB, what its two roles share read twice, at 3.4 TB/s, half of
+// the wave time waiting, matrix cores busy for 13 % (two chunks in flight: it has no registers for more); fp32 - latency:
+// with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is (mask bytes ahead: 32 x 2048
+// rows, d = 64, forward 79 -> 71.6;  1024 x 200 backward 149 -> 144;  8 x 200 backward 12.7, now 13.2).
 //
 // 16-bit results differ from those of 208-row chunks in the places where sums are rounded, by about as much
 // as either differs from a 64-bit evaluation (bf16, 256 x 1001 rows: 3e-3; from 64 bits 2.9e-3 ... 3.3e-3

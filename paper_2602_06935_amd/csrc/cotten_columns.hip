@@ -1,5 +1,5 @@
-// Wide rows, sequences that are not cut: one workgroup per slice and direction, every wave the owner of 32
-// columns of the results.
+// Wide rows, sequences that are not cut: one workgroup per slice, every wave the owner of 32 columns of the results
+// (fp32 d_h = 128 in both directions, 16-bit d_h = 128 in the backward).
 //
 //     S = sum_j xhat_j^T y_j       each wave one or two 32 x 32 blocks of it, over all rows
 //     T = X W                      each wave 32 columns of T, its part of W held in registers
