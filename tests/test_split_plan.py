@@ -105,6 +105,13 @@ def test_fp32_runs_whole_without_a_workspace(oracle, d, slices, N, fwd, bwd):
         asked = binding.cotten_attn_workspace_bytes(slices, 1, N, d, F32, is_bwd)
         assert asked == (0 if parts == 1 else _bytes(d, slices, parts, is_bwd))
     _parity_in(oracle, d, slices, N, (16, 16))
+    # the static scratch serves as a workspace of its size
+    q, k, v, g = (torch.randn(slices, 1, N, d, device="cuda") for _ in range(4))
+    out = [torch.empty_like(q) for _ in range(3)]
+    binding.cotten_attn_bwd(q, k, v, None, g, *out, static_scratch=True)
+    ref = binding.cotten_attn_bwd(q, k, v, None, g, workspace=torch.empty(32 << 20, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(out, ref))
 
 
 def _parity_in(oracle, d, slices, N, sizes):
