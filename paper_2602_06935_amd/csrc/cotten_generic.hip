@@ -237,7 +237,9 @@ long wide_splits16(long BH, long N, bool bwd) {
 //   8: 56);  backward 128 x 1000 73 whole (4: 87);  250 x 600 86 (2: 109);  200 x 1800, 3: 211 (1: 220);  32 x 1000, 8: 27 (4: 29);
 //   64 x 1800, 4: 73 (7: 82);  64 x 3500, 11: 143 (4: 147);  20 x 1000, 4: 21.2 (8: 22.4);  4 x 4000, 21: 21 (32: 23);  8 x 8000, 32: 42
 //   (16: 49);  just over half as many slices as units, 129 x 680, 2: 59 (1: 65);  140 x 950, 2: 91 (1: 104);  150 x 800, 2: 73 (1: 79);  129 x 800, 2:
-//   62.5 (1: 60.4);  140 x 560 53.7 (2: 54.2);  160 x 950 99 (2: 101).  (The forward of 32 x 3600 is faster in 15 parts of 256 rows, 33 to 39, but
+//   62.5 (1: 60.4);  140 x 560 53.7 (2: 54.2);  160 x 950 99 (2: 101).  Forward of 154 ... 226 slices, whole up to 1150 rows:  154 x 1034
+//   41 (4: 45);  165 x 1100 51.1 (4: 52.1);  176 x 1034 48 (4: 58);  183 x 1034 45.7 (4: 57.7; errors 1.46e-7 and 1.48e-7);  192 x 1150 61.3 (4:
+//   64.8), x 1200 65.6 (4: 60.6);  205 x 1150 63.8 (3: 64.9).  (The forward of 32 x 3600 is faster in 15 parts of 256 rows, 33 to 39, but
 //   these are not summed apart: error 1.8e-7 against 1.5e-7.)
 long wide_splits32(long BH, long N, int D, bool bwd) {
   if (N <= 256) return 1;  // (calls of this length need no workspace)
@@ -258,7 +260,9 @@ long wide_splits32(long BH, long N, int D, bool bwd) {
     return up_to(N * BH > 180000 || (BH > 32 && N > 2400) ? one : N > 450 * few ? one / 2 : few, most);
   }
   if (!bwd) {
-    if (N > (one == 1 ? 1300 * BH / kUnits : 550 * one)) return up_to(one == 1 || 200 * three > 318 * two ? three : two, long_parts);
+    long far = one == 1 ? 1300 * BH / kUnits : 550 * one;
+    if (BH >= 154 && far < 1150) far = 1150;
+    if (N > far) return up_to(one == 1 || 200 * three > 318 * two ? three : two, long_parts);
     return N <= 200 + 2 * BH ? 1 : up_to(one, most);
   }
   if (BH > 128 && BH <= 150 && N > 600 && N <= 8 * BH) return 2;

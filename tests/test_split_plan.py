@@ -50,6 +50,7 @@ def test_split_rule(slices, N, dtype, splits):
     (64, 1800, 128, 4, 2), (86, 331, 128, 2, 1), (128, 330, 128, 1, 1), (128, 2000, 128, 2, 1), (129, 256, 128, 1, 1), (255, 4000, 128, 1, 1),
     # two pieces per row: up to three workgroups per compute unit
     (1, 3500, 64, 28, 28), (20, 1000, 64, 8, 4), (32, 1000, 64, 8, 8), (64, 328, 64, 1, 1), (64, 420, 64, 4, 1), (64, 1800, 64, 4, 4), (90, 3500, 64, 8, 8),
+    (153, 800, 64, 4, 1), (154, 1150, 64, 1, 1), (154, 1151, 64, 4, 1), (192, 1150, 64, 1, 1), (226, 1150, 64, 1, 1), (226, 1151, 64, 3, 1),
     (129, 600, 64, 1, 1), (129, 601, 64, 1, 2), (150, 1000, 64, 4, 2), (151, 1000, 64, 4, 1),
     (128, 1000, 64, 2, 1), (150, 1800, 64, 5, 5), (200, 1600, 64, 3, 1), (250, 1200, 64, 1, 1),
 ])
@@ -124,7 +125,7 @@ def _parity_in(oracle, d, slices, N, sizes):
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d,slices,N", [
     ("f32", 128, 4, 257), ("f32", 128, 86, 340), ("f32", 128, 150, 290), ("f32", 128, 46, 310), ("f32", 128, 72, 1001), ("f32", 128, 92, 2420), ("f32", 128, 131, 1450), ("f32", 64, 20, 333), ("f32", 64, 64, 421),
-    ("f32", 64, 150, 1300), ("f32", 64, 131, 650), ("f32", 64, 200, 310), ("bf16", 128, 64, 300), ("bf16", 128, 40, 310), ("f16", 128, 128, 520), ("bf16", 128, 48, 700),
+    ("f32", 64, 150, 1300), ("f32", 64, 131, 650), ("f32", 64, 154, 1150), ("f32", 64, 154, 1151), ("f32", 64, 200, 310), ("bf16", 128, 64, 300), ("bf16", 128, 40, 310), ("f16", 128, 128, 520), ("bf16", 128, 48, 700),
     ("bf16", 128, 32, 1300), ("f16", 128, 150, 1300),
 ])
 def test_wide_rows_on_both_sides_of_the_split_rule(oracle, dtype, d, slices, N):
