@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from paper_2602_06935_amd import binding
-from tests.gpu_util import bar_for, check_tensor, to_f64, to_gpu
+from tests.gpu_util import bar_for, check_tensor, rel_l2, to_f64, to_gpu
 
 F32, BF16, F16 = binding.COTTEN_F32, binding.COTTEN_BF16, binding.COTTEN_F16
 
@@ -141,6 +141,46 @@ def test_wide_rows_on_both_sides_of_the_split_rule(oracle, dtype, d, slices, N):
 def test_both_sides_of_the_split_rule(oracle, dtype, slices, N):
     print(f"[split plan] {dtype} {slices} x {N}", flush=True)
     _parity(oracle, dtype, 32 if dtype == "f32" else 64, slices, N)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,slices,N", [(128, 129, 1401), (128, 72, 1010), (64, 131, 650), (64, 160, 1100), (32, 150, 400)])
+def test_options_where_the_rule_cuts(oracle, d, slices, N):
+    """Kept state, d loss / d log(scale), ELU + 1, and a captured call replayed three times, in fp32."""
+    print(f"[split plan] options d={d} {slices} x {N}", flush=True)
+    rng = np.random.default_rng(91 + N)
+    Q, K, V, dO = (rng.standard_normal((slices, 1, N, d)).astype(np.float32) for _ in range(4))
+    mask = (np.arange(N)[None, :] >= rng.integers(0, N, slices)[:, None]).astype(np.uint8)
+    q, k, v, g = (to_gpu(x, "f32") for x in (Q, K, V, dO))
+    m = torch.from_numpy(mask).cuda()
+    state, dlog = torch.zeros(slices, 1, d, d, device="cuda"), torch.zeros(slices, 1, device="cuda")
+    O = binding.cotten_attn_fwd(q, k, v, m, saved_state=state)
+    grads = binding.cotten_attn_bwd(q, k, v, m, g, dlog_scale=dlog)
+    kept = binding.cotten_attn_bwd(q, k, v, m, g, saved_state=state)
+    elu = (binding.cotten_attn_fwd(q, k, v, m, feature_map="elu1"), *binding.cotten_attn_bwd(q, k, v, m, g, feature_map="elu1"))
+    torch.cuda.synchronize()
+    bar = bar_for("f32")
+    ref_o, refs = oracle.fwd_linear(Q, K, V, mask), oracle.bwd(Q, K, V, dO, mask)
+    assert rel_l2(state.double().cpu().numpy(), oracle.state(K, V, mask)) <= bar
+    for name, got, ref in zip(("O", "dQ", "dK", "dV", "dQ", "dK", "dV"), (O, *grads, *kept), (ref_o, *refs, *refs)):
+        check_tensor(name, to_f64(got), ref, bar)
+    few = [np.ascontiguousarray(x[-4:]) for x in (Q, K, V, dO)]  # (that oracle works from the N x N definition)
+    for name, got, ref in zip(("O", "dQ", "dK", "dV"), elu, (oracle.elu_fwd(*few[:3], mask[-4:].copy()), *oracle.elu_bwd(*few, mask[-4:].copy()))):
+        check_tensor(name, to_f64(got[-4:]), ref, bar)
+    ref_dlog = (dO.astype(np.float64) * ref_o).sum(axis=(2, 3))
+    size = np.sqrt(((dO.astype(np.float64) * ref_o) ** 2).sum(axis=(2, 3)))  # a sum with cancellation
+    assert np.all(np.abs(dlog.double().cpu().numpy() - ref_dlog) <= bar * np.maximum(size, np.abs(ref_dlog)))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        again = (binding.cotten_attn_fwd(q, k, v, m), *binding.cotten_attn_bwd(q, k, v, m, g))
+    for _ in range(3):
+        for t in again:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(again, (O, *grads)))
 
 
 def _parity(oracle, dtype, d, slices, N, workspaces=(None, None)):
