@@ -586,14 +586,15 @@ __global__ __launch_bounds__(64 * WAVES) void wide_bwd_kernel(const LaunchArgs a
 //
 // LDS: [SETS x four images][per wave: four tiles, 16 floats]; the tile sets double as the round
 // buffer of the state phase and as the place where accumulators meet.
-template <class F, int SETS>
+template <class F, int SETS, int WAVES = 8>
 struct FusedLds {
-  static constexpr int kWaves = 8;
+  static constexpr int kWaves = WAVES;
   static constexpr int kSetBytes = 4 * F::kImageBytes;
   static constexpr int kTiles = SETS * kSetBytes;
   static constexpr int kWaveBytes = 4 * kTileBytes + TR * 4;
   static constexpr int kBytes = kTiles + kWaves * kWaveBytes;
-  static_assert(4 * F::Acc::kGroups * 64 * 16 + 64 <= kWaves * kWaveBytes, "accumulators meet in the tile sets");
+  static_assert(WAVES == 4 || 4 * F::Acc::kGroups * 64 * 16 + 64 <= kWaves * kWaveBytes,
+                "accumulators meet in the tile sets (four waves: each has a quadrant to itself)");
 };
 
 // The state phase of a group of four waves (wave & 3: the quadrant): every wave stages the 16 rows
@@ -694,31 +695,19 @@ __global__ __launch_bounds__(512) void wide_fused_fwd_kernel(const LaunchArgs a,
   plain_tiles<F, 8, true, true>(r, images, sets + L.wave * Lds::kWaveBytes, L, &first);
 }
 
-// The forward with two slices per workgroup (waves 0-3 one slice, waves 4-7 the next), for
-// launches with more slices than compute units: the LDS of a compute unit admits one of these
-// workgroups at a time, and two slices that share it overlap their waits.  A group of four waves
-// owns its slice completely (one quadrant per wave, rounds of 64 rows, no sums to meet), so the
-// only thing the two groups share is the barriers of the state phase.
+// A group of four waves owns its slice completely: one quadrant of the state per wave, rounds of 64 rows, no sums
+// to meet.  `rows`: N, or 0 where the group has no slice and only keeps step.
 template <class F>
-__global__ __launch_bounds__(512) void wide_paired_fwd_kernel(const LaunchArgs a, int slices,
-                                                              float* __restrict__ kept) {
-  using Lds = FusedLds<F, 2>;
-  constexpr int Dh = F::D, D = 2 * Dh;
-  const Lane L;
-  const int quadrant = L.wave & 3, group = L.wave >> 2;
-  const int slice = 2 * blockIdx.x + group;
-  const bool exists = slice < slices;
-  const int bh = exists ? slice : 0;
-  const int rows = exists ? a.N : 0;
+__device__ __forceinline__ void owned_slice_fwd(const LaunchArgs& a, int bh, int rows, unsigned char* images,
+                                                unsigned char* sets, float* __restrict__ kept, const Lane& L) {
+  constexpr int kWaveBytes = FusedLds<F, 1>::kWaveBytes, Dh = F::D, D = 2 * Dh;
+  const int quadrant = L.wave & 3;
   const size_t base = a.st.slice_base(bh, a.H);
-  unsigned char* images = smem + group * Lds::kSetBytes;
-  unsigned char* sets = smem + Lds::kTiles;
   typename F::Acc acc;
   {
     const WideSrc kv(a.K + base, a.V + base, a.N, a.st.row.stride);
     const uint8_t* keys = a.mask == nullptr ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * a.N;
-    fused_state_pass<F, Lds::kWaveBytes>(acc, kv, keys, a.N, quadrant * TR, 4 * TR, a.eps, sets, L, false,
-                                         rows);
+    fused_state_pass<F, kWaveBytes>(acc, kv, keys, a.N, quadrant * TR, 4 * TR, a.eps, sets, L, false, rows);
   }
   const float scale = a.slice_scale != nullptr ? a.slice_scale[bh] : a.scale;
   Lane Lg = L;  // the wave's place in its group
@@ -737,7 +726,7 @@ __global__ __launch_bounds__(512) void wide_paired_fwd_kernel(const LaunchArgs a
   request_first_tile<4>(first, r, Lg);
   const auto own = [&](int g) { return acc.group(g); };
   quadrant_image<F, false>(own, scale, images + quadrant * F::kImageBytes, L);
-  if (kept != nullptr && exists) {  // S as it is, row-major, for the caller's backward call
+  if (kept != nullptr && rows > 0) {  // S as it is, row-major, for the caller's backward call
     float* __restrict__ out = kept + static_cast<size_t>(bh) * D * D;
     const int p = quadrant >> 1, q = quadrant & 1;
 #pragma unroll
@@ -749,7 +738,25 @@ __global__ __launch_bounds__(512) void wide_paired_fwd_kernel(const LaunchArgs a
     }
   }
   __syncthreads();
-  plain_tiles<F, 4, true, true>(r, images, sets + L.wave * Lds::kWaveBytes, Lg, &first);
+  plain_tiles<F, 4, true, true>(r, images, sets + L.wave * kWaveBytes, Lg, &first);
+}
+
+// The forward with a workgroup of four waves per slice, two of them on a compute unit, each slice at a pace of its own.
+template <class F>
+__global__ __launch_bounds__(256, 2) void wide_small_fwd_kernel(const LaunchArgs a, float* __restrict__ kept) {
+  owned_slice_fwd<F>(a, blockIdx.x, a.N, smem, smem + FusedLds<F, 1, 4>::kTiles, kept, Lane());
+}
+
+// The forward with two slices per workgroup (waves 0-3 one slice, waves 4-7 the next), which share the barriers.
+template <class F>
+__global__ __launch_bounds__(512) void wide_paired_fwd_kernel(const LaunchArgs a, int slices,
+                                                              float* __restrict__ kept) {
+  using Lds = FusedLds<F, 2>;
+  const Lane L;
+  const int group = L.wave >> 2, slice = 2 * blockIdx.x + group;
+  const bool exists = slice < slices;
+  owned_slice_fwd<F>(a, exists ? slice : 0, exists ? a.N : 0, smem + group * Lds::kSetBytes, smem + Lds::kTiles, kept,
+                     L);
 }
 
 // d loss / d log(scale) = scale <S, dS> of the slice: the dS accumulators (waves 4-7) meet the S
@@ -1121,12 +1128,23 @@ hipError_t fused(const Problem& p, const Plan& plan, bool bwd) {
                          : reinterpret_cast<const void*>(wide_fused_fwd_kernel<F>);
   const hipError_t err = grant_dynamic_lds(kern, max_lds_bytes<8>());
   if (err != hipSuccess) return err;
-  if (!bwd && blocks > static_cast<unsigned>(kUnits)) {  // two slices per workgroup
+  // Forward, more slices than compute units: four waves per slice.  A workgroup each while all of them run at once (in pairs,
+  // 260 slices would leave every other compute unit idle) or the sequences are shorter than a round or little more, pairs in
+  // one workgroup beyond.  us, pairs and one each, bf16: 260 x 200 rows 17.5, 15.2;  300 x 200 18.1, 16.5;  512 x 100 11.1, 10.8;
+  // 2048 x 20 20.5, 19.0;  1024 x 50 12.8, 12.4;  1024 x 200 35.8, 37.3.
+  if (!bwd && blocks > static_cast<unsigned>(kUnits)) {
+    constexpr int lds_small = FusedLds<F, 1, 4>::kBytes;
+    static_assert(lds_small <= max_lds_bytes<4>(), "two workgroups per compute unit");
+    const bool small = blocks <= static_cast<unsigned>(2 * kUnits) || p.N <= 64;
     const hipError_t e2 =
-        grant_dynamic_lds(reinterpret_cast<const void*>(wide_paired_fwd_kernel<F>), max_lds_bytes<8>());
+        small ? grant_dynamic_lds(reinterpret_cast<const void*>(wide_small_fwd_kernel<F>), max_lds_bytes<4>())
+              : grant_dynamic_lds(reinterpret_cast<const void*>(wide_paired_fwd_kernel<F>), max_lds_bytes<8>());
     if (e2 != hipSuccess) return e2;
-    hipLaunchKernelGGL((wide_paired_fwd_kernel<F>), dim3((blocks + 1) / 2), dim3(512), lds_bwd, p.stream,
-                       a, static_cast<int>(blocks), p.saved_state);
+    if (small)
+      hipLaunchKernelGGL((wide_small_fwd_kernel<F>), dim3(blocks), dim3(256), lds_small, p.stream, a, p.saved_state);
+    else
+      hipLaunchKernelGGL((wide_paired_fwd_kernel<F>), dim3((blocks + 1) / 2), dim3(512), lds_bwd, p.stream, a,
+                         static_cast<int>(blocks), p.saved_state);
     return hipGetLastError();
   }
   if (bwd)

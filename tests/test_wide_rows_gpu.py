@@ -146,3 +146,12 @@ def test_wide_rows_without_mask(oracle, dtype, B, H, N, d):
     bar = bar_for(dtype)
     for n, g, r in zip(("O", "dQ", "dK", "dV"), (O, *grads), (ref_o, *ref_g)):
         check_tensor(n, to_f64(g), r, bar)
+
+
+@pytest.mark.parametrize("dtype,B,H,N,d", [
+    ("f16", 257, 1, 65, 128), ("bf16", 256, 2, 63, 128),    # forward: a workgroup of four waves per slice
+    ("bf16", 171, 3, 64, 128),                              # beyond 512 slices, still one round
+    ("bf16", 171, 3, 65, 128),                              # pairs, the last slice alone
+])
+def test_wide_forward_of_many_slices(oracle, dtype, B, H, N, d):
+    test_wide_rows_parity(oracle, dtype, B, H, N, d)
