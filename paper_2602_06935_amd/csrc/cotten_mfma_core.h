@@ -191,6 +191,18 @@ struct Half64 {
     return 16 * (2 * (n >> 5) + ((n >> 2) & 1)) + 4 * ((n >> 3) & 3) + (n & 3);
   }
 
+  // Products over 32 rows (32x32x16, W^T X^T as well) leave lane (row lane%32, half lane/32) with the columns
+  // 32 nb + 16 t + 8 half .. + 7 (t = 0, 1: values 8 t .. of block nb), which is also what it holds of X: 16 bytes of
+  // every 32.  Their images keep row n at rows32(n).
+  struct Image32 {
+    static __device__ __forceinline__ int rows32(int n) { return (n & ~12) | ((n & 4) << 1) | ((n & 8) >> 1); }
+    static __device__ __forceinline__ int image_offset(int n, int k) { return (rows32(n) * kImageStride + k) * 2; }
+  };
+  // operand of columns 32 nb .. + 31 and the k of step ks (16 each)
+  static __device__ __forceinline__ v8_t operand32(const unsigned char* image, int nb, int ks, const Lane& L) {
+    return *reinterpret_cast<const v8_t*>(image + ((32 * nb + (L.lane & 31)) * kImageStride + 16 * ks + 8 * (L.lane >> 5)) * 2);
+  }
+
   static __device__ __forceinline__ void unpack(const u32x4_t r, float (&f)[8]) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1260,7 +1272,8 @@ __device__ __forceinline__ void own_rows(const OwnRaw<P>& t, typename F::TileRow
 // one column) into its operand image: transposed straight from the lane (two row pairs of its
 // column), natural with the neighbouring lane's column (even lanes write the first two rows of a
 // group, odd lanes the last two; each gets the other column of its rows from its neighbour).
-template <class F, bool NATURAL, class Get>
+// IMAGE: the order of the image's rows (F, or F::Image32).
+template <class F, bool NATURAL, class IMAGE = F, class Get>
 __device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned char* image, const Lane& L) {
   // (row, column) of the first value of a group = a part that depends on the lane only plus a
   // part that depends on the group only; the image offsets of the two add up, so the second
@@ -1269,8 +1282,27 @@ __device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned ch
   const bool odd = (lane_col & 1) != 0;
   Lane zero = L;
   zero.set(0);
-  unsigned char* at = image + (NATURAL ? F::image_offset(lane_row + (odd ? 2 : 0), lane_col & ~1)
-                                       : F::image_offset(lane_col, lane_row));
+  unsigned char* at = image + (NATURAL ? IMAGE::image_offset(lane_row + (odd ? 2 : 0), lane_col & ~1)
+                                       : IMAGE::image_offset(lane_col, lane_row));
+  if constexpr (NATURAL && F::kElemBytes == 2) {
+    // 16 bits: rounded first, so that one move per group brings the neighbour's column of both rows
+    const uint32_t lows = odd ? 0x01000504u : 0x05040100u, highs = odd ? 0x03020706u : 0x07060302u;
+#pragma unroll
+    for (int g = 0; g < F::Acc::kGroups; ++g) {
+      const f32x4_t v = get(g) * scale;
+      const int row = F::Acc::group_row(g, zero), col = F::Acc::group_col(g, zero);
+      const uint32_t first = F::Elem::pack2(v[0], v[1]), second = F::Elem::pack2(v[2], v[3]);
+      const uint32_t mine = odd ? second : first;
+      int sent = static_cast<int>(odd ? first : second);  // (chosen on the sending side, see below)
+      asm volatile("" : "+v"(sent));
+      int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
+      asm volatile("" : "+v"(got));
+      // (mine: bytes 0 ... 3 of the pair of words, got: 4 ... 7)
+      *reinterpret_cast<uint32_t*>(at + IMAGE::image_offset(row, col)) = __builtin_amdgcn_perm(got, mine, lows);
+      *reinterpret_cast<uint32_t*>(at + IMAGE::image_offset(row + 1, col)) = __builtin_amdgcn_perm(got, mine, highs);
+    }
+    return;
+  }
   float top = 0.0f;
   if (F::kPieces) {
 #pragma unroll
@@ -1283,7 +1315,7 @@ __device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned ch
       const f32x4_t v = get(g) * scale;
       const int row = F::Acc::group_row(g, zero), col = F::Acc::group_col(g, zero);  // the group's part
       if (!NATURAL) {
-        F::template write_four_at<kInf>(at + F::image_offset(col, row), v);
+        F::template write_four_at<kInf>(at + IMAGE::image_offset(col, row), v);
       } else {
         // The lane sends what its neighbour wants (the choice is made on the sending side: a
         // choice between two values received from the neighbour would be evaluated over there).
@@ -1295,7 +1327,7 @@ __device__ __forceinline__ void quadrant_image(Get get, float scale, unsigned ch
           int got = __builtin_amdgcn_update_dpp(0, sent, 0xB1, 0xF, 0xF, true);  // lane ^ 1
           asm volatile("" : "+v"(got));
           const float other = __builtin_bit_cast(float, got);
-          F::template write_pair_at<kInf>(at + F::image_offset(row + i, col), odd ? other : mine, odd ? mine : other);
+          F::template write_pair_at<kInf>(at + IMAGE::image_offset(row + i, col), odd ? other : mine, odd ? mine : other);
         }
       }
     }

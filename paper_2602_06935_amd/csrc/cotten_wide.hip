@@ -52,7 +52,7 @@ struct WideSrc {
   int stride;
   __device__ __forceinline__ WideSrc(const unsigned char* X, const unsigned char* Y, int N, int stride_bytes)
       : stride(stride_bytes) {
-    const int bytes = (N - 1) * stride + P * kHalfBytes;
+    const int bytes = N > 0 ? (N - 1) * stride + P * kHalfBytes : 0;
     x = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(X), 0, bytes, 0x00020000);
     y = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(Y), 0, bytes, 0x00020000);
   }
@@ -848,171 +848,312 @@ __global__ __launch_bounds__(512) void wide_fused_bwd_kernel(const LaunchArgs a,
 
 // ---- short sequences (N <= 256), backward: every tile requested at once and kept in registers -----
 //
-// The backward for sequences of at most 256 rows: a wave asks for all its tiles at the start
+// The backward for sequences of at most 256 rows: a wave asks for all its rows at the start
 // (everything the slice needs is in flight together) and keeps them in registers, so the apply
-// roles read nothing again.  Waves 0-3, which hold (K, V) tiles, compute dV and dK for them and
-// waves 4-7, which hold (Q, dO) tiles, dQ; all three image sets are written as
-// soon as the states are complete (LDS: [S natural | dS natural | dS transposed][per wave: two
-// tiles, 16 floats]; the unit rows and the other tensor's rows of a tile take turns in the two
-// tiles), and the two round buffers of the state phase lie over the same memory.
+// roles read nothing again.  Waves 0-3, which hold rows of (K, V), compute dV and dK for them and
+// waves 4-7, which hold rows of (Q, dO), dQ; all three image sets are written as soon as the states are
+// complete (LDS: [S natural | dS natural | dS transposed], and over the same memory the two round buffers
+// of the state phase).  A wave holds 32 consecutive rows at a time, 16 staged per round; when both halves are
+// staged it reads them back as it needs them for products over 32 rows (xhat and y, 16 of every 32 bytes of
+// a row): these take half the operand reads of products over 16, and nothing is staged or normalised again.
+//
+// Bound by what follows one another in a workgroup (one per compute unit): the first rows' way from memory, the states, the
+// images, the products, the stores.  us, products over 16 rows staged again and this, bf16: 1024 slices x 200 rows 88.4, 81.1 (3.9
+// TB/s); 512 x 100 27.6, 23.2; 300 x 256 45.1, 42.2; 90 x 200 20.7, 17.3; 1024 x 50 35.9, 31.2; ELU + 1, 512 x 200 53.3, 46.1.
 constexpr int kKeptRows = 256;
+// Sequences of so many rounds of 64 rows: a workgroup takes one slice after the other, the next one's rows requested ahead.  Longer
+// ones leave no registers for that (1024 x 50 rows 35.0 without, 31.2; two rounds, 1024 x 128: 47.1 without, 49.5; four, 300 x 256: 42.2, 47.2).
+constexpr int kAheadRounds = 1;
 
 template <class F>
 struct KeptLds {
   static constexpr int kSetBytes = 4 * F::kImageBytes;
-  static constexpr int kTiles = 3 * kSetBytes;
-  static constexpr int kWaveBytes = 2 * kTileBytes + TR * 4;
   static constexpr int kRoundWave = 4 * kTileBytes;  // state phase: two round buffers from offset 0
   static constexpr int kRoundBuffer = 8 * kRoundWave;
-  static constexpr int kBytes =
-      kTiles + 8 * kWaveBytes > 2 * kRoundBuffer ? kTiles + 8 * kWaveBytes : 2 * kRoundBuffer;
+  static constexpr int kBytes = 3 * kSetBytes > 2 * kRoundBuffer ? 3 * kSetBytes : 2 * kRoundBuffer;
   static_assert(4 * F::Acc::kGroups * 64 * 16 + 64 <= kBytes, "accumulators meet in the same memory");
 };
 
-// The state phase over tiles already in registers (see fused_state_pass); `rounds`: how many of
-// them hold rows of the sequence.  Two round buffers (the second `SECOND_BUFFER` bytes behind the
-// first) take turns: the tiles of the next round are staged while those of this one are added
-// up, one barrier per round.  Ends with a barrier (the buffers are free).
-template <class F, int ROUNDS, int WAVE_BYTES, int SECOND_BUFFER>
+// 32 rows of a tensor pair in the layout of products over 32 rows: chunk c is bytes 32 c + 16 half .. + 15 of row
+// lane%32, half = lane/32.  inv: 1/r of the row (see stage_wide).
+template <class F>
+struct Rows32 {
+  typename F::v8_t x[8], y[8];
+  float inv;
+  bool live;  // a row takes part (uniform)
+};
+
+// The two staged tiles of a wave (`first`: rows 0-15, `second`: rows 16-31, each [xhat pieces | y pieces] with 1/r in
+// the padding of the first piece's rows).
+template <class F>
+__device__ __forceinline__ void fetch_rows32(Rows32<F>& t, const unsigned char* first, const unsigned char* second,
+                                             bool has_second, const Lane& L) {
+  const unsigned char* at = ((L.lane & 16) != 0 && has_second ? second : first) + L.i16 * kTileStride;
+  const int half = 16 * (L.lane >> 5);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const unsigned char* piece = at + (c >> 2) * kTileBytes + 32 * (c & 3) + half;
+    t.x[c] = *reinterpret_cast<const typename F::v8_t*>(piece);
+    t.y[c] = *reinterpret_cast<const typename F::v8_t*>(piece + P * kTileBytes);
+  }
+  t.inv = *reinterpret_cast<const float*>(at + kRowBytes);
+}
+
+// The state phase over tiles already in registers (see fused_state_pass).  Two round buffers take turns: the tiles of the
+// next round are staged while those of this one are added up, one barrier per round.  Ends with a barrier (the
+// buffers are free).  An odd number of rounds: the last rows are 16, twice.
+template <class F, int ROUNDS>
 __device__ __forceinline__ void kept_state_pass(typename F::Acc& acc, const WideRaw (&kept)[ROUNDS],
-                                                int rounds, float eps, unsigned char* sets,
-                                                const Lane& L, bool swapped) {
-  const int quadrant = L.wave & 3, p = quadrant >> 1, q = quadrant & 1, group = L.wave >> 2;
+                                                Rows32<F> (&rows)[(ROUNDS + 1) / 2], float eps, const Lane& L0,
+                                                bool swapped) {
+  constexpr int kRoundWave = KeptLds<F>::kRoundWave, kSecond = KeptLds<F>::kRoundBuffer;
+  const int quadrant = L0.wave & 3, p = quadrant >> 1, q = quadrant & 1, group = L0.wave >> 2;
   const int left = (swapped ? 2 + q : p) * kTileBytes, right = (swapped ? p : 2 + q) * kTileBytes;
-  unsigned char* mine = sets + L.wave * WAVE_BYTES;
+  unsigned char* mine = smem + L0.wave * kRoundWave;
+  const auto stage = [&](int r) {
+    const Lane L = L0.again();
+    float inv[2];
+    unsigned char* tiles = mine + (r & 1) * kSecond;
+    stage_wide<F, mapped_mode<F>(), true>(kept[r], L, eps, tiles, inv);
+    if (L.ch == 0) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) *reinterpret_cast<float*>(tiles + (L.r8 + 8 * h) * kTileStride + kRowBytes) = inv[h];
+    }
+  };
   acc.zero();
-  float inv[2];
-  stage_wide<F, mapped_mode<F>(), true>(kept[0], L, eps, mine, inv);
+  stage(0);
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    if (r < rounds) {
-      __syncthreads();  // round r is staged; nobody reads the other buffer any more
-      if (r + 1 < ROUNDS && r + 1 < rounds)
-        stage_wide<F, mapped_mode<F>(), true>(kept[r + 1 < ROUNDS ? r + 1 : 0], L, eps,
-                                  mine + ((r + 1) & 1) * SECOND_BUFFER, inv);
+    __syncthreads();  // round r is staged; nobody reads the other buffer any more
+    const Lane L = L0.again();
+    if ((r & 1) != 0 || r + 1 == ROUNDS) {  // (the wave's own tiles: written before the barrier)
+      Rows32<F>& t = rows[r / 2];
+      fetch_rows32<F>(t, mine, mine + kSecond, (r & 1) != 0, L);
+      t.live = __builtin_amdgcn_ballot_w64((kept[r & ~1].live | ((r & 1) != 0 ? kept[r].live : 0)) != 0) != 0;
+      wave_lds_fence();
+    }
+    if (r + 1 < ROUNDS) stage(r + 1 < ROUNDS ? r + 1 : 0);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const unsigned char* tile = sets + (r & 1) * SECOND_BUFFER + (4 * group + t) * WAVE_BYTES;
-        acc.mfma(tile + left, tile + right, L);
-      }
+    for (int t = 0; t < 4; ++t) {
+      const unsigned char* tile = smem + (r & 1) * kSecond + (4 * group + t) * kRoundWave;
+      acc.mfma(tile + left, tile + right, L);
     }
   }
   __syncthreads();
 }
 
-// The y rows of a tile, as they are, into the two tiles of a wave.
-__device__ __forceinline__ void stage_y(const WideRaw& r, const Lane& L, unsigned char* tiles) {
+// Block nb of the rows (values 8 t .. of a lane: 16 bytes at 64 nb + 32 t + 16 half of its row).  The lanes of rows 0-15
+// and 16-31 exchange chunks first, so that a store writes 64 contiguous bytes of each of 16 rows: with 32 of
+// each of 32 the streamed stores reach memory as parts of lines (1024 slices x 200 rows, backward: 220 us).
+struct StoreRows32 {
+  __amdgpu_buffer_rsrc_t out;  // ends with row end - 1: rows beyond are dropped without a branch
+  uint32_t at;                 // of the first store: row lane%16, bytes 32 (group & 1) + 16 (group / 2)
+  int stride;
+  __device__ __forceinline__ StoreRows32(unsigned char* base, int row0, int end, int stride_bytes, const Lane& L)
+      : out(__builtin_amdgcn_make_buffer_rsrc(base, 0, end > row0 ? (end - 1) * stride_bytes + P * kHalfBytes : 0, 0x00020000)),
+        at(static_cast<uint32_t>(row0 + L.i16) * stride_bytes + 32 * (L.g16 & 1) + 16 * (L.g16 >> 1)),
+        stride(stride_bytes) {}
+  template <class F>
+  __device__ __forceinline__ void store(int nb, const f32x16_t& v) const {
+    u32x4_t t[2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int off = (L.r8 + 8 * h) * kTileStride + L.ch * 16;
+    for (int k = 0; k < 2; ++k) {
+      float f[8];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) *reinterpret_cast<u32x4_t*>(tiles + c * kTileBytes + off) = r.y[h][c];
+      for (int i = 0; i < 8; ++i) f[i] = v[8 * k + i];
+      t[k] = F::pack(f);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const auto swapped = __builtin_amdgcn_permlane16_swap(t[0][i], t[1][i], false, false);
+      t[0][i] = swapped[0];
+      t[1][i] = swapped[1];
+    }
+    __builtin_amdgcn_raw_buffer_store_b128(t[0], out, at + 64 * nb, 0, kStoreStreamed);
+    __builtin_amdgcn_raw_buffer_store_b128(t[1], out, at + 16 * stride + 64 * nb, 0, kStoreStreamed);
+  }
+};
+
+// Blocks 0 and 1 of a half row of the product of 32 rows X with the images first, first + step: sum over the halves of X.
+// (Two chains of products that wait for themselves only.)
+template <class F>
+__device__ __forceinline__ void blocks32(const typename F::v8_t (&X)[8], const unsigned char* images, int first,
+                                         int step, const Lane& L, f32x16_t& v0, f32x16_t& v1) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v0[i] = v1[i] = 0.0f;
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const unsigned char* image = images + (first + (c >> 2) * step) * F::kImageBytes;
+    v0 = F::Elem::mfma32(F::operand32(image, 0, c & 3, L), X[c], v0);
+    v1 = F::Elem::mfma32(F::operand32(image, 1, c & 3, L), X[c], v1);
   }
 }
 
-// One kept tile in the backward: xhat rows staged, then (K tiles only) dV = khat (scale dS); the y
-// rows staged over them, g = y (natural images)^T and out = (g - xhat (xhat . g)) / r.
+// 32 kept rows in the backward: (K rows only) dV = khat (scale dS), then g = y (natural images)^T and
+// out = (g - xhat (xhat . g)) / r.
 template <class F>
-__device__ __forceinline__ void kept_tile_bwd(const WideRaw& t, int row0, int N, bool plain_too,
-                                              const unsigned char* natural,
-                                              const unsigned char* transposed,
-                                              unsigned char* out_projected, unsigned char* out_plain,
-                                              int stride, float eps, unsigned char* tiles,
+__device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, bool plain_too,
+                                              const unsigned char* natural, const unsigned char* transposed,
+                                              unsigned char* out_projected, unsigned char* out_plain, int stride,
                                               const Lane& L) {
-  if (tile_dead(t)) {
-    if (plain_too) store_zero_rows<F>(out_plain, row0, N, stride, L);
-    store_zero_rows<F>(out_projected, row0, N, stride, L);
+  const StoreRows32 projected(out_projected, row0, end, stride, L), plain(out_plain, row0, end, stride, L);
+  if (!t.live) {  // zeros
+    f32x16_t z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      if (plain_too) plain.store<F>(nb, z);
+      projected.store<F>(nb, z);
+    }
     return;
   }
-  float* inv_slot = reinterpret_cast<float*>(tiles + 2 * kTileBytes);
-  float inv[2];
-  stage_wide<F, mapped_mode<F>(), false>(t, L, eps, tiles, inv);
-  const float inv_r = inv_by_row(inv_slot, L, inv);
-  typename F::TileRows E[2];
-  E[0].load(tiles, L);
-  E[1].load(tiles + kTileBytes, L);
-  const int row = row0 + L.i16;
   if (plain_too) {
-    const Quadrants<F, false> W(transposed, L);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      float o[2 * F::EPL];
-      W.apply(E, q, 2, L, o);
-      if (row < N)
-        store_product_row<F, kStoreStreamed>(out_plain + q * kHalfBytes, row, RowAddr{stride, kHalfBytes}, L, o);
+      f32x16_t o[2];
+      blocks32<F>(t.x, transposed, q, 2, L, o[0], o[1]);
+      plain.store<F>(2 * q, o[0]);
+      plain.store<F>(2 * q + 1, o[1]);
     }
   }
-  wave_lds_fence();
-  stage_y(t, L, tiles);
-  wave_lds_fence();
-  typename F::TileRows Y[2];
-  Y[0].load(tiles, L);
-  Y[1].load(tiles + kTileBytes, L);
-  const Quadrants<F, false> W(natural, L);
-  float g[2][2 * F::EPL];
+  f32x16_t g[4];
 #pragma unroll
-  for (int p = 0; p < 2; ++p) W.apply(Y, 2 * p, 1, L, g[p]);
-  finish_projected<F>(g, E, inv_r, L);
+  for (int p = 0; p < 2; ++p) blocks32<F>(t.y, natural, 2 * p, 1, L, g[2 * p], g[2 * p + 1]);
+  const auto unit = [&](int c, float (&u)[8]) { F::unpack(__builtin_bit_cast(u32x4_t, t.x[c]), u); };
+  if (F::kMap == kMapElu1) {
 #pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    if (row < N)
-      store_product_row<F, kStoreStreamed>(out_projected + p * kHalfBytes, row, RowAddr{stride, kHalfBytes}, L, g[p]);
+    for (int c = 0; c < 8; ++c) {
+      float u[8];
+      unit(c, u);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) g[c >> 1][8 * (c & 1) + i] *= fminf(u[i], 1.0f);
+    }
+  } else {
+    float proj = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      float u[8];
+      unit(c, u);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) proj += u[i] * g[c >> 1][8 * (c & 1) + i];
+    }
+    proj += __shfl_xor(proj, 32);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      u32x4_t again = __builtin_bit_cast(u32x4_t, t.x[c]);  // (unpacked again rather than kept: 64 registers)
+      asm volatile("" : "+v"(again));
+      float u[8];
+      F::unpack(again, u);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) g[c >> 1][8 * (c & 1) + i] = (g[c >> 1][8 * (c & 1) + i] - u[i] * proj) * t.inv;
+    }
   }
-  wave_lds_fence();
+#pragma unroll
+  for (int nb = 0; nb < 4; ++nb) projected.store<F>(nb, g[nb]);
 }
 
-template <class F>
-__global__ __launch_bounds__(512) void wide_kept_bwd_kernel(const LaunchArgs a, float* __restrict__ dlog) {
+// For sequences of ROUNDS rounds of 64 rows.  A workgroup takes slices blockIdx.x, + gridDim.x, ... (ROUNDS <= kAheadRounds; the
+// others one), the rows of the next one requested when this one's are no longer needed.  (No branch around
+// loads or rounds: what is held would no longer fit the registers.)
+template <class F, int ROUNDS>
+__global__ __launch_bounds__(512) void wide_kept_bwd_kernel(const LaunchArgs a, int slices, float* __restrict__ dlog) {
   using Lds = KeptLds<F>;
-  constexpr int kRounds = kKeptRows / (4 * TR);
-  const Lane L;
-  const int bh = blockIdx.x;
-  const size_t base = a.st.slice_base(bh, a.H);
-  const int stride = a.st.row.stride;
-  const int quadrant = L.wave & 3;
-  const bool second = L.wave >= 4;  // waves 4-7: (Q, dO) tiles, dS = sum_i qhat_i^T dO_i, dQ
-  // which 16 rows of a round the wave holds: the two waves of a SIMD (w and w + 4) take different
-  // ones, so that the round with a ragged end does not leave both with a tile more than the rest
+  constexpr int kPairs = (ROUNDS + 1) / 2;
+  constexpr bool kAhead = ROUNDS <= kAheadRounds;
+  const Lane L0;
+  const int stride = a.st.row.stride, N = a.N;
+  const int quadrant = L0.wave & 3;
+  const bool second = L0.wave >= 4;  // waves 4-7: (Q, dO) rows, dS = sum_i qhat_i^T dO_i, dQ
+  // Which 32 of 128 rows the wave holds (16, and one round for all of them, where 64 or fewer are left): the two waves of a
+  // SIMD (w and w + 4) take different ones, so that a ragged end does not leave both with more rows than the rest
   const int slot = second ? (quadrant + 2) & 3 : quadrant;
-  WideRaw kept[kRounds];
-  {
-    const WideSrc src((second ? a.Q : a.K) + base, (second ? a.dO : a.V) + base, a.N, stride);
-    const uint8_t* m = (second || a.mask == nullptr) ? nullptr : a.mask + static_cast<size_t>(bh / a.H) * a.N;
+  const auto rows_of = [&](int j) { return 2 * j + 1 < ROUNDS ? 32 : TR; };
+  const auto first_of = [&](int j) { return 128 * j + rows_of(j) * slot; };
+  const auto first_of_round = [&](int r) { return first_of(r / 2) + TR * (r & 1); };
+  // the key mask's bytes of the lane's rows, requested long before the rows
+  const bool masked = !second && a.mask != nullptr;
+  struct KeyBytes {
+    unsigned of[ROUNDS][2];
+  };
+  const auto request_keys = [&](int bh, const Lane& L) {
+    const auto keys = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(a.mask) + (masked ? static_cast<size_t>(bh / a.H) * N : 0), 0, masked ? N : 0, 0x00020000);
+    KeyBytes b;
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-      const int row0 = (4 * r + slot) * TR;
-      load_wide<true>(kept[r], L, src, row0, row_bits(m, row0, a.N, L));
-    }
-  }
-  const int rounds = (a.N + 4 * TR - 1) / (4 * TR);
-  typename F::Acc acc;
+    for (int r = 0; r < ROUNDS; ++r)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        b.of[r][h] = __builtin_amdgcn_raw_buffer_load_b8(keys, first_of_round(r) + L.r8 + 8 * h, 0, 0);
+    return b;
+  };
+  const auto request = [&](WideRaw& t, const WideSrc& src, const KeyBytes& b, int r, const Lane& L) {
+    const int row0 = first_of_round(r);
+    int bits = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      bits |= static_cast<int>(row0 + L.r8 + 8 * h < N && (!masked || b.of[r][h] != 0)) << h;
+    load_wide<true>(t, L, src, row0, bits);
+  };
+  const auto source = [&](int bh, int n) {  // n = 0: nothing is fetched
+    const size_t base = a.st.slice_base(bh, a.H);
+    return WideSrc((second ? a.Q : a.K) + base, (second ? a.dO : a.V) + base, n, stride);
+  };
   // S is needed as natural images only: its waves sum up the transposed quadrants, unless the
   // accumulators of S and dS are to meet lane by lane for <S, dS>
   const bool swapped = !second && dlog == nullptr;
-  kept_state_pass<F, kRounds, Lds::kRoundWave, Lds::kRoundBuffer>(acc, kept, rounds, a.eps, smem, L, swapped);
-  const float scale = a.slice_scale != nullptr ? a.slice_scale[bh] : a.scale;
-  if (dlog != nullptr) state_dot<F>(acc, second, scale, smem, dlog + bh, L);
-  const auto own = [&](int g) { return acc.group(g); };
-  if (swapped) {
-    quadrant_image<F, false>(own, scale, smem + quadrant * F::kImageBytes, L);
-  } else if (!second) {
-    quadrant_image<F, true>(own, scale, smem + quadrant * F::kImageBytes, L);
-  } else {
-    quadrant_image<F, true>(own, scale, smem + Lds::kSetBytes + quadrant * F::kImageBytes, L);
-    quadrant_image<F, false>(own, scale, smem + 2 * Lds::kSetBytes + quadrant * F::kImageBytes, L);
-  }
-  __syncthreads();
-  unsigned char* tiles = smem + Lds::kTiles + L.wave * Lds::kWaveBytes;
-  const unsigned char* natural = smem + (second ? 0 : Lds::kSetBytes);
-  unsigned char* out_projected = (second ? a.dQ : a.dK) + base;
-#pragma unroll 1
-  for (int r = 0; r < rounds; ++r) {
-    const int row0 = (4 * r + slot) * TR;
-    if (row0 < a.N)
-      kept_tile_bwd<F>(kept[0], row0, a.N, !second, natural, smem + 2 * Lds::kSetBytes, out_projected,
-                       a.dV + base, stride, a.eps, tiles, L);
+
+  WideRaw kept[ROUNDS];
+  int bh = blockIdx.x;
+  {
+    // (each masked tile behind the bytes that decide on it, and these behind the tile before: what is needed first comes first)
+    const WideSrc src = source(bh, N);
+    const uint8_t* m = masked ? a.mask + static_cast<size_t>(bh / a.H) * N : nullptr;
 #pragma unroll
-    for (int k = 0; k + 1 < kRounds; ++k) kept[k] = kept[k + 1];
+    for (int r = 0; r < ROUNDS; ++r) load_wide<true>(kept[r], L0, src, first_of_round(r), row_bits(m, first_of_round(r), N, L0));
+  }
+#pragma unroll 1
+  while (true) {
+    const int next = bh + static_cast<int>(gridDim.x);
+    const bool more = next < slices;
+    typename F::Acc acc;
+    Rows32<F> rows[kPairs];
+    kept_state_pass<F, ROUNDS>(acc, kept, rows, a.eps, L0, swapped);
+    const Lane L = L0.again();
+    KeyBytes next_keys;
+    if (kAhead) next_keys = request_keys(more ? next : bh, L);
+    const float scale = a.slice_scale != nullptr ? a.slice_scale[bh] : a.scale;
+    if (dlog != nullptr) state_dot<F>(acc, second, scale, smem, dlog + bh, L);
+    typedef typename F::Image32 Image;
+    const auto own = [&](int g) { return acc.group(g); };
+    if (swapped) {
+      quadrant_image<F, false, Image>(own, scale, smem + quadrant * F::kImageBytes, L);
+    } else if (!second) {
+      quadrant_image<F, true, Image>(own, scale, smem + quadrant * F::kImageBytes, L);
+    } else {
+      quadrant_image<F, true, Image>(own, scale, smem + Lds::kSetBytes + quadrant * F::kImageBytes, L);
+      quadrant_image<F, false, Image>(own, scale, smem + 2 * Lds::kSetBytes + quadrant * F::kImageBytes, L);
+    }
+    __syncthreads();
+    const size_t base = a.st.slice_base(bh, a.H);
+    unsigned char* out_projected = (second ? a.dQ : a.dK) + base;
+    const WideSrc src = source(more ? next : bh, more ? N : 0);
+    // (opaque: as constants they would be added to every address, the sets lying beyond the 64 KB that an LDS read can add)
+    int natural_at = second ? 0 : Lds::kSetBytes, transposed_at = 2 * Lds::kSetBytes;
+    asm volatile("" : "+s"(natural_at), "+s"(transposed_at));
+    const unsigned char *natural = smem + natural_at, *transposed = smem + transposed_at;
+#pragma unroll
+    for (int j = 0; j < kPairs; ++j) {
+      const Lane L = L0.again();
+      const int row0 = first_of(j), end = row0 + rows_of(j) < N ? row0 + rows_of(j) : N;
+      if (row0 < N)
+        kept_rows_bwd<F>(rows[j], row0, end, !second, natural, transposed, out_projected, a.dV + base, stride, L);
+#pragma unroll
+      for (int r = 2 * j; kAhead && r < 2 * j + 2 && r < ROUNDS; ++r) request(kept[r], src, next_keys, r, L);
+    }
+    if (!kAhead || !more) break;
+    bh = next;
+    __syncthreads();  // the images are written over next
   }
 }
 
@@ -1116,13 +1257,20 @@ hipError_t fused(const Problem& p, const Plan& plan, bool bwd) {
   const unsigned blocks = static_cast<unsigned>(p.B) * p.H;
   if (bwd && p.N <= kKeptRows) {
     constexpr int lds_kept = KeptLds<F>::kBytes;
-    static_assert(lds_kept <= max_lds_bytes<8>(), "three image sets and the tile sets");
-    const hipError_t err =
-        grant_dynamic_lds(reinterpret_cast<const void*>(wide_kept_bwd_kernel<F>), max_lds_bytes<8>());
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL((wide_kept_bwd_kernel<F>), dim3(blocks), dim3(512), lds_kept, p.stream, a,
-                       p.dlog_scale);
-    return hipGetLastError();
+    static_assert(lds_kept <= max_lds_bytes<8>(), "three image sets, two round buffers");
+    const auto launch = [&](auto kernel) {
+      const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), max_lds_bytes<8>());
+      if (err != hipSuccess) return err;
+      hipLaunchKernelGGL(kernel, dim3(p.N <= 4 * TR * kAheadRounds && blocks > kUnits ? kUnits : blocks), dim3(512), lds_kept, p.stream, a,
+                         static_cast<int>(blocks), p.dlog_scale);
+      return hipGetLastError();
+    };
+    switch ((p.N - 1) / (4 * TR)) {
+      case 0: return launch(wide_kept_bwd_kernel<F, 1>);
+      case 1: return launch(wide_kept_bwd_kernel<F, 2>);
+      case 2: return launch(wide_kept_bwd_kernel<F, 3>);
+      default: return launch(wide_kept_bwd_kernel<F, 4>);
+    }
   }
   const void* kern = bwd ? reinterpret_cast<const void*>(wide_fused_bwd_kernel<F>)
                          : reinterpret_cast<const void*>(wide_fused_fwd_kernel<F>);

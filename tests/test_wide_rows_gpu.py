@@ -155,3 +155,13 @@ def test_wide_rows_without_mask(oracle, dtype, B, H, N, d):
 ])
 def test_wide_forward_of_many_slices(oracle, dtype, B, H, N, d):
     test_wide_rows_parity(oracle, dtype, B, H, N, d)
+
+
+@pytest.mark.parametrize("dtype,B,H,N,d", [
+    ("f16", 300, 2, 16, 128), ("bf16", 258, 1, 33, 128),    # one round, several slices per workgroup
+    ("bf16", 90, 1, 128, 128), ("f16", 45, 2, 129, 128),    # two rounds, three
+    ("bf16", 90, 1, 192, 128), ("bf16", 45, 2, 193, 128),   # the longest of three, the shortest of four
+])
+def test_wide_kept_backward(oracle, dtype, B, H, N, d):
+    test_wide_rows_parity(oracle, dtype, B, H, N, d)
+    test_wide_rows_layout_scales_state_dlog(oracle, dtype, d, B, H, N)
