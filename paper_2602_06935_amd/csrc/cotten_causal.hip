@@ -22,12 +22,12 @@
 // straight in the layout of the products; only the rows that other waves read go through LDS.
 //
 // Measured (fwd / bwd, us): fp32 d = 64, 128 slices x 200 rows 13.4 / 30.6, where a scan on the vector
-// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 30 / 73, where 208-row
+// units (16 rows per step) took 89 / 149; bf16 d = 64, 256 x 1001 rows 28 / 67, where 208-row
 // chunks joined by states in memory took 56 / 101 (three launches, 13 * 14 / 2 tile pairs per chunk
 // instead of 8 * 9 / 2 per 128 rows).  Bound: bf16 - the forward by memory, at about 4 TB/s with two chunks of loads in
 // flight per wave (with one, and the bytes of the key mask waited for before the loads of their rows, 33.2; 64 x 1001
-// rows 20.3, now 17.1), the backward by waits, with one: 249 MB, what its two roles share read twice, at 3.4 TB/s, half of
-// the wave time waiting, matrix cores busy for 13 % (two chunks in flight: it has no registers for more); fp32 - latency:
+// rows 20.3, now 17.1), the backward by waits, with one: 249 MB, what its two roles share read twice, at 3.7 TB/s (without
+// any product the same loads and stores take 54 of its 67 us; two chunks in flight: it has no registers for more); fp32 - latency:
 // with its products as bf16 pieces (44.5 -> 43.5 per step) the matrix rate no longer is (mask bytes ahead: 32 x 2048
 // rows, d = 64, forward 79 -> 71.6;  1024 x 200 backward 149 -> 144;  8 x 200 backward 12.7, now 13.2).
 //
@@ -574,7 +574,9 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
             for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
           }
         }
-#pragma unroll 1
+        // (two at a time: what the second reads need not wait for the products of the first.  One at a time, forward / backward, us,
+        // bf16: 256 slices x 1001 rows 28.9 / 72.9, now 27.7 / 67.4;  32 x 300 8.0 / 15.1, 7.6 / 13.3;  64 x 2000 30.5 / 51.7, 29.8 / 48.5)
+#pragma unroll 2
         for (int u = 0; u <= wave; ++u) {
           if (((flags >> u) & 1) == 0) continue;  // no valid key in the tile
           const unsigned char* tu = smem + u * Lds::kWaveBytes;
@@ -640,7 +642,7 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
                 for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
               }
             }
-#pragma unroll 1
+#pragma unroll 2
             for (int t = wave; t < WAVES; ++t) {
               if (((flags >> t) & 1) == 0) continue;  // beyond the sequence
               const unsigned char* tt = smem + t * Lds::kWaveBytes;
