@@ -574,9 +574,9 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
             for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
           }
         }
-        // (two at a time: what the second reads need not wait for the products of the first.  One at a time, forward / backward, us,
-        // bf16: 256 slices x 1001 rows 28.9 / 72.9, now 27.7 / 67.4;  32 x 300 8.0 / 15.1, 7.6 / 13.3;  64 x 2000 30.5 / 51.7, 29.8 / 48.5)
-#pragma unroll 2
+        // (No `unroll 1`: the compiler gives the wave's own tile, the last one, a copy of the body and spares the others its selects and
+        // branches.  With it, forward / backward, us, bf16: 256 slices x 1001 rows 28.9 / 72.9, without 27.7 / 67.4;  32 x 300 8.0 / 15.1,
+        // 7.6 / 13.3;  64 x 2000 30.5 / 51.7, 29.8 / 48.5.  The next tile's rows read ahead by hand: 27.6 / 68.9, fp32 spills.)
         for (int u = 0; u <= wave; ++u) {
           if (((flags >> u) & 1) == 0) continue;  // no valid key in the tile
           const unsigned char* tu = smem + u * Lds::kWaveBytes;
@@ -642,7 +642,6 @@ __device__ __forceinline__ void scan_segment(const Args& a, int bh, int segment)
                 for (int nt = 0; nt < F::NT; ++nt) out[c][nt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
               }
             }
-#pragma unroll 2
             for (int t = wave; t < WAVES; ++t) {
               if (((flags >> t) & 1) == 0) continue;  // beyond the sequence
               const unsigned char* tt = smem + t * Lds::kWaveBytes;
