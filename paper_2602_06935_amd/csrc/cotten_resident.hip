@@ -1,4 +1,4 @@
-// Resident kernels for short sequences of 16-bit elements (bf16 or fp16, N <= 208, d_h = 64).
+// Resident kernels for short sequences of 16-bit elements (bf16 or fp16, N <= 208, d_h = 64); up to 128 rows: short_*_kernel.
 //
 // One persistent workgroup of 16 waves owns one slice at a time and keeps it in LDS: wave w
 // loads and stages the 16-row tile w, so every global load of the slice is issued at once and
@@ -122,6 +122,20 @@ __device__ __forceinline__ void publish_inv(float* dst, const Lane& L, const flo
   }
 }
 
+// A block as it is (fp32, unscaled) into the caller's d x d array: the lane holds column
+// c0 + lane%32 of rows r0 + 8j + 4*(lane/32) .. +3, so 32 lanes write 128 contiguous bytes.
+template <class Acc>
+__device__ __forceinline__ void save_block(const Acc& acc, const Lane& L, int r0, int c0, float* save_to, int d) {
+  const int c = c0 + (L.lane & 31);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int r = r0 + 8 * j + 4 * (L.lane >> 5) + v;
+      if (r < d && c < d) save_to[r * d + c] = acc.v[4 * j + v];
+    }
+}
+
 // One wave per state block: walks all kMaxTiles resident tiles and then writes its block into
 // the images.  Tiles that contribute nothing must hold zeros.  The operands of the next
 // kAhead tiles are requested from LDS before the matrix cores start on a tile (the scheduler
@@ -162,18 +176,7 @@ __device__ __forceinline__ void build_state(const Lane& L, int block, int x_off,
   const int r0 = Acc::block_row0(block), c0 = Acc::block_col0(block);
   if (TRANSPOSED) acc_t.write_image(L, r0, c0, scale, transposed);
   if (NATURAL) acc_n.write_image(L, c0, r0, scale, natural);
-  // the block as it is (fp32, unscaled) into the caller's d x d array: the lane holds column
-  // c0 + lane%32 of rows r0 + 8j + 4*(lane/32) .. +3, so 32 lanes write 128 contiguous bytes
-  if (TRANSPOSED && save_to != nullptr) {
-    const int c = c0 + (L.lane & 31);
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int r = r0 + 8 * j + 4 * (L.lane >> 5) + v;
-        if (r < d && c < d) save_to[r * d + c] = acc_t.v[4 * j + v];
-      }
-  }
+  if (TRANSPOSED && save_to != nullptr) save_block(acc_t, L, r0, c0, save_to, d);
   // <this state, the state whose natural image is given>, this wave's block of it
   if (NATURAL && dot_out != nullptr) {
     const float dot = wave_sum(acc_n.dot_image(L, c0, r0, other_natural));
@@ -418,6 +421,210 @@ __global__ __launch_bounds__(kThreads) void resident_bwd_kernel(const Args a) {
   }
 }
 
+// ---- sequences of a few tiles: a workgroup of a wave per tile and slice, several on a compute unit ------
+//
+// Up to 128 rows.  The persistent kernels above hold a compute unit with sixteen waves whatever the length, and slices
+// follow one another on it; here every slice has a workgroup of four or eight waves, 27 (forward) or 37 KB of LDS for four, and
+// their phases overlap.  The states are built as above, a 32 x 32 block per wave (the same sums); own rows are
+// held in the layout of the products by the time the operand images go over the tiles.
+// Bound by the way to memory and back of a workgroup while few run, by memory beyond.  Forward / backward, us, the
+// persistent kernels and these, bf16 d = 64: 16 slices x 50 rows 4.3 / 6.3, 3.2 / 4.3;  512 x 50 6.3 / 10.7, 4.7 / 6.7;  4096 x 50 33.6 / 67.8, 18.3 / 37;
+// 16 x 100 4.6 / 6.9, 3.7 / 5.3;  512 x 100 7.3 / 12.9, 6.1 / 9.4;  2048 x 128 23.4 / 49.5, 20.4 / 41.9;  d = 32, 2048 x 20 15.4 / 29.9, 6.0 / 12.0; 2048 x
+// 128 19.9 / 40.7, 11.5 / 28.  (K and V requested together with the mask, and what is masked dropped on arrival: 16 x 50 3.2 / 4.3, 512
+// x 50 5.0 / 7.0, 2048 x 128 27 / 50, where the masked rows cost traffic.)
+
+// Valid-key bits of the wave's tile, see key_rows (no branch, the slice exists).
+__device__ __forceinline__ int short_key_rows(const Args& a, const Lane& L, int bh, int tile) {
+  int keys = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int row = tile * TR + L.r8 + 8 * h;
+    const uint8_t key = a.mask == nullptr ? 1 : a.mask[static_cast<size_t>(bh / a.H) * a.N + (row < a.N ? row : 0)];
+    keys |= static_cast<int>(row < a.N && key != 0) << h;
+  }
+  return keys;
+}
+
+// Forward.  DIRECT: rows of Q narrower than 128 bytes come straight in the layout of the products (d = 32, 2048 x 128
+// 17.6 us through LDS, 14.9 this way; with rows of 128 bytes, 64 of which a load then takes, 512 x 50 4.7, 5.0).
+template <class F, int WAVES, bool DIRECT>
+__global__ __launch_bounds__(64 * WAVES, 4) void short_fwd_kernel(const Args a) {
+  typedef typename F::BlockAcc Acc;
+  constexpr int kStride = (DIRECT ? 2 : 3) * kTileBytes;  // of a tile: khat, v, q
+  const Lane L;
+  const int bh = blockIdx.x, tile = L.wave, N = a.N;
+  const size_t base = a.st.slice_base(bh, a.H);
+  const int row = tile * TR + L.i16;
+  unsigned char* blk = smem + tile * kStride;
+  float* invs = reinterpret_cast<float*>(smem + WAVES * kStride) + tile * TR;
+  OwnRaw<1> own;
+  {
+    Raw rk, rq;
+    const int keys = short_key_rows(a, L, bh, tile);
+    if (DIRECT) load_own<1>(own, L, Buffers(a.Q + base, N, a.st.row), a.st.row, tile * TR, row < N);
+    fetch<false, DIRECT ? 1 : 3>(rq, rk, a, L, bh, tile, keys);
+    const bool cols = L.ch * 16 < a.st.row.bytes;
+    float inv[2];
+    stage<F, mapped_mode<F>(), true>(rk, L, a.eps, blk + kKt, blk + kVt, inv, cols);
+    if (!DIRECT) {
+      stage<F, F::kMap == kMapElu1 ? kXFeature : kXRaw, false>(rq, L, a.eps, blk + kQt, nullptr, inv, cols);
+      publish_inv(invs, L, inv);
+    }
+  }
+  __syncthreads();
+  const bool builds = tile < Acc::kBlocks;
+  const int r0 = Acc::block_row0(tile), c0 = Acc::block_col0(tile);
+  Acc state;
+  if (builds) {
+    state.zero();
+#pragma unroll
+    for (int t = 0; t < WAVES; ++t) state.mma(Acc::fetch(smem + t * kStride + kKt, smem + t * kStride + kVt, L, tile));
+  }
+  // cosine map: the raw rows go through the product and 1/r is applied to the result; ELU + 1: phi(q), and 1
+  typename F::TileRows x;
+  float factor = 1.0f;
+  if (!DIRECT) {
+    x.load(blk + kQt, L);
+    factor = invs[L.i16];
+  } else {
+    float f[2 * F::EPL];
+    own_values<F, 1>(own, 0, f);
+    if (F::kMap == kMapElu1) {
+#pragma unroll
+      for (int i = 0; i < 2 * F::EPL; ++i)
+        f[i] = elu1_or_zero(f[i], (row < N) & (64 * (i / F::EPL) + 16 * L.g16 < a.st.row.bytes));
+      x.set(f);
+    } else {
+      x.set(own.r[0][0], own.r[0][1]);
+      float ss = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 2 * F::EPL; ++i) ss += f[i] * f[i];
+      factor = inv_norm_or_zero(row_sum_groups(ss, L), a.eps, row < N);
+    }
+  }
+  __syncthreads();  // nobody reads the tiles any more
+  if (builds) {
+    state.write_image(L, r0, c0, a.scales != nullptr ? a.scales[bh] : a.scale, smem);
+    if (a.saved != nullptr) save_block(state, L, r0, c0, a.saved + static_cast<size_t>(bh) * a.d * a.d, a.d);
+  }
+  __syncthreads();
+  if (tile * TR >= N) return;
+  typename F::Operand W;
+  W.load(smem, L);
+  f32x4_t out[F::NT];
+  F::apply(x, W, out);
+  float o[2 * F::EPL];
+  product_rows<F>(out, o);
+#pragma unroll
+  for (int i = 0; i < 2 * F::EPL; ++i) o[i] *= factor;
+  if (row < N) store_product_row<F, kStoreStreamed>(a.O + base, row, a.st.row, L, o);
+}
+
+template <class F, int WAVES>
+struct ShortLds {
+  static constexpr int kForwardDirect = WAVES * 2 * kTileBytes, kForward = WAVES * (3 * kTileBytes + TR * 4);
+  static_assert(kForwardDirect >= F::kImageBytes, "the image goes over the tiles");
+  static constexpr int kSpace = WAVES * kBlockBytes > 3 * F::kImageBytes ? WAVES * kBlockBytes : 3 * F::kImageBytes;
+  static constexpr int kInv = kSpace, kDots = kInv + WAVES * 2 * TR * 4;
+  static constexpr int kBackward = kDots + 4 * 4;
+};
+
+template <class F, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 4) void short_bwd_kernel(const Args a) {
+  typedef typename F::BlockAcc Acc;
+  typedef ShortLds<F, WAVES> Lds;
+  constexpr int kB = Acc::kBlocks;
+  static_assert(kB == 4 && (WAVES == 4 || WAVES == 8), "wave roles below");
+  const Lane L;
+  const int bh = blockIdx.x, tile = L.wave;
+  const size_t base = a.st.slice_base(bh, a.H);
+  unsigned char* blk = smem + tile * kBlockBytes;
+  unsigned char *img_s = smem, *img_ds = img_s + F::kImageBytes, *img_dst = img_ds + F::kImageBytes;
+  float* invs = reinterpret_cast<float*>(smem + Lds::kInv) + tile * 2 * TR;
+  float* dots = reinterpret_cast<float*>(smem + Lds::kDots);
+  const bool cols = L.ch * 16 < a.st.row.bytes;
+  Raw rq, rk;
+  fetch<true>(rq, rk, a, L, bh, tile, short_key_rows(a, L, bh, tile));
+  float inv[2];
+  stage<F, mapped_mode<F>(), true>(rk, L, a.eps, blk + kKt, blk + kVt, inv, cols);
+  publish_inv(invs + TR, L, inv);
+  stage<F, mapped_mode<F>(), true>(rq, L, a.eps, blk + kQt, blk + kGt, inv, cols);
+  publish_inv(invs, L, inv);
+  const bool any_key = __ballot(rk.live != 0) != 0;
+  __syncthreads();
+  // the wave's own rows, and a block of dS and of S (eight waves: of one of them)
+  typename F::TileRows q, g, k, v;
+  q.load(blk + kQt, L);
+  g.load(blk + kGt, L);
+  k.load(blk + kKt, L);
+  v.load(blk + kVt, L);
+  const float inv_q = invs[L.i16], inv_k = invs[TR + L.i16];
+  const int block = tile % kB;
+  const bool has_ds = WAVES == kB || tile < kB, has_s = WAVES == kB || tile >= kB;
+  Acc ds_t, ds_n, s_n;
+  ds_t.zero();
+  ds_n.zero();
+  s_n.zero();
+  if (has_ds) {
+#pragma unroll
+    for (int t = 0; t < WAVES; ++t) {
+      const typename Acc::Frag f = Acc::fetch(smem + t * kBlockBytes + kQt, smem + t * kBlockBytes + kGt, L, block);
+      ds_t.mma(f);
+      ds_n.mma_swapped(f);
+    }
+  }
+  if (has_s) {
+#pragma unroll
+    for (int t = 0; t < WAVES; ++t)
+      s_n.mma_swapped(Acc::fetch(smem + t * kBlockBytes + kKt, smem + t * kBlockBytes + kVt, L, block));
+  }
+  __syncthreads();  // the images go over the tiles
+  const float scale = a.scales != nullptr ? a.scales[bh] : a.scale;
+  const int r0 = Acc::block_row0(block), c0 = Acc::block_col0(block);
+  if (has_ds) {
+    ds_t.write_image(L, r0, c0, scale, img_dst);
+    ds_n.write_image(L, c0, r0, scale, img_ds);
+  }
+  if (has_s) s_n.write_image(L, c0, r0, scale, img_s);
+  __syncthreads();
+  // d loss / d log(scale) = sum_i dO_i . O_i = <S, scale * dS>, blocks in order
+  if (a.dlog != nullptr) {
+    if (has_s) {
+      const float dot = wave_sum(s_n.dot_image(L, c0, r0, img_ds));
+      if (L.lane == 0) dots[block] = dot;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) a.dlog[bh] = ((dots[0] + dots[1]) + dots[2]) + dots[3];
+  }
+  // (see apply_tile)
+  const int row = tile * TR + L.i16;
+  if (tile * TR >= a.N) return;
+  const auto product = [&](const typename F::TileRows& x, const unsigned char* image, float (&p)[2 * F::EPL]) {
+    typename F::Operand W;
+    W.load(image, L);
+    f32x4_t out[F::NT];
+    F::apply(x, W, out);
+    product_rows<F>(out, p);
+  };
+  const auto finish = [&](float (&p)[2 * F::EPL], typename F::TileRows& e, float inv_r) {
+    if (F::kMap == kMapElu1) feature_grad_rows<F>(p, e);
+    else project_rows<F, true>(p, e, inv_r, L);
+  };
+  float p[2 * F::EPL];
+  product(g, img_s, p);
+  finish(p, q, inv_q);
+  if (row < a.N) store_product_row<F, kStoreStreamed>(a.dQ + base, row, a.st.row, L, p);
+#pragma unroll
+  for (int c = 0; c < 2 * F::EPL; ++c) p[c] = 0.0f;
+  if (any_key) product(k, img_dst, p);
+  if (row < a.N) store_product_row<F, kStoreStreamed>(a.dV + base, row, a.st.row, L, p);
+  if (any_key) {
+    product(v, img_ds, p);
+    finish(p, k, inv_k);
+  }
+  if (row < a.N) store_product_row<F, kStoreStreamed>(a.dK + base, row, a.st.row, L, p);
+}
+
 // ---- causal variant on the matrix cores ------------------------------------------------------
 // Row i attends the valid keys j <= i.  With the whole slice in LDS this is done tile pair by
 // tile pair, (query tile t, key tile u <= t), all pairs independent:
@@ -637,9 +844,23 @@ Args make_args(const Problem& p) {
   return a;
 }
 
+template <class F, int WAVES>
+hipError_t run_short(const Problem& p, const Args& a, bool bwd) {
+  const auto launch = [&](auto kernel, int bytes) {
+    const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), bytes);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.slices)), dim3(64 * WAVES), bytes, p.stream, a);
+    return hipGetLastError();
+  };
+  if (bwd) return launch(short_bwd_kernel<F, WAVES>, ShortLds<F, WAVES>::kBackward);
+  return a.st.row.bytes < kRowBytes ? launch(short_fwd_kernel<F, WAVES, true>, ShortLds<F, WAVES>::kForwardDirect)
+                                    : launch(short_fwd_kernel<F, WAVES, false>, ShortLds<F, WAVES>::kForward);
+}
+
 template <class F>
 hipError_t run(const Problem& p, bool bwd) {
   const Args a = make_args(p);
+  if (p.N <= 8 * TR) return p.N <= 4 * TR ? run_short<F, 4>(p, a, bwd) : run_short<F, 8>(p, a, bwd);  // (see there)
   const int units = compute_units();
   const dim3 grid(static_cast<unsigned>(a.slices < units ? a.slices : units));
   const size_t lds = Lds<F>::kBytes;

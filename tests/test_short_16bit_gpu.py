@@ -1,0 +1,61 @@
+"""Short 16-bit sequences (rows of up to 128 bytes, at most 128 rows): a workgroup of four waves (64 rows)
+or eight per slice, at the edges of tiles and ranges, rows of 128, 64 and 32 bytes, both feature maps,
+both layouts, per-slice scales with their gradient, the state the forward writes."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_06935_amd import binding
+from tests.gpu_util import bar_for, check_tensor, rel_l2, to_f64, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d,B,H,N,fmap", [
+    ("bf16", 64, 5, 2, 9, "cosine"), ("f16", 32, 5, 2, 16, "cosine"), ("bf16", 16, 5, 2, 33, "elu1"),
+    ("f16", 64, 5, 2, 64, "elu1"), ("bf16", 32, 150, 2, 64, "cosine"),       # four waves
+    ("bf16", 64, 5, 2, 65, "cosine"), ("f16", 16, 5, 2, 112, "cosine"), ("bf16", 32, 5, 2, 113, "elu1"),
+    ("f16", 64, 5, 2, 128, "elu1"), ("bf16", 64, 150, 2, 128, "cosine"),     # eight
+    ("bf16", 64, 5, 2, 129, "cosine"),                                       # the shortest beyond
+])
+def test_short_16bit(oracle, dtype, d, B, H, N, fmap):
+    print(f"[short 16 bit] {dtype} B={B} H={H} N={N} d={d} {fmap}", flush=True)
+    rng = np.random.default_rng(6200 + N + d)
+    Q, K, V, dO = (to_gpu(rng.standard_normal((B, H, N, d)).astype(np.float32) * 0.5, dtype) for _ in range(4))
+    mask = (rng.random((B, N)) < 0.5).astype(np.uint8)
+    mask[0] = np.arange(N) >= N // 2      # padded at the front
+    mask[1] = 0                           # no key at all
+    mask[2] = 1
+    tm = torch.from_numpy(mask).cuda()
+    dead = (tm == 0)[:, None, :, None].expand_as(K)
+    K2, V2 = K.clone(), V.clone()
+    K2[dead], V2[dead] = float("nan"), float("inf")
+    ss = torch.rand(B, H, device="cuda") * 0.05 + 0.01
+    opts = dict(slice_scale=ss, eps=1e-6, feature_map=fmap)
+    state = torch.empty(B, H, d, d, device="cuda")
+    dlog = torch.empty(B, H, device="cuda")
+    O = binding.cotten_attn_fwd(Q, K, V, tm, saved_state=state, **opts)
+    grads = binding.cotten_attn_bwd(Q, K, V, tm, dO, dlog_scale=dlog, **opts)
+    sw = lambda t: t.permute(0, 2, 1, 3).contiguous()
+    O2 = binding.cotten_attn_fwd(sw(Q), sw(K2), sw(V2), tm, layout="bnhd", **opts)
+    grads2 = binding.cotten_attn_bwd(sw(Q), sw(K2), sw(V2), tm, sw(dO), layout="bnhd", saved_state=state, **opts)
+    unmasked = binding.cotten_attn_fwd(Q, K, V, None, **opts)
+    torch.cuda.synchronize()
+    assert torch.equal(sw(O), O2) and all(torch.equal(sw(a), c) for a, c in zip(grads, grads2))
+    assert torch.equal(unmasked[2], O[2])
+    s64 = ss.double().cpu().numpy()[:, :, None, None]
+    q, k, v, g = (to_f64(t) for t in (Q, K, V, dO))
+    if fmap == "elu1":
+        ref = (oracle.elu_fwd(q, k, v, mask, scale=1.0), *oracle.elu_bwd(q, k, v, g, mask, scale=1.0))
+    else:
+        ref = (oracle.fwd_linear(q, k, v, mask, scale=1.0, eps=1e-6), *oracle.bwd(q, k, v, g, mask, scale=1.0, eps=1e-6))
+    ref = [r * s64 for r in ref]
+    bar = bar_for(dtype)
+    for n, t, r in zip(("O", "dQ", "dK", "dV"), (O, *grads), ref):
+        check_tensor(n, to_f64(t), r, bar)
+    # (a sum over all rows of a slice, with cancellation: five times the bar, as elsewhere)
+    assert rel_l2(dlog.double().cpu().numpy(), (g * ref[0]).sum((2, 3))) <= 5 * bar
+    if fmap == "cosine":
+        assert rel_l2(state.double().cpu().numpy(), oracle.state(K.float().cpu().numpy(), V.float().cpu().numpy(), mask)) <= bar
