@@ -131,10 +131,21 @@ def _prep(name: str, t: torch.Tensor, like: Optional[torch.Tensor] = None) -> to
     return t
 
 
+def _prep_like(Q: torch.Tensor, others) -> None:
+    """The checks of _prep on Q and on the (name, tensor) pairs that must match it.  Attributes of Q are read once and
+    the checks written as one condition: the attribute reads are most of what a check costs."""
+    if not (Q.is_cuda and Q.is_contiguous()):
+        _prep("Q", Q)
+    shape, dtype, device = Q.shape, Q.dtype, Q.device
+    for name, t in others:
+        if not (t.shape == shape and t.dtype is dtype and t.device == device and t.is_contiguous()):
+            _prep(name, t, Q)
+
+
 def _mask_ptr(mask: Optional[torch.Tensor], B: int, N: int, dev) -> Optional[int]:
     if mask is None:
         return None
-    if mask.dtype != torch.uint8 or mask.shape != (B, N) or not mask.is_contiguous() or mask.device != dev:
+    if mask.dtype is not torch.uint8 or mask.shape != (B, N) or not mask.is_contiguous() or mask.device != dev:
         raise ValueError("mask must be a contiguous uint8 [B,N] tensor on the same device")
     return mask.data_ptr()
 
@@ -198,15 +209,8 @@ def _workspace_need(B: int, H: int, N: int, d: int, is_bwd: bool, dtype: int, ca
     return cotten_attn_workspace_bytes_ex(B, H, N, d, is_bwd, dtype=dtype, causal=causal)
 
 
-def _workspace(Q: torch.Tensor, dims, is_bwd: bool, stream_handle: int,
-               given: Optional[torch.Tensor], causal: bool = False) -> Optional[torch.Tensor]:
-    """The workspace tensor of a call: the caller's, or one of this module's."""
-    if given is not None:
-        return given
-    B, H, N, d = dims
-    need = _workspace_need(B, H, N, d, is_bwd, _dtype_code(Q), bool(causal))
-    if need == 0:
-        return None
+def _workspace(Q: torch.Tensor, need: int, stream_handle: int) -> torch.Tensor:
+    """A workspace of this module's for a call that needs one and was given none."""
     with torch.cuda.device(Q.device):
         if torch.cuda.is_current_stream_capturing():
             return torch.empty(need, dtype=torch.uint8, device=Q.device)
@@ -226,9 +230,13 @@ _current_stream_handle = getattr(torch._C, "_cuda_getCurrentRawStream",
                                  lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
+# The current device likewise (a GPU tensor is at hand wherever it is asked for: the runtime is up).
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+
+
 def _stream_handle(stream) -> int:
     if stream is None:  # that of the current device
-        return _current_stream_handle(torch.cuda.current_device())
+        return _current_stream_handle(_current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)
@@ -236,8 +244,10 @@ def _stream_handle(stream) -> int:
 
 def _on_device(device: torch.device, entry, *args) -> None:
     """One call into the library with `device` current."""
-    if device.index == torch.cuda.current_device():
-        _check(entry(*args))
+    if device.index == _current_device():
+        status = entry(*args)
+        if status != 0:
+            _check(status)
     else:
         with torch.cuda.device(device):
             _check(entry(*args))
@@ -256,12 +266,15 @@ def cotten_attn_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     `layout` "bnhd" means all tensors are [B,N,H,d_h] instead of [B,H,N,d_h];
     `saved_state` ([B,H,d_h,d_h] float32) receives the state S of every slice for the
     backward call."""
-    lib = load_library()
-    Q = _prep("Q", Q); K = _prep("K", K, Q); V = _prep("V", V, Q)
+    lib = _lib or load_library()
+    _prep_like(Q, (("K", K), ("V", V)))
     B, H, N, d = _dims(Q, layout)
     O = torch.empty_like(Q) if O is None else _prep("O", O, Q)
     handle = _stream_handle(stream)
-    workspace = _workspace(Q, (B, H, N, d), False, handle, workspace, causal)
+    if workspace is None:
+        need = _workspace_need(B, H, N, d, False, _dtype_code(Q), bool(causal))
+        if need != 0:
+            workspace = _workspace(Q, need, handle)
     prm = _params(Q, scale, eps, workspace, slice_scale, None, layout, causal, saved_state, feature_map)
     _on_device(Q.device, lib.cotten_attn_fwd_ex, Q.data_ptr(), K.data_ptr(), V.data_ptr(),
                _mask_ptr(mask, B, N, Q.device), O.data_ptr(), B, H, N, d, handle, ctypes.byref(prm))
@@ -286,8 +299,8 @@ def cotten_attn_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     scratch array serves (the output tensors must then be given, nothing is allocated here).
     `saved_state`: the state the forward call of the same inputs wrote; read instead of being
     rebuilt from K, V."""
-    lib = load_library()
-    Q = _prep("Q", Q); K = _prep("K", K, Q); V = _prep("V", V, Q); dO = _prep("dO", dO, Q)
+    lib = _lib or load_library()
+    _prep_like(Q, (("K", K), ("V", V), ("dO", dO)))
     B, H, N, d = _dims(Q, layout)
     dQ = torch.empty_like(Q) if dQ is None else _prep("dQ", dQ, Q)
     dK = torch.empty_like(Q) if dK is None else _prep("dK", dK, Q)
@@ -295,8 +308,10 @@ def cotten_attn_bwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
     handle = _stream_handle(stream)
     if static_scratch:
         workspace = None
-    else:
-        workspace = _workspace(Q, (B, H, N, d), True, handle, workspace, causal)
+    elif workspace is None:
+        need = _workspace_need(B, H, N, d, True, _dtype_code(Q), bool(causal))
+        if need != 0:
+            workspace = _workspace(Q, need, handle)
     prm = _params(Q, scale, eps, workspace, slice_scale, dlog_scale, layout, causal, saved_state,
                   feature_map)
     entry = lib.cotten_attn_bwd_static if static_scratch else lib.cotten_attn_bwd_ex
