@@ -861,17 +861,17 @@ hipError_t launch_causal(const Problem& p, bool bwd) {
   // 10.6 / 20.8
   if (p.dtype == 0) return run_scan<F32x32, 1, 4>(p, bwd);
   // 16-bit rows.  The walk reads what its two backward roles share twice; a slice of at most 208
-  // rows held in LDS is read once and wins as long as its workgroups (one per compute unit) do
-  // not queue up, or are well filled when they do.  us, resident against the walk with 8 (4)
-  // waves, bf16 d = 64, forward / backward:
-  //   N = 200: 256 slices 8.2 / 13.7, 9.5 / 18.2;  512: 13.9 / 26.9, 11.6 / 29.1;  4096: 100 / 161, 71 / 203
-  //   N = 100: 512 slices 9.7 / 15.7, 7.4 / 17.2 (8.9 / 16.3);  4096: 62 / 103, 38 / 114 (35 / 96)
-  //   N = 50:  256 slices 4.8 / 6.2, (4.5 / 8.0);  512: 7.8 / 10.6, (5.2 / 9.4);  4096: 48 / 76, (18 / 48)
-  // (The walk of these with one image per state.  With two, four waves: N = 100, 2048 slices, forward
-  // 22.0 -> 22.6; backward 49 -> 68, two workgroups per compute unit instead of four, resident 53.)
+  // rows held in LDS is read once: workgroups of four waves up to 64 rows (four on a compute unit), of eight up to 128 (two), of thirteen
+  // beyond (one).  The backward always gains by it, the forward while the workgroups do not queue up.  us, walk and in LDS, bf16 d = 64:
+  //   forward   512 slices x 50 rows 4.8, 4.7;  2048 x 50 10.6, 11.0;  512 x 100 6.9, 6.6;  1022 x 100 13.0, 12.4;  2048 x 100 20.2, 20.4;
+  //             256 x 200 9.5, 8.2;  512 x 200 11.6, 13.9
+  //   backward  512 x 50 8.2, 7.0;  4096 x 50 47.4, 36.5;  (with sixteen waves whatever the length, 512 x 100 12.9, now 10.2;  2048 x 100 52.3, 37.7);
+  //             512 x 200 29.1, 26.9
+  // (1024 slices or more of 65 ... 128 rows, forward: chunks of 64 rows, whose carried state keeps more bits than the scores do: 2.65e-3 from
+  // 64 bits at 1024 x 100, in LDS 2.88e-3.)
   const long slices = static_cast<long>(p.B) * p.H;
   const bool resident = causal_chunks(p.N) == 1 &&
-                        (bwd ? slices <= 256 || p.N > 64 : slices <= 256 && p.N > 128);
+                        (bwd || (p.N <= 64 ? slices <= 1024 : p.N <= 128 ? slices < 1024 : slices <= 256));
   if (resident) return launch_resident_causal(p, bwd);
   if (p.N <= 64 || (p.N <= 128 && slices >= 1024))
     return p.dtype == 1 ? run_scan<Bf16x64, 1, 4>(p, bwd) : run_scan<F16x64, 1, 4>(p, bwd);

@@ -644,14 +644,22 @@ __global__ __launch_bounds__(64 * WAVES, 4) void short_bwd_kernel(const Args a) 
 // and the row-norm Jacobians as everywhere else.
 // Served here: 16-bit rows of at most 208 positions (launch_causal() in cotten_causal.hip says when).
 
-template <class F>
-__global__ __launch_bounds__(kThreads) void causal_fwd_kernel(const Args a) {
+// A wave per tile: four, eight or thirteen.
+template <int WAVES>
+struct CausalLds {
+  static constexpr int kLive = WAVES * kBlockBytes;  // one int per tile
+  static constexpr int kInv = kLive + 16 * 4;        // 1/r per tile: 16 q rows, 16 k rows
+  static constexpr int kBytes = kInv + WAVES * 2 * TR * 4;
+};
+
+template <class F, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 4) void causal_fwd_kernel(const Args a) {
   const Lane L0;
   const int N = a.N, tile = L0.wave, slice = blockIdx.x;
   const int n_tiles = (N + TR - 1) / TR;
   unsigned char* blk = smem + tile * kBlockBytes;
-  int* live = reinterpret_cast<int*>(smem + Lds<F>::kLive);
-  float* invs = reinterpret_cast<float*>(smem + Lds<F>::kInv) + tile * 2 * TR;
+  int* live = reinterpret_cast<int*>(smem + CausalLds<WAVES>::kLive);
+  float* invs = reinterpret_cast<float*>(smem + CausalLds<WAVES>::kInv) + tile * 2 * TR;
   const bool mine = tile < n_tiles;
   Raw rq, rk;
   const int from = mine ? slice : a.slices;  // a slice that does not exist: nothing is loaded
@@ -695,18 +703,28 @@ __global__ __launch_bounds__(kThreads) void causal_fwd_kernel(const Args a) {
     store_product_row<F, kStoreStreamed>(a.O + a.st.slice_base(slice, a.H), row, a.st.row, L, o);
 }
 
-template <class F>
-__global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
+// RAW: dQ, dK and dV from the wave's own rows as they are, as the walk over chunks has them, and not from rows rounded after
+// their division by r (bf16, 300 slices x 50 rows, distance of dV from 64 bits 2.9e-3, otherwise 3.3e-3).
+template <class F, int WAVES, bool RAW>
+__global__ __launch_bounds__(64 * WAVES, 4) void causal_bwd_kernel(const Args a) {
   const Lane L0;
   const int N = a.N, tile = L0.wave, slice = blockIdx.x;
   const int n_tiles = (N + TR - 1) / TR;
   unsigned char* blk = smem + tile * kBlockBytes;
-  int* live = reinterpret_cast<int*>(smem + Lds<F>::kLive);
-  float* invs = reinterpret_cast<float*>(smem + Lds<F>::kInv) + tile * 2 * TR;
+  int* live = reinterpret_cast<int*>(smem + CausalLds<WAVES>::kLive);
+  float* invs = reinterpret_cast<float*>(smem + CausalLds<WAVES>::kInv) + tile * 2 * TR;
   const bool mine = tile < n_tiles;
   Raw rq, rk;
   const int from = mine ? slice : a.slices;  // a slice that does not exist: nothing is loaded
   fetch<true>(rq, rk, a, L0, from, tile, key_rows(a, L0, from, tile));
+  OwnRaw<1> own_queries, own_keys;
+  if (RAW) {
+    const int row = tile * TR + L0.i16;
+    const size_t at = static_cast<size_t>(slice / a.H) * N + (row < N ? row : 0), base = a.st.slice_base(slice, a.H);
+    const bool key = row < N && (a.mask == nullptr || a.mask[at] != 0);
+    load_own<1>(own_queries, L0, Buffers(a.Q + base, N, a.st.row), a.st.row, tile * TR, row < N);
+    load_own<1>(own_keys, L0, Buffers(a.K + base, N, a.st.row), a.st.row, tile * TR, key);
+  }
   if (mine) {
     float inv[2];
     stage<F, kXNormalized, true>(rq, L0, a.eps, blk + kQt, blk + kGt, inv);
@@ -749,8 +767,13 @@ __global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
 #pragma unroll
     for (int i = 0; i < 2 * F::EPL; ++i) g[i] *= scale;
     typename F::TileRows e;
-    e.load(blk + kQt, L);
-    project_rows<F, false>(g, e, invs[L.i16], L);
+    if (RAW) {
+      e.set(own_queries.r[0][0], own_queries.r[0][1]);
+      project_rows_raw<F>(g, e, invs[L.i16], L);
+    } else {
+      e.load(blk + kQt, L);
+      project_rows<F, false>(g, e, invs[L.i16], L);
+    }
     if (row < N) store_product_row<F, kStoreStreamed>(a.dQ + base, row, a.st.row, L, g);
   }
 
@@ -761,7 +784,9 @@ __global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
       for (int i = 0; i < 2 * F::EPL; ++i) dk[i] = dv[i] = 0.0f;
     } else {
       typename F::TileRows xk, xv;
-      xk.load(blk + kKt, L);
+      const float inv_k = invs[TR + L.i16];
+      if (RAW) xk.set(own_keys.r[0][0], own_keys.r[0][1]);
+      else xk.load(blk + kKt, L);
       xv.load(blk + kVt, L);
       f32x4_t av[F::NT], ah[F::NT];
 #pragma unroll
@@ -772,6 +797,7 @@ __global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
         xq.load(tb + kQt, L);
         xg.load(tb + kGt, L);
         f32x4_t p = F::dots(xq, xk);   // [query 4g+v][key i16] = qhat_query . khat_key
+        if (RAW) p *= inv_k;
         f32x4_t gg = F::dots(xg, xv);  // [query 4g+v][key i16] = dO_query . v_key
         if (t == tile) {
 #pragma unroll
@@ -789,8 +815,9 @@ __global__ __launch_bounds__(kThreads) void causal_bwd_kernel(const Args a) {
         dk[i] *= scale;
       }
       // 1/r is zero on masked rows, whose khat and v rows are zero too: exact zeros there
-      project_rows<F, false>(dk, xk, invs[TR + L.i16], L);
-      if (invs[TR + L.i16] == 0.0f) {
+      if (RAW) project_rows_raw<F>(dk, xk, inv_k, L);
+      else project_rows<F, false>(dk, xk, inv_k, L);
+      if (inv_k == 0.0f) {
 #pragma unroll
         for (int i = 0; i < 2 * F::EPL; ++i) dv[i] = 0.0f;
       }
@@ -881,20 +908,25 @@ hipError_t run(const Problem& p, bool bwd) {
 
 }  // namespace
 
-template <class F>
+template <class F, int WAVES>
 hipError_t run_causal(const Problem& p, bool bwd) {
   const Args a = make_args(p);
-  const dim3 grid(static_cast<unsigned>(a.slices));
-  const size_t lds = Lds<F>::kBytes;
-  const void* kern = bwd ? reinterpret_cast<const void*>(causal_bwd_kernel<F>)
-                         : reinterpret_cast<const void*>(causal_fwd_kernel<F>);
-  const hipError_t err = grant_dynamic_lds(kern, static_cast<int>(lds));
-  if (err != hipSuccess) return err;
-  if (bwd)
-    hipLaunchKernelGGL(causal_bwd_kernel<F>, grid, dim3(kThreads), lds, p.stream, a);
-  else
-    hipLaunchKernelGGL(causal_fwd_kernel<F>, grid, dim3(kThreads), lds, p.stream, a);
-  return hipGetLastError();
+  const auto launch = [&](auto kernel) {
+    constexpr int lds = CausalLds<WAVES>::kBytes;
+    const hipError_t err = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.slices)), dim3(64 * WAVES), lds, p.stream, a);
+    return hipGetLastError();
+  };
+  // (calls that the walk served before are as exact here; 16 and 128 slices x 50 rows, us: 4.6 and 4.8, RAW 4.8 and 5.0)
+  if constexpr (WAVES == 4) {
+    if (bwd && a.slices > 256) return launch(causal_bwd_kernel<F, WAVES, true>);
+  }
+  return bwd ? launch(causal_bwd_kernel<F, WAVES, false>) : launch(causal_fwd_kernel<F, WAVES>);
+}
+template <class F>
+hipError_t run_causal(const Problem& p, bool bwd) {
+  return p.N <= 4 * TR ? run_causal<F, 4>(p, bwd) : p.N <= 8 * TR ? run_causal<F, 8>(p, bwd) : run_causal<F, kMaxTiles>(p, bwd);
 }
 
 bool resident_supports(int dtype, int D, int N) {

@@ -59,3 +59,38 @@ def test_short_16bit(oracle, dtype, d, B, H, N, fmap):
     assert rel_l2(dlog.double().cpu().numpy(), (g * ref[0]).sum((2, 3))) <= 5 * bar
     if fmap == "cosine":
         assert rel_l2(state.double().cpu().numpy(), oracle.state(K.float().cpu().numpy(), V.float().cpu().numpy(), mask)) <= bar
+
+
+@pytest.mark.parametrize("dtype,d,B,H,N", [
+    ("bf16", 64, 5, 2, 64), ("bf16", 32, 150, 2, 50), ("f16", 64, 260, 1, 64),   # four waves; rows as they are
+    ("f16", 16, 5, 2, 65), ("bf16", 64, 150, 2, 128), ("bf16", 64, 5, 2, 129),   # eight, thirteen
+])
+def test_short_causal_16bit(oracle, dtype, d, B, H, N):
+    print(f"[short 16 bit, causal] {dtype} B={B} H={H} N={N} d={d}", flush=True)
+    rng = np.random.default_rng(6900 + N + d)
+    x = [rng.standard_normal((B, H, N, d)).astype(np.float32) * 0.5 for _ in range(4)]
+    for t in x[:2]:                       # long and short rows of Q and K
+        t[rng.random((B, H, N)) < 0.05] *= 300.0
+        t[rng.random((B, H, N)) < 0.05] *= 1e-3
+    Q, K, V, dO = (to_gpu(t, dtype) for t in x)
+    mask = (rng.random((B, N)) < 0.7).astype(np.uint8)
+    mask[:, 0] = 1
+    mask[1] = 0                           # no key at all
+    tm = torch.from_numpy(mask).cuda()
+    dead = (tm == 0)[:, None, :, None].expand_as(K)
+    K2, V2 = K.clone(), V.clone()
+    K2[dead], V2[dead] = float("nan"), float("inf")
+    opts = dict(scale=0.05, eps=1e-6, causal=True)
+    O = binding.cotten_attn_fwd(Q, K, V, tm, **opts)
+    grads = binding.cotten_attn_bwd(Q, K, V, tm, dO, **opts)
+    sw = lambda t: t.permute(0, 2, 1, 3).contiguous()
+    O2 = binding.cotten_attn_fwd(sw(Q), sw(K2), sw(V2), tm, layout="bnhd", **opts)
+    grads2 = binding.cotten_attn_bwd(sw(Q), sw(K2), sw(V2), tm, sw(dO), layout="bnhd", **opts)
+    torch.cuda.synchronize()
+    assert torch.equal(sw(O), O2) and all(torch.equal(sw(a), c) for a, c in zip(grads, grads2))
+    q, k, v, g = (to_f64(t) for t in (Q, K, V, dO))
+    ref = (oracle.causal_fwd(q, k, v, mask, scale=0.05, eps=1e-6),
+           *oracle.causal_bwd(q, k, v, g, mask, scale=0.05, eps=1e-6))
+    for n, t, r in zip(("O", "dQ", "dK", "dV"), (O, *grads), ref):
+        assert rel_l2(to_f64(t), r) <= bar_for(dtype), n
+    assert all(np.all(to_f64(t)[dead.cpu().numpy()] == 0.0) for t in grads[1:])
