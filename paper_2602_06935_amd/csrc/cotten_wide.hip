@@ -12,7 +12,7 @@
 // with the row norm taken over both halves.  Three launches (partial states in the caller's
 // workspace, [kinds][slices * splits][D * D] floats, then the reduced states):
 //
-//   wide_state_kernel   a workgroup of four (or eight) waves reduces a block of rows of one slice
+//   wide_state_kernel   a workgroup of four (or eight) waves reduces its share of the rows of a slice
 //                       to a partial state: per round every wave stages one 16-row tile in LDS,
 //                       then wave (p, q) adds four tiles of the round to its quadrant (with eight
 //                       waves two waves share a quadrant and their sums meet at the end)
@@ -199,23 +199,29 @@ __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
   const WideSrc src((second ? Q : K) + base, (second ? dO : V) + base, N, st.row.stride);
   const uint8_t* __restrict__ m =
       (second || mask == nullptr) ? nullptr : mask + static_cast<size_t>(bh / H) * N;
-  const int r_begin = split * rows_per_split;
-  const int r_end = N < r_begin + rows_per_split ? N : r_begin + rows_per_split;
+  // Forward (rows_per_split = 0): rounds are dealt to the workgroups in turn, so that padding at one end of the sequence is shared
+  // evenly; backward: consecutive rows.  us, consecutive and dealt, bf16: forward 32 slices x 3000 rows 34.6, 31.6 (no mask 34.9, 34.9);
+  // 128 x 4096 121, 116;  100 x 1500 49.5, 48.3;  backward 32 x 3000 79.2, 78.2 (no mask 71.4, 74.0); 8 x 1000 21.0, 21.5.  (Two rounds on their
+  // way: 32.5 / 80.6 at 32 x 3000.)
+  const bool dealt = rows_per_split == 0;
+  const int step = dealt ? splits * kRoundRows : kRoundRows, begin = split * (dealt ? kRoundRows : rows_per_split);
+  const int end = dealt || N < begin + rows_per_split ? N : begin + rows_per_split;
   // this wave's block of the state, and (8 waves) which four tiles of a round it adds up
   const int quadrant = L.wave & 3, part = L.wave >> 2;
   unsigned char* mine = round + L.wave * kSetBytes;
 
   typename F::Acc acc;
   acc.zero();
+  const int first = begin + L.wave * TR;
   WideRaw cur;
-  load_wide<true>(cur, L, src, r_begin + L.wave * TR, row_bits(m, r_begin + L.wave * TR, r_end, L));
-  int next_bits = row_bits(m, r_begin + kRoundRows + L.wave * TR, r_end, L);
-  for (int r0 = r_begin; r0 < r_end; r0 += kRoundRows) {
+  load_wide<true>(cur, L, src, first, row_bits(m, first, end, L));
+  int next_bits = row_bits(m, first + step, end, L);
+  for (int r0 = begin; r0 < end; r0 += step) {
     float inv[2];
     stage_wide<F, mapped_mode<F>(), true>(cur, L, eps, mine, inv);
     // the wave's tile of the next round travels while this round is added up
-    load_wide<true>(cur, L, src, r0 + kRoundRows + L.wave * TR, next_bits);
-    next_bits = row_bits(m, r0 + 2 * kRoundRows + L.wave * TR, r_end, L);
+    load_wide<true>(cur, L, src, r0 + step + L.wave * TR, next_bits);
+    next_bits = row_bits(m, r0 + 2 * step + L.wave * TR, end, L);
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -1211,7 +1217,7 @@ hipError_t states_w(const Problem& p, const Plan& plan, bool bwd) {
                      p.stream, static_cast<const unsigned char*>(p.Q),
                      static_cast<const unsigned char*>(p.K), static_cast<const unsigned char*>(p.V),
                      static_cast<const unsigned char*>(p.dO), p.mask, p.workspace, p.H, p.N,
-                     plan.splits, plan.rows_per_split, second, p.eps, byte_strides(p));
+                     plan.splits, bwd ? plan.rows_per_split : 0, second, p.eps, byte_strides(p));
   return hipGetLastError();
 }
 
