@@ -34,7 +34,7 @@ struct Granted {
   std::atomic<const void*> kernel{nullptr};
   std::atomic<uint64_t> devices{0};
 };
-constexpr int kMaxGranted = 256;
+constexpr int kMaxGranted = 512;  // (about 250 kernels ask)
 Granted g_granted[kMaxGranted];
 std::atomic<int> g_granted_count{0};
 std::mutex g_grant_mutex;
