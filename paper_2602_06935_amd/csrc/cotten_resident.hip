@@ -887,7 +887,11 @@ hipError_t run_short(const Problem& p, const Args& a, bool bwd) {
 template <class F>
 hipError_t run(const Problem& p, bool bwd) {
   const Args a = make_args(p);
-  if (p.N <= 8 * TR) return p.N <= 4 * TR ? run_short<F, 4>(p, a, bwd) : run_short<F, 8>(p, a, bwd);  // (see there)
+  // (A launch has fewer than 2^32 threads: with more slices than that admits, 2^24 of up to 64 rows or 2^23 of up to 128, the persistent
+  // kernels below, whose launches have as many workgroups as there are compute units.)
+  const int short_waves = p.N <= 4 * TR ? 4 : 8;
+  if (p.N <= 8 * TR && static_cast<int64_t>(a.slices) * 64 * short_waves < int64_t{1} << 32)
+    return short_waves == 4 ? run_short<F, 4>(p, a, bwd) : run_short<F, 8>(p, a, bwd);
   const int units = compute_units();
   const dim3 grid(static_cast<unsigned>(a.slices < units ? a.slices : units));
   const size_t lds = Lds<F>::kBytes;

@@ -94,3 +94,28 @@ def test_short_causal_16bit(oracle, dtype, d, B, H, N):
     for n, t, r in zip(("O", "dQ", "dK", "dV"), (O, *grads), ref):
         assert rel_l2(to_f64(t), r) <= bar_for(dtype), n
     assert all(np.all(to_f64(t)[dead.cpu().numpy()] == 0.0) for t in grads[1:])
+
+
+@pytest.mark.parametrize("slices,N,backward", [(1 << 24, 1, True), (1 << 23, 65, False)])
+def test_more_slices_than_a_launch_of_one_workgroup_each_admits(oracle, slices, N, backward):
+    """Every count up to the 2^24 slices that the entry points take runs: 2^24 workgroups of four waves, or 2^23 of eight,
+    would be 2^32 threads, which no launch has."""
+    d, H = 16, 8
+    print(f"[short 16 bit] {slices} slices x {N} rows", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(slices + N)
+    make = lambda: torch.empty(slices // H, H, N, d, device="cuda", dtype=torch.bfloat16).normal_(generator=gen)
+    Q = make()
+    K, V, dO = (make(), make(), make()) if N == 1 else (Q, Q, Q)     # (17 GB each at 65 rows)
+    opts = dict(scale=0.5, eps=1e-6)
+    out = [binding.cotten_attn_fwd(Q, K, V, None, **opts)]
+    if backward:
+        out += binding.cotten_attn_bwd(Q, K, V, None, dO, **opts)
+    few = torch.tensor([0, 1, slices // H // 2, slices // H - 1], device="cuda")
+    q, k, v, g = (to_f64(t[few]) for t in (Q, K, V, dO))
+    mask = np.ones((len(few), N), np.uint8)
+    ref = (oracle.fwd_linear(q, k, v, mask, **opts), *oracle.bwd(q, k, v, g, mask, **opts))
+    bar = bar_for("bf16")
+    for n, t, r in zip(("O", "dQ", "dK", "dV"), out, ref):
+        check_tensor(n, to_f64(t[few]), r, bar)
+    del Q, K, V, dO, out, t
+    torch.cuda.empty_cache()
