@@ -33,8 +33,22 @@ __device__ __forceinline__ float row_sum8(float x) {
 }
 
 // 1/sqrt(ss + eps) for a live row (hardware reciprocal square root, about 1 ulp), 0 otherwise.
+// (MARK: -0 instead, see zero_masked.)
+template <bool MARK = false>
 __device__ __forceinline__ float inv_norm_or_zero(float ss, float eps, bool live) {
-  return live ? __builtin_amdgcn_rsqf(ss + eps) : 0.0f;
+  return live ? __builtin_amdgcn_rsqf(ss + eps) : MARK ? -0.0f : 0.0f;
+}
+
+// dK and dV rows of masked keys are zeros by selection: as products of zero rows they would be NaN where the state or a
+// later row is not finite.  The rows are told by their 1/r, -0, which reaches the layout of the products anyway (+0: a
+// row that takes part and whose square sum overflows).
+__device__ __forceinline__ bool is_masked(float inv_r) { return __builtin_bit_cast(uint32_t, inv_r) == 0x80000000u; }
+template <int N>
+__device__ __forceinline__ void zero_masked(float inv_r, float (&dk)[N], float (&dv)[N]) {
+  if (is_masked(inv_r)) {  // (one branch over both: selects took 1 % of a causal backward)
+#pragma unroll
+    for (int i = 0; i < N; ++i) dk[i] = dv[i] = 0.0f;
+  }
 }
 
 __device__ __forceinline__ void wave_lds_fence() {
@@ -1037,11 +1051,11 @@ constexpr int mapped_mode() {
   return F::kMap == kMapElu1 ? kXFeature : kXNormalized;
 }
 
-// inv[h] = 1/r of row h (0 for rows that do not take part; their registers are zero).
+// inv[h] = 1/r of row h (0, with MARK -0, for rows that do not take part; their registers are zero).
 // Xt receives nothing, the raw rows, xhat, or phi(x) (kXFeature: then inv[h] is 1 for a row
 // that takes part, and `cols` says whether the lane's columns exist - phi(0) is not 0, so
 // padding columns and absent rows are written as zeros explicitly); Yt the raw y rows.
-template <class F, int XMODE, bool USE_Y>
+template <class F, int XMODE, bool USE_Y, bool MARK = false>
 __device__ __forceinline__ void stage(const Raw& r, const Lane& L, float eps, unsigned char* Xt,
                                       unsigned char* Yt, float (&inv)[2], bool cols = true) {
   // one row: x (INF: phi(x) may be infinite), y
@@ -1051,7 +1065,7 @@ __device__ __forceinline__ void stage(const Raw& r, const Lane& L, float eps, un
     const int row = L.r8 + 8 * h;
     if (XMODE == kXFeature) {
       const bool live = ((r.live >> h) & 1) != 0, on = live & cols;
-      inv[h] = live ? 1.0f : 0.0f;
+      inv[h] = live ? 1.0f : MARK ? -0.0f : 0.0f;
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[i] = elu1_or_zero(f[i], on);
       F::template put<decltype(inf)::value>(Xt, row, L.ch, f);
@@ -1060,7 +1074,7 @@ __device__ __forceinline__ void stage(const Raw& r, const Lane& L, float eps, un
     float ss = 0.0f;
 #pragma unroll
     for (int i = 0; i < F::EPL; ++i) ss += f[i] * f[i];
-    inv[h] = inv_norm_or_zero(row_sum8(ss), eps, (r.live >> h) & 1);
+    inv[h] = inv_norm_or_zero<MARK>(row_sum8(ss), eps, (r.live >> h) & 1);
     if (XMODE == kXNormalized) {
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) f[i] *= inv[h];

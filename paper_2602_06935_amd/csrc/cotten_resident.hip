@@ -731,7 +731,7 @@ __global__ __launch_bounds__(64 * WAVES, 4) void causal_bwd_kernel(const Args a)
     publish_inv(invs, L0, inv);
     const bool any_key = __ballot(rk.live != 0) != 0;
     if (any_key) {
-      stage<F, kXNormalized, true>(rk, L0, a.eps, blk + kKt, blk + kVt, inv);
+      stage<F, kXNormalized, true, true>(rk, L0, a.eps, blk + kKt, blk + kVt, inv);
       publish_inv(invs + TR, L0, inv);
     }
     if (L0.lane == 0) live[tile] = any_key;
@@ -814,13 +814,9 @@ __global__ __launch_bounds__(64 * WAVES, 4) void causal_bwd_kernel(const Args a)
         dv[i] *= scale;
         dk[i] *= scale;
       }
-      // 1/r is zero on masked rows, whose khat and v rows are zero too: exact zeros there
       if (RAW) project_rows_raw<F>(dk, xk, inv_k, L);
       else project_rows<F, false>(dk, xk, inv_k, L);
-      if (inv_k == 0.0f) {
-#pragma unroll
-        for (int i = 0; i < 2 * F::EPL; ++i) dv[i] = 0.0f;
-      }
+      zero_masked(inv_k, dk, dv);
     }
     if (row < N) {
       store_product_row<F, kStoreStreamed>(a.dK + base, row, a.st.row, L, dk);
