@@ -91,9 +91,9 @@ __device__ __forceinline__ void load_wide(WideRaw& r, const Lane& L, const WideS
 // The tile into LDS as 2 P tiles of 16 x 128 bytes [x pieces | y pieces] (each in the layout of
 // cotten_mfma_core.h); x raw, normalised over the whole row, or through the element-wise map of
 // the format (XMODE, see stage() in cotten_mfma_core.h).
-// inv[h] = 1/r of row r8 + 8 h (0 for a row that does not take part; with the element-wise map 1
+// inv[h] = 1/r of row r8 + 8 h (0, with MARK -0, for a row that does not take part; with the element-wise map 1
 // for a row that does, and a row that does not is written as zeros explicitly: phi(0) is not 0).
-template <class F, int XMODE, bool USE_Y>
+template <class F, int XMODE, bool USE_Y, bool MARK = false>
 __device__ __forceinline__ void stage_wide(const WideRaw& r, const Lane& L, float eps,
                                            unsigned char* tiles, float (&inv)[2]) {
 #pragma unroll
@@ -102,7 +102,7 @@ __device__ __forceinline__ void stage_wide(const WideRaw& r, const Lane& L, floa
     const bool live = ((r.live >> h) & 1) != 0;
     const int off = (L.r8 + 8 * h) * kTileStride + L.ch * 16;
     if (XMODE == kXFeature) {
-      inv[h] = live ? 1.0f : 0.0f;
+      inv[h] = live ? 1.0f : MARK ? -0.0f : 0.0f;
 #pragma unroll
       for (int c = 0; c < P; ++c) {
         F::unpack(r.x[h][c], f[c]);
@@ -120,7 +120,7 @@ __device__ __forceinline__ void stage_wide(const WideRaw& r, const Lane& L, floa
 #pragma unroll
       for (int i = 0; i < F::EPL; ++i) ss += f[c][i] * f[c][i];
     }
-    inv[h] = inv_norm_or_zero(row_sum8(ss), eps, live);
+    inv[h] = inv_norm_or_zero<MARK>(row_sum8(ss), eps, live);
 #pragma unroll
     for (int c = 0; c < P; ++c) {
       if (XMODE == kXNormalized) {
@@ -881,12 +881,11 @@ struct KeptLds {
 };
 
 // 32 rows of a tensor pair in the layout of products over 32 rows: chunk c is bytes 32 c + 16 half .. + 15 of row
-// lane%32, half = lane/32.  inv: 1/r of the row (see stage_wide).
+// lane%32, half = lane/32.
 template <class F>
 struct Rows32 {
   typename F::v8_t x[8], y[8];
-  float inv;
-  bool live;  // a row takes part (uniform)
+  float inv;  // 1/r, -0: the row does not take part
 };
 
 // The two staged tiles of a wave (`first`: rows 0-15, `second`: rows 16-31, each [xhat pieces | y pieces] with 1/r in
@@ -920,7 +919,7 @@ __device__ __forceinline__ void kept_state_pass(typename F::Acc& acc, const Wide
     const Lane L = L0.again();
     float inv[2];
     unsigned char* tiles = mine + (r & 1) * kSecond;
-    stage_wide<F, mapped_mode<F>(), true>(kept[r], L, eps, tiles, inv);
+    stage_wide<F, mapped_mode<F>(), true, true>(kept[r], L, eps, tiles, inv);
     if (L.ch == 0) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) *reinterpret_cast<float*>(tiles + (L.r8 + 8 * h) * kTileStride + kRowBytes) = inv[h];
@@ -935,7 +934,6 @@ __device__ __forceinline__ void kept_state_pass(typename F::Acc& acc, const Wide
     if ((r & 1) != 0 || r + 1 == ROUNDS) {  // (the wave's own tiles: written before the barrier)
       Rows32<F>& t = rows[r / 2];
       fetch_rows32<F>(t, mine, mine + kSecond, (r & 1) != 0, L);
-      t.live = __builtin_amdgcn_ballot_w64((kept[r & ~1].live | ((r & 1) != 0 ? kept[r].live : 0)) != 0) != 0;
       wave_lds_fence();
     }
     if (r + 1 < ROUNDS) stage(r + 1 < ROUNDS ? r + 1 : 0);
@@ -951,14 +949,18 @@ __device__ __forceinline__ void kept_state_pass(typename F::Acc& acc, const Wide
 // Block nb of the rows (values 8 t .. of a lane: 16 bytes at 64 nb + 32 t + 16 half of its row).  The lanes of rows 0-15
 // and 16-31 exchange chunks first, so that a store writes 64 contiguous bytes of each of 16 rows: with 32 of
 // each of 32 the streamed stores reach memory as parts of lines (1024 slices x 200 rows, backward: 220 us).
+// `rows`: which of the 32 are written (bit i: row row0 + i); the stores of the others lie outside the buffer.
 struct StoreRows32 {
-  __amdgpu_buffer_rsrc_t out;  // ends with row end - 1: rows beyond are dropped without a branch
-  uint32_t at;                 // of the first store: row lane%16, bytes 32 (group & 1) + 16 (group / 2)
-  int stride;
-  __device__ __forceinline__ StoreRows32(unsigned char* base, int row0, int end, int stride_bytes, const Lane& L)
-      : out(__builtin_amdgcn_make_buffer_rsrc(base, 0, end > row0 ? (end - 1) * stride_bytes + P * kHalfBytes : 0, 0x00020000)),
-        at(static_cast<uint32_t>(row0 + L.i16) * stride_bytes + 32 * (L.g16 & 1) + 16 * (L.g16 >> 1)),
-        stride(stride_bytes) {}
+  __amdgpu_buffer_rsrc_t out;
+  uint32_t at[2];  // of the first store: row lane%16 (+ 16), bytes 32 (group & 1) + 16 (group / 2)
+  __device__ __forceinline__ StoreRows32(unsigned char* base, int row0, int stride, uint32_t rows, const Lane& L)
+      : out(__builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000)) {
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      at[k] = ((rows >> (16 * k + L.i16)) & 1) != 0
+                  ? static_cast<uint32_t>(row0 + 16 * k + L.i16) * stride + 32 * (L.g16 & 1) + 16 * (L.g16 >> 1)
+                  : kOutOfBuffer;
+  }
   template <class F>
   __device__ __forceinline__ void store(int nb, const f32x16_t& v) const {
     u32x4_t t[2];
@@ -975,8 +977,15 @@ struct StoreRows32 {
       t[0][i] = swapped[0];
       t[1][i] = swapped[1];
     }
-    __builtin_amdgcn_raw_buffer_store_b128(t[0], out, at + 64 * nb, 0, kStoreStreamed);
-    __builtin_amdgcn_raw_buffer_store_b128(t[1], out, at + 16 * stride + 64 * nb, 0, kStoreStreamed);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) __builtin_amdgcn_raw_buffer_store_b128(t[k], out, at[k] + 64 * nb, 0, kStoreStreamed);
+  }
+  __device__ __forceinline__ void store_zeros() const {
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+      for (int k = 0; k < 2; ++k)
+        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0, 0, 0, 0}, out, at[k] + 64 * nb, 0, kStoreStreamed);
   }
 };
 
@@ -1002,18 +1011,15 @@ __device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, b
                                               const unsigned char* natural, const unsigned char* transposed,
                                               unsigned char* out_projected, unsigned char* out_plain, int stride,
                                               const Lane& L) {
-  const StoreRows32 projected(out_projected, row0, end, stride, L), plain(out_plain, row0, end, stride, L);
-  if (!t.live) {  // zeros
-    f32x16_t z;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb) {
-      if (plain_too) plain.store<F>(nb, z);
-      projected.store<F>(nb, z);
-    }
-    return;
+  // masked rows: zeros by stores of their own (as products they would be NaN where the state is not finite)
+  const uint32_t exist = end - row0 < 32 ? (1u << (end - row0)) - 1 : ~0u;
+  const uint32_t live = exist & ~static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(is_masked(t.inv)));
+  if (live != exist) {
+    StoreRows32(out_projected, row0, stride, exist & ~live, L).store_zeros();
+    if (plain_too) StoreRows32(out_plain, row0, stride, exist & ~live, L).store_zeros();
+    if (live == 0) return;
   }
+  const StoreRows32 projected(out_projected, row0, stride, live, L), plain(out_plain, row0, stride, live, L);
   if (plain_too) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -1027,11 +1033,16 @@ __device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, b
 #pragma unroll
   for (int p = 0; p < 2; ++p) blocks32<F>(t.y, natural, 2 * p, 1, L, g[2 * p], g[2 * p + 1]);
   const auto unit = [&](int c, float (&u)[8]) { F::unpack(__builtin_bit_cast(u32x4_t, t.x[c]), u); };
+  const auto unit_late = [&](int c, float (&u)[8]) {  // (unpacked here, neither earlier nor kept from before: 64 registers)
+    u32x4_t x = __builtin_bit_cast(u32x4_t, t.x[c]);
+    asm volatile("" : "+v"(x));
+    F::unpack(x, u);
+  };
   if (F::kMap == kMapElu1) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       float u[8];
-      unit(c, u);
+      unit_late(c, u);
 #pragma unroll
       for (int i = 0; i < 8; ++i) g[c >> 1][8 * (c & 1) + i] *= fminf(u[i], 1.0f);
     }
@@ -1047,10 +1058,8 @@ __device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, b
     proj += __shfl_xor(proj, 32);
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-      u32x4_t again = __builtin_bit_cast(u32x4_t, t.x[c]);  // (unpacked again rather than kept: 64 registers)
-      asm volatile("" : "+v"(again));
       float u[8];
-      F::unpack(again, u);
+      unit_late(c, u);
 #pragma unroll
       for (int i = 0; i < 8; ++i) g[c >> 1][8 * (c & 1) + i] = (g[c >> 1][8 * (c & 1) + i] - u[i] * proj) * t.inv;
     }

@@ -37,3 +37,11 @@ def check(dtype, slices, N, d, **opts):
 ])
 def test_causal(dtype, slices, N, d):
     check(dtype, slices, N, d, causal=True)
+
+
+@pytest.mark.parametrize("fmap", ["cosine", "elu1"])
+@pytest.mark.parametrize("dtype,slices,N,d", [
+    ("bf16", 300, 50, 128), ("f16", 100, 100, 128), ("bf16", 100, 150, 128), ("f16", 100, 250, 128),   # one to four rounds
+])
+def test_16bit_wide_kept(dtype, slices, N, d, fmap):
+    check(dtype, slices, N, d, feature_map=fmap)
