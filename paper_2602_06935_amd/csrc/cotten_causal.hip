@@ -823,11 +823,18 @@ hipError_t run_scan(const Problem& p, bool bwd) {
   // Calls without a mask have kernels of their own where that gains (bytes of an empty buffer, us, and none): bf16 d = 64, forward 256 x 600 22.7,
   // 21.5; 128 x 318 10.3, 9.4; backward 21.7, 20.6; 256 x 1001 79.4, 80.5;  fp32 d = 64, backward 8 x 200 13.3, 12.9; 128 x 200 31.9, 31.5.  Not the
   // fp32 forward (8 x 2800 87.8, 91.6) nor fp32 d = 32 (backward 64 x 820 37.9, 43.7).
-  if constexpr (F::kElemBytes == 2 || P == 2)
-    if (p.mask == nullptr && bwd) return launch(causal_scan_bwd_kernel<F, P, WAVES, true>);
+  // (16-bit rows in chunks of four tiles: forward only, see launch_causal)
+  if (bwd) {
+    if constexpr (F::kElemBytes == 2 && WAVES == 4) return hipErrorInvalidValue;
+    else {
+      if constexpr (F::kElemBytes == 2 || P == 2)
+        if (p.mask == nullptr) return launch(causal_scan_bwd_kernel<F, P, WAVES, true>);
+      return launch(causal_scan_bwd_kernel<F, P, WAVES, false>);
+    }
+  }
   if constexpr (F::kElemBytes == 2)
-    if (p.mask == nullptr && !bwd) return launch(causal_scan_fwd_kernel<F, P, WAVES, true>);
-  return bwd ? launch(causal_scan_bwd_kernel<F, P, WAVES, false>) : launch(causal_scan_fwd_kernel<F, P, WAVES, false>);
+    if (p.mask == nullptr) return launch(causal_scan_fwd_kernel<F, P, WAVES, true>);
+  return launch(causal_scan_fwd_kernel<F, P, WAVES, false>);
 }
 
 }  // namespace
