@@ -142,7 +142,7 @@ def test_causal_over_several_chunks(oracle, dtype, B, H, N, d):
     ("bf16", 70, 1, 520, 64),    # four segments, walked
     ("f16", 260, 1, 209, 64),    # one segment, the second chunk short
     ("bf16", 64, 4, 700, 16),    # one segment of six chunks, narrow rows
-    ("bf16", 300, 1, 60, 64),    # four-wave workgroups, one chunk
+    ("bf16", 300, 1, 60, 64),    # (by tile pairs in both directions; walks of one chunk: test_causal_forward_of_many_slices)
     ("f16", 1030, 1, 100, 32),   # forward the same with two chunks, backward by tile pairs
     ("bf16", 300, 1, 150, 64),   # forward walked, backward resident
 ])
@@ -178,7 +178,8 @@ def test_causal_walk(oracle, dtype, B, H, N, d):
 @pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5])
 def test_causal_walk_of_few_chunks(oracle, dtype, B, H, d, chunks):
     """Walks of one segment with each number of chunks on their way at the start, the last chunk of a single row or whole,
-    with a key mask and without one: forwards and backwards against the oracle on the first and last sequences."""
+    with a key mask and without one: forwards and backwards against the oracle on the first and last sequences.  (16 bits, up to
+    128 rows: by tile pairs, and with two chunks of 129 rows the backward as well.)"""
     rows = 64 if dtype == "f32" else 128
     for N in (rows * (chunks - 1) + 1, rows * chunks):
         print(f"[causal] few chunks {dtype} B={B} H={H} N={N} d={d}", flush=True)
@@ -198,6 +199,41 @@ def test_causal_walk_of_few_chunks(oracle, dtype, B, H, d, chunks):
                 check_tensor(n, to_f64(g[pick]), r, bar_for(dtype), few_terms=True)
             if m is not None:
                 assert (out[2][-1, :, :N - 1] == 0).all() and (out[3][-1, :, :N - 1] == 0).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f16", 64), ("f16", 32)])
+@pytest.mark.parametrize("slices,N", [
+    (1024, 50), (1024, 64), (1023, 65), (1023, 128),                # by tile pairs in LDS, four and eight waves
+    (1025, 1), (1025, 50), (1025, 64),                              # walks of four waves, one chunk, no state carried
+    (1024, 65), (1024, 128),                                        # and two chunks
+])
+def test_causal_forward_of_many_slices(oracle, dtype, d, slices, N):
+    """16-bit forwards on both sides of the numbers of slices from which they walk, with a key mask and without one."""
+    H = 5 if slices % 5 == 0 else 1
+    B = slices // H
+    print(f"[causal] many slices {dtype} B={B} H={H} N={N} d={d}", flush=True)
+    Q, K, V, _, mask = _inputs(5600 + N + d, dtype, B, H, N, d)
+    mask[-1] = 0
+    mask[-1, N // 2:] = 1
+    tq, tk, tv = (to_gpu(x, dtype) for x in (Q, K, V))
+    tm = torch.from_numpy(mask).cuda()
+    dead = (tm == 0)[:, None, :, None].expand_as(tk)
+    tk2, tv2 = tk.clone(), tv.clone()
+    tk2[dead], tv2[dead] = float("nan"), float("inf")
+    pick = [0, 1, B // 2, B - 1]
+    sw = lambda t: t.permute(0, 2, 1, 3).contiguous()
+    few = [np.ascontiguousarray(x[pick]) for x in (Q, K, V)]
+    for m in (tm, None):
+        O = binding.cotten_attn_fwd(tq, tk, tv, m, scale=0.2, causal=True)
+        k, v = (tk, tv) if m is None else (tk2, tv2)               # masked rows may hold anything
+        O2 = binding.cotten_attn_fwd(sw(tq), sw(k), sw(v), m, scale=0.2, causal=True, layout="bnhd")
+        assert torch.equal(sw(O), O2)
+        fm = np.ones((len(pick), N), np.uint8) if m is None else np.ascontiguousarray(mask[pick])
+        check_tensor("O", to_f64(O[pick]), oracle.causal_fwd(*few, fm, scale=0.2), bar_for(dtype), few_terms=True)
+        # every sequence, not only those: the same as in a call of a few sequences (tile pairs there, whatever serves here)
+        alone = torch.cat([binding.cotten_attn_fwd(tq[i:i + 64], tk[i:i + 64], tv[i:i + 64], None if m is None else m[i:i + 64],
+                                                   scale=0.2, causal=True) for i in range(0, B, 64)])
+        assert rel_l2(to_f64(O), to_f64(alone)) <= 2 * bar_for(dtype)
 
 
 def test_causal_chunks_layout_scales_workspace(oracle):

@@ -26,6 +26,7 @@ CASES = [
     ("f32", 1, 1, 1, 32),
     ("bf16", 4, 2, 200, 128),    # 256-byte rows: one-launch forward, three-launch backward
     ("bf16", 100, 1, 130, 128),  # one launch per direction, the backward's tiles kept
+    ("f16", 171, 3, 70, 128),    # forward with two slices per workgroup, the last one alone
     ("f32", 100, 1, 77, 64),
     ("f32", 128, 2, 300, 64),    # one launch per direction, tiles streamed
     ("f16", 2, 2, 600, 128),     # sequence cut over several workgroups

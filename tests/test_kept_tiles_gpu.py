@@ -1,6 +1,6 @@
 """Short fp32 sequences (rows of up to 128 bytes): the kernels that keep one, two, three or four 16-row
-tiles per wave, at the edges of their ranges; with one tile per wave K and V are requested without
-waiting for the key mask, so what masked rows hold must not matter."""
+tiles per wave, at the edges of their ranges.  What masked rows hold must not matter: their loads go
+nowhere, with one tile per wave by key bytes that do not pass through LDS."""
 from __future__ import annotations
 
 import numpy as np

@@ -1,5 +1,6 @@
 """dK and dV rows of masked keys are exact zeros whatever the rows that take part hold, infinities and NaN
-included: each kernel that writes them, next to valid keys of the same 16 and 32 rows."""
+included, next to valid keys of the same 16 and 32 rows: the causal kernels, and the backward of 16-bit rows of
+256 bytes that keeps its rows in registers."""
 from __future__ import annotations
 
 import pytest

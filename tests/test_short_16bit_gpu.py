@@ -57,8 +57,9 @@ def test_short_16bit(oracle, dtype, d, B, H, N, fmap):
         check_tensor(n, to_f64(t), r, bar)
     # (a sum over all rows of a slice, with cancellation: five times the bar, as elsewhere)
     assert rel_l2(dlog.double().cpu().numpy(), (g * ref[0]).sum((2, 3))) <= 5 * bar
-    if fmap == "cosine":
-        assert rel_l2(state.double().cpu().numpy(), oracle.state(K.float().cpu().numpy(), V.float().cpu().numpy(), mask)) <= bar
+    ref_state = (np.einsum("bn,bhnc,bhne->bhce", mask, np.where(k > 0, k + 1, np.exp(np.minimum(k, 0))), v) if fmap == "elu1"
+                 else oracle.state(K.float().cpu().numpy(), V.float().cpu().numpy(), mask))
+    assert rel_l2(state.double().cpu().numpy(), ref_state) <= bar
 
 
 @pytest.mark.parametrize("dtype,d,B,H,N", [
@@ -94,6 +95,23 @@ def test_short_causal_16bit(oracle, dtype, d, B, H, N):
     for n, t, r in zip(("O", "dQ", "dK", "dV"), (O, *grads), ref):
         assert rel_l2(to_f64(t), r) <= bar_for(dtype), n
     assert all(np.all(to_f64(t)[dead.cpu().numpy()] == 0.0) for t in grads[1:])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_short_causal_backward_from_rows_as_they_are(oracle, dtype):
+    """More than 256 slices of up to 64 rows: dV takes the keys as they are and divides its result, fewer round them after the
+    division.  The same sequences one way and the other, both against 64 bits: a rounding less shows (2.9e-3 and 3.3e-3 in bf16)."""
+    B, N, d = 300, 50, 64
+    print(f"[short 16 bit, causal] rows as they are, {dtype}", flush=True)
+    rng = np.random.default_rng(6500)
+    Q, K, V, dO = (to_gpu(rng.standard_normal((B, 1, N, d)).astype(np.float32), dtype) for _ in range(4))
+    opts = dict(scale=0.05, eps=1e-6, causal=True)
+    raw = binding.cotten_attn_bwd(Q, K, V, None, dO, **opts)[2][:256]
+    few = binding.cotten_attn_bwd(Q[:256], K[:256], V[:256], None, dO[:256], **opts)[2]
+    ref = oracle.causal_bwd(*(to_f64(t[:256]) for t in (Q, K, V, dO)), np.ones((256, N), np.uint8), scale=0.05, eps=1e-6)[2]
+    e_raw, e_few = rel_l2(to_f64(raw), ref), rel_l2(to_f64(few), ref)
+    print(f"[short 16 bit, causal]   dV {e_raw:.3e}, rounded {e_few:.3e}", flush=True)
+    assert e_raw <= 0.95 * e_few <= bar_for(dtype)
 
 
 @pytest.mark.parametrize("slices,N,backward", [(1 << 24, 1, True), (1 << 23, 65, False)])

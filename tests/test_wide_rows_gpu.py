@@ -38,7 +38,7 @@ def _inputs(seed, dtype, B, H, N, d):
 @pytest.mark.parametrize("dtype,B,H,N,d", [
     ("bf16", 3, 2, 1, 128), ("bf16", 3, 2, 17, 128), ("bf16", 4, 2, 200, 128),
     ("f16", 3, 2, 130, 128), ("f32", 3, 2, 65, 64), ("f32", 4, 2, 200, 64),
-    ("bf16", 300, 2, 70, 128),      # 600 slices: one workgroup per slice, no reduction
+    ("bf16", 300, 2, 70, 128),      # 600 slices: no reduction; forward with two slices per workgroup
     ("f32", 280, 2, 100, 64),
     ("bf16", 2, 2, 3000, 128),      # long sequences cut over many workgroups
     ("f32", 1, 3, 2500, 64),
@@ -49,7 +49,7 @@ def _inputs(seed, dtype, B, H, N, d):
     ("bf16", 100, 1, 257, 128),     # the shortest it does not
     ("f16", 128, 2, 300, 128),      # one launch, tiles streamed, fp16
     ("f16", 2, 2, 600, 128),        # three launches, workgroups of eight waves, fp16
-    ("bf16", 257, 1, 40, 128),      # forward with two slices per workgroup, the last one alone
+    ("bf16", 257, 1, 40, 128),      # forward: a workgroup of four waves per slice
     ("f32", 129, 3, 90, 64),
     ("bf16", 100, 2, 600, 128),     # one launch per direction, tiles streamed
     ("f32", 100, 2, 600, 64),       # three launches, workgroups of four waves (600 of them)
@@ -84,6 +84,7 @@ def test_wide_rows_parity(oracle, dtype, B, H, N, d):
     ("bf16", 128, 3, 3, 333), ("f32", 64, 3, 3, 333),    # state, reduction, apply launches
     ("bf16", 128, 45, 2, 120), ("f32", 64, 45, 2, 120),  # one launch, the backward's tiles kept
     ("bf16", 128, 130, 2, 300), ("f32", 64, 130, 2, 300),  # one launch, tiles streamed
+    ("bf16", 128, 171, 3, 130), ("f16", 128, 171, 3, 65),  # forward with two slices per workgroup, the last one alone
 ])
 def test_wide_rows_layout_scales_state_dlog(oracle, dtype, d, B, H, N):
     """[B,N,H,d] layout bit for bit; per-slice scales; the kept state against the oracle's and
@@ -132,9 +133,9 @@ def test_wide_rows_layout_scales_state_dlog(oracle, dtype, d, B, H, N):
 
 
 @pytest.mark.parametrize("dtype,B,H,N,d", [("bf16", 100, 1, 200, 128), ("f32", 128, 2, 300, 64),
-                                           ("bf16", 3, 1, 700, 128)])
+                                           ("bf16", 3, 1, 700, 128), ("bf16", 171, 3, 100, 128)])
 def test_wide_rows_without_mask(oracle, dtype, B, H, N, d):
-    """mask = NULL: every key takes part (kept tiles, streamed tiles, three launches)."""
+    """mask = NULL: every key takes part (kept tiles, streamed tiles, three launches; forward in pairs)."""
     print(f"[wide rows] no mask: {dtype} B={B} H={H} N={N} d={d}", flush=True)
     Q, K, V, dO, _ = _inputs(7100 + N + d, dtype, B, H, N, d)
     tq, tk, tv, tg = (to_gpu(x, dtype) for x in (Q, K, V, dO))
