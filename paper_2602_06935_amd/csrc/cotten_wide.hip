@@ -200,9 +200,10 @@ __global__ __launch_bounds__(64 * WAVES) void wide_state_kernel(
   const uint8_t* __restrict__ m =
       (second || mask == nullptr) ? nullptr : mask + static_cast<size_t>(bh / H) * N;
   // Forward (rows_per_split = 0): rounds are dealt to the workgroups in turn, so that padding at one end of the sequence is shared
-  // evenly; backward: consecutive rows.  us, consecutive and dealt, bf16: forward 32 slices x 3000 rows 34.6, 31.6 (no mask 34.9, 34.9);
-  // 128 x 4096 121, 116;  100 x 1500 49.5, 48.3;  backward 32 x 3000 79.2, 78.2 (no mask 71.4, 74.0); 8 x 1000 21.0, 21.5.  (Two rounds on their
-  // way: 32.5 / 80.6 at 32 x 3000.)
+  // evenly; backward: consecutive rows.  us, consecutive and dealt, bf16, lengths uniform in N/4 ... N, buffers in turn:  padded on the left, as
+  // histories are, 16 slices x 3000 rows 25.3, 25.2;  32 x 3000 36.9, 35.5;  32 x 4096 44.4, 42.5;  64 x 4096 69.4, 67.0;  128 x 4096 122, 119;  on the right
+  // 32 x 3000 37.3, 37.0;  32 x 4096 44.3, 45.4;  24 x 4096 38.2, 40.3 (the worst of 100 shapes);  128 x 4096 123, 123;  not padded +-1 %;  backward
+  // 32 x 3000 79.2, 78.2 (no mask 71.4, 74.0); 8 x 1000 21.0, 21.5.  (Two rounds on their way, 32 x 3000: 3 % slower.)
   const bool dealt = rows_per_split == 0;
   const int step = dealt ? splits * kRoundRows : kRoundRows, begin = split * (dealt ? kRoundRows : rows_per_split);
   const int end = dealt || N < begin + rows_per_split ? N : begin + rows_per_split;
@@ -864,11 +865,12 @@ __global__ __launch_bounds__(512) void wide_fused_bwd_kernel(const LaunchArgs a,
 // a row): these take half the operand reads of products over 16, and nothing is staged or normalised again.
 //
 // Bound by what follows one another in a workgroup (one per compute unit): the first rows' way from memory, the states, the
-// images, the products, the stores.  us, products over 16 rows staged again and this, bf16: 1024 slices x 200 rows 88.4, 81.1 (3.9
-// TB/s); 512 x 100 27.6, 23.2; 300 x 256 45.1, 42.2; 90 x 200 20.7, 17.3; 1024 x 50 35.9, 31.2; ELU + 1, 512 x 200 53.3, 46.1.
+// images, the products, the stores.  us, products over 16 rows staged again and this, bf16, left-padded lengths uniform in 0 ... N, over
+// the same buffers: 1024 slices x 200 rows 78.8, 72.5 (fresh ones 80.5, 3.9 TB/s); 512 x 100 24.7, 20.5; 300 x 256 41.5, 38.3; 90 x 200
+// 19.3, 15.9; 1024 x 50 33.5, 28.2; ELU + 1, 512 x 200 50.2, 41.7.  Traffic: each row once (256 x 200: 39.1 MB fetched, 39.3 written).
 constexpr int kKeptRows = 256;
 // Sequences of so many rounds of 64 rows: a workgroup takes one slice after the other, the next one's rows requested ahead.  Longer
-// ones leave no registers for that (1024 x 50 rows 35.0 without, 31.2; two rounds, 1024 x 128: 47.1 without, 49.5; four, 300 x 256: 42.2, 47.2).
+// ones leave no registers for that (fresh buffers, 1024 x 50 rows 35.0 without, 31.2; two rounds, 1024 x 128: 47.1 without, 49.5; four, 300 x 256: 42.2, 47.2).
 constexpr int kAheadRounds = 1;
 
 template <class F>
@@ -949,18 +951,14 @@ __device__ __forceinline__ void kept_state_pass(typename F::Acc& acc, const Wide
 // Block nb of the rows (values 8 t .. of a lane: 16 bytes at 64 nb + 32 t + 16 half of its row).  The lanes of rows 0-15
 // and 16-31 exchange chunks first, so that a store writes 64 contiguous bytes of each of 16 rows: with 32 of
 // each of 32 the streamed stores reach memory as parts of lines (1024 slices x 200 rows, backward: 220 us).
-// `rows`: which of the 32 are written (bit i: row row0 + i); the stores of the others lie outside the buffer.
 struct StoreRows32 {
-  __amdgpu_buffer_rsrc_t out;
-  uint32_t at[2];  // of the first store: row lane%16 (+ 16), bytes 32 (group & 1) + 16 (group / 2)
-  __device__ __forceinline__ StoreRows32(unsigned char* base, int row0, int stride, uint32_t rows, const Lane& L)
-      : out(__builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000)) {
-#pragma unroll
-    for (int k = 0; k < 2; ++k)
-      at[k] = ((rows >> (16 * k + L.i16)) & 1) != 0
-                  ? static_cast<uint32_t>(row0 + 16 * k + L.i16) * stride + 32 * (L.g16 & 1) + 16 * (L.g16 >> 1)
-                  : kOutOfBuffer;
-  }
+  __amdgpu_buffer_rsrc_t out;  // ends with row end - 1: rows beyond are dropped without a branch
+  uint32_t at;                 // of the first store: row lane%16, bytes 32 (group & 1) + 16 (group / 2)
+  int stride;
+  __device__ __forceinline__ StoreRows32(unsigned char* base, int row0, int end, int stride_bytes, const Lane& L)
+      : out(__builtin_amdgcn_make_buffer_rsrc(base, 0, end > row0 ? (end - 1) * stride_bytes + P * kHalfBytes : 0, 0x00020000)),
+        at(static_cast<uint32_t>(row0 + L.i16) * stride_bytes + 32 * (L.g16 & 1) + 16 * (L.g16 >> 1)),
+        stride(stride_bytes) {}
   template <class F>
   __device__ __forceinline__ void store(int nb, const f32x16_t& v) const {
     u32x4_t t[2];
@@ -977,17 +975,22 @@ struct StoreRows32 {
       t[0][i] = swapped[0];
       t[1][i] = swapped[1];
     }
-#pragma unroll
-    for (int k = 0; k < 2; ++k) __builtin_amdgcn_raw_buffer_store_b128(t[k], out, at[k] + 64 * nb, 0, kStoreStreamed);
-  }
-  __device__ __forceinline__ void store_zeros() const {
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-      for (int k = 0; k < 2; ++k)
-        __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{0, 0, 0, 0}, out, at[k] + 64 * nb, 0, kStoreStreamed);
+    __builtin_amdgcn_raw_buffer_store_b128(t[0], out, at + 64 * nb, 0, kStoreStreamed);
+    __builtin_amdgcn_raw_buffer_store_b128(t[1], out, at + 16 * stride + 64 * nb, 0, kStoreStreamed);
   }
 };
+
+// Zeros over some of 32 rows (bit i: row row0 + i), four lanes a row.
+__device__ __forceinline__ void zero_rows32(unsigned char* base, int row0, int end, int stride, uint32_t rows, const Lane& L) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int i = 16 * k + L.i16;
+    if (((rows >> i) & 1) == 0 || row0 + i >= end) continue;
+    u32x4_t* at = reinterpret_cast<u32x4_t*>(base + static_cast<size_t>(row0 + i) * stride) + L.g16;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) at[4 * c] = u32x4_t{0, 0, 0, 0};
+  }
+}
 
 // Blocks 0 and 1 of a half row of the product of 32 rows X with the images first, first + step: sum over the halves of X.
 // (Two chains of products that wait for themselves only.)
@@ -1011,15 +1014,19 @@ __device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, b
                                               const unsigned char* natural, const unsigned char* transposed,
                                               unsigned char* out_projected, unsigned char* out_plain, int stride,
                                               const Lane& L) {
-  // masked rows: zeros by stores of their own (as products they would be NaN where the state is not finite)
-  const uint32_t exist = end - row0 < 32 ? (1u << (end - row0)) - 1 : ~0u;
-  const uint32_t live = exist & ~static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(is_masked(t.inv)));
-  if (live != exist) {
-    StoreRows32(out_projected, row0, stride, exist & ~live, L).store_zeros();
-    if (plain_too) StoreRows32(out_plain, row0, stride, exist & ~live, L).store_zeros();
-    if (live == 0) return;
+  const StoreRows32 projected(out_projected, row0, end, stride, L), plain(out_plain, row0, end, stride, L);
+  const uint32_t masked = static_cast<uint32_t>(__builtin_amdgcn_ballot_w64(is_masked(t.inv)));  // (absent rows too)
+  if (masked == ~0u) {  // zeros
+    f32x16_t z;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb) {
+      if (plain_too) plain.store<F>(nb, z);
+      projected.store<F>(nb, z);
+    }
+    return;
   }
-  const StoreRows32 projected(out_projected, row0, stride, live, L), plain(out_plain, row0, stride, live, L);
   if (plain_too) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
@@ -1033,18 +1040,20 @@ __device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, b
 #pragma unroll
   for (int p = 0; p < 2; ++p) blocks32<F>(t.y, natural, 2 * p, 1, L, g[2 * p], g[2 * p + 1]);
   const auto unit = [&](int c, float (&u)[8]) { F::unpack(__builtin_bit_cast(u32x4_t, t.x[c]), u); };
-  const auto unit_late = [&](int c, float (&u)[8]) {  // (unpacked here, neither earlier nor kept from before: 64 registers)
-    u32x4_t x = __builtin_bit_cast(u32x4_t, t.x[c]);
-    asm volatile("" : "+v"(x));
-    F::unpack(x, u);
-  };
+  float check = 0.0f;  // masked rows: 0 if the state is finite, NaN if not
   if (F::kMap == kMapElu1) {
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
       float u[8];
-      unit_late(c, u);
+      unit(c, u);
 #pragma unroll
       for (int i = 0; i < 8; ++i) g[c >> 1][8 * (c & 1) + i] *= fminf(u[i], 1.0f);
+    }
+    if (masked != 0) {
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) check += g[nb][i];
     }
   } else {
     float proj = 0.0f;
@@ -1056,16 +1065,28 @@ __device__ __forceinline__ void kept_rows_bwd(Rows32<F>& t, int row0, int end, b
       for (int i = 0; i < 8; ++i) proj += u[i] * g[c >> 1][8 * (c & 1) + i];
     }
     proj += __shfl_xor(proj, 32);
+    check = proj;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
+      u32x4_t again = __builtin_bit_cast(u32x4_t, t.x[c]);  // (unpacked again rather than kept: 64 registers)
+      asm volatile("" : "+v"(again));
       float u[8];
-      unit_late(c, u);
+      F::unpack(again, u);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) g[c >> 1][8 * (c & 1) + i] = (g[c >> 1][8 * (c & 1) + i] - u[i] * proj) * t.inv;
+      for (int i = 0; i < 8; ++i)  // (1/r of masked rows is -0: the sign would reach their zeros)
+        g[c >> 1][8 * (c & 1) + i] = (g[c >> 1][8 * (c & 1) + i] - u[i] * proj) * fabsf(t.inv);
     }
   }
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) projected.store<F>(nb, g[nb]);
+  // Masked rows are zeros as products of zero rows, but NaN where a value of the state is not finite.  That value is in the
+  // sums of g of every row, and so in `check`: then zeros go over them, which costs the others nothing.
+  const uint64_t not_zero = __builtin_amdgcn_ballot_w64(is_masked(t.inv) && !(check == 0.0f));  // (ELU + 1: each lane of its half row)
+  if (not_zero != 0) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (behind the stores above)
+    zero_rows32(out_projected, row0, end, stride, static_cast<uint32_t>(not_zero | not_zero >> 32), L);
+    if (plain_too) zero_rows32(out_plain, row0, end, stride, static_cast<uint32_t>(not_zero | not_zero >> 32), L);
+  }
 }
 
 // For sequences of ROUNDS rounds of 64 rows.  A workgroup takes slices blockIdx.x, + gridDim.x, ... (ROUNDS <= kAheadRounds; the
@@ -1292,7 +1313,7 @@ hipError_t fused(const Problem& p, const Plan& plan, bool bwd) {
   const hipError_t err = grant_dynamic_lds(kern, max_lds_bytes<8>());
   if (err != hipSuccess) return err;
   // Forward, more slices than compute units: four waves per slice.  A workgroup each while all of them run at once (in pairs,
-  // 260 slices would leave every other compute unit idle) or the sequences are shorter than a round or little more, pairs in
+  // 260 slices would leave every other compute unit idle) or the sequences are a round of 64 rows at most, pairs in
   // one workgroup beyond.  us, pairs and one each, bf16: 260 x 200 rows 17.5, 15.2;  300 x 200 18.1, 16.5;  512 x 100 11.1, 10.8;
   // 2048 x 20 20.5, 19.0;  1024 x 50 12.8, 12.4;  1024 x 200 35.8, 37.3.
   if (!bwd && blocks > static_cast<unsigned>(kUnits)) {

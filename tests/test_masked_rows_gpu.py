@@ -20,14 +20,16 @@ def check(dtype, slices, N, d, **opts):
     mask = (torch.rand(slices, N, device="cuda", generator=gen) < 0.5).to(torch.uint8)
     mask[1::3, : N // 2] = 0
     dead = (mask == 0)[:, None, :, None].expand_as(K)
-    for what, value in (("dO", float("inf")), ("Q", float("nan"))):
+    # (columns that different lanes of a row hold: under ELU + 1 a NaN of Q reaches one row of the state only)
+    for what, column, value in (("dO", 3, float("inf")), ("Q", 3, float("nan")), ("Q", 11, float("nan")), ("Q", d - 1, float("nan"))):
         x = dict(Q=Q.clone(), dO=dO.clone())
-        x[what][:, :, N - 1, 3] = value
+        x[what][:, :, N - 1, column] = value
         for layout in ("bhnd", "bnhd"):
             to = lambda t: t if layout == "bhnd" else t.permute(0, 2, 1, 3).contiguous()
             _, dK, dV = binding.cotten_attn_bwd(to(x["Q"]), to(K), to(V), mask, to(x["dO"]), scale=0.1, eps=1e-6,
                                                 layout=layout, **opts)
-            assert (to(dK)[dead] == 0).all() and (to(dV)[dead] == 0).all(), (what, layout)
+            for g in (dK, dV):                                  # (of either sign would be equal)
+                assert (to(g)[dead].view(torch.int32 if dtype == "f32" else torch.int16) == 0).all(), (what, column, layout)
             assert not torch.isfinite(to(dV).float()).all()     # (it is not for want of anything to hide)
 
 
