@@ -869,11 +869,12 @@ hipError_t launch_causal(const Problem& p, bool bwd) {
   if (p.dtype == 0) return run_scan<F32x32, 1, 4>(p, bwd);
   // 16-bit rows.  The walk reads what its two backward roles share twice; a slice of at most 208
   // rows held in LDS is read once: workgroups of four waves up to 64 rows (four on a compute unit), of eight up to 128 (two), of thirteen
-  // beyond (one).  The backward always gains by it, the forward while the workgroups do not queue up.  us, walk and in LDS, bf16 d = 64:
-  //   forward   512 slices x 50 rows 4.8, 4.7;  2048 x 50 10.6, 11.0;  512 x 100 6.9, 6.6;  1022 x 100 13.0, 12.4;  2048 x 100 20.2, 20.4;
-  //             256 x 200 9.5, 8.2;  512 x 200 11.6, 13.9
-  //   backward  512 x 50 8.2, 7.0;  4096 x 50 47.4, 36.5;  (with sixteen waves whatever the length, 512 x 100 12.9, now 10.2;  2048 x 100 52.3, 37.7);
-  //             512 x 200 29.1, 26.9
+  // beyond (one).  The backward always gains by it, the forward while the workgroups do not queue up.  us, walk and in LDS, bf16 d = 64,
+  // with a key mask (left-padded lengths uniform in 0 ... N) and without, over the same buffers:
+  //   forward   512 slices x 50 rows 3.9, 3.8 and 4.0, 3.7;  1024 x 50 5.0, 4.6 and 4.7, 4.4;  512 x 100 5.7, 5.0 and 5.3, 5.0;  1022 x 100 11.1, 9.0 and
+  //             10.6, 10.4;  over fresh ones 2048 x 50 10.6, 11.0;  2048 x 100 20.2, 20.4;  256 x 200 9.5, 8.2;  512 x 200 11.6, 13.9
+  //   backward  512 x 50 7.3, 5.8 and 6.9, 5.6;  4096 x 50 39.0, 27.2 and 42.5, 30.4;  (with sixteen waves whatever the length, 512 x 100 11.0,
+  //             now 8.1;  2048 x 100 42.9, 28.8);  over fresh ones 512 x 200 29.1, 26.9
   // (1024 slices or more of 65 ... 128 rows, forward: chunks of 64 rows, whose carried state keeps more bits than the scores do: 2.65e-3 from
   // 64 bits at 1024 x 100, in LDS 2.88e-3.)
   const long slices = static_cast<long>(p.B) * p.H;

@@ -427,11 +427,13 @@ __global__ __launch_bounds__(kThreads) void resident_bwd_kernel(const Args a) {
 // follow one another on it; here every slice has a workgroup of four or eight waves, 27 (forward) or 37 KB of LDS for four, and
 // their phases overlap.  The states are built as above, a 32 x 32 block per wave (the same sums); own rows are
 // held in the layout of the products by the time the operand images go over the tiles.
-// Bound by the way to memory and back of a workgroup while few run, by memory beyond.  Forward / backward, us, the
-// persistent kernels and these, bf16 d = 64: 16 slices x 50 rows 4.3 / 6.3, 3.2 / 4.3;  512 x 50 6.3 / 10.7, 4.7 / 6.7;  4096 x 50 33.6 / 67.8, 18.3 / 37;
-// 16 x 100 4.6 / 6.9, 3.7 / 5.3;  512 x 100 7.3 / 12.9, 6.1 / 9.4;  2048 x 128 23.4 / 49.5, 20.4 / 41.9;  d = 32, 2048 x 20 15.4 / 29.9, 6.0 / 12.0; 2048 x
-// 128 19.9 / 40.7, 11.5 / 28.  (K and V requested together with the mask, and what is masked dropped on arrival: 16 x 50 3.2 / 4.3, 512
-// x 50 5.0 / 7.0, 2048 x 128 27 / 50, where the masked rows cost traffic.)
+// Bound by the way to memory and back of a workgroup while few run, by memory beyond.  Forward / backward, us (left-padded lengths
+// uniform in 0 ... N, over the same buffers), the persistent kernels and these, bf16 d = 64: 16 slices x 50 rows 4.4 / 6.3, 3.3 / 4.4;  512 x 50
+// 6.2 / 10.1, 3.7 / 5.5;  4096 x 50 31.3 / 62.5, 15.8 / 28.8;  16 x 100 4.6 / 6.9, 3.8 / 5.4;  512 x 100 7.0 / 11.7, 4.9 / 7.7;  2048 x 128 21.5 / 41.5,
+// 19.4 / 33.8;  d = 32, 2048 x 20 14.4 / 28.8, 5.6 / 11.6;  2048 x 128 19.4 / 37.5, 10.8 / 24.5.  Without a mask 512 x 100 6.3 / 11.5, 4.7 / 7.7; the
+// forward of 2048 ... 6000 slices x 80 ... 128 rows of 128 bytes loses 1 ... 6 % where the buffers stay in the memory-side cache (2048 x 128 22.0,
+// 23.0) and gains up to 5 % where they do not (4096 x 96 41.0, 39.5).  (K and V requested together with the mask, and what is masked
+// dropped on arrival: as fast for 16 x 50, 6 % slower at 512 x 50, 2048 x 128 30 % and 20 %, where the masked rows cost traffic.)
 
 // Valid-key bits of the wave's tile, see key_rows (no branch, the slice exists).
 __device__ __forceinline__ int short_key_rows(const Args& a, const Lane& L, int bh, int tile) {
@@ -918,7 +920,8 @@ hipError_t run_causal(const Problem& p, bool bwd) {
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(a.slices)), dim3(64 * WAVES), lds, p.stream, a);
     return hipGetLastError();
   };
-  // (calls that the walk served before are as exact here; 16 and 128 slices x 50 rows, us: 4.6 and 4.8, RAW 4.8 and 5.0)
+  // (RAW from 257 slices on: dV is then as far from 64 bits as the walk over chunks leaves it, bf16, 300 x 50 2.88e-3, without 3.33e-3.  Fewer slices
+  // wait for its loads of the own rows: 16 and 128 slices x 50 rows 4.6 and 4.8 us, RAW 4.8 and 5.0.)
   if constexpr (WAVES == 4) {
     if (bwd && a.slices > 256) return launch(causal_bwd_kernel<F, WAVES, true>);
   }

@@ -866,8 +866,8 @@ __global__ __launch_bounds__(512) void wide_fused_bwd_kernel(const LaunchArgs a,
 //
 // Bound by what follows one another in a workgroup (one per compute unit): the first rows' way from memory, the states, the
 // images, the products, the stores.  us, products over 16 rows staged again and this, bf16, left-padded lengths uniform in 0 ... N, over
-// the same buffers: 1024 slices x 200 rows 78.8, 72.5 (fresh ones 80.5, 3.9 TB/s); 512 x 100 24.7, 20.5; 300 x 256 41.5, 38.3; 90 x 200
-// 19.3, 15.9; 1024 x 50 33.5, 28.2; ELU + 1, 512 x 200 50.2, 41.7.  Traffic: each row once (256 x 200: 39.1 MB fetched, 39.3 written).
+// the same buffers: 1024 slices x 200 rows 78.8, 75.1 (fresh ones 80.6, 3.9 TB/s); 512 x 100 24.9, 20.9; 300 x 256 41.5, 39.6; 90 x 200
+// 19.3, 16.0; 1024 x 50 33.5, 28.3; ELU + 1, 512 x 200 49.8, 42.5.  Traffic: each row once (256 x 200: 39.1 MB fetched, 39.3 written).
 constexpr int kKeptRows = 256;
 // Sequences of so many rounds of 64 rows: a workgroup takes one slice after the other, the next one's rows requested ahead.  Longer
 // ones leave no registers for that (fresh buffers, 1024 x 50 rows 35.0 without, 31.2; two rounds, 1024 x 128: 47.1 without, 49.5; four, 300 x 256: 42.2, 47.2).
